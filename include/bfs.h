@@ -161,7 +161,12 @@ typedef struct bfs_run_options {
  *                    one atomic masks the visited rows (smaller words) and
  *                    keeps the smallest frontier in-neighbour (Lemma 1's
  *                    min-select), and the offer that finds the top bit set
- *                    lists the row (Theorem 2's single claim).  Levels whose frontier
+ *                    lists the row (Theorem 2's single claim).  On graphs
+ *                    whose out-degrees are all at most 8 the waves carry
+ *                    their shares on for many levels per launch without
+ *                    waiting for each other (a row offered too high a level
+ *                    first is set right by the smaller offer, and offers
+ *                    again).  On others, levels whose frontier
  *                    holds at most 8192 columns and 2^16 entries run in one
  *                    workgroup, many levels per launch, the frontier in LDS;
  *                    wider levels one launch each over the whole grid.  For

@@ -16,12 +16,15 @@
 // vertex are never written before its final value is known: a pass at the
 // end splits the words into the callers' level and parent arrays.
 //
-// Two forms of a level:
+// Three forms:
+//   - deep (thin graphs: every out-degree at most 8 - grids, road-like graphs,
+//     thousands of thin levels): waves go on from their share of the list by
+//     themselves for up to 128 levels, the rows they improve queued in LDS, with
+//     no barrier and no launch between levels;
 //   - narrow: one workgroup of 1024 threads runs level after level with the
 //     frontier in LDS (up to 8192 columns and 2^16 entries per level), so a
 //     level costs a few dependent memory round trips and a workgroup barrier
-//     instead of a grid-wide launch (deep, thin searches: grids, road-like
-//     graphs);
+//     instead of a grid-wide launch (the first and last levels of the others);
 //   - wide: a launch per level over the frontier lists in global memory
 //     (short columns a lane each, long ones in chunks of 1024 entries a wave
 //     each, as the paper's work-splitting of long columns suggests).
@@ -112,6 +115,11 @@ __device__ __forceinline__ void append_wide(const CwParams &P, const CwLists &L,
 struct Ref {                                   // a column's graph and query
     const int32_t *ptr, *idx;
     uint32_t base;
+};
+
+struct RowRef {                                // a thin graph's fixed-width rows and the query
+    const int4 *rows;
+    uint32_t base, quads;
 };
 
 template <bool kSingle>
@@ -240,6 +248,7 @@ __global__ __launch_bounds__(kCwBlock) void k_cw_fill(CwParams P) {
     for (uint32_t v = blockIdx.x * kCwBlock + threadIdx.x; v < Q.n; v += gridDim.x * kCwBlock) {
         const uint32_t deg = (uint32_t)(Q.out_ptr[v + 1] - Q.out_ptr[v]);
         P.cw[Q.base + v] = deg >= kCwLong ? kUnreachedLong : kUnreached;
+        if (P.stamp) P.stamp[Q.base + v] = 0u;
     }
     const uint32_t gid = (blockIdx.y == 0) ? blockIdx.x * kCwBlock + threadIdx.x : 0xFFFFFFFFu;
     if (gid < 12) P.st->cnt[gid / 4][gid % 4] = 0u;
@@ -560,14 +569,279 @@ __global__ __launch_bounds__(kCwNarrowThreads) void k_cw_narrow(CwParams P, uint
     }
 }
 
-// The words into the callers' arrays: a block row per query.
-__global__ __launch_bounds__(kCwBlock) void k_cw_out(CwParams P) {
+// ---------------------------------------------------------------------------
+// the deep form: many levels per launch, a wave at a time
+// ---------------------------------------------------------------------------
+
+// Orders a wave's LDS writes before the same wave's later LDS reads by other lanes.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A thin graph's out-lists in rows of `width` entries (4 or 8), -1 past a
+// list's end.
+__global__ __launch_bounds__(kCwBlock) void k_cw_rows(const int32_t *ptr, const int32_t *idx, int32_t n, int32_t width,
+                                                      int32_t *rows) {
+    const size_t stride = (size_t)gridDim.x * kCwBlock, cells = (size_t)n * (size_t)width;
+    for (size_t i = (size_t)blockIdx.x * kCwBlock + threadIdx.x; i < cells; i += stride) {
+        const size_t v = i / (size_t)width;
+        const int32_t e = ptr[v] + (int32_t)(i % (size_t)width);
+        rows[i] = e < ptr[v + 1] ? idx[e] : -1;
+    }
+}
+
+// The rows of virtual id x's query: one query (mode 0), queries on one graph
+// (mode 1: the bases are multiples of its size), queries on any (mode 2).
+template <int kMode>
+__device__ __forceinline__ RowRef deep_ref(const CwParams &P, const RowRef &one, uint32_t x) {
+    if (kMode == 0) return one;
+    if (kMode == 1) return RowRef{one.rows, x - x % P.same_n, one.quads};
+    const CwQuery &Q = P.q[query_of(P, x)];
+    return RowRef{Q.rows, Q.base, Q.quads};
+}
+
+// A wave's queue of improved vertices: virtual ids and the levels they were
+// improved to.
+struct DeepQueue {
+    uint32_t x[kDeepQueue], l[kDeepQueue];
+};
+constexpr uint32_t kDeepFirst = 0u;            // no improved row has level 0
+
+// The lanes' vertices x (those with ok) onto the next launch's list, each
+// vertex once per launch: the first to raise its stamp lists it.  Every lane
+// calls it.
+__device__ __forceinline__ void deep_list(const CwParams &P, const CwLists &N, uint32_t t, uint32_t tag, bool ok,
+                                          uint32_t x) {
+    const bool fresh = ok && atomicMax(&P.stamp[x], tag) < tag;
+    const unsigned long long bm = __ballot(fresh);
+    if (!bm) return;
+    uint32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(&P.st->cnt[t][0], (uint32_t)__popcll(bm));
+    base = __shfl(base, 0, 64);
+    if (fresh) N.s[base + lanes_below(bm)] = x;
+}
+
+// The queue's n entries onto the next launch's list: the stamps of 256 at a
+// time in flight together, the fresh ones gathered at the queue's front, then
+// one counter atomic for all of them.  Entries of level kDeepFirst (flat
+// launches: rows reached for the first time, which one offer each finds) need
+// no stamp; a row improved once more in the same launch may then be listed
+// twice, so a list holds up to 2 V entries (its array and the long columns'
+// behind it, which a thin graph has none of).
+__device__ __forceinline__ void deep_spill(const CwParams &P, const CwLists &N, uint32_t t, uint32_t tag,
+                                           DeepQueue &q, uint32_t n) {
+    const uint32_t lane = lane_id();
+    uint32_t kept = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += 256u) {                          // uniform
+        uint32_t x[4], old[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            const uint32_t i = i0 + 64u * j + lane;
+            x[j] = q.x[i < n ? i : n - 1u];
+            old[j] = i < n ? 0u : tag;
+            if (i < n && q.l[i] != kDeepFirst) old[j] = atomicMax(&P.stamp[x[j]], tag);
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) settle_after_issue32(old[j]);
+        wave_lds_sync();
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            const bool fresh = old[j] < tag;
+            const unsigned long long bm = __ballot(fresh);
+            if (fresh) q.x[kept + lanes_below(bm)] = x[j];              // kept <= i0 + 64 j: read already
+            kept += (uint32_t)__popcll(bm);
+        }
+        wave_lds_sync();
+    }
+    if (!kept) return;
+    uint32_t base = 0;
+    if (lane == 0) base = atomicAdd(&P.st->cnt[t][0], kept);
+    base = __shfl(base, 0, 64);
+    for (uint32_t i = lane; i < kept; i += 64u) N.s[base + i] = q.x[i];
+}
+
+// U columns per lane (x at level l, those with ok): offers to all their rows
+// (a thin graph keeps its lists in fixed-width rows of kE entries, -1 past a
+// list's end, so one load gives a column with no look at its bounds), every load and then every atomic of the lane in flight
+// together; the rows improved go to queue q (its size m, the same in every
+// lane), or to the next launch's list once it is full.
+template <int kMode, int kE, int U>
+__device__ __forceinline__ void deep_expand(const CwParams &P, const CwLists &N, const RowRef &one, uint32_t t,
+                                            uint32_t tag, bool pre, bool flat, const uint32_t (&x)[U],
+                                            const uint32_t (&l)[U], const bool (&ok)[U], DeepQueue &q, uint32_t &m) {
+    constexpr int kQuads = kE / 4;
+    uint32_t base[U];
+    int4 d[U][kQuads];
+#pragma unroll
+    for (int c = 0; c < U; ++c) {
+        const RowRef r = deep_ref<kMode>(P, one, x[c]);
+        base[c] = r.base;
+#pragma unroll
+        for (int h = 0; h < kQuads; ++h) {
+            d[c][h] = make_int4(-1, -1, -1, -1);
+            // (graphs of either width may share a launch of the wider kind)
+            const uint32_t quads = kMode == 2 ? r.quads : (uint32_t)kQuads;
+            if (ok[c] && (uint32_t)h < quads) d[c][h] = r.rows[(size_t)(x[c] - r.base) * quads + h];
+        }
+    }
+    uint32_t v[U][kE];
+    bool on[U][kE];
+#pragma unroll
+    for (int c = 0; c < U; ++c)
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+            const int4 &w = d[c][e / 4];
+            const int32_t i = (e & 3) == 0 ? w.x : ((e & 3) == 1 ? w.y : ((e & 3) == 2 ? w.z : w.w));
+            on[c][e] = i >= 0;
+            v[c][e] = base[c] + (uint32_t)(i >= 0 ? i : 0);
+        }
+    unsigned long long old[U][kE];
+    if (pre) {
+#pragma unroll
+        for (int c = 0; c < U; ++c)
+#pragma unroll
+            for (int e = 0; e < kE; ++e) {
+                old[c][e] = 0ull;
+                if (on[c][e]) old[c][e] = P.cw[v[c][e]];
+            }
+#pragma unroll
+        for (int c = 0; c < U; ++c)
+#pragma unroll
+            for (int e = 0; e < kE; ++e) settle_after_issue(old[c][e]);
+    }
+#pragma unroll
+    for (int c = 0; c < U; ++c) {
+        const unsigned long long key = offer_key(l[c] + 1u, x[c] - base[c]);
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+            // the words only decrease, so a stale copy is never below the true value
+            const bool go = on[c][e] && (!pre || old[c][e] > key);
+            old[c][e] = 0ull;
+            if (go) old[c][e] = atomicMin(&P.cw[v[c][e]], key);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < U; ++c)
+#pragma unroll
+        for (int e = 0; e < kE; ++e) settle_after_issue(old[c][e]);
+#pragma unroll
+    for (int c = 0; c < U; ++c)
+#pragma unroll
+        for (int e = 0; e < kE; ++e) {
+            // a lower level than the row had (or its first): the row's own
+            // offers follow; the same level: only its parent changed
+            const bool imp = (uint32_t)(old[c][e] >> 32) > l[c] + 1u;
+            const unsigned long long bm = __ballot(imp);
+            if (!bm) continue;
+            const uint32_t pos = m + lanes_below(bm);
+            if (imp && pos < kDeepQueue) {
+                q.x[pos] = v[c][e];
+                q.l[pos] = (flat && unreached(old[c][e])) ? kDeepFirst : l[c] + 1u;
+            }
+            const uint32_t end = m + (uint32_t)__popcll(bm);
+            if (end > kDeepQueue) deep_list(P, N, t, tag, imp && pos >= kDeepQueue, v[c][e]);
+            m = end < kDeepQueue ? end : kDeepQueue;
+        }
+}
+
+// A wave per block takes a share of the list and goes on from it by itself:
+// the rows its offers improve are its next columns, level after level, in LDS,
+// with no word to the other waves.  Nothing waits at a level's end, so a level
+// costs the chain row - atomics - LDS instead of a launch with its counts and lists around that chain.  Waves drift apart, so a
+// row may first be offered a level above its own; the word's minimum sets it
+// right whenever the smaller offer comes, and whoever lowers a row's level
+// makes that row's own offers again.  When no improved row is left every word
+// holds its smallest offer from columns that made theirs at their final
+// level: the level, and the smallest in-neighbour one level up.
+//
+// After `iters` levels (or with kDeepStop rows in the queue: the frontier
+// grows, other waves should share it) the queue goes to the next launch's
+// list, whose entries carry no level: the next launch reads it from the
+// word.  A list longer than one step of the whole grid is expanded one level
+// only, as the wide form does: it keeps every wave busy by itself, and a wave
+// going on alone would run ahead of columns still waiting in the list.
+template <int kMode, int kE>
+__global__ __launch_bounds__(64) void k_cw_deep(CwParams P, uint32_t seq, uint32_t iters) {
+    __shared__ DeepQueue s_q[2];
+    CwState *st = P.st;
+    const uint32_t t0 = seq % 3, t1 = (seq + 1) % 3, t2 = (seq + 2) % 3;
+    const CwLists C = P.lists[seq & 1], N = P.lists[(seq + 1) & 1];
+    const uint32_t lane = lane_id(), tag = seq + 1u;
+    const uint32_t ns = st->cnt[t0][0];
+    if (blockIdx.x == 0 && lane < 4) st->cnt[t2][lane] = 0u;
+    const bool flat = ns > kDeepWaves * 64u;
+    const uint32_t nw = flat ? gridDim.x : kDeepWaves;
+    if (blockIdx.x >= nw) return;
+    const RowRef one = RowRef{P.q[0].rows, P.q[0].base, P.q[0].quads};
+    const uint32_t want = (ns + nw - 1u) / nw;
+    const uint32_t per = flat ? 64u : (want < kDeepShare ? kDeepShare : want);
+    const bool pre = ns >= kDeepCheck;
+    uint32_t m = 0;                                                     // entries of s_q[0], flat only
+    for (uint32_t b = blockIdx.x * per; b < ns; b += nw * per) {        // uniform; once unless flat
+        uint32_t x1[1] = {0u}, l1[1] = {0u};
+        bool ok1[1] = {lane < per && b + lane < ns};
+        if (ok1[0]) {
+            x1[0] = C.s[b + lane];
+            l1[0] = (uint32_t)(ld_agent64(&P.cw[x1[0]]) >> 32);
+        }
+        if (flat) {
+            deep_expand<kMode, kE, 1>(P, N, one, t1, tag, pre, true, x1, l1, ok1, s_q[0], m);
+            if (m > kDeepQueue / 2) {
+                wave_lds_sync();
+                deep_spill(P, N, t1, tag, s_q[0], m);
+                m = 0;
+            }
+            continue;
+        }
+        uint32_t cur = 0, n = 0;
+        deep_expand<kMode, kE, 1>(P, N, one, t1, tag, pre, false, x1, l1, ok1, s_q[0], n);
+        wave_lds_sync();
+        for (uint32_t i = 1; i < iters && n != 0u && n <= kDeepStop; ++i) {     // uniform
+            DeepQueue &q = s_q[cur], &o = s_q[cur ^ 1u];
+            uint32_t no = 0;
+            if (n <= 64u) {
+                uint32_t x[1] = {q.x[lane < n ? lane : 0u]}, l[1] = {q.l[lane < n ? lane : 0u]};
+                const bool ok[1] = {lane < n};
+                deep_expand<kMode, kE, 1>(P, N, one, t1, tag, pre, false, x, l, ok, o, no);
+            } else {
+                for (uint32_t j = 0; j < n; j += 128u) {                // uniform
+                    const uint32_t i0 = j + lane, i1 = j + 64u + lane;
+                    uint32_t x[2] = {q.x[i0 < n ? i0 : 0u], q.x[i1 < n ? i1 : 0u]};
+                    uint32_t l[2] = {q.l[i0 < n ? i0 : 0u], q.l[i1 < n ? i1 : 0u]};
+                    const bool ok[2] = {i0 < n, i1 < n};
+                    deep_expand<kMode, kE, 2>(P, N, one, t1, tag, pre, false, x, l, ok, o, no);
+                }
+            }
+            wave_lds_sync();
+            cur ^= 1u;
+            n = no;
+        }
+        deep_spill(P, N, t1, tag, s_q[cur], n);
+    }
+    if (flat) {
+        wave_lds_sync();
+        deep_spill(P, N, t1, tag, s_q[0], m);
+    }
+}
+
+// The words into the callers' arrays: a block row per query.  With deepest
+// set, the largest level over all queries goes to st->last.
+__global__ __launch_bounds__(kCwBlock) void k_cw_out(CwParams P, uint32_t deepest) {
     const CwQuery &Q = P.q[blockIdx.y];
+    int32_t top = 0;
     for (uint32_t v = blockIdx.x * kCwBlock + threadIdx.x; v < Q.n; v += gridDim.x * kCwBlock) {
         const unsigned long long w = P.cw[Q.base + v];
         const bool r = !unreached(w);
-        Q.level[v] = r ? (int32_t)(w >> 32) : -1;
+        const int32_t l = r ? (int32_t)(w >> 32) : -1;
+        Q.level[v] = l;
         Q.parent[v] = r ? (int32_t)(uint32_t)w : -1;
+        top = l > top ? l : top;
+    }
+    if (deepest) {
+        top = wave_max(top);
+        if (lane_id() == 0 && (uint32_t)top > ld_agent(&P.st->last)) atomicMax(&P.st->last, (uint32_t)top);
     }
 }
 
@@ -583,6 +857,31 @@ hipError_t launch_cw_init(const CwParams &p, hipStream_t s) {
 
 hipError_t launch_cw_wide(const CwParams &p, uint32_t k, uint32_t grid, hipStream_t s) {
     hipLaunchKernelGGL(k_cw_wide, dim3(grid), dim3(kCwBlock), 0, s, p, k);
+    return hipGetLastError();
+}
+
+hipError_t launch_cw_rows(const int32_t *ptr, const int32_t *idx, int32_t n, int32_t width, int32_t *rows,
+                          hipStream_t s) {
+    const size_t want = ((size_t)n * (size_t)width + kCwBlock - 1) / kCwBlock;
+    hipLaunchKernelGGL(k_cw_rows, dim3((uint32_t)(want < 8192 ? want : 8192)), dim3(kCwBlock), 0, s, ptr, idx, n,
+                       width, rows);
+    return hipGetLastError();
+}
+
+hipError_t launch_cw_deep(const CwParams &p, uint32_t seq, uint32_t iters, uint32_t grid, bool wide_rows,
+                          hipStream_t s) {
+    const dim3 g(grid), b(64);
+    const int mode = p.nq == 1 ? 0 : (p.same_n ? 1 : 2);
+    if (mode == 0) {
+        if (wide_rows) hipLaunchKernelGGL((k_cw_deep<0, 8>), g, b, 0, s, p, seq, iters);
+        else hipLaunchKernelGGL((k_cw_deep<0, 4>), g, b, 0, s, p, seq, iters);
+    } else if (mode == 1) {
+        if (wide_rows) hipLaunchKernelGGL((k_cw_deep<1, 8>), g, b, 0, s, p, seq, iters);
+        else hipLaunchKernelGGL((k_cw_deep<1, 4>), g, b, 0, s, p, seq, iters);
+    } else {
+        if (wide_rows) hipLaunchKernelGGL((k_cw_deep<2, 8>), g, b, 0, s, p, seq, iters);
+        else hipLaunchKernelGGL((k_cw_deep<2, 4>), g, b, 0, s, p, seq, iters);
+    }
     return hipGetLastError();
 }
 
@@ -637,10 +936,10 @@ hipError_t launch_unpack(const PackParams &p, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_cw_out(const CwParams &p, hipStream_t s) {
+hipError_t launch_cw_out(const CwParams &p, bool deepest, hipStream_t s) {
     uint32_t gx = (p.max_n + kCwBlock - 1) / kCwBlock;
     gx = gx < 1024u ? (gx ? gx : 1u) : 1024u;
-    hipLaunchKernelGGL(k_cw_out, dim3(gx, p.nq), dim3(kCwBlock), 0, s, p);
+    hipLaunchKernelGGL(k_cw_out, dim3(gx, p.nq), dim3(kCwBlock), 0, s, p, deepest ? 1u : 0u);
     return hipGetLastError();
 }
 

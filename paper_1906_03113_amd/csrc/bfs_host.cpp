@@ -79,6 +79,10 @@ struct bfs_graph {
     bfsi::SlChunk *sl_chunks = nullptr;
     uint32_t sl_S = 0, sl_sw = 0;
     uint32_t sl_chunk_off[bfsi::kSlMaxSlices + 1] = {};
+    // a thin graph's out-lists in rows of thin_width entries (4 or 8), -1 past
+    // a list's end, for the claim-word push's deep form
+    int32_t *thin_rows = nullptr;
+    uint32_t thin_width = 0;
     std::mutex mu;
     GraphExecCache gcache;
     std::vector<hipEvent_t> events;   // pool for per-launch timing
@@ -86,6 +90,8 @@ struct bfs_graph {
 };
 
 namespace {
+
+constexpr uint32_t kClaimMaxDeg = 8;   // a thin graph's largest out-degree
 
 thread_local std::string g_detail;
 
@@ -178,6 +184,7 @@ void free_graph(bfs_graph *g) {
     if (g->sl_seg) (void)hipFree(g->sl_seg);
     if (g->sl_occ) (void)hipFree(g->sl_occ);
     if (g->sl_chunks) (void)hipFree(g->sl_chunks);
+    if (g->thin_rows) (void)hipFree(g->thin_rows);
     delete g;
 }
 
@@ -317,6 +324,19 @@ bfs_status upload_padded(int32_t **dst, const std::vector<int32_t> &idx, size_t 
     bytes += cnt * 4;
     HIP_TRY(hipMemset(*dst, 0, cnt * 4));
     if (!idx.empty()) HIP_TRY(hipMemcpy(*dst, idx.data(), idx.size() * 4, hipMemcpyHostToDevice));
+    return BFS_OK;
+}
+
+// A thin graph's fixed-width rows, made on the device from its uploaded lists.
+bfs_status build_thin_rows(bfs_graph *g) {
+    if (g->max_deg > kClaimMaxDeg) return BFS_OK;
+    const uint32_t width = g->max_deg <= 4u ? 4u : 8u;
+    const size_t b = (size_t)g->n * width * sizeof(int32_t);
+    if (hipMalloc((void **)&g->thin_rows, b) != hipSuccess) return fail(BFS_ENOMEM, "hipMalloc(%zu) failed", b);
+    g->bytes += b;
+    HIP_TRY(launch_cw_rows(g->out_ptr, g->out_idx, g->n, (int32_t)width, g->thin_rows, nullptr));
+    HIP_TRY(hipStreamSynchronize(nullptr));
+    g->thin_width = width;
     return BFS_OK;
 }
 
@@ -778,6 +798,15 @@ constexpr uint32_t kCwNarrowEdgesMax = 4096;
 constexpr uint32_t kCwWidePerSync = 32;          // wide levels between two reads of the counts, at most
 constexpr uint32_t kCwWideMinGrid = 64;          // workgroups of a wide launch at least
 
+// The deep form's launch: kDeepGrid waves (kDeepWaves of them where they go on
+// alone, up to kDeepIters levels each: past that a wave's share has drifted too
+// far from its neighbours' - 2048^2 grid 4.71 / 4.27 / 4.18 / 4.38 ms at 512 /
+// 256 / 128 / 64, 16 sources of a 2200 x 2111 grid 12.6 / 9.59 / 9.35 / 9.57
+// ms); launches between two reads of the count, at most.
+constexpr uint32_t kDeepGrid = 4096;
+constexpr uint32_t kDeepIters = 128;
+constexpr uint32_t kDeepPerSync = 8;
+
 struct ClaimQuery {
     const bfs_graph *g;
     int32_t source;
@@ -800,9 +829,10 @@ size_t claim_workspace(const ClaimQuery *qs, int32_t nq) {
     return cw_layout(V, E, (uint32_t)nq).total;
 }
 
-// The searches of qs together: the narrow kernel while a level fits one
-// workgroup, the wide one otherwise (a level it hands back unexpanded runs
-// wide), the frontier counts read back after every launch.
+// The searches of qs together.  On thin graphs the deep kernel, many levels a
+// launch, until a launch lists nothing; on others the narrow kernel while a
+// level fits one workgroup, the wide one otherwise (a level it hands back
+// unexpanded runs wide), the frontier counts read back after every launch.
 bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t ws_bytes, hipStream_t s,
                      int cus, bfs_run_options *opt) {
     uint64_t E = 0;
@@ -825,7 +855,8 @@ bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t w
         d.base = base;
         d.n = (uint32_t)qs[q].g->n;
         d.source = qs[q].source;
-        d.pad = 0;
+        d.rows = (const int4 *)qs[q].g->thin_rows;
+        d.quads = qs[q].g->thin_width / 4u;
         hb[(size_t)q] = base;
         base += d.n;
         max_n = std::max(max_n, d.n);
@@ -844,6 +875,17 @@ bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t w
                          (uint32_t *)(b + L.c1)};
     P.spill = (uint32_t *)(b + L.spill);
     P.st = (CwState *)(b + L.st);
+    // every graph thin: the deep form, its stamps in the narrow form's spill
+    // array (its lists may hold 2 V entries, counted in 32 bits)
+    bool thin = V < (1ull << 31), same = true;
+    uint32_t width = 4;
+    for (int32_t q = 0; q < nq; ++q) {
+        thin = thin && qs[q].g->thin_rows != nullptr;
+        same = same && qs[q].g == qs[0].g;
+        width = std::max(width, qs[q].g->thin_width);
+    }
+    P.stamp = thin ? P.spill : nullptr;
+    P.same_n = same ? (uint32_t)qs[0].g->n : 0u;
     HIP_TRY(hipMemcpyAsync(b + L.q, hq.data(), hq.size() * sizeof(CwQuery), hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(b + L.bases, hb.data(), hb.size() * 4, hipMemcpyHostToDevice, s));
     const bool tk = opt && opt->time_kernels;
@@ -882,6 +924,25 @@ bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t w
         // launches few levels past its end, a deep one syncs rarely)
         const uint32_t fixed_sync = opt ? opt->levels_per_sync : 0u;
         uint32_t per_sync = fixed_sync ? fixed_sync : 2u;
+        if (thin) {
+            uint32_t seq = 0;
+            for (uint64_t guard = 0; hst.cnt[seq % 3][0] != 0u; ++guard) {
+                if (guard > V + 4) return fail(BFS_EHIP, "claim-word loop did not terminate");
+                for (uint32_t i = 0; i < per_sync; ++i) {
+                    HIP_TRY(launch([&]() {
+                        return launch_cw_deep(P, seq + i, kDeepIters, kDeepGrid, width == 8u, s);
+                    }));
+                    ++launches;
+                }
+                seq += per_sync;
+                HIP_TRY(read_state());
+                if (!fixed_sync) per_sync = std::min(2 * per_sync, kDeepPerSync);
+            }
+            HIP_TRY(launch_cw_out(P, true, s));
+            HIP_TRY(read_state());
+            levels = hst.last + 1;
+            return BFS_OK;
+        }
         for (uint64_t guard = 0;; ++guard) {
             if (guard > V + 4) return fail(BFS_EHIP, "claim-word loop did not terminate");
             const uint32_t *c = hst.cnt[k % 3];
@@ -921,7 +982,7 @@ bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t w
             narrow_refused = false;
         }
         levels = k;
-        HIP_TRY(launch_cw_out(P, s));
+        HIP_TRY(launch_cw_out(P, false, s));
         return BFS_OK;
     };
     uint32_t levels = 0, launches = 0;
@@ -969,7 +1030,6 @@ uint32_t sl_grid(const bfs_graph *g) {
 //   - otherwise the list form (ER 2^18 x 16: 0.29 ms, sliced 0.57; the ER
 //     pack: 1.00 ms, sliced 2.74).
 constexpr int32_t kSlMinAuto = 1 << 17;
-constexpr uint32_t kClaimMaxDeg = 8;
 constexpr uint64_t kSlSkew = 16;
 
 // Thin: every out-degree at most kClaimMaxDeg.
@@ -1291,6 +1351,7 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
     try {
         if (st == BFS_OK) st = build_long(n, ptr, &g->lo, &g->lomap, g->nlo, g->nlo_chunks, g->bytes);
         if (st == BFS_OK) st = build_slices(g, ptr, idx);
+        if (st == BFS_OK) st = build_thin_rows(g);
         if (st == BFS_OK && directed) {
             st = build_long(n, iptr, &g->li, &g->limap, g->nli, g->nli_chunks, g->bytes);
         } else if (st == BFS_OK) {

@@ -298,13 +298,20 @@ constexpr uint32_t kCwLong = 256;             // wide: a column this long is spl
 constexpr uint32_t kCwChunk = 1024;           // wide: entries per chunk
 constexpr uint32_t kCwPrecheck = 1u << 16;    // wide: frontier entries from which a word is read first
 constexpr uint32_t kCwMaxQueries = 4096;
+constexpr uint32_t kDeepCheck = 4096;         // deep: list length from which a word is read first
+constexpr uint32_t kDeepWaves = 2048;         // deep: waves that go on alone (8 per compute unit)
+constexpr uint32_t kDeepQueue = 512;          // deep: rows a wave queues in LDS
+constexpr uint32_t kDeepStop = 128;           // deep: queued rows from which a wave hands them on
+constexpr uint32_t kDeepShare = 4;            // deep: columns a wave starts from at least (2048^2 grid
+                                              // 11.3 / 8.4 / 6.9 / 6.2 / 5.9 ms at 64 / 32 / 16 / 8 / 4)
 
 struct CwQuery {
     const int32_t *out_ptr, *out_idx;
+    const int4 *rows;                         // a thin graph's fixed-width rows, else null
     int32_t *level, *parent;                  // the query's outputs (n each)
     uint32_t base, n;                         // virtual ids [base, base + n)
     int32_t source;
-    uint32_t pad;
+    uint32_t quads;                           // 16-byte quads per fixed-width row (1 or 2)
 };
 
 struct CwLists {                              // one level's frontier
@@ -331,6 +338,8 @@ struct CwParams {
     unsigned long long *cw;                   // [V]
     CwLists lists[2];                         // level k lists in lists[k & 1]
     uint32_t *spill;                          // narrow: next-frontier entries beyond the LDS
+    uint32_t *stamp;                          // deep: [V] last launch (+1) that listed a vertex, else null
+    uint32_t same_n;                          // every query on one graph of this many vertices, else 0
     CwState *st;
 };
 
@@ -343,7 +352,13 @@ hipError_t launch_cw_init(const CwParams &p, hipStream_t s);
 hipError_t launch_cw_wide(const CwParams &p, uint32_t k, uint32_t grid, hipStream_t s);
 hipError_t launch_cw_narrow(const CwParams &p, uint32_t k, uint32_t max_levels, uint32_t max_next,
                             uint32_t max_edges, hipStream_t s);
-hipError_t launch_cw_out(const CwParams &p, hipStream_t s);
+hipError_t launch_cw_rows(const int32_t *ptr, const int32_t *idx, int32_t n, int32_t width, int32_t *rows,
+                          hipStream_t s);
+// seq: the launch's number in its search, from 0; wide_rows: columns of 5 to 8 entries exist
+hipError_t launch_cw_deep(const CwParams &p, uint32_t seq, uint32_t iters, uint32_t grid, bool wide_rows,
+                          hipStream_t s);
+// deepest: the largest level over all queries into st->last
+hipError_t launch_cw_out(const CwParams &p, bool deepest, hipStream_t s);
 
 // Queries on different graphs searched as one block-diagonal graph by the
 // list form: the library packs the graphs' out-lists (vertex ids offset by
