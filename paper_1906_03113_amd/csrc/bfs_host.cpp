@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <iterator>
 #include <mutex>
 #include <new>
 #include <string>
@@ -83,6 +84,7 @@ struct bfs_graph {
     // a list's end, for the claim-word push's deep form
     int32_t *thin_rows = nullptr;
     uint32_t thin_width = 0;
+    bool slow_growth = false;         // a thin graph whose searches look deep (grows_slowly)
     std::mutex mu;
     GraphExecCache gcache;
     std::vector<hipEvent_t> events;   // pool for per-launch timing
@@ -340,6 +342,37 @@ bfs_status build_thin_rows(bfs_graph *g) {
     return BFS_OK;
 }
 
+// Whether searches on a thin graph look deep: from four of its vertices, level k
+// of the first kGrowthLevels holds at most 5 k^2 + 8 vertices (planar graphs hold
+// about 4 k to 8 k, three-dimensional grids 4 k^2; a random graph of degree 3
+// holds 3 x 2^(k-1) and is through in 25 levels).  Visits a few thousand
+// vertices at most.
+constexpr uint32_t kGrowthLevels = 12;
+
+bool grows_slowly(int32_t n, const std::vector<int32_t> &ptr, const std::vector<int32_t> &idx) {
+    std::vector<int32_t> front, next, seen;
+    for (int32_t t = 0; t < 4; ++t) {
+        int64_t s = (int64_t)n * t / 4;
+        while (s < n && ptr[(size_t)s + 1] == ptr[(size_t)s]) ++s;
+        if (s == n) continue;
+        front.assign(1, (int32_t)s);
+        seen = front;
+        for (uint32_t k = 1; k <= kGrowthLevels && !front.empty(); ++k) {
+            next.clear();
+            for (int32_t u : front) next.insert(next.end(), idx.begin() + ptr[(size_t)u], idx.begin() + ptr[(size_t)u + 1]);
+            std::sort(next.begin(), next.end());
+            next.erase(std::unique(next.begin(), next.end()), next.end());
+            front.clear();
+            std::set_difference(next.begin(), next.end(), seen.begin(), seen.end(), std::back_inserter(front));
+            if (front.size() > 5u * k * k + 8u) return false;
+            const size_t mid = seen.size();
+            seen.insert(seen.end(), front.begin(), front.end());
+            std::inplace_merge(seen.begin(), seen.begin() + (std::ptrdiff_t)mid, seen.end());
+        }
+    }
+    return true;
+}
+
 // The sliced push's graph data: S slices of sw words (sw a multiple of 4, at
 // most kSlMaxSliceWords); seg[v] = {ptr[v], first entry of v's sorted list in
 // slice 1, 2, 3} (ptr[v + 1] for slices past the last); and every slice part
@@ -467,7 +500,7 @@ MsLayout ms_layout(int32_t n, int32_t nq, bool staged) {
     return L;
 }
 
-CwLayout cw_layout(uint64_t V, uint64_t nnz, uint32_t nq) {
+CwLayout cw_layout(uint64_t V, uint64_t nnz, uint32_t nq, bool thin) {
     CwLayout L{};
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align256(off + bytes); return o; };
@@ -480,12 +513,12 @@ CwLayout cw_layout(uint64_t V, uint64_t nnz, uint32_t nq) {
     L.cw = take((size_t)V * 8);
     L.s0 = take((size_t)V * 4);
     L.l0 = take((size_t)V * 4);
-    L.b0 = take((size_t)V * 4);
-    L.c0 = take(chunks * 4);
+    L.b0 = take(thin ? 0 : (size_t)V * 4);
+    L.c0 = take(thin ? 0 : chunks * 4);
     L.s1 = take((size_t)V * 4);
     L.l1 = take((size_t)V * 4);
-    L.b1 = take((size_t)V * 4);
-    L.c1 = take(chunks * 4);
+    L.b1 = take(thin ? 0 : (size_t)V * 4);
+    L.c1 = take(thin ? 0 : chunks * 4);
     L.spill = take((size_t)V * 4);
     L.total = off;
     return L;
@@ -833,14 +866,15 @@ size_t claim_workspace(const ClaimQuery *qs, int32_t nq) {
 // launch, until a launch lists nothing; on others the narrow kernel while a
 // level fits one workgroup, the wide one otherwise (a level it hands back
 // unexpanded runs wide), the frontier counts read back after every launch.
+// compact: graphs known to be thin, the workspace without the long columns' arrays.
 bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t ws_bytes, hipStream_t s,
-                     int cus, bfs_run_options *opt) {
+                     int cus, bfs_run_options *opt, bool compact = false) {
     uint64_t E = 0;
     const uint64_t V = claim_vertices(qs, nq, &E);
     if (V >= 0xFFFFFFFFull) return fail(BFS_EINVAL, "the queries hold %llu vertices (at most 2^32 - 2)",
                                         (unsigned long long)V);
     if ((uint32_t)nq > kCwMaxQueries) return fail(BFS_EINVAL, "%d queries (at most %u)", nq, kCwMaxQueries);
-    const CwLayout L = cw_layout(V, E, (uint32_t)nq);
+    const CwLayout L = cw_layout(V, E, (uint32_t)nq, compact);
     if (ws_bytes < L.total) return fail(BFS_EINVAL, "workspace has %zu bytes, needs %zu", ws_bytes, L.total);
     char *b = (char *)workspace;
     std::vector<CwQuery> hq((size_t)nq);
@@ -1064,6 +1098,63 @@ bool claim_batch_applies(const bfs_graph *g, const bfs_run_options *opt) {
     const uint32_t loop = opt ? opt->loop_mode : BFS_LOOP_HOST;
     if (impl == BFS_PUSH_CLAIM) return true;
     return impl == BFS_PUSH_AUTO && pol == kPush && loop == BFS_LOOP_HOST && thin_graph(g) && g->sl_S == 0;
+}
+
+// Many sources on one thin graph whose searches look deep (slow_growth), under
+// the direction policies that leave the form open: claim-word searches in
+// lockstep, as many at a time as the workspace holds (28 bytes per vertex and
+// source; bfs_workspace_size asks for room for kDeepGroup, the multi-source
+// workspace alone holds about 20 per mask word).  The multi-source
+// kernels pay two grid-wide launches and a host round trip for each of the
+// hundreds of thin levels.  Measured with 2 / 16 / 64 sources (all at once),
+// multi-source learned against claim-word: 512^2 grid 17.3 / 20.6 / 25.1 against
+// 1.10 / 1.58 / 2.42 ms, 128^2 grid 3.56 / 5.92 / 5.91 against 0.30 / 0.36 /
+// 0.55 ms, 32^2 grid 1.26 / 1.83 / 1.97 against 0.15 / 0.15 / 0.20 ms; on graphs
+// that grow fast many sources share the multi-source levels' reads (a random
+// graph of degree 8 and 200,000 vertices, 64 sources: 0.74 against 2.89 ms), so
+// those stay.  A call that asks for the levels' directions (trace) gets them.
+constexpr int32_t kDeepGroup = 64;
+
+size_t deep_workspace(const bfs_graph *g, int32_t m) {
+    return cw_layout((uint64_t)g->n * (uint64_t)m, 0, (uint32_t)m, true).total;
+}
+
+bool deep_batch_applies(const bfs_graph *g, const bfs_run_options *opt) {
+    if (!g->slow_growth) return false;
+    if (!opt) return true;
+    return opt->push_impl == BFS_PUSH_AUTO && opt->loop_mode == BFS_LOOP_HOST && !opt->trace &&
+           opt->ms_ranges <= 1 && (opt->variant == kPush || opt->variant == kHeuristic || opt->variant == kLearned);
+}
+
+bfs_status run_deep_batch(bfs_graph *g, int32_t nq, const int32_t *sources, int32_t *const *level,
+                          int32_t *const *parent, bfs_run_options *opt, void *workspace, size_t ws_bytes,
+                          hipStream_t s) {
+    int32_t most = std::min(nq, kDeepGroup);
+    while (most > 1 && deep_workspace(g, most) > ws_bytes) --most;   // one search fits what bfs_run asks for
+    const int32_t groups = (nq + most - 1) / most, per = (nq + groups - 1) / groups;
+    std::vector<ClaimQuery> qs;
+    uint32_t levels = 0, launches = 0;
+    float kernel_us = 0.f;
+    for (int32_t q0 = 0; q0 < nq; q0 += per) {
+        const int32_t m = std::min(per, nq - q0);
+        qs.clear();
+        for (int32_t q = q0; q < q0 + m; ++q) qs.push_back(ClaimQuery{g, sources[q], level[q], parent[q]});
+        bfs_status st = run_claim(qs.data(), m, workspace, ws_bytes, s, g->cus, opt, true);
+        if (st != BFS_OK) return st;
+        if (opt) {
+            levels = std::max(levels, opt->levels);
+            launches += opt->launches;
+            kernel_us += opt->kernel_us;
+        }
+    }
+    if (opt) {
+        opt->levels = levels;
+        if (opt->time_kernels) {
+            opt->launches = launches;
+            opt->kernel_us = kernel_us;
+        }
+    }
+    return BFS_OK;
 }
 
 // Queries on different graphs: the list form over the graphs packed into one
@@ -1352,6 +1443,7 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
         if (st == BFS_OK) st = build_long(n, ptr, &g->lo, &g->lomap, g->nlo, g->nlo_chunks, g->bytes);
         if (st == BFS_OK) st = build_slices(g, ptr, idx);
         if (st == BFS_OK) st = build_thin_rows(g);
+        if (st == BFS_OK && g->thin_rows) g->slow_growth = grows_slowly(n, ptr, idx);
         if (st == BFS_OK && directed) {
             st = build_long(n, iptr, &g->li, &g->limap, g->nli, g->nli_chunks, g->bytes);
         } else if (st == BFS_OK) {
@@ -1400,6 +1492,9 @@ size_t bfs_workspace_size(const bfs_graph *g, int32_t num_queries, uint32_t run_
     const size_t single = ws_single(g);
     if (num_queries == 1) return single;
     size_t need = std::max(single, ms_layout(g->n, num_queries).total);
+    // room for kDeepGroup claim-word searches side by side (fewer run in turn)
+    if (g->slow_growth)
+        need = std::max(need, deep_workspace(g, std::min(num_queries, kDeepGroup)));
     // thin graphs (or when asked): room for the claim-word batch too (see
     // claim_batch_applies)
     if ((thin_graph(g) && g->sl_S == 0) || (run_flags & BFS_WS_CLAIM))
@@ -1702,20 +1797,29 @@ static uint32_t ms_grid(const bfs_graph *g, const bfs_run_options *opt) {
     return std::max<uint32_t>(8u * cus, want);
 }
 
+// What the multi-source search refuses in its options.
+static bfs_status check_multi_source(const bfs_graph *g, const bfs_run_options *opt) {
+    if (!opt) return BFS_OK;
+    if (opt->ms_pull_shift > 31) return fail(BFS_EINVAL, "ms_pull_shift %u above 31", opt->ms_pull_shift);
+    if (opt->variant > kShortCircuit) return fail(BFS_EINVAL, "unknown variant %u", opt->variant);
+    const uint32_t grid = ms_grid(g, opt);
+    if (grid == 0 || grid > 65535) return fail(BFS_EINVAL, "grid_blocks %u outside [1, 65535]", grid);
+    if (opt->ms_ranges > 64) return fail(BFS_EINVAL, "ms_ranges %u above 64", opt->ms_ranges);
+    return BFS_OK;
+}
+
 // All queries on one graph: the multi-source kernels (outputs as ms_prepare).
 static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sources,
                                    int32_t *const *level, int32_t *const *parent,
                                    bfs_run_options *opt, void *workspace, hipStream_t s,
                                    int32_t *vm_level = nullptr, int32_t *vm_parent = nullptr) {
     const uint32_t pull_shift = (opt && opt->ms_pull_shift) ? opt->ms_pull_shift : 5u;
-    if (pull_shift > 31) return fail(BFS_EINVAL, "ms_pull_shift %u above 31", pull_shift);
-    if (opt && opt->variant > kShortCircuit) return fail(BFS_EINVAL, "unknown variant %u", opt->variant);
+    bfs_status st = check_multi_source(g, opt);
+    if (st != BFS_OK) return st;
     const uint32_t grid = ms_grid(g, opt);
-    if (grid == 0 || grid > 65535) return fail(BFS_EINVAL, "grid_blocks %u outside [1, 65535]", grid);
-    if (opt && opt->ms_ranges > 64) return fail(BFS_EINVAL, "ms_ranges %u above 64", opt->ms_ranges);
     MsLevel p;
     HostSlot *hs = nullptr;
-    bfs_status st = ms_prepare(g, nq, sources, level, parent, workspace, s, vm_level, vm_parent, grid, p, hs);
+    st = ms_prepare(g, nq, sources, level, parent, workspace, s, vm_level, vm_parent, grid, p, hs);
     if (st != BFS_OK) return st;
     if (opt && opt->ms_ranges && p.W == 1) p.rp_ranges = opt->ms_ranges;
     if (p.rp_ranges > 1) ms_caller_order(g, p);       // its passes walk lists sorted by label
@@ -1786,8 +1890,15 @@ extern "C" bfs_status bfs_run_batch(int32_t num_queries, bfs_graph *const *graph
         same = same && graphs[q] == graphs[0];
     }
     if (same && num_queries > 1 && !claim_batch_applies(graphs[0], opt)) {
-        const size_t need = bfs_workspace_size(graphs[0], num_queries, 0);
+        // (what bfs_workspace_size asks for beyond this lets more claim-word
+        // searches run side by side)
+        const size_t need = std::max(ws_single(graphs[0]), ms_layout(graphs[0]->n, num_queries).total);
         if (ws_bytes < need) return fail(BFS_EINVAL, "workspace has %zu bytes, needs %zu", ws_bytes, need);
+        bfs_status st = check_multi_source(graphs[0], opt);
+        if (st != BFS_OK) return st;
+        if (deep_batch_applies(graphs[0], opt))
+            return run_deep_batch(graphs[0], num_queries, sources, level, parent, opt, workspace, ws_bytes,
+                                  (hipStream_t)hip_stream);
         return run_multi_source(graphs[0], num_queries, sources, level, parent, opt, workspace,
                                 (hipStream_t)hip_stream);
     }

@@ -346,7 +346,8 @@ struct CwParams {
 struct CwLayout {
     size_t q, bases, st, cw, s0, l0, b0, c0, s1, l1, b1, c1, spill, total;
 };
-CwLayout cw_layout(uint64_t V, uint64_t nnz, uint32_t nq);
+// thin: without the long columns' arrays (the deep form's lists: s and l together)
+CwLayout cw_layout(uint64_t V, uint64_t nnz, uint32_t nq, bool thin = false);
 
 hipError_t launch_cw_init(const CwParams &p, hipStream_t s);
 hipError_t launch_cw_wide(const CwParams &p, uint32_t k, uint32_t grid, hipStream_t s);

@@ -2,6 +2,8 @@
 many levels per launch: frontiers that grow past one step of the grid, rows of
 one to eight entries, one vertex, deep paths, several queries on one graph and
 on graphs of both row widths.  Bit for bit the oracle's."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -71,3 +73,32 @@ def test_deep_on_graphs_of_both_row_widths():
     for q, g in enumerate(gs):
         wl, wp = oracle.bfs_graph(g, src[q])
         assert np.array_equal(lv[q].cpu().numpy(), wl) and np.array_equal(pa[q].cpu().numpy(), wp), q
+
+
+@pytest.mark.parametrize("variant,nq", [("learned", 2), ("heuristic", 21), ("push", 64), ("learned", 130)])
+def test_deep_batch_policies(variant, nq):
+    """Many sources on a slowly growing thin graph: one group of claim-word
+    searches or several, in a workspace of exactly the size asked for and in a
+    smaller one; with a trace the multi-source levels run.  All the oracle's
+    results and one level count."""
+    import torch
+    P = need_gpu()
+    g = CASES["grid_ragged"]()
+    G = P.Graph.from_graphgen(g)
+    src = [int(s) for s in np.random.default_rng(nq).integers(0, g.n, nq)]
+    counts = set()
+    L = P._lib.lib()
+    small = max(G.workspace_size(1), g.n * 600 * ((nq + 63) // 64) + 65536)     # the multi-source masks
+    for trace, size in ((False, G.workspace_size(nq)), (False, small), (True, G.workspace_size(nq))):
+        say(f"[deep] {variant} nq={nq} trace={trace} workspace={size}")
+        ws = P.Workspace(size)
+        lv = [torch.empty(g.n, dtype=torch.int32, device="cuda") for _ in src]
+        pa = [torch.empty_like(x) for x in lv]
+        opt, recs = P.make_options(variant, trace_capacity=(g.n + 2) if trace else 0)
+        ptrs = lambda a: (ctypes.c_void_p * nq)(*[x.data_ptr() for x in a])
+        P._lib.check(L.bfs_run_batch(nq, (ctypes.c_void_p * nq)(*[G.handle] * nq), (ctypes.c_int32 * nq)(*src),
+                                     ptrs(lv), ptrs(pa), ctypes.byref(opt), ws.ptr, ws.nbytes, None))
+        torch.cuda.synchronize()
+        check_all(g, src, lambda q: (lv[q].cpu().numpy(), pa[q].cpu().numpy()), f"deep {variant}")
+        counts.add(int(opt.levels))
+    assert len(counts) == 1
