@@ -34,6 +34,12 @@ __device__ __forceinline__ unsigned long long wave_sum64(unsigned long long x) {
     return x;
 }
 
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+    return x;
+}
+
 __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {

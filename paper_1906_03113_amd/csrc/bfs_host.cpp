@@ -21,13 +21,13 @@ using namespace bfsi;
 struct LoopKey {
     uint32_t kind = 0;                 // 0: list-form level kernel, 1: sliced push
     const void *ws = nullptr, *level = nullptr, *parent = nullptr;
-    uint32_t policy = 0, grid = 0, heavy = 0, chunk = 0, levels = 0, fb = 0, stats = 0;
+    uint32_t policy = 0, grid = 0, heavy = 0, chunk = 0, levels = 0, fb = 0, small = 0;
     const float *sel = nullptr;
     const void *trace = nullptr, *slot = nullptr;
     bool operator==(const LoopKey &o) const {
         return kind == o.kind && ws == o.ws && level == o.level && parent == o.parent &&
                policy == o.policy && grid == o.grid && heavy == o.heavy && chunk == o.chunk &&
-               levels == o.levels && fb == o.fb && stats == o.stats && sel == o.sel &&
+               levels == o.levels && fb == o.fb && small == o.small && sel == o.sel &&
                trace == o.trace && slot == o.slot;
     }
 };
@@ -568,8 +568,6 @@ bfs_status make_params(bfs_graph *g, int32_t *level, int32_t *parent, const RunC
     P.trace = trace ? (DevLevelRec *)(b + L.trace) : nullptr;
     P.mlp = c.sel;
     P.maintain_fb = (c.policy == kBitmap || c.policy == kLearned || c.policy == kHeuristic) ? 1u : 0u;
-    // the level sums also pick the short-circuit levels
-    P.stats = (c.policy == kLearned || c.policy == kHeuristic || c.policy == kShortCircuit || trace) ? 1u : 0u;
     return BFS_OK;
 }
 
@@ -789,11 +787,14 @@ bfs_status run_levels(bfs_graph *g, LevelParams &P, const RunCfg &c, hipStream_t
         if (!done) return fail(BFS_EHIP, "persistent search stopped at level %u with a nonempty frontier "
                                          "(grid barrier spin limit)", level);
     } else {
+        // several small levels to a launch, unless the launches are the levels:
+        // traced (their times), or counted
+        P.small = (P.trace || P.atomics) ? 0u : 1u;
         LoopKey key;
         key.kind = 0;
         key.ws = P.st; key.level = P.level; key.parent = P.parent; key.policy = c.policy;
         key.grid = c.grid; key.heavy = c.heavy; key.chunk = c.chunk; key.levels = c.per_sync;
-        key.sel = c.sel; key.fb = P.maintain_fb; key.stats = P.stats;
+        key.sel = c.sel; key.fb = P.maintain_fb; key.small = P.small;
         key.trace = (const void *)P.trace; key.slot = (const void *)P.host_status;
         const LevelParams Pc = P;
         const uint32_t grid = c.grid;
@@ -1995,7 +1996,6 @@ extern "C" bfs_status bfs_profile_levels(bfs_graph *g, int32_t source, int32_t *
     LevelParams P;
     make_params(g, level, parent, c, workspace, false, P);
     P.maintain_fb = 1;
-    P.stats = 1;
     HostSlot *hs = nullptr;
     st = host_slot(hs);
     if (st != BFS_OK) return st;

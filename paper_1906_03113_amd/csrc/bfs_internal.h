@@ -18,6 +18,12 @@ constexpr int kMlpTotal = kMlpParams + 2 * kMlpIn;
 
 enum Variant : uint32_t { kPush = 0, kPull = 1, kBitmap = 2, kLearned = 3, kHeuristic = 4, kShortCircuit = 5 };
 
+// What one workgroup's run of small levels leaves for the launch's close.
+struct SmallOut {
+    uint32_t level, variant, nf, visited_cnt;
+    unsigned long long heavy, sdf, visited_deg;
+};
+
 // Device-resident search state (first bytes of every workspace).
 struct alignas(256) BfsState {
     uint32_t level;          // current level k
@@ -42,6 +48,7 @@ struct alignas(256) BfsState {
     // watched by the groups' last arrivals only, everyone else watches its group
     uint32_t bar_gen_group[kBarGroups * 16];
     unsigned long long atomics;          // parent atomicMin operations issued (when counted)
+    SmallOut small;
 };
 // Per-level record kept on the device (a trace ring of kTraceCap entries).
 struct DevLevelRec {
@@ -82,7 +89,7 @@ struct LevelParams {
     const float *mlp;        // selector weights (kMlpTotal floats) or nullptr
     uint32_t *host_status;   // pinned host memory: [0] level, [1] its frontier size
     uint32_t maintain_fb;
-    uint32_t stats;
+    uint32_t small;                // small levels run several to a launch (not while levels are timed apart)
     unsigned long long *atomics;   // count the push's parent atomicMin operations here, or nullptr
     uint32_t no_preread;           // 1: every unmasked pair issues its atomicMin (no pre-read)
 };

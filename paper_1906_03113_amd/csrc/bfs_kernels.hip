@@ -169,6 +169,7 @@ struct LevelPtrs {
     const uint32_t *c_cur;
     uint32_t *c_nxt;
     int32_t *u_nxt;
+    uint32_t deg_sum;         // out-degrees of the vertices this thread appended (all of them: < 2^31)
 };
 
 __device__ __forceinline__ LevelPtrs level_ptrs(const LevelParams &P, uint32_t k) {
@@ -194,6 +195,7 @@ __device__ __forceinline__ LevelPtrs level_ptrs(const LevelParams &P, uint32_t k
     L.u_nxt = nullptr;
     L.sc = false;
     L.pre = true;
+    L.deg_sum = 0;
     return L;
 }
 
@@ -210,6 +212,10 @@ __device__ __forceinline__ void out_init(OutLds &O) {
 // Write the staged entries out.  Called by every thread of the block; `final`
 // also folds the block's degree sum into the level's counter.
 __device__ __forceinline__ void out_flush(const LevelParams &P, const LevelPtrs &L, OutLds &O, bool final) {
+    if (final) {
+        const uint32_t d = wave_sum(L.deg_sum);
+        if (lane_id() == 0 && d) atomicAdd(&O.sdf, (unsigned long long)d);
+    }
     __syncthreads();
     const uint32_t tid = threadIdx.x;
     const uint32_t qn = O.qn, ln = O.ln, un = O.un;
@@ -243,7 +249,7 @@ __device__ __forceinline__ void out_flush(const LevelParams &P, const LevelPtrs 
             O.lcb = (uint32_t)(old >> 32);
         }
         if (un) O.ubase = atomicAdd(&P.st->u_wr, un);
-        if (final && P.stats && O.sdf) atomicAdd(&P.st->sdf[L.ns], O.sdf);
+        if (final && O.sdf) atomicAdd(&P.st->sdf[L.ns], O.sdf);
     }
     __syncthreads();
     for (uint32_t t = tid; t < qn; t += kBlock) L.q_nxt[O.qbase + t] = O.q[t];
@@ -314,7 +320,7 @@ __device__ __forceinline__ void or_bits_grouped(uint32_t *bm, bool on, int32_t v
 // level's chunk queue (long column).  `grouped` combines the bitmap updates of
 // lanes that hold vertices of the same word (the pull form reaches vertices in
 // ascending order).
-__device__ __forceinline__ void append_next(const LevelParams &P, const LevelPtrs &L, OutLds &O,
+__device__ __forceinline__ void append_next(const LevelParams &P, LevelPtrs &L, OutLds &O,
                                             bool owner, int32_t i, bool grouped = false,
                                             int32_t kr0 = -1, int32_t kr1 = -1) {
     const unsigned long long any = __ballot(owner);
@@ -361,10 +367,7 @@ __device__ __forceinline__ void append_next(const LevelParams &P, const LevelPtr
         O.lv[slot] = i;
         O.lch[slot] = (deg + P.chunk - 1u) / P.chunk;
     }
-    if (P.stats) {
-        const unsigned long long d = wave_sum64(owner ? (unsigned long long)deg : 0ull);
-        if (lane == 0) atomicAdd(&O.sdf, d);
-    }
+    if (owner) L.deg_sum += deg;
 }
 
 struct TileLds {
@@ -405,7 +408,7 @@ __device__ __forceinline__ bool unmasked(int32_t i, uint32_t mw) {
     return (i >= 0) && !((mw >> (i & 31)) & 1u);
 }
 
-__device__ __forceinline__ void settle4(const LevelParams &P, const LevelPtrs &L, OutLds &O,
+__device__ __forceinline__ void settle4(const LevelParams &P, LevelPtrs &L, OutLds &O,
                                         int32_t i0, int32_t j0, uint32_t m0, int32_t i1, int32_t j1,
                                         uint32_t m1, int32_t i2, int32_t j2, uint32_t m2, int32_t i3,
                                         int32_t j3, uint32_t m3) {
@@ -479,7 +482,7 @@ __device__ __forceinline__ void settle4(const LevelParams &P, const LevelPtrs &L
 // of the degrees places the tile's entries on one line, lane t takes entries
 // t, t + 256, ... and finds its column by binary search over the prefix.
 // Consecutive lanes read consecutive entries of a column: coalesced.
-__device__ __forceinline__ void expand_tile(const LevelParams &P, const LevelPtrs &L, TileLds &T, OutLds &O,
+__device__ __forceinline__ void expand_tile(const LevelParams &P, LevelPtrs &L, TileLds &T, OutLds &O,
                             int32_t j, int32_t r0, uint32_t deg) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const uint32_t incl = wave_incl_scan(deg);
@@ -515,7 +518,7 @@ __device__ __forceinline__ void expand_tile(const LevelParams &P, const LevelPtr
 // One chunk of a long frontier column: every lane of the block takes entries
 // of the chunk in turn.  Chunk 0 of a column also moves the column into B_{k+1}
 // (unless the level copies B_k word by word).
-__device__ __forceinline__ void expand_chunk(const LevelParams &P, const LevelPtrs &L, OutLds &O, uint32_t c,
+__device__ __forceinline__ void expand_chunk(const LevelParams &P, LevelPtrs &L, OutLds &O, uint32_t c,
                              uint32_t nlong, bool carry) {
     __shared__ HeavyItem s_it;
     (void)nlong;
@@ -564,19 +567,23 @@ __device__ __forceinline__ void carry_words(const LevelParams &P, const LevelPtr
 
 // Push: work items are the tiles of the short-column list followed by the
 // chunks of the long columns, dealt round-robin to the blocks.
-__device__ __forceinline__ void push_level(const LevelParams &P, const LevelPtrs &L, TileLds &T, OutLds &O,
+__device__ __forceinline__ void push_level(const LevelParams &P, LevelPtrs &L, TileLds &T, OutLds &O,
                            uint32_t nreg, uint32_t nlong, uint32_t nchunks, uint32_t bid,
                            uint32_t nblocks) {
     const bool wc = word_carry(P, nreg + nlong);
     if (wc) carry_words(P, L, bid, nblocks);
-    const uint32_t ntiles = (nreg + kBlock - 1) / kBlock;
+    // columns per tile: kBlock, or a quarter of that while the whole list is
+    // still one step of the grid (a short list then spreads over four times the
+    // workgroups and a tile's entries mostly take one round)
+    const uint32_t cols = (nreg + kBlock / 4 - 1) / (kBlock / 4) + nchunks <= nblocks ? kBlock / 4 : kBlock;
+    const uint32_t ntiles = (nreg + cols - 1) / cols;
     const uint32_t items = ntiles + nchunks;
     for (uint32_t it = bid; it < items; it += nblocks) {
         if (it < ntiles) {
-            const uint32_t pos = it * kBlock + threadIdx.x;
+            const uint32_t pos = it * cols + threadIdx.x;
             int32_t j = -1, r0 = 0;
             uint32_t deg = 0;
-            if (pos < nreg) {
+            if (threadIdx.x < cols && pos < nreg) {
                 const QEnt e = L.q_cur[pos];
                 j = e.v;
                 r0 = e.r0;
@@ -593,7 +600,7 @@ __device__ __forceinline__ void push_level(const LevelParams &P, const LevelPtrs
 // Push with the frontier read from the bitmap: items are 256-word groups of
 // the frontier bitmap (one frontier column per thread per round, lowest bit
 // first) followed by the chunks of the long columns.
-__device__ __forceinline__ void bitmap_level(const LevelParams &P, const LevelPtrs &L, TileLds &T, OutLds &O,
+__device__ __forceinline__ void bitmap_level(const LevelParams &P, LevelPtrs &L, TileLds &T, OutLds &O,
                              uint32_t nlong, uint32_t nchunks, uint32_t bid, uint32_t nblocks) {
     const uint32_t ngroups = (P.words + kBlock - 1) / kBlock;
     const uint32_t items = ngroups + nchunks;
@@ -877,35 +884,76 @@ __device__ __forceinline__ Closed finish_level(const LevelParams &P, uint32_t k,
     return c;
 }
 
-__device__ __forceinline__ uint32_t frontier_size(const BfsState *st, uint32_t slot) {
-    return st->nf[slot] + (uint32_t)st->heavy[slot];
-}
+// One workgroup's small levels: the frontier's columns (vertex, first entry,
+// entries before it), and the network's weights.
+constexpr uint32_t kSmall = 4 * kBlock;       // columns and entries of a small level at most
+struct SmallLds {
+    int32_t v[kSmall];
+    int32_t r0[kSmall];
+    uint32_t pre[kSmall];
+    uint32_t wsum[kBlock / 64];
+    uint32_t n, nlong;
+    float w[kMlpTotal];
+};
 
-// The level kernels' LDS: one level's tiles, or, once the level is done, the
-// network's weights for the next level's decision.
+// The level kernels' LDS: one level's tiles and staged output; a workgroup's
+// small levels; once the level is done, the network's weights for the next
+// level's decision.
 union LevelLds {
-    TileLds t;                                // push / push-bitmap
-    PullLds p;                                // pull
+    struct {
+        union {
+            TileLds t;                        // push / push-bitmap
+            PullLds p;                        // pull
+        };
+        OutLds out;
+    } big;
+    SmallLds small;
     float w[kMlpTotal];                       // decision of the next level's form
 };
 
-__device__ __forceinline__ void level_body(const LevelParams &P, uint32_t k, uint32_t bid, uint32_t nblocks,
-                                           LevelLds &lds) {
-    TileLds &tl = lds.t;
-    PullLds &pl = lds.p;
-    __shared__ OutLds ol;
-    const BfsState *st = P.st;
+// The counters of level k, read together with every other slot's (one round
+// trip instead of one for the level and one for its slot).
+struct Counters {
+    uint32_t nf, nf_before;                   // short columns of F_k; all of F_{k-1}
+    unsigned long long heavy, sdf;
+    uint32_t variant;
+};
+
+template <typename T>
+__device__ __forceinline__ T ring(T a, T b, T c, T d, uint32_t i) {
+    return i == 0 ? a : (i == 1 ? b : (i == 2 ? c : d));
+}
+
+__device__ __forceinline__ Counters read_counters(const BfsState *st, uint32_t &k) {
+    k = st->level;
+    const uint32_t f0 = st->nf[0], f1 = st->nf[1], f2 = st->nf[2], f3 = st->nf[3];
+    const unsigned long long h0 = st->heavy[0], h1 = st->heavy[1], h2 = st->heavy[2], h3 = st->heavy[3];
+    const unsigned long long s0 = st->sdf[0], s1 = st->sdf[1], s2 = st->sdf[2], s3 = st->sdf[3];
+    Counters c;
+    c.variant = st->variant;
+    const uint32_t i = k & 3, j = (k + 3) & 3;
+    c.nf = ring(f0, f1, f2, f3, i);
+    c.heavy = ring(h0, h1, h2, h3, i);
+    c.sdf = ring(s0, s1, s2, s3, i);
+    c.nf_before = k == 0 ? 0u : ring(f0, f1, f2, f3, j) + (uint32_t)ring(h0, h1, h2, h3, j);
+    return c;
+}
+
+__device__ __forceinline__ void level_body(const LevelParams &P, uint32_t k, const Counters &c, uint32_t bid,
+                                           uint32_t nblocks, LevelLds &lds) {
+    TileLds &tl = lds.big.t;
+    PullLds &pl = lds.big.p;
+    OutLds &ol = lds.big.out;
     LevelPtrs L = level_ptrs(P, k);
     // short-circuit claims on the levels whose frontier columns hold at least
     // n / 8 entries (there atomics bound the level, and the rows they reach
     // find their parent one level up quickly); the min-select elsewhere
-    L.sc = (P.policy == kShortCircuit) && st->sdf[L.cs] * 8ull >= (unsigned long long)P.n;
-    const uint32_t nreg = st->nf[L.cs];
-    const unsigned long long hp = st->heavy[L.cs];
-    const uint32_t nlong = (uint32_t)hp, nchunks = (uint32_t)(hp >> 32);
+    L.sc = (P.policy == kShortCircuit) && c.sdf * 8ull >= (unsigned long long)P.n;
+    const uint32_t nreg = c.nf;
+    const uint32_t nlong = (uint32_t)c.heavy, nchunks = (uint32_t)(c.heavy >> 32);
     // small level: fewer than 8192 short columns and under 2^20 entries in long ones
     L.pre = !(nreg < 8192u && (unsigned long long)nchunks * P.chunk < (1ull << 20));
-    const uint32_t v = level_form(P, st->variant);     // decided before the launch
+    const uint32_t v = level_form(P, c.variant);       // decided before the launch
     if (bid == 0 && threadIdx.x == 0) {
         BfsState *w = P.st;
         const uint32_t fs = (k + 2) & 3;     // slot of level k+2: free since level k-2
@@ -1025,7 +1073,6 @@ __global__ __launch_bounds__(kBlock) void k_init_roots(LevelParams P, int32_t nr
     if (lane_id() == 0 && c) {
         atomicAdd(&P.st->visited_deg, d);
         atomicAdd(&P.st->visited_cnt, (uint32_t)c);
-        if (!P.stats) atomicAdd(&P.st->sdf[0], d);
     }
     out_flush(P, L, ol, true);
 }
@@ -1095,16 +1142,254 @@ __device__ __forceinline__ void close_level(const LevelParams &P, uint32_t k, ui
     if (threadIdx.x == 0) report_status(P, k + 1, c.nf);
 }
 
+// A level of at most kSmall columns and kSmall entries, none of them a long
+// column, in the push form: one workgroup's work (four entries a thread).
+// With frontier bitmaps the level before has to be as small, so that its bits
+// can be cleared from its list.  Every workgroup of a launch finds the same.
+__device__ __forceinline__ bool small_level(const LevelParams &P, uint32_t k, const Counters &c) {
+    return P.small && level_form(P, c.variant) == kPush && P.policy != kShortCircuit && (uint32_t)c.heavy == 0u &&
+           c.nf <= kSmall && c.sdf <= (unsigned long long)kSmall && (!P.maintain_fb || c.nf_before <= kSmall);
+}
+
+constexpr uint32_t kSmallLevels = 4096;       // small levels in one launch at most
+
+// Small levels, one after the other, by one workgroup, from level k until the
+// next one is not small or not a push (or the search ends).  A level costs the
+// chain entry - mask - atomicMin - column bounds and three workgroup barriers;
+// as a launch it also pays the launch, the state and list reads, the list's
+// counter, every workgroup's arrival and the close (Erdos-Renyi n = 16,384: 16.6
+// us a level).  The masks are read coherently and a level's new bits set (in
+// both visited bitmaps: either one is then B_k) after every thread's tests.
+// Nothing in the state changes while the other workgroups of the launch may
+// still read it: the outcome goes to st->small and the last to arrive takes it
+// over (take_small).
+__device__ __forceinline__ void small_levels(const LevelParams &P, uint32_t k, const Counters &c, SmallLds &S) {
+    BfsState *st = P.st;
+    const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    uint32_t *fbk = k % 3 == 0 ? P.fb[0] : (k % 3 == 1 ? P.fb[1] : P.fb[2]);
+    uint32_t *fbo = k % 3 == 0 ? P.fb[2] : (k % 3 == 1 ? P.fb[0] : P.fb[1]);
+    const QEnt *q = (k & 1) ? P.q[1] : P.q[0], *qo = (k & 1) ? P.q[0] : P.q[1];
+    const HeavyItem *ho = (k & 1) ? P.hl[0] : P.hl[1];
+    uint32_t *vbn = (k & 1) ? P.vb[0] : P.vb[1];
+    const bool net = (P.policy == kLearned) && P.mlp != nullptr;
+    if (net)
+        for (uint32_t i = tid; i < (uint32_t)kMlpTotal; i += kBlock) S.w[i] = P.mlp[i];
+    // the level's columns into LDS; its bits into the other bitmap, its own and
+    // the former level's frontier bits cleared (set again on the way out)
+    uint32_t nf = c.nf;
+    for (uint32_t i = tid; i < nf; i += kBlock) {
+        const QEnt e = q[i];
+        S.v[i] = e.v;
+        S.r0[i] = e.r0;
+        S.pre[i] = (uint32_t)(e.r1 - e.r0);
+        atomicOr(&vbn[(uint32_t)e.v >> 5], 1u << (e.v & 31));
+        if (P.maintain_fb) fbk[(uint32_t)e.v >> 5] = 0u;
+    }
+    if (P.maintain_fb && k != 0) {
+        const uint32_t slot = (k + 3) & 3, ns = st->nf[slot];
+        for (uint32_t i = tid; i < c.nf_before; i += kBlock) {
+            const int32_t v = i < ns ? qo[i].v : ho[i - ns].v;
+            fbo[(uint32_t)v >> 5] = 0u;
+        }
+    }
+    uint32_t visited = st->visited_cnt;
+    unsigned long long vdeg = st->visited_deg, sdf = c.sdf;
+    uint32_t form = kPush, n_long = 0;
+    for (uint32_t done = 0;; ++done) {
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);            // the bits above are performed
+        __syncthreads();
+        if (tid == 0) {
+            S.n = 0;
+            S.nlong = 0;
+        }
+        // exclusive prefix of the columns' entry counts (kSmall / kBlock = 4 a thread)
+        uint32_t d[4], mine = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            d[j] = 4 * tid + j < nf ? S.pre[4 * tid + j] : 0u;
+            mine += d[j];
+        }
+        const uint32_t incl = wave_incl_scan(mine);
+        if (lane == 63) S.wsum[wave] = incl;
+        __syncthreads();
+        uint32_t at = incl - mine, total = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kBlock / 64; ++w) {
+            at += w < wave ? S.wsum[w] : 0u;
+            total += S.wsum[w];
+        }
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            if (4 * tid + j < nf) S.pre[4 * tid + j] = at;
+            at += d[j];
+        }
+        __syncthreads();
+        // the entries, four a thread
+        int32_t i[4], jj[4];
+        bool on[4];
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            const uint32_t e = tid + t * kBlock;
+            on[t] = e < total;
+            uint32_t lo = 0, hi = nf - 1u;                  // the last column with pre <= e
+            if (on[t]) {
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi + 1) >> 1;
+                    if (S.pre[mid] <= e) lo = mid;
+                    else hi = mid - 1;
+                }
+            }
+            jj[t] = on[t] ? S.v[lo] : 0;
+            i[t] = 0;
+            if (on[t]) i[t] = P.out_idx[S.r0[lo] + (int32_t)(e - S.pre[lo])];
+        }
+        uint32_t m[4], old[4];
+        const uint32_t *vb = P.vb[0];
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) m[t] = on[t] ? ld_agent(&vb[(uint32_t)i[t] >> 5]) : 0xFFFFFFFFu;
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            on[t] = on[t] && !((m[t] >> (i[t] & 31)) & 1u);
+            old[t] = 0u;
+            if (on[t]) old[t] = atomicMin(&P.parent[i[t]], (uint32_t)jj[t]);
+        }
+        int32_t b0[4], b1[4];
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            on[t] = on[t] && old[t] == 0xFFFFFFFFu;         // reached here first
+            b0[t] = on[t] ? P.out_ptr[i[t]] : 0;
+            b1[t] = on[t] ? P.out_ptr[i[t] + 1] : 0;
+        }
+        __syncthreads();                                    // every test of the level is done
+        uint32_t dsum = 0;
+#pragma unroll
+        for (uint32_t t = 0; t < 4; ++t) {
+            if (!on[t]) continue;
+            const uint32_t bit = 1u << (i[t] & 31), w = (uint32_t)i[t] >> 5;
+            atomicOr(&P.vb[0][w], bit);
+            atomicOr(&P.vb[1][w], bit);
+            P.level[i[t]] = (int32_t)(k + 1);
+            const uint32_t pos = atomicAdd(&S.n, 1u), deg = (uint32_t)(b1[t] - b0[t]);
+            S.v[pos] = i[t];
+            S.r0[pos] = b0[t];
+            S.pre[pos] = deg;
+            dsum += deg;
+            if (deg >= P.heavy_min) atomicAdd(&S.nlong, 1u);
+        }
+        dsum = wave_sum(dsum);                              // below 2^31 over the block
+        if (lane == 0) S.wsum[wave] = dsum;
+        __syncthreads();
+        const uint32_t nn = S.n;
+        n_long = S.nlong;
+        unsigned long long sn = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < kBlock / 64; ++w) sn += S.wsum[w];
+        visited += nn;
+        vdeg += sn;
+        nf = nn;
+        sdf = sn;
+        ++k;
+        if (nf == 0) break;
+        form = kPush;
+        if (P.policy == kLearned || P.policy == kHeuristic) {
+            __syncthreads();                                // wsum is read
+            if (tid < 64) {
+                const uint32_t f = decide_wave(P, S.w, k, (float)nf, (float)sdf, (float)((uint32_t)P.n - visited),
+                                               (float)((unsigned long long)P.nnz - vdeg));
+                if (tid == 0) S.wsum[0] = f;
+            }
+            __syncthreads();
+            form = S.wsum[0];
+        }
+        if (form != kPush || n_long != 0 || sdf > (unsigned long long)kSmall || done + 1 == kSmallLevels) break;
+    }
+    // F_k's columns to the global lists (long ones with their chunks), its bits
+    // to the frontier bitmap
+    uint32_t *fbx = k % 3 == 0 ? P.fb[0] : (k % 3 == 1 ? P.fb[1] : P.fb[2]);
+    QEnt *qx = (k & 1) ? P.q[1] : P.q[0];
+    HeavyItem *hx = (k & 1) ? P.hl[1] : P.hl[0];
+    uint32_t *cx = (k & 1) ? P.cmap[1] : P.cmap[0];
+    __syncthreads();
+    if (tid == 0) {
+        S.n = 0;
+        S.nlong = 0;
+        S.wsum[0] = 0;                                      // chunks
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < nf; i += kBlock) {
+        const int32_t v = S.v[i];
+        const uint32_t deg = S.pre[i];
+        if (P.maintain_fb) atomicOr(&fbx[(uint32_t)v >> 5], 1u << (v & 31));
+        if (deg >= P.heavy_min) {
+            const uint32_t nch = (deg + P.chunk - 1u) / P.chunk;
+            const uint32_t pos = atomicAdd(&S.nlong, 1u), cb = atomicAdd(&S.wsum[0], nch);
+            HeavyItem it;
+            it.v = v;
+            it.chunk_base = cb;
+            hx[pos] = it;
+            for (uint32_t x = 0; x < nch; ++x) cx[cb + x] = pos;
+        } else {
+            QEnt e;
+            e.v = v;
+            e.r0 = S.r0[i];
+            e.r1 = S.r0[i] + (int32_t)deg;
+            e.pad = 0;
+            qx[atomicAdd(&S.n, 1u)] = e;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        SmallOut &o = st->small;
+        __hip_atomic_store(&o.level, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&o.variant, form, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&o.nf, S.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&o.visited_cnt, visited, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&o.visited_deg, vdeg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&o.sdf, sdf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&o.heavy, (unsigned long long)S.nlong | ((unsigned long long)S.wsum[0] << 32),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// The state as the small levels left it (one thread, every workgroup of the
+// launch has arrived): the next level's counters in its slot, the other
+// slots empty (F_{k-1}'s frontier bits are cleared already).
+__device__ __forceinline__ void take_small(const LevelParams &P) {
+    BfsState *st = P.st;
+    const SmallOut &o = st->small;
+    const uint32_t k = ld_agent(&o.level), nf = ld_agent(&o.nf), variant = ld_agent(&o.variant);
+    const uint32_t vc = ld_agent(&o.visited_cnt);
+    const unsigned long long vd = ld_agent64(&o.visited_deg), sdf = ld_agent64(&o.sdf), hv = ld_agent64(&o.heavy);
+    for (uint32_t r = 0; r < (uint32_t)kRing; ++r) {
+        const bool here = r == (k & 3);
+        st->nf[r] = here ? nf : 0u;
+        st->heavy[r] = here ? hv : 0ull;
+        st->sdf[r] = here ? sdf : 0ull;
+    }
+    st->visited_cnt = vc;
+    st->visited_deg = vd;
+    st->variant = variant;
+    st->level = k;
+    report_status(P, k, nf + (uint32_t)hv);
+}
+
 // One level: the level body on every block, then the last block to finish
-// closes the level, so a level is one launch.  Launches after the end of the
-// search (empty frontier) return at once.
+// closes the level, so a level is one launch.  A small level, and those after
+// it while they are small, is the first block's alone.  Launches after the end
+// of the search (empty frontier) return at once.
 __global__ __launch_bounds__(kBlock, 8) void k_level(LevelParams P) {
     __shared__ LevelLds lds;
     BfsState *st = P.st;
-    const uint32_t k = st->level;
-    const uint32_t nf = frontier_size(st, k & 3);
+    uint32_t k;
+    const Counters c = read_counters(st, k);
+    const uint32_t nf = c.nf + (uint32_t)c.heavy;
     if (nf == 0) return;
-    level_body(P, k, blockIdx.x, gridDim.x, lds);
+    if (small_level(P, k, c)) {
+        if (blockIdx.x == 0) small_levels(P, k, c, lds.small);
+        if (last_to_arrive(st, gridDim.x) && threadIdx.x == 0) take_small(P);
+        return;
+    }
+    level_body(P, k, c, blockIdx.x, gridDim.x, lds);
     if (last_to_arrive(st, gridDim.x)) close_level(P, k, nf, lds.w, false);
 }
 
@@ -1199,9 +1484,14 @@ __global__ __launch_bounds__(kBlock) void k_persistent(LevelParams P) {
     const uint32_t nb = gridDim.x;
     for (;;) {
         const uint32_t k = ld_agent(&st->level);
-        const uint32_t nf = ld_agent(&st->nf[k & 3]) + (uint32_t)ld_agent64(&st->heavy[k & 3]);
+        Counters c{};
+        c.nf = ld_agent(&st->nf[k & 3]);
+        c.heavy = ld_agent64(&st->heavy[k & 3]);
+        c.sdf = ld_agent64(&st->sdf[k & 3]);
+        c.variant = ld_agent(&st->variant);
+        const uint32_t nf = c.nf + (uint32_t)c.heavy;
         if (nf == 0) break;
-        level_body(P, k, blockIdx.x, nb, lds);
+        level_body(P, k, c, blockIdx.x, nb, lds);
         if (!level_barrier(P, k, nf, nb, &s_role, lds.w)) break;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
