@@ -79,6 +79,7 @@ struct bfs_graph {
     uint32_t *sl_occ = nullptr;       // per slice, the vertices whose part there is short and not empty
     bfsi::SlChunk *sl_chunks = nullptr;
     uint32_t sl_S = 0, sl_sw = 0;
+    uint32_t near_deg = 0;            // mean out-degree of a list entry: sum d^2 / sum d
     uint32_t sl_chunk_off[bfsi::kSlMaxSlices + 1] = {};
     // a thin graph's out-lists in rows of thin_width entries (4 or 8), -1 past
     // a list's end, for the claim-word push's deep form
@@ -186,7 +187,6 @@ void free_graph(bfs_graph *g) {
     if (g->sl_seg) (void)hipFree(g->sl_seg);
     if (g->sl_occ) (void)hipFree(g->sl_occ);
     if (g->sl_chunks) (void)hipFree(g->sl_chunks);
-    if (g->thin_rows) (void)hipFree(g->thin_rows);
     delete g;
 }
 
@@ -319,26 +319,21 @@ bfs_status build_degree_order(bfs_graph *g, const std::vector<int32_t> &ptr, con
 }
 
 // The out-lists, padded with zeros to a multiple of four entries plus four, so
-// that the sliced push may read any list in aligned 16-byte quads.
-bfs_status upload_padded(int32_t **dst, const std::vector<int32_t> &idx, size_t &bytes) {
+// that the sliced push may read any list in aligned 16-byte quads; behind them,
+// in the same allocation, a thin graph's fixed-width rows, made on the device
+// from the lists (the null stream: later copies wait for them).
+bfs_status upload_lists(bfs_graph *g, const std::vector<int32_t> &idx) {
     const size_t cnt = ((idx.size() + 3) & ~size_t(3)) + 4;
-    if (hipMalloc((void **)dst, cnt * 4) != hipSuccess) return fail(BFS_ENOMEM, "hipMalloc(%zu) failed", cnt * 4);
-    bytes += cnt * 4;
-    HIP_TRY(hipMemset(*dst, 0, cnt * 4));
-    if (!idx.empty()) HIP_TRY(hipMemcpy(*dst, idx.data(), idx.size() * 4, hipMemcpyHostToDevice));
-    return BFS_OK;
-}
-
-// A thin graph's fixed-width rows, made on the device from its uploaded lists.
-bfs_status build_thin_rows(bfs_graph *g) {
-    if (g->max_deg > kClaimMaxDeg) return BFS_OK;
-    const uint32_t width = g->max_deg <= 4u ? 4u : 8u;
-    const size_t b = (size_t)g->n * width * sizeof(int32_t);
-    if (hipMalloc((void **)&g->thin_rows, b) != hipSuccess) return fail(BFS_ENOMEM, "hipMalloc(%zu) failed", b);
+    const uint32_t width = g->max_deg > kClaimMaxDeg ? 0u : (g->max_deg <= 4u ? 4u : 8u);
+    const size_t b = (cnt + (size_t)g->n * width) * 4;
+    if (hipMalloc((void **)&g->out_idx, b) != hipSuccess) return fail(BFS_ENOMEM, "hipMalloc(%zu) failed", b);
     g->bytes += b;
-    HIP_TRY(launch_cw_rows(g->out_ptr, g->out_idx, g->n, (int32_t)width, g->thin_rows, nullptr));
-    HIP_TRY(hipStreamSynchronize(nullptr));
+    HIP_TRY(hipMemset(g->out_idx, 0, cnt * 4));
+    if (!idx.empty()) HIP_TRY(hipMemcpy(g->out_idx, idx.data(), idx.size() * 4, hipMemcpyHostToDevice));
+    if (width == 0) return BFS_OK;
+    g->thin_rows = g->out_idx + cnt;
     g->thin_width = width;
+    HIP_TRY(launch_cw_rows(g->out_ptr, g->out_idx, g->n, (int32_t)width, g->thin_rows, nullptr));
     return BFS_OK;
 }
 
@@ -1285,6 +1280,7 @@ SlParams make_sl_params(bfs_graph *g, int32_t *level, int32_t *parent, void *ws,
     P.sw = g->sl_sw;
     P.words = g->sl_S * g->sl_sw;
     P.streams = sl_grid(g) / g->sl_S;
+    P.near_deg = g->near_deg;
     P.seg = g->sl_seg;
     P.occ = g->sl_occ;
     P.out_idx4 = (const int4 *)g->out_idx;
@@ -1426,13 +1422,19 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
     if (!g) return fail(BFS_ENOMEM, "host allocation failed");
     g->n = n;
     g->nnz = (uint32_t)ptr[n];
-    for (int32_t v = 0; v < n; ++v) g->max_deg = std::max<uint32_t>(g->max_deg, (uint32_t)(ptr[v + 1] - ptr[v]));
+    uint64_t squares = 0;
+    for (int32_t v = 0; v < n; ++v) {
+        const uint32_t d = (uint32_t)(ptr[v + 1] - ptr[v]);
+        g->max_deg = std::max(g->max_deg, d);
+        squares += (uint64_t)d * d;
+    }
+    g->near_deg = g->nnz ? (uint32_t)(squares / g->nnz) : 0u;
     g->directed = directed;
     if (hipGetDevice(&g->device) != hipSuccess) { delete g; return fail(BFS_EHIP, "hipGetDevice failed"); }
     if (hipDeviceGetAttribute(&g->cus, hipDeviceAttributeMultiprocessorCount, g->device) != hipSuccess)
         g->cus = 0;                           // launch sizes then assume 256 compute units
     bfs_status st = upload(&g->out_ptr, ptr.data(), ptr.size(), g->bytes);
-    if (st == BFS_OK) st = upload_padded(&g->out_idx, idx, g->bytes);
+    if (st == BFS_OK) st = upload_lists(g, idx);
     if (st == BFS_OK && directed) {
         st = upload(&g->in_ptr, iptr.data(), iptr.size(), g->bytes);
         if (st == BFS_OK) st = upload(&g->in_idx, iidx.data(), iidx.size(), g->bytes);
@@ -1443,7 +1445,6 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
     try {
         if (st == BFS_OK) st = build_long(n, ptr, &g->lo, &g->lomap, g->nlo, g->nlo_chunks, g->bytes);
         if (st == BFS_OK) st = build_slices(g, ptr, idx);
-        if (st == BFS_OK) st = build_thin_rows(g);
         if (st == BFS_OK && g->thin_rows) g->slow_growth = grows_slowly(n, ptr, idx);
         if (st == BFS_OK && directed) {
             st = build_long(n, iptr, &g->li, &g->limap, g->nli, g->nli_chunks, g->bytes);
@@ -1463,6 +1464,8 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
     } catch (const std::bad_alloc &) {
         st = fail(BFS_ENOMEM, "host allocation failed");
     }
+    if (st == BFS_OK && g->thin_rows && hipStreamSynchronize(nullptr) != hipSuccess)
+        st = fail(BFS_EHIP, "making the fixed-width rows failed");
     if (st != BFS_OK) {
         std::string keep = g_detail;
         free_graph(g);

@@ -61,11 +61,19 @@ struct SlLds {
     unsigned long long red[kSlWaves][3];      // per-wave sums for the block reduction
 };
 
-// A level with at most this many frontier vertices (an upper bound: the claim
-// count of the level that built it) runs eager.
-__device__ __forceinline__ bool eager_level(uint32_t nclaim, int32_t n) {
+// A level runs eager when its frontier holds few vertices (nclaim, an upper
+// bound: the claim count of the level that built it) and, at `degree` entries
+// each, at most kEagerEntries entries: an eager pair costs two memory-side
+// atomics (about 27 G/s), a lazy level some 20 us for its slices whatever its
+// size.  `degree` is the mean degree of the level before (the vertices a search
+// reaches first have the largest degrees), at the roots the mean degree of a
+// neighbour.  By the vertices alone a hub level of 8,000 vertices and 20 M
+// entries ran eager (R-MAT s22, from a source whose level 2 holds that many: 567
+// us, lazy 130).
+constexpr unsigned long long kEagerEntries = 1ull << 19;
+__device__ __forceinline__ bool eager_level(uint32_t nclaim, unsigned long long degree, int32_t n) {
     const uint32_t lim = ((uint32_t)n >> 9) > 256u ? ((uint32_t)n >> 9) : 256u;
-    return nclaim <= lim;
+    return nclaim <= lim && nclaim * degree <= kEagerEntries;
 }
 
 // Orders a wave's LDS writes before the same wave's later LDS reads by other lanes.
@@ -451,6 +459,8 @@ __device__ __forceinline__ void sl_close(const SlParams &P, uint32_t k) {
     const uint32_t vc = st->visited_cnt + nf;
     const unsigned long long vd = st->visited_deg + deg;
     st->nclaim[(k + 1) & 3] = claims;
+    const unsigned long long mean = nf ? deg / nf : 0ull;
+    st->eager[(k + 1) & 3] = eager_level(claims, k == 0 && P.near_deg > mean ? P.near_deg : mean, P.n) ? 1u : 0u;
     st->nf[k & 3] = nf;
     st->sdf[k & 3] = deg;
     st->visited_cnt = vc;
@@ -501,6 +511,7 @@ __global__ __launch_bounds__(256) void k_sl_init(SlParams P, int32_t single_root
             st->sdf[r] = 0ull;
         }
         st->nclaim[0] = nroots;
+        st->eager[0] = eager_level(nroots, 1ull, P.n) ? 1u : 0u;
         st->visited_cnt = 0;
         st->visited_deg = 0ull;
         for (int g = 0; g < kBarGroups; ++g) {
@@ -588,9 +599,9 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
     const uint32_t k = st->level;
     const uint32_t nck = st->nclaim[k & 3];
     if (nck == 0u) return;
-    const bool eager = eager_level(nck, P.n);
+    const bool eager = st->eager[k & 3] != 0u;
     // F_k was settled by level k - 1 when that level ran eager
-    const bool settle_now = (k == 0) || !eager_level(st->nclaim[(k + 3) & 3], P.n);
+    const bool settle_now = (k == 0) || st->eager[(k + 3) & 3] == 0u;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const uint32_t b = blockIdx.x;
     const uint32_t S = P.S;
