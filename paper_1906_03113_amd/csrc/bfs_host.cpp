@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -616,6 +617,38 @@ bfs_status wait_progress(const HostSlot *hs, hipStream_t s, bool &done, uint32_t
     level = hs->h[0];
     done = (hs->h[1] == 0);
     return BFS_OK;
+}
+
+// Wait until the device has reported level `want` or the end of the search (an
+// empty frontier); `frontier` receives the size of the reported level's
+// frontier.  The slot is polled: its one 64-bit word (level, size) arrives a
+// microsecond or two after the level's last workgroup has written it, where
+// waiting for the stream takes the kernel's end and the completion signal as
+// well.  Now and then the stream is asked, so that an error in it (or a stream
+// that ended without the report) ends the wait too.
+constexpr uint32_t kNoLevel = 0xFFFFFFFFu;       // no level reported yet
+
+bfs_status wait_level(const HostSlot *hs, hipStream_t s, uint32_t want, uint32_t &frontier) {
+    const volatile uint64_t *slot = (const volatile uint64_t *)hs->h;
+    for (uint32_t spin = 1;; ++spin) {
+        const uint64_t x = *slot;
+        const uint32_t level = (uint32_t)x, size = (uint32_t)(x >> 32);
+        if (level != kNoLevel && (size == 0 || level >= want)) {
+            std::atomic_thread_fence(std::memory_order_acquire);
+            frontier = size;
+            return BFS_OK;
+        }
+        if (spin % 4096u == 0) {
+            const hipError_t e = hipStreamQuery(s);
+            if (e == hipErrorNotReady) continue;
+            if (e != hipSuccess) return fail(BFS_EHIP, "the search's launches failed: %s", hipGetErrorString(e));
+            const uint64_t y = *slot;
+            const uint32_t l2 = (uint32_t)y, n2 = (uint32_t)(y >> 32);
+            if (l2 != kNoLevel && (n2 == 0 || l2 >= want)) continue;
+            return fail(BFS_EHIP, "the search stopped at level %u before level %u", l2, want);
+        }
+        __builtin_ia32_pause();
+    }
 }
 
 // The host loop and the captured-graph loop around a level launch: `launch`
@@ -1749,20 +1782,20 @@ static hipError_t ms_level(MsLevel &p, uint32_t k, bool pull, uint32_t frontier,
         // time, each range's masks resident in the XCDs' L2
         for (uint32_t r = 0; r < p.rp_ranges; ++r)
             if ((e = launch_ms_rpull(p, k, r, grid, s)) != hipSuccess) return e;
-        return launch_ms(p, 5, k, grid, s);
+        return launch_ms(p, kMsReport, k, grid, s);
     }
     if (pull) {
         // a sparse union frontier: the pull tests its bitmap before each
         // mask gather (most in-neighbours are then skipped on chip)
         p.use_fbits = ((uint64_t)frontier << kMsFbitsShift) <= (uint64_t)p.n ? 1u : 0u;
-        if (p.use_fbits && (e = launch_ms(p, 8, k, grid, s)) != hipSuccess) return e;
-        if ((e = launch_ms(p, 4, k, grid, s)) != hipSuccess) return e;
-        if (p.long_split && (e = launch_ms(p, 9, k, grid, s)) != hipSuccess) return e;
-        if ((e = launch_ms(p, 6, k, grid, s)) != hipSuccess) return e;
-        return launch_ms(p, 5, k, grid, s);
+        if (p.use_fbits && (e = launch_ms(p, kMsFbits, k, grid, s)) != hipSuccess) return e;
+        if ((e = launch_ms(p, kMsWide, k, grid, s)) != hipSuccess) return e;
+        if ((e = launch_ms(p, kMsShortRows, k, grid, s)) != hipSuccess) return e;
+        if (p.long_split && (e = launch_ms(p, kMsRest, k, grid, s)) != hipSuccess) return e;
+        return launch_ms(p, kMsClose, k, grid, s);
     }
-    if ((e = launch_ms(p, 2, k, grid, s)) != hipSuccess) return e;
-    return launch_ms(p, 3, k, grid, s);
+    if ((e = launch_ms(p, kMsPush, k, grid, s)) != hipSuccess) return e;
+    return launch_ms(p, kMsSettle, k, grid, s);
 }
 
 // The multi-source parameters over the caller's vertex order instead of the
@@ -1835,12 +1868,14 @@ static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sour
     const uint32_t pol = opt ? opt->variant : kPush;
     const bool learned = pol == kLearned && opt->selector != nullptr;
     p.mlp = learned ? opt->selector : nullptr;
-    HIP_TRY(launch_ms(p, 0, 0, grid, s));
-    HIP_TRY(launch_ms(p, 1, 0, grid, s));
+    hs->h[0] = kNoLevel;
+    hs->h[1] = 1;
+    HIP_TRY(launch_ms(p, kMsClear, 0, grid, s));
+    HIP_TRY(launch_ms(p, kMsRoots, 0, grid, s));
     uint32_t k = 0, frontier = 1, dir = 0;
     if (learned) {
-        HIP_TRY(launch_ms(p, 10, 0, grid, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        st = wait_level(hs, s, 0u, frontier);
+        if (st != BFS_OK) return st;
         dir = hs->h[2];
     }
     for (;; ++k) {
@@ -1859,19 +1894,15 @@ static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sour
             }
             k += group - 1;
         }
-        if (learned) HIP_TRY(launch_ms(p, 10, k + 1, grid, s));   // the next level's direction
-        bool done = false;
-        uint32_t lv = 0;
-        st = wait_progress(hs, s, done, lv);
+        st = wait_level(hs, s, k + 1, frontier);
         if (st != BFS_OK) return st;
-        if (done) {
-            k = lv - 1;                       // the level whose step found nothing
+        if (frontier == 0) {
+            k = hs->h[0] - 1;                 // the level whose step found nothing
             break;
         }
-        frontier = hs->h[1];
         dir = hs->h[2];
     }
-    if (vm_level == nullptr) HIP_TRY(launch_ms(p, 7, k, grid, s));   // staged results -> per-source arrays
+    if (vm_level == nullptr) HIP_TRY(launch_ms(p, kMsOut, k, grid, s));   // staged results -> per-source arrays
     if (opt) {
         opt->levels = k + 1;
         opt->trace_count = opt->trace ? std::min<uint32_t>(k + 1, opt->trace_capacity) : 0u;
@@ -2311,8 +2342,8 @@ extern "C" bfs_status bfs_ms_profile_levels(bfs_graph *g, int32_t num_sources, c
     bfs_status result = BFS_OK;
     auto run = [&]() -> hipError_t {
         hipError_t e;
-        if ((e = launch_ms(p, 0, 0, grid, s)) != hipSuccess) return e;
-        if ((e = launch_ms(p, 1, 0, grid, s)) != hipSuccess) return e;
+        if ((e = launch_ms(p, kMsClear, 0, grid, s)) != hipSuccess) return e;
+        if ((e = launch_ms(p, kMsRoots, 0, grid, s)) != hipSuccess) return e;
         uint32_t cnt[4];
         std::vector<unsigned long long> stat(kMsStatWords);
         for (uint32_t k = 0;; ++k) {

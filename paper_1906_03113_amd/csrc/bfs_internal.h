@@ -233,7 +233,8 @@ struct MsLevel {
     int32_t *const *level;         // device array of nq device pointers
     int32_t *const *parent;
     const int32_t *sources;        // device, nq
-    uint32_t *host_status;         // pinned host: [0] level, [1] next frontier size
+    uint32_t *host_status;         // pinned host: [0] level, [1] its union frontier's size
+                                   // (one 64-bit store), [2] its direction (stored before)
     uint32_t fill_levels;          // slev / spar are the caller's vertex-major outputs:
                                    // every level starts at -1 (no transpose at the end)
     // union-frontier bitmap of the level a pull runs on (bit v = some source
@@ -285,7 +286,14 @@ hipError_t launch_parents(const LevelParams &p, uint32_t grid, hipStream_t s);
 hipError_t launch_persistent(const LevelParams &p, uint32_t grid, hipStream_t s);
 uint32_t persistent_max_grid(int device);
 
-hipError_t launch_ms(const MsLevel &p, int phase, uint32_t k, uint32_t grid, hipStream_t s);
+// The multi-source launches: the start (clear, roots); a push level (push,
+// settle); a pull level (the frontier bitmap where it is used, rows by class,
+// the long rows' later chunks where they are split, close; after range passes
+// report); the staged results into per-source arrays.
+enum MsPhase {
+    kMsClear, kMsRoots, kMsPush, kMsSettle, kMsFbits, kMsShortRows, kMsWide, kMsRest, kMsClose, kMsReport, kMsOut
+};
+hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t grid, hipStream_t s);
 hipError_t launch_ms_rpull(const MsLevel &p, uint32_t k, uint32_t r, uint32_t grid, hipStream_t s);
 
 // ---------------------------------------------------------------------------

@@ -177,29 +177,6 @@ __global__ __launch_bounds__(kBlock) void k_ms_clear(MsLevel p) {
     if (gid < (size_t)kMsStatWords) p.mstat[gid] = 0ull;
 }
 
-// Sources: bit q set in cur and vis of its vertex, level 0, parent itself; each
-// distinct source vertex enters the level-0 list once.
-__global__ __launch_bounds__(kBlock) void k_ms_roots(MsLevel p) {
-    const uint32_t gid = blockIdx.x * kBlock + threadIdx.x, gs = gridDim.x * kBlock;
-    for (uint32_t q = gid; q < p.nq; q += gs) {
-        const int32_t s = p.sources[q];                       // the caller's id
-        const int32_t x = label_of(p, s);
-        const unsigned long long bit = 1ull << (q & 63);
-        atomicOr(&row(p.m[0], x, p.W)[q >> 6], bit);
-        atomicOr(&row(p.vis, x, p.W)[q >> 6], bit);
-        p.slev[stage(p, srow(p, x), q)] = 0;
-        p.spar[stage(p, srow(p, x), q)] = (uint32_t)s;
-        const int g = (int)(q % kMsDegGroups);
-        atomicAdd(&p.mstat[ms_line(0, g) + 1], 1ull);              // one pair per source
-        atomicAdd(&p.mstat[ms_line(kMsCumSlot, g) + 1], 1ull);
-        if (atomicMax(&p.flag[x], 1u) < 1u) {
-            p.fq[0][atomicAdd(&p.cnt[0], 1u)] = x;
-            atomicAdd(&p.mstat[ms_line(0, g)], (unsigned long long)(p.out_ptr[x + 1] - p.out_ptr[x]));
-            atomicAdd(&p.mstat[ms_line(kMsCumSlot, g)], 1ull);
-        }
-    }
-}
-
 // Level k, push half.  Work items: the frontier list, up to 64 columns per
 // wave step - the entries of those with at most kMsShort entries dealt out one per
 // lane, each longer one below kMsLong entries taken by the whole wave - then
@@ -402,37 +379,142 @@ __device__ __forceinline__ void add_stats(const MsLevel &p, uint32_t t, unsigned
     }
 }
 
-// List slot t's statistics to zero and the list's size into the running
-// total (called by one thread, before the list's statistics are added).
-__device__ __forceinline__ void start_stats(const MsLevel &p, uint32_t t_clear, uint32_t listed) {
-    for (int g = 0; g < kMsDegGroups; ++g) {
-        p.mstat[ms_line((int)t_clear, g)] = 0ull;
-        p.mstat[ms_line((int)t_clear, g) + 1] = 0ull;
+// Whether the calling block is the launch's last to get here (every thread
+// calls it): arrivals on a counter per group of blocks, the groups' last on
+// one for the groups, in words 2 and 3 of mstat's lines; every counter is back
+// at zero afterwards.  Each wave drains its memory operations first, so the
+// last block finds every other block's atomics done.
+constexpr int kWaitVmcnt0 = 0x0F70;           // s_waitcnt vmcnt(0) alone
+
+__device__ __forceinline__ bool ms_last_to_arrive(const MsLevel &p) {
+    __shared__ uint32_t s_last;
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t nb = gridDim.x;
+        const uint32_t groups = nb < (uint32_t)kMsDegGroups ? nb : (uint32_t)kMsDegGroups;
+        const uint32_t g = blockIdx.x % groups, in_group = (nb - g + groups - 1) / groups;
+        unsigned long long *mine = &p.mstat[ms_line(0, (int)g) + 2], *top = &p.mstat[ms_line(0, 0) + 3];
+        uint32_t last = 0;
+        if (atomicAdd(mine, 1ull) == in_group - 1) {
+            __hip_atomic_store(mine, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (atomicAdd(top, 1ull) == groups - 1) {
+                __hip_atomic_store(top, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                last = 1;
+            }
+        }
+        s_last = last;
     }
-    atomicAdd(&p.mstat[ms_line(kMsCumSlot, 0)], (unsigned long long)listed);
+    __syncthreads();
+    return s_last != 0;
+}
+
+// The direction of level k: the network's argmin between push (0) and pull (1)
+// over the level's twelve features, push when an output is not finite (or
+// without a network).  Features, from f = |F_k| (the union frontier), d = its
+// out-degree sum, c = the summed union frontier sizes of levels 0..k, u = the
+// (vertex, source) pairs not reached through level k, q sources, k, n and nnz.
+__device__ __forceinline__ float ms_feature(uint32_t i, float f, float d, float c, float u, float q,
+                                            float k, float n, float nnz) {
+    switch (i) {
+        case 0: return logf(1.f + f);
+        case 1: return logf(1.f + d);
+        case 2: return logf(1.f + c);
+        case 3: return logf(1.f + q);
+        case 4: return logf(1.f + k);
+        case 5: return nnz / n;
+        case 6: return logf((f + 1.f) / n);
+        case 7: return logf((d + 1.f) / (nnz + 1.f));
+        case 8: return logf((u + 1.f) / (n * q));
+        case 9: return logf((d + 1.f) / (f + 1.f));
+        case 10: return logf((f + 1.f) * q / n);
+        case 11: return logf((d + 1.f) / (nnz - d + 1.f));
+        default: return 0.f;
+    }
+}
+
+// The end of a level, by the last block of its last launch (a launch of its own
+// for the direction cost 5 us a level): level k's list (slot k % 3) is
+// complete, the next level's list starts empty (next_list), the direction of
+// level k is decided, and the level, the list's size and the direction go to
+// the host, which polls for them.  Every thread of the block calls it.
+__device__ __forceinline__ void ms_close(const MsLevel &p, uint32_t k, bool next_list, bool report) {
+    const uint32_t lane = __lane_id(), t = k % 3, tn = (k + 1) % 3;
+    if (threadIdx.x >= 64) return;
+    const uint32_t f = ld_agent(&p.cnt[t]);
+    unsigned long long d = 0, c = 0, r = 0;
+    if (lane < (uint32_t)kMsDegGroups) {
+        d = ld_agent64(&p.mstat[ms_line((int)t, (int)lane)]);
+        c = ld_agent64(&p.mstat[ms_line(kMsCumSlot, (int)lane)]);
+        r = ld_agent64(&p.mstat[ms_line(kMsCumSlot, (int)lane) + 1]);
+    }
+    if (next_list) {
+        // the sizes of the lists so far, this one with them; the next list's statistics
+        if (lane < (uint32_t)kMsDegGroups) {
+            p.mstat[ms_line((int)tn, (int)lane)] = 0ull;
+            p.mstat[ms_line((int)tn, (int)lane) + 1] = 0ull;
+        }
+        if (lane == 0) {
+            p.mstat[ms_line(kMsCumSlot, 0)] = c + f;
+            p.cnt[tn] = 0u;
+            c += f;
+        }
+    }
+    uint32_t dir = 0;
+    if (p.mlp != nullptr) {
+        d = wave_sum64(d);
+        c = wave_sum64(c);
+        r = wave_sum64(r);
+        const unsigned long long pairs = (unsigned long long)p.n * p.nq;
+        const unsigned long long u = pairs > r ? pairs - r : 0ull;
+        const float feat = ms_feature(lane, (float)f, (float)d, (float)c, (float)u, (float)p.nq, (float)k, (float)p.n,
+                                      (float)p.out_ptr[p.n]);
+        const int b = mlp_argmin(p.mlp, feat, 2);
+        dir = b < 0 ? 0u : (uint32_t)b;
+    }
+    if (lane == 0 && report) {
+        p.host_status[2] = dir;
+        __hip_atomic_store((unsigned long long *)p.host_status, (unsigned long long)k | ((unsigned long long)f << 32),
+                           __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// Sources: bit q set in cur and vis of its vertex, level 0, parent itself; each
+// distinct source vertex enters the level-0 list once.
+__global__ __launch_bounds__(kBlock) void k_ms_roots(MsLevel p) {
+    const uint32_t gid = blockIdx.x * kBlock + threadIdx.x, gs = gridDim.x * kBlock;
+    for (uint32_t q = gid; q < p.nq; q += gs) {
+        const int32_t s = p.sources[q];                       // the caller's id
+        const int32_t x = label_of(p, s);
+        const unsigned long long bit = 1ull << (q & 63);
+        atomicOr(&row(p.m[0], x, p.W)[q >> 6], bit);
+        atomicOr(&row(p.vis, x, p.W)[q >> 6], bit);
+        p.slev[stage(p, srow(p, x), q)] = 0;
+        p.spar[stage(p, srow(p, x), q)] = (uint32_t)s;
+        const int g = (int)(q % kMsDegGroups);
+        atomicAdd(&p.mstat[ms_line(0, g) + 1], 1ull);              // one pair per source
+        atomicAdd(&p.mstat[ms_line(kMsCumSlot, g) + 1], 1ull);
+        if (atomicMax(&p.flag[x], 1u) < 1u) {
+            p.fq[0][atomicAdd(&p.cnt[0], 1u)] = x;
+            atomicAdd(&p.mstat[ms_line(0, g)], (unsigned long long)(p.out_ptr[x + 1] - p.out_ptr[x]));
+            atomicAdd(&p.mstat[ms_line(kMsCumSlot, g)], 1ull);
+        }
+    }
+    if (ms_last_to_arrive(p)) ms_close(p, 0u, false, true);
 }
 
 // Level k, settle half, one lane per newly listed vertex v: the new bits
 // (nxt[v]) join vis and get level k+1 (their parents were set by the push).
-// The progress report is written only for a level that had a frontier, so
-// levels launched past the end of the search (an empty frontier: push and
-// settle then change nothing) leave the last level's report in place.
+// The level is reported only when it had a frontier, so levels launched past
+// the end of the search (an empty frontier: push and settle then change
+// nothing) leave the last level's report in place.
 __global__ __launch_bounds__(kBlock) void k_ms_settle(MsLevel p, uint32_t k) {
-    const uint32_t s0 = k % 3, s1 = (k + 1) % 3, s2 = (k + 2) % 3;
+    const uint32_t s0 = k % 3, s1 = (k + 1) % 3;
     const unsigned long long *nxt = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], s1);
     const int32_t *fnxt = pick3<const int32_t *>(p.fq[0], p.fq[1], p.fq[2], s1);
-    const uint32_t nnext = p.cnt[s1];
+    const uint32_t nnext = p.cnt[s1], ncur = p.cnt[s0];
     const uint32_t W = p.W;
     const uint32_t gt = blockIdx.x * kBlock + threadIdx.x, gs = gridDim.x * kBlock;
-    if (gt == 0) {
-        p.cnt[s2] = 0u;                       // the list of level k+2 starts empty
-        start_stats(p, s2, nnext);
-        if (p.cnt[s0] != 0u) {
-            p.host_status[0] = k + 1;
-            p.host_status[1] = nnext;
-            __threadfence_system();
-        }
-    }
     unsigned long long deg = 0, pairs = 0;
     for (uint32_t i = gt; i < nnext; i += gs) {
         const int32_t v = fnxt[i];
@@ -448,6 +530,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_settle(MsLevel p, uint32_t k) {
         }
     }
     add_stats(p, s1, deg, pairs);
+    if (ms_last_to_arrive(p)) ms_close(p, k + 1, true, ncur != 0u);
 }
 
 // The union-frontier bitmap of level k: bit v of fbits = some word of v's
@@ -567,205 +650,138 @@ __device__ __forceinline__ void long_chunk(const MsLevel &p, const unsigned long
 }
 
 constexpr int32_t kMsSerial = 16;        // longest row one lane scans alone
-constexpr uint32_t kMsGroupRow = 64;     // longest row a group of 16 lanes scans
+constexpr int kMsWriteRows = 8;          // rows whose staged results a wave writes together
 
-__global__ __launch_bounds__(kBlock) void k_ms_pull(MsLevel p, uint32_t k) {
-    __shared__ int32_t s_list[kMsRows];
-    __shared__ int32_t s_long[kMsRows];
-    __shared__ uint32_t s_off[kBlock][9];          // a row's found bits: entry offset, 4 bits each
-    __shared__ unsigned long long s_fnd[kBlock];   // a row's found bits (one word)
+__device__ __forceinline__ unsigned long long full_word(const MsLevel &p, uint32_t w) {
+    const uint32_t tail = p.nq & 63u;
+    return (w == p.W - 1u && tail) ? ((1ull << tail) - 1ull) : ~0ull;
+}
+
+// The rows of up to kMsSerial entries: a lane per (row, word), consecutive lanes
+// on the words of one row.  A lane records, per found bit, the offset of the
+// entry that gave it (LDS); then each wave writes its lanes' rows, one at a
+// time with the 64 sources of the word on the 64 lanes, so that the staged
+// results of a row go out as one 256-byte store.  Waves do not wait for each
+// other anywhere.  Also clears F_{k-1}'s masks.
+template <bool kOne>
+__global__ __launch_bounds__(kBlock) void k_ms_pull_short(MsLevel p, uint32_t k) {
+    __shared__ uint32_t s_off[kBlock][9];          // found bits: entry offset, 4 bits each
+    __shared__ unsigned long long s_fnd[kBlock];   // found bits
     __shared__ int32_t s_e0[kBlock];
-    __shared__ uint32_t s_n, s_nl, s_base;
     const uint32_t s0 = k % 3, s1 = (k + 1) % 3, s2 = (k + 2) % 3;
     const unsigned long long *cur = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], s0);
     unsigned long long *nxt = pick3(p.m[0], p.m[1], p.m[2], s1);
     unsigned long long *old = pick3(p.m[0], p.m[1], p.m[2], s2);
-    int32_t *fnxt = pick3(p.fq[0], p.fq[1], p.fq[2], s1);
     const int32_t *fold = pick3<const int32_t *>(p.fq[0], p.fq[1], p.fq[2], s2);
     const uint32_t nold = p.cnt[s2];
-    const uint32_t W = p.W;
-    const uint32_t tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
+    const uint32_t W = kOne ? 1u : p.W;
+    const uint32_t tid = threadIdx.x, lane = __lane_id();
     const uint32_t gt = blockIdx.x * kBlock + tid, gs = gridDim.x * kBlock;
-    for (uint32_t t = gt; t < nold * W; t += gs) {
+    for (size_t t = gt; t < (size_t)nold * W; t += gs) {
         const uint32_t u = (uint32_t)fold[t / W];
         old[(size_t)u * W + (t % W)] = 0ull;
     }
-    const uint32_t tail = p.nq & 63u;
-    const uint32_t lk = k + 1;
-    // row chunks of kMsRows rows, or the graph's own chunk bounds (at most
-    // kMsRows rows and about the same number of list entries each: the
-    // degree-ordered copy puts its heaviest rows side by side)
-    const uint32_t nrc = p.row_chunks ? p.nrow_chunks : (uint32_t)(((size_t)p.n + kMsRows - 1) / kMsRows);
-    for (uint32_t c = blockIdx.x; c < nrc; c += gridDim.x) {
-        if (tid == 0) {
-            s_n = 0;
-            s_nl = 0;
+    const int32_t lk = (int32_t)(k + 1);
+    const size_t items = (size_t)p.n * W;
+    for (size_t i0 = gt - lane; i0 < items; i0 += gs) {                          // uniform per wave
+        const size_t item = i0 + lane;
+        int32_t v = 0, e0 = 0, e1 = 0;
+        uint32_t w = 0;
+        unsigned long long rem = 0ull, found = 0ull, sv = 0ull;
+        if (item < items) {
+            v = (int32_t)(item / W);
+            w = (uint32_t)(item - (size_t)v * W);
+            e0 = p.in_ptr[v];
+            e1 = p.in_ptr[v + 1];
+            sv = p.vis[item];
+            if (e1 - e0 <= kMsSerial) rem = full_word(p, w) & ~sv;
         }
-        __syncthreads();
-        const uint32_t c0 = p.row_chunks ? (uint32_t)p.row_chunks[c] : c * kMsRows;
-        const uint32_t c1 = p.row_chunks ? (uint32_t)p.row_chunks[c + 1]
-                                         : ((c0 + kMsRows < (uint32_t)p.n) ? c0 + kMsRows : (uint32_t)p.n);
-        // Rows of up to kMsSerial entries, one lane each, 256 at a time.  A
-        // lane records, per found bit, the offset of the entry that gave it
-        // (LDS); then each wave writes its lanes' rows, one row at a time
-        // with the 64 sources of the word on the 64 lanes, so the staged
-        // results of a row go out as one 256-byte store.
-        for (uint32_t r0 = c0; r0 < c1; r0 += kBlock) {
-            const uint32_t vv = r0 + tid;
-            const int32_t v = (int32_t)vv;
-            int32_t e0 = 0, e1 = 0;
-            bool mine = false;
-            if (vv < c1) {
-                e0 = p.in_ptr[v];
-                e1 = p.in_ptr[v + 1];
-                if (e1 > e0 && (uint32_t)(e1 - e0) < kMsLong) {        // long rows: chunks below
-                    const unsigned long long *vis = row(p.vis, v, W);
-                    bool open = false;
-                    for (uint32_t w = 0; w < W && !open; ++w) {
-                        const unsigned long long full = (w == W - 1 && tail) ? ((1ull << tail) - 1ull) : ~0ull;
-                        open = (full & ~vis[w]) != 0ull;
-                    }
-                    if (open) {                      // else every source has reached v
-                        if (e1 - e0 > kMsSerial) s_long[atomicAdd(&s_nl, 1u)] = v;
-                        else mine = true;
-                    }
-                }
-            }
-            s_e0[tid] = e0;
-            bool any = false;
-            for (uint32_t w = 0; w < W; ++w) {
-                unsigned long long found = 0ull;
+        s_e0[tid] = e0;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) s_off[tid][i] = 0u;
-                if (mine) {
-                    unsigned long long *vis = row(p.vis, v, W);
-                    const unsigned long long full = (w == W - 1 && tail) ? ((1ull << tail) - 1ull) : ~0ull;
-                    const unsigned long long sv = vis[w];
-                    unsigned long long rem = full & ~sv;
-                    // four entries at a time: their index and mask loads are
-                    // all issued before the first is used; positions past e1
-                    // repeat the last entry, whose bits are then already taken
-                    for (int32_t e = e0; e < e1 && rem; e += 4) {
-                        int32_t uu[4];
-                        unsigned long long mm[4];
+        for (int i = 0; i < 8; ++i) s_off[tid][i] = 0u;
+        // four entries at a time: their index and mask loads are all issued
+        // before the first is used; positions past e1 repeat the last entry,
+        // whose bits are then already taken
+        for (int32_t e = e0; e < e1 && rem; e += 4) {
+            int32_t uu[4];
+            unsigned long long mm[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) uu[j] = p.in_idx[e + j < e1 ? e + j : e1 - 1];
+            for (int j = 0; j < 4; ++j) uu[j] = p.in_idx[e + j < e1 ? e + j : e1 - 1];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) mm[j] = in_frontier(p, uu[j]) ? row(cur, uu[j], W)[w] : 0ull;
+            for (int j = 0; j < 4; ++j) mm[j] = in_frontier(p, uu[j]) ? row(cur, uu[j], W)[w] : 0ull;
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            unsigned long long hit = mm[j] & rem;
-                            rem &= ~hit;
-                            found |= hit;
-                            const uint32_t off = (uint32_t)(e - e0 + j);
-                            while (hit) {
-                                const uint32_t b = (uint32_t)__ffsll((long long)hit) - 1u;
-                                hit &= hit - 1ull;
-                                s_off[tid][b >> 3] |= off << ((b & 7u) * 4u);
-                            }
-                        }
-                    }
-                    if (found) {
-                        row(nxt, v, W)[w] = found;
-                        vis[w] = sv | found;
-                        any = true;
-                    }
+            for (int j = 0; j < 4; ++j) {
+                unsigned long long hit = mm[j] & rem;
+                rem &= ~hit;
+                found |= hit;
+                const uint32_t off = (uint32_t)(e - e0 + j);
+                while (hit) {
+                    const uint32_t b = (uint32_t)__ffsll((long long)hit) - 1u;
+                    hit &= hit - 1ull;
+                    s_off[tid][b >> 3] |= off << ((b & 7u) * 4u);
                 }
-                s_fnd[tid] = found;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                // this wave's lanes' rows that found something, one at a time
-                for (unsigned long long rows = __ballot(found != 0ull); rows; rows &= rows - 1ull) {
-                    const uint32_t rr = (tid & ~63u) + (uint32_t)__ffsll((long long)rows) - 1u;
-                    const unsigned long long fm = s_fnd[rr];
-                    if ((fm >> lane) & 1ull) {
-                        const uint32_t j = (s_off[rr][lane >> 3] >> ((lane & 7u) * 4u)) & 15u;
-                        const size_t at = stage(p, srow(p, (int32_t)(r0 + rr)), w * 64u + lane);
-                        const int32_t e = s_e0[rr] + (int32_t)j;
-                        p.slev[at] = (int32_t)lk;
-                        p.spar[at] = (uint32_t)(p.ent ? p.ent[e] : p.in_idx[e]);
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            }
-            if (any) s_list[atomicAdd(&s_n, 1u)] = v;
-        }
-        __syncthreads();
-        // rows longer than kMsSerial: four at a time per wave, a group of 16
-        // lanes each for rows of up to kMsGroupRow entries, then the longer
-        // ones of the four by the whole wave
-        const uint32_t nl = s_nl;
-        for (uint32_t i0 = wave * 4u; i0 < nl; i0 += (kBlock / 64) * 4u) {
-            const uint32_t gi = i0 + (lane >> 4), gl = lane & 15u;
-            int32_t v = -1, e0 = 0, e1 = 0;
-            bool wide = false;
-            if (gi < nl) {                                   // uniform in the group
-                v = s_long[gi];
-                e0 = p.in_ptr[v];
-                e1 = p.in_ptr[v + 1];
-                wide = (uint32_t)(e1 - e0) > kMsGroupRow;
-                if (!wide) {
-                    unsigned long long *vis = row(p.vis, v, W);
-                    bool any = false;
-                    for (uint32_t w = 0; w < W; ++w) {
-                        const unsigned long long full = (w == W - 1 && tail) ? ((1ull << tail) - 1ull) : ~0ull;
-                        const unsigned long long sv = vis[w];
-                        unsigned long long rem = full & ~sv, found = 0ull;
-                        for (int32_t eb = e0; eb < e1 && rem; eb += 16) {
-                            const unsigned long long f = scan_step<16>(p, cur, srow(p, v), w, eb, e1, rem,
-                                                                       lk, true);
-                            rem &= ~f;
-                            found |= f;
-                        }
-                        if (found) {
-                            if (gl == 0) {
-                                row(nxt, v, W)[w] = found;
-                                vis[w] = sv | found;
-                            }
-                            any = true;
-                        }
-                    }
-                    if (any && gl == 0) s_list[atomicAdd(&s_n, 1u)] = v;
-                }
-            }
-            for (unsigned long long wm = __ballot(wide && gl == 0); wm; wm &= wm - 1ull) {   // uniform
-                const int src = (int)__ffsll((long long)wm) - 1;
-                const int32_t wv = __shfl(v, src, 64), we0 = __shfl(e0, src, 64), we1 = __shfl(e1, src, 64);
-                unsigned long long *vis = row(p.vis, wv, W);
-                bool any = false;
-                for (uint32_t w = 0; w < W; ++w) {
-                    const unsigned long long full = (w == W - 1 && tail) ? ((1ull << tail) - 1ull) : ~0ull;
-                    const unsigned long long sv = vis[w];
-                    const unsigned long long found = scan_wave4(p, cur, srow(p, wv), w, we0, we1, full & ~sv,
-                                                                lk, true, false);
-                    if (found) {
-                        if (lane == 0) {
-                            row(nxt, wv, W)[w] = found;
-                            vis[w] = sv | found;
-                        }
-                        any = true;
-                    }
-                }
-                if (any && lane == 0) s_list[atomicAdd(&s_n, 1u)] = wv;
             }
         }
-        __syncthreads();
-        if (tid == 0 && s_n) s_base = atomicAdd(&p.cnt[s1], s_n);
-        __syncthreads();
-        for (uint32_t i = tid; i < s_n; i += kBlock) fnxt[s_base + i] = s_list[i];
-        __syncthreads();
+        if (found) nxt[item] = found;
+        s_fnd[tid] = found;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        // kMsWriteRows rows together: their parents (entries of the row's list)
+        // are loaded for all of them before the first is stored
+        const int32_t vo = found ? srow(p, v) : 0;
+        for (unsigned long long rows = __ballot(found != 0ull); rows;) {         // uniform
+            bool on[kMsWriteRows];
+            size_t at[kMsWriteRows];
+            int32_t u[kMsWriteRows];
+#pragma unroll
+            for (int x = 0; x < kMsWriteRows; ++x) {
+                const int src = rows ? (int)__ffsll((long long)rows) - 1 : 0;
+                const uint32_t rr = (tid & ~63u) + (uint32_t)src;
+                on[x] = rows != 0ull && ((s_fnd[rr] >> lane) & 1ull) != 0ull;
+                const int32_t rv = __shfl(vo, src, 64);
+                const uint32_t rw = kOne ? 0u : (uint32_t)__shfl((int)w, src, 64);
+                at[x] = stage(p, rv, rw * 64u + lane);
+                const int32_t e = s_e0[rr] + (int32_t)((s_off[rr][lane >> 3] >> ((lane & 7u) * 4u)) & 15u);
+                u[x] = 0;
+                if (on[x]) u[x] = p.ent ? p.ent[e] : p.in_idx[e];
+                rows &= rows - 1ull;
+            }
+#pragma unroll
+            for (int x = 0; x < kMsWriteRows; ++x) {
+                if (on[x]) {
+                    p.slev[at[x]] = lk;
+                    p.spar[at[x]] = (uint32_t)u[x];
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    // The long rows, one wave per chunk.  With long_split, only each row's
-    // first chunk here: it holds the row's smallest in-neighbours, so what
-    // it finds is final - those bits go into vis now (no other wave touches
-    // this row's vis in this kernel) and k_ms_pull_rest then scans the later
-    // chunks for the other sources only.  Without it, every chunk here, all
-    // looking for the same unsettled sources (vis is not written).
+}
+
+constexpr int32_t kMsWideRows = 16;            // consecutive rows a wave looks at together
+constexpr uint32_t kMsAlone = 2;               // open rows from which each gets the whole wave
+
+// One mask word: the rows of more than kMsSerial entries below kMsLong, a wave
+// per kMsWideRows consecutive rows, four rows to a step with 16 lanes each, four
+// such steps (all sixteen rows) in flight together: a row's scan is a chain of
+// dependent loads (entry, mask, caller's id), and with one row group after
+// another a wave had one of them in flight at a time.  Once at most kMsAlone
+// rows are open, each is finished by the whole wave.  Before that the long
+// rows, a wave per chunk: with long_split only each row's first chunk - it
+// holds the row's smallest in-neighbours, so what it finds is final: those
+// bits go into vis now and k_ms_pull_rest then scans the later chunks for the
+// other sources only; without it every chunk here, all looking for the same
+// unsettled sources.
+__global__ __launch_bounds__(kBlock) void k_ms_pull_wide(MsLevel p, uint32_t k) {
+    const unsigned long long *cur = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], k % 3);
+    unsigned long long *nxt = pick3(p.m[0], p.m[1], p.m[2], (k + 1) % 3);
+    const uint32_t lane = __lane_id(), lk = k + 1;
+    const uint32_t gw = (blockIdx.x * kBlock + threadIdx.x) >> 6, nw = (gridDim.x * kBlock) >> 6;
     const uint32_t nitems = p.long_split ? p.nli : p.nli_chunks;
-    for (uint32_t c = gt >> 6; c < nitems; c += gs >> 6) {           // uniform per wave
+    for (uint32_t c = gw; c < nitems; c += nw) {                                 // uniform per wave
         int32_t v;
         uint32_t j = 0;
         if (p.long_split) {
@@ -776,6 +792,81 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull(MsLevel p, uint32_t k) {
             j = c - L.chunk_base;
         }
         long_chunk(p, cur, nxt, v, j, k, p.long_split != 0u);
+    }
+    const unsigned long long full = full_word(p, 0u);
+    const uint32_t nsteps = ((uint32_t)p.n + kMsWideRows - 1) / kMsWideRows;
+    const int g = (int)(lane >> 4);
+    const int32_t gl = (int32_t)(lane & 15u);
+    for (uint32_t c = gw; c < nsteps; c += nw) {                                 // uniform per wave
+        const int32_t v0 = (int32_t)(c * kMsWideRows);
+        int32_t b = 0, e = 0;
+        unsigned long long r0 = 0ull;
+        if (lane < (uint32_t)kMsWideRows && v0 + (int32_t)lane < p.n) {
+            b = p.in_ptr[v0 + (int32_t)lane];
+            e = p.in_ptr[v0 + (int32_t)lane + 1];
+            r0 = full & ~p.vis[v0 + (int32_t)lane];
+            if (e - b <= kMsSerial || (uint32_t)(e - b) >= kMsLong) r0 = 0ull;
+        }
+        unsigned long long open = __ballot(r0 != 0ull);
+        if (!open) continue;
+        int32_t at[4], end[4];
+        unsigned long long rem[4], fnd[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int src = 4 * t + g;
+            at[t] = __shfl(b, src, 64);
+            end[t] = __shfl(e, src, 64);
+            rem[t] = __shfl(r0, src, 64);
+            fnd[t] = 0ull;
+        }
+        while ((uint32_t)__popcll(open) > kMsAlone) {                            // uniform
+            int32_t uu[4], oo[4];
+            bool ok[4];
+            unsigned long long mm[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) uu[t] = (rem[t] && at[t] + gl < end[t]) ? p.in_idx[at[t] + gl] : -1;
+            if (p.use_fbits) {
+                unsigned long long fb[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) fb[t] = uu[t] >= 0 ? p.fbits[(uint32_t)uu[t] >> 6] : 0ull;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) ok[t] = ((fb[t] >> ((uint32_t)uu[t] & 63u)) & 1ull) != 0ull;
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) ok[t] = uu[t] >= 0;
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) mm[t] = ok[t] ? cur[uu[t]] : 0ull;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) oo[t] = (mm[t] & rem[t]) ? caller_id(p, uu[t]) : -1;
+            open = 0ull;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int32_t v = v0 + 4 * t + g;
+                const unsigned long long f = scan_resolve<16>(p, srow(p, v < p.n ? v : 0), 0u, oo[t], mm[t] & rem[t],
+                                                              lk, true);
+                rem[t] &= ~f;
+                fnd[t] |= f;
+                at[t] += 16;
+                if (at[t] >= end[t]) rem[t] = 0ull;
+                // row 4 t + g is open: one bit, from its group's first lane
+                const unsigned long long o = __ballot(gl == 0 && rem[t] != 0ull);
+                open |= ((o & 1ull) | ((o >> 15) & 2ull) | ((o >> 30) & 4ull) | ((o >> 45) & 8ull)) << (4 * t);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            for (unsigned long long o = (open >> (4 * t)) & 15ull; o; o &= o - 1ull) {       // uniform
+                const int og = (int)__ffsll((long long)o) - 1, src = 16 * og;
+                const int32_t a = __shfl(at[t], src, 64), z = __shfl(end[t], src, 64);
+                const unsigned long long rr = __shfl(rem[t], src, 64);
+                const unsigned long long f = scan_wave4(p, cur, srow(p, v0 + 4 * t + og), 0u, a, z, rr, lk, true, false);
+                if (g == og) fnd[t] |= f;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            if (gl == 0 && fnd[t]) nxt[v0 + 4 * t + g] = fnd[t];
     }
 }
 
@@ -799,38 +890,274 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_rest(MsLevel p, uint32_t k) 
     }
 }
 
-// After a pull level, the long rows: bits their chunks found join vis, and
-// rows with any are listed.
-__global__ __launch_bounds__(kBlock) void k_ms_fixup(MsLevel p, uint32_t k) {
-    const uint32_t s1 = (k + 1) % 3;
-    const unsigned long long *nxt = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], s1);
-    int32_t *fnxt = pick3(p.fq[0], p.fq[1], p.fq[2], s1);
-    const uint32_t W = p.W;
-    const uint32_t lane = __lane_id();
-    const uint32_t gt = blockIdx.x * kBlock + threadIdx.x, gs = gridDim.x * kBlock;
-    for (uint32_t base_i = gt - lane; base_i < p.nli; base_i += gs) {     // whole waves iterate
-        const uint32_t i = base_i + lane;
-        bool any = false;
-        int32_t v = -1;
-        if (i < p.nli) {
-            v = p.li[i].v;
-            for (uint32_t w = 0; w < W; ++w) {
-                const unsigned long long f = row(nxt, v, W)[w];
-                if (f) {
-                    row(p.vis, v, W)[w] |= f;
-                    any = true;
+// ---------------------------------------------------------------------------
+// several mask words per vertex (more than 64 sources)
+// ---------------------------------------------------------------------------
+//
+// A lane of a scan step holds one word of one entry: lane l has word l % kWp
+// and entry l / kWp of the step, so an entry's index is read once for kWp words
+// and its mask words, which lie side by side, come in one access, where a scan
+// per word reads the list and gathers a line per entry again for every word.
+// Measured, directed R-MAT of 2^20 vertices, 256 sources (four words): the
+// pulls of a call took 3.15 ms a word at a time.
+
+// The bits of a step: each bit of a lane's hit goes to the lowest entry of the
+// step that holds it.  Parents pass through the wave's LDS rows (one of 64
+// slots per word) and go out by source, kWp * 64 consecutive entries of the
+// staged row.  Returns the bits found of the lane's word.
+template <uint32_t kWp>
+__device__ __forceinline__ unsigned long long words_resolve(const MsLevel &p, int32_t vo, uint32_t w0, int32_t uc,
+                                                            unsigned long long hit, uint32_t lk, bool owner_alone,
+                                                            uint32_t *slots) {
+    if (__ballot(hit != 0ull) == 0ull) return 0ull;        // uniform
+    const uint32_t lane = __lane_id(), word = lane % kWp;
+    unsigned long long incl = hit;
+#pragma unroll
+    for (uint32_t d = kWp; d < 64u; d <<= 1) {
+        const unsigned long long t = __shfl_up(incl, d, 64);
+        if (lane >= d) incl |= t;
+    }
+    unsigned long long below = __shfl_up(incl, kWp, 64);
+    if (lane < kWp) below = 0ull;
+    unsigned long long own = hit & ~below;
+    const unsigned long long found = __shfl(incl, (int)(64u - kWp + word), 64);
+    uint32_t *slot = slots + word * 64u;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    while (own) {
+        const uint32_t b = (uint32_t)__ffsll((long long)own) - 1u;
+        own &= own - 1ull;
+        slot[b] = (uint32_t)uc;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (uint32_t x = 0; x < kWp; ++x) {
+        const unsigned long long fx = __shfl(found, (int)x, 64);
+        if ((fx >> lane) & 1ull) {
+            const size_t at = stage(p, vo, (w0 + x) * 64u + lane);
+            const uint32_t pu = slots[x * 64u + lane];
+            p.slev[at] = (int32_t)lk;
+            if (owner_alone) p.spar[at] = pu;
+            else atomicMin(&p.spar[at], pu);
+        }
+    }
+    return found;
+}
+
+// Entries [e0, e1) of row v scanned by the whole wave for words w0 .. w0 + kWp -
+// 1 (rem: the sources looked for of the lane's word), four steps of 64 / kWp
+// entries at a time; prune as scan_wave4.
+template <uint32_t kWp>
+__device__ __forceinline__ unsigned long long words_scan(const MsLevel &p, const unsigned long long *cur, int32_t vo,
+                                                         uint32_t w0, int32_t e0, int32_t e1, unsigned long long rem,
+                                                         uint32_t lk, bool owner_alone, bool prune, uint32_t *slots) {
+    constexpr int32_t kStep = 64 / (int32_t)kWp;
+    const uint32_t W = p.W, lane = __lane_id(), word = lane % kWp;
+    const int32_t entry = (int32_t)(lane / kWp);
+    const uint32_t w = w0 + word < W ? w0 + word : W - 1u;   // a word past the last looks for nothing
+    unsigned long long found = 0ull;
+    for (int32_t eb = e0; eb < e1 && __ballot(rem != 0ull); eb += 4 * kStep) {               // uniform
+        int32_t uu[4], oo[4];
+        unsigned long long mm[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int32_t e = eb + t * kStep + entry;
+            uu[t] = e < e1 ? p.in_idx[e] : -1;
+        }
+        if (prune) {
+            const uint32_t first = (uint32_t)(p.ent ? p.ent[eb] : __shfl(uu[0], 0, 64));
+            uint32_t sp[kWp];
+#pragma unroll
+            for (uint32_t x = 0; x < kWp; ++x)
+                sp[x] = w0 + x < W ? p.spar[stage(p, vo, (w0 + x) * 64u + lane)] : 0u;
+#pragma unroll
+            for (uint32_t x = 0; x < kWp; ++x) {
+                const unsigned long long done = __ballot(sp[x] < first);
+                if (word == x) rem &= ~done;
+            }
+            if (!__ballot(rem != 0ull)) break;                                              // uniform
+        }
+        bool ok[4];
+        if (p.use_fbits) {
+            unsigned long long fb[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) fb[t] = uu[t] >= 0 ? p.fbits[(uint32_t)uu[t] >> 6] : 0ull;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ok[t] = ((fb[t] >> ((uint32_t)uu[t] & 63u)) & 1ull) != 0ull;
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) ok[t] = uu[t] >= 0;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) mm[t] = ok[t] ? row(cur, uu[t], W)[w] : 0ull;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) oo[t] = (mm[t] & rem) ? caller_id(p, uu[t]) : -1;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const unsigned long long f = words_resolve<kWp>(p, vo, w0, oo[t], mm[t] & rem, lk, owner_alone, slots);
+            rem &= ~f;
+            found |= f;
+        }
+    }
+    return found;
+}
+
+// Chunk j of long row v by one wave, kWp words at a time (long_chunk's work).
+template <uint32_t kWp>
+__device__ __forceinline__ void words_chunk(const MsLevel &p, const unsigned long long *cur, unsigned long long *nxt,
+                                            int32_t v, uint32_t j, uint32_t k, bool first, uint32_t *slots) {
+    const uint32_t W = p.W, lane = __lane_id();
+    const int32_t r1 = p.in_ptr[v + 1];
+    const int32_t e0 = p.in_ptr[v] + (int32_t)(j * kMsChunk);
+    const int32_t e1 = (e0 + (int32_t)kMsChunk < r1) ? e0 + (int32_t)kMsChunk : r1;
+    for (uint32_t w0 = 0; w0 < W; w0 += kWp) {
+        const uint32_t w = w0 + lane % kWp;
+        const unsigned long long rem = w < W ? full_word(p, w) & ~row(p.vis, v, W)[w] : 0ull;
+        const unsigned long long found =
+            words_scan<kWp>(p, cur, srow(p, v), w0, e0, e1, rem, k + 1, false, j != 0, slots);
+        if (found && lane < kWp) {                          // lane x has word w0 + x
+            atomicOr(&row(nxt, v, W)[w], found);
+            if (first) row(p.vis, v, W)[w] |= found;
+        }
+    }
+}
+
+// k_ms_pull_wide for W >= 2 words: four rows of a wave's kMsWideRows in flight
+// for their first step, kWp words each; a row with sources left goes on alone.
+template <uint32_t kWp>
+__global__ __launch_bounds__(kBlock) void k_ms_wide_words(MsLevel p, uint32_t k) {
+    __shared__ uint32_t s_par[kBlock / 64][kWp * 64];
+    constexpr int32_t kStep = 64 / (int32_t)kWp;
+    const unsigned long long *cur = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], k % 3);
+    unsigned long long *nxt = pick3(p.m[0], p.m[1], p.m[2], (k + 1) % 3);
+    const uint32_t W = p.W, lane = __lane_id(), lk = k + 1, word = lane % kWp;
+    const int32_t entry = (int32_t)(lane / kWp);
+    const uint32_t gw = (blockIdx.x * kBlock + threadIdx.x) >> 6, nw = (gridDim.x * kBlock) >> 6;
+    uint32_t *slots = s_par[threadIdx.x >> 6];
+    const uint32_t nitems = p.long_split ? p.nli : p.nli_chunks;
+    for (uint32_t c = gw; c < nitems; c += nw) {                                 // uniform per wave
+        int32_t v;
+        uint32_t j = 0;
+        if (p.long_split) {
+            v = p.li[c].v;
+        } else {
+            const MsLong L = p.li[p.limap[c]];
+            v = L.v;
+            j = c - L.chunk_base;
+        }
+        words_chunk<kWp>(p, cur, nxt, v, j, k, p.long_split != 0u, slots);
+    }
+    const uint32_t nsteps = ((uint32_t)p.n + kMsWideRows - 1) / kMsWideRows;
+    for (uint32_t c = gw; c < nsteps; c += nw) {                                 // uniform per wave
+        const int32_t v0 = (int32_t)(c * kMsWideRows);
+        int32_t b = 0, e = 0;
+        if (lane < (uint32_t)kMsWideRows && v0 + (int32_t)lane < p.n) {
+            b = p.in_ptr[v0 + (int32_t)lane];
+            e = p.in_ptr[v0 + (int32_t)lane + 1];
+        }
+        unsigned long long wide = __ballot(e - b > kMsSerial && (uint32_t)(e - b) < kMsLong);
+        while (wide) {                                                           // uniform
+            int32_t v[4], at[4], end[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int src = wide ? (int)__ffsll((long long)wide) - 1 : 0;
+                v[t] = wide ? v0 + src : -1;
+                at[t] = wide ? __shfl(b, src, 64) : 0;
+                end[t] = wide ? __shfl(e, src, 64) : 0;
+                wide &= wide - 1ull;
+            }
+            for (uint32_t w0 = 0; w0 < W; w0 += kWp) {
+                const uint32_t w = w0 + word;
+                const bool has = w < W;
+                unsigned long long rem[4], mm[4];
+                int32_t uu[4], oo[4];
+                bool ok[4];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    rem[t] = (has && v[t] >= 0) ? full_word(p, w) & ~row(p.vis, v[t], W)[w] : 0ull;
+                    uu[t] = at[t] + entry < end[t] ? p.in_idx[at[t] + entry] : -1;
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) ok[t] = uu[t] >= 0 && rem[t] != 0ull && in_frontier(p, uu[t]);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) mm[t] = ok[t] ? row(cur, uu[t], W)[w] : 0ull;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) oo[t] = (mm[t] & rem[t]) ? caller_id(p, uu[t]) : -1;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    if (v[t] < 0) continue;                                      // uniform
+                    const int32_t vo = srow(p, v[t]);
+                    unsigned long long f = words_resolve<kWp>(p, vo, w0, oo[t], mm[t] & rem[t], lk, true, slots);
+                    if (at[t] + kStep < end[t])
+                        f |= words_scan<kWp>(p, cur, vo, w0, at[t] + kStep, end[t], rem[t] & ~f, lk, true, false, slots);
+                    if (f && lane < kWp) row(nxt, v[t], W)[w] = f;
                 }
             }
         }
-        const unsigned long long bm = __ballot(any);
-        if (bm) {
-            const uint32_t leader = (uint32_t)__ffsll((long long)bm) - 1u;
-            uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(&p.cnt[s1], (uint32_t)__popcll(bm));
-            base = __shfl(base, (int)leader, 64);
-            if (any) fnxt[base + lanes_below(bm)] = v;
-        }
     }
+}
+
+// k_ms_pull_rest for W >= 2 words.
+template <uint32_t kWp>
+__global__ __launch_bounds__(kBlock) void k_ms_rest_words(MsLevel p, uint32_t k) {
+    __shared__ uint32_t s_par[kBlock / 64][kWp * 64];
+    const unsigned long long *cur = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], k % 3);
+    unsigned long long *nxt = pick3(p.m[0], p.m[1], p.m[2], (k + 1) % 3);
+    const uint32_t gt = blockIdx.x * kBlock + threadIdx.x, gs = gridDim.x * kBlock;
+    const uint32_t nrest = p.nli_chunks - p.nli;
+    for (uint32_t i = gt >> 6; i < nrest; i += gs >> 6) {                       // uniform per wave
+        const uint32_t c = p.lirest[i];
+        const MsLong L = p.li[p.limap[c]];
+        words_chunk<kWp>(p, cur, nxt, L.v, c - L.chunk_base, k, false, s_par[threadIdx.x >> 6]);
+    }
+}
+
+// After a pull level, over all rows: the bits found join vis, the rows with any
+// are listed (a block's kMsCloseRows rows through LDS, one counter atomic for
+// them), the list's statistics are summed; the last block closes the level.
+// Reading every row's mask once (W x 8 bytes in order) replaces a list kept by
+// the pull's blocks, which tied their waves together with barriers.
+constexpr uint32_t kMsCloseRows = 4 * kBlock;
+
+__global__ __launch_bounds__(kBlock) void k_ms_pull_close(MsLevel p, uint32_t k) {
+    __shared__ int32_t s_list[kMsCloseRows];
+    __shared__ uint32_t s_n, s_base;
+    const uint32_t s1 = (k + 1) % 3;
+    const unsigned long long *nxt = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], s1);
+    int32_t *fnxt = pick3(p.fq[0], p.fq[1], p.fq[2], s1);
+    const uint32_t W = p.W, tid = threadIdx.x;
+    unsigned long long deg = 0, pairs = 0;
+    for (uint32_t c0 = blockIdx.x * kMsCloseRows; c0 < (uint32_t)p.n; c0 += gridDim.x * kMsCloseRows) {
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t j = 0; j < kMsCloseRows / kBlock; ++j) {
+            const uint32_t v = c0 + j * kBlock + tid;
+            if (v >= (uint32_t)p.n) continue;
+            bool any = false;
+            for (uint32_t w = 0; w < W; ++w) {
+                const unsigned long long nb = row(nxt, (int32_t)v, W)[w];
+                if (!nb) continue;
+                any = true;
+                pairs += (unsigned long long)__popcll(nb);
+                row(p.vis, (int32_t)v, W)[w] |= nb;
+            }
+            if (any) {
+                deg += (unsigned long long)(p.out_ptr[v + 1] - p.out_ptr[v]);
+                s_list[atomicAdd(&s_n, 1u)] = (int32_t)v;
+            }
+        }
+        __syncthreads();
+        if (tid == 0 && s_n) s_base = atomicAdd(&p.cnt[s1], s_n);
+        __syncthreads();
+        for (uint32_t i = tid; i < s_n; i += kBlock) fnxt[s_base + i] = s_list[i];
+        __syncthreads();
+    }
+    add_stats(p, s1, deg, pairs);
+    if (ms_last_to_arrive(p)) ms_close(p, k + 1, true, true);
 }
 
 // The staged results into the callers' arrays: a block per 64 vertices and 64
@@ -1150,23 +1477,17 @@ __global__ __launch_bounds__(kBlock) void k_ms_rpull(MsLevel p, uint32_t k, uint
     }
 }
 
-// After a pull level: the lists of level k+2 start empty; report to the host;
-// the statistics of the level-(k+1) list.
+// After a range-ordered pull (whose passes list the rows themselves): the
+// statistics of the level-(k+1) list, and the level's close.
 __global__ __launch_bounds__(kBlock) void k_ms_report(MsLevel p, uint32_t k) {
-    const uint32_t s1 = (k + 1) % 3, s2 = (k + 2) % 3;
+    const uint32_t s1 = (k + 1) % 3;
     const uint32_t nnext = p.cnt[s1];
     const int32_t *fnxt = pick3<const int32_t *>(p.fq[0], p.fq[1], p.fq[2], s1);
     const unsigned long long *nxt = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], s1);
     const uint32_t W = p.W;
     const uint32_t gt = blockIdx.x * kBlock + threadIdx.x, gs = gridDim.x * kBlock;
-    if (gt == 0) {
-        p.cnt[s2] = 0u;
+    if (gt == 0)
         for (int t = 0; t < 3; ++t) p.rcnt[t] = 0u;           // the range passes' open rows
-        start_stats(p, s2, nnext);
-        p.host_status[0] = k + 1;
-        p.host_status[1] = nnext;
-        __threadfence_system();
-    }
     unsigned long long deg = 0, pairs = 0;
     for (uint32_t i = gt; i < nnext; i += gs) {
         const int32_t v = fnxt[i];
@@ -1174,55 +1495,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_report(MsLevel p, uint32_t k) {
         for (uint32_t w = 0; w < W; ++w) pairs += (unsigned long long)__popcll(row(nxt, v, W)[w]);
     }
     add_stats(p, s1, deg, pairs);
-}
-
-// The direction of level k (one wave): the network's argmin between push (0)
-// and pull (1) over the level's twelve features, push when an output is not
-// finite (or without a network); written to host_status[2].  Features, from
-// f = |F_k| (the union frontier), d = its out-degree sum, c = the summed union
-// frontier sizes of levels 0..k, u = the (vertex, source) pairs not reached
-// through level k, q sources, k, n and nnz.
-__device__ __forceinline__ float ms_feature(uint32_t i, float f, float d, float c, float u, float q,
-                                            float k, float n, float nnz) {
-    switch (i) {
-        case 0: return logf(1.f + f);
-        case 1: return logf(1.f + d);
-        case 2: return logf(1.f + c);
-        case 3: return logf(1.f + q);
-        case 4: return logf(1.f + k);
-        case 5: return nnz / n;
-        case 6: return logf((f + 1.f) / n);
-        case 7: return logf((d + 1.f) / (nnz + 1.f));
-        case 8: return logf((u + 1.f) / (n * q));
-        case 9: return logf((d + 1.f) / (f + 1.f));
-        case 10: return logf((f + 1.f) * q / n);
-        case 11: return logf((d + 1.f) / (nnz - d + 1.f));
-        default: return 0.f;
-    }
-}
-
-__global__ void k_ms_decide(MsLevel p, uint32_t k) {
-    const uint32_t t = k % 3;
-    const uint32_t f = p.cnt[t];
-    unsigned long long d = 0, c = 0, r = 0;
-    for (int g = 0; g < kMsDegGroups; ++g) {
-        d += p.mstat[ms_line((int)t, g)];
-        c += p.mstat[ms_line(kMsCumSlot, g)];
-        r += p.mstat[ms_line(kMsCumSlot, g) + 1];
-    }
-    const unsigned long long pairs = (unsigned long long)p.n * p.nq;
-    const unsigned long long u = pairs > r ? pairs - r : 0ull;
-    uint32_t v = 0;
-    if (p.mlp != nullptr) {
-        const float feat = ms_feature(__lane_id(), (float)f, (float)d, (float)c, (float)u, (float)p.nq,
-                                      (float)k, (float)p.n, (float)p.out_ptr[p.n]);
-        const int b = mlp_argmin(p.mlp, feat, 2);
-        v = b < 0 ? 0u : (uint32_t)b;
-    }
-    if (threadIdx.x == 0) {
-        p.host_status[2] = v;
-        __threadfence_system();
-    }
+    if (ms_last_to_arrive(p)) ms_close(p, k + 1, true, true);
 }
 
 hipError_t launch_ms_rpull(const MsLevel &p, uint32_t k, uint32_t r, uint32_t grid, hipStream_t s) {
@@ -1230,24 +1503,37 @@ hipError_t launch_ms_rpull(const MsLevel &p, uint32_t k, uint32_t r, uint32_t gr
     return hipGetLastError();
 }
 
-hipError_t launch_ms(const MsLevel &p, int phase, uint32_t k, uint32_t grid, hipStream_t s) {
-    // the list walks after a level (settle, fixup, report) end in one pair of
-    // counter atomics per workgroup on the same two words: at most 2,048
-    // workgroups for them (R-MAT s22: the report 25-31 us at 8,192, 17-22 us
-    // at 1,024-2,048)
+hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t grid, hipStream_t s) {
+    // the walks over a level's list end in a few atomics per workgroup on the
+    // same words: at most 2,048 workgroups for them (R-MAT s22: 25-31 us at
+    // 8,192, 17-22 us at 1,024-2,048), and no more than the rows can fill
+    const uint32_t rows = (uint32_t)(((size_t)p.n + kMsCloseRows - 1) / kMsCloseRows);
     const uint32_t small = grid < 2048u ? grid : 2048u;
+    const uint32_t close = small < rows ? small : rows;
+    const dim3 g(grid), b(kBlock);
     switch (phase) {
-        case 0: hipLaunchKernelGGL(k_ms_clear, dim3(grid), dim3(kBlock), 0, s, p); break;
-        case 1: hipLaunchKernelGGL(k_ms_roots, dim3(grid), dim3(kBlock), 0, s, p); break;
-        case 2: hipLaunchKernelGGL(k_ms_push, dim3(grid), dim3(kBlock), 0, s, p, k); break;
-        case 3: hipLaunchKernelGGL(k_ms_settle, dim3(small), dim3(kBlock), 0, s, p, k); break;
-        case 4: hipLaunchKernelGGL(k_ms_pull, dim3(grid), dim3(kBlock), 0, s, p, k); break;
-        case 6: hipLaunchKernelGGL(k_ms_fixup, dim3(small), dim3(kBlock), 0, s, p, k); break;
-        case 7: hipLaunchKernelGGL(k_ms_out, dim3(grid), dim3(kBlock), 0, s, p); break;
-        case 8: hipLaunchKernelGGL(k_ms_fbits, dim3(grid), dim3(kBlock), 0, s, p, k); break;
-        case 9: hipLaunchKernelGGL(k_ms_pull_rest, dim3(grid), dim3(kBlock), 0, s, p, k); break;
-        case 10: hipLaunchKernelGGL(k_ms_decide, dim3(1), dim3(64), 0, s, p, k); break;
-        default: hipLaunchKernelGGL(k_ms_report, dim3(small), dim3(kBlock), 0, s, p, k); break;
+        case kMsClear: hipLaunchKernelGGL(k_ms_clear, g, b, 0, s, p); break;
+        case kMsRoots: hipLaunchKernelGGL(k_ms_roots, dim3((p.nq + kBlock - 1) / kBlock), b, 0, s, p); break;
+        case kMsPush: hipLaunchKernelGGL(k_ms_push, g, b, 0, s, p, k); break;
+        case kMsSettle: hipLaunchKernelGGL(k_ms_settle, dim3(close), b, 0, s, p, k); break;
+        case kMsFbits: hipLaunchKernelGGL(k_ms_fbits, g, b, 0, s, p, k); break;
+        case kMsShortRows:
+            if (p.W == 1) hipLaunchKernelGGL(k_ms_pull_short<true>, g, b, 0, s, p, k);
+            else hipLaunchKernelGGL(k_ms_pull_short<false>, g, b, 0, s, p, k);
+            break;
+        case kMsWide:
+            if (p.W == 1) hipLaunchKernelGGL(k_ms_pull_wide, g, b, 0, s, p, k);
+            else if (p.W == 2) hipLaunchKernelGGL(k_ms_wide_words<2>, g, b, 0, s, p, k);
+            else hipLaunchKernelGGL(k_ms_wide_words<4>, g, b, 0, s, p, k);
+            break;
+        case kMsRest:
+            if (p.W == 1) hipLaunchKernelGGL(k_ms_pull_rest, g, b, 0, s, p, k);
+            else if (p.W == 2) hipLaunchKernelGGL(k_ms_rest_words<2>, g, b, 0, s, p, k);
+            else hipLaunchKernelGGL(k_ms_rest_words<4>, g, b, 0, s, p, k);
+            break;
+        case kMsClose: hipLaunchKernelGGL(k_ms_pull_close, dim3(close), b, 0, s, p, k); break;
+        case kMsReport: hipLaunchKernelGGL(k_ms_report, dim3(small), b, 0, s, p, k); break;
+        case kMsOut: hipLaunchKernelGGL(k_ms_out, g, b, 0, s, p); break;
     }
     return hipGetLastError();
 }
