@@ -65,8 +65,6 @@ struct bfs_graph {
     bfsi::MsLong *do_long = nullptr;
     uint32_t *do_map = nullptr, *do_rest = nullptr;
     uint32_t do_nlong = 0, do_nchunks = 0;
-    int32_t *do_rows = nullptr;       // the pull's row chunk bounds over the labels
-    uint32_t do_nrows = 0;
     // a directed graph's out-lists over the same labels (the lists above are
     // then its in-lists), with their caller ids and long columns
     int32_t *do_optr = nullptr, *do_oidx = nullptr, *do_oent = nullptr;
@@ -173,7 +171,7 @@ void free_graph(bfs_graph *g) {
     if (g->lo) (void)hipFree(g->lo);
     if (g->lomap) (void)hipFree(g->lomap);
     if (g->lirest) (void)hipFree(g->lirest);
-    for (int32_t *a : {g->do_ptr, g->do_idx, g->do_ent, g->do_orig, g->do_pos, g->do_rows, g->do_optr,
+    for (int32_t *a : {g->do_ptr, g->do_idx, g->do_ent, g->do_orig, g->do_pos, g->do_optr,
                        g->do_oidx, g->do_oent})
         if (a) (void)hipFree(a);
     if (g->do_olong) (void)hipFree(g->do_olong);
@@ -289,33 +287,6 @@ bfs_status build_degree_order(bfs_graph *g, const std::vector<int32_t> &ptr, con
     if (st == BFS_OK) st = upload(&g->do_pos, pos.data(), pos.size(), g->bytes);
     if (st == BFS_OK) st = build_long(n, dptr, &g->do_long, &g->do_map, g->do_nlong, g->do_nchunks, g->bytes);
     if (st == BFS_OK) st = build_rest(n, dptr, &g->do_rest, g->bytes);
-    // the pull's row chunks: runs of at most kMsRows labels holding about the
-    // entries kMsRows rows hold on average (rows of kMsLong+ entries count
-    // nothing: their chunks are dealt apart), so that the heaviest rows,
-    // which now lie side by side, spread over many workgroups
-    uint64_t short_entries = 0;
-    for (int32_t x = 0; x < n; ++x) {
-        const uint32_t d = (uint32_t)(dptr[(size_t)x + 1] - dptr[(size_t)x]);
-        if (d < bfsi::kMsLong) short_entries += d;
-    }
-    const uint64_t target = std::max<uint64_t>(1, short_entries * bfsi::kMsRows / (uint64_t)n);
-    std::vector<int32_t> rows{0};
-    uint64_t acc = 0;
-    uint32_t cnt = 0;
-    for (int32_t x = 0; x < n; ++x) {
-        const uint32_t d = (uint32_t)(dptr[(size_t)x + 1] - dptr[(size_t)x]);
-        const uint64_t wgt = d < bfsi::kMsLong ? d : 0;
-        if (cnt > 0 && (cnt == bfsi::kMsRows || acc + wgt > target)) {
-            rows.push_back(x);
-            acc = 0;
-            cnt = 0;
-        }
-        acc += wgt;
-        ++cnt;
-    }
-    rows.push_back(n);
-    g->do_nrows = (uint32_t)(rows.size() - 1);
-    if (st == BFS_OK) st = upload(&g->do_rows, rows.data(), rows.size(), g->bytes);
     return st;
 }
 
@@ -1736,8 +1707,6 @@ static bfs_status ms_prepare(bfs_graph *g, int32_t nq, const int32_t *sources,
         p.nlo_chunks = p.nli_chunks = g->do_nchunks;
         p.nli = g->do_nlong;
         p.lirest = g->do_rest;
-        p.row_chunks = g->do_rows;
-        p.nrow_chunks = g->do_nrows;
         if (g->directed) {            // the out-lists for the push
             p.out_ptr = g->do_optr;
             p.out_idx = g->do_oidx;
@@ -1752,7 +1721,8 @@ static bfs_status ms_prepare(bfs_graph *g, int32_t nq, const int32_t *sources,
     }
     p.slev = vm ? vm_level : (int32_t *)(b + L.slev);
     p.spar = vm ? (uint32_t *)vm_parent : (uint32_t *)(b + L.spar);
-    p.fill_levels = vm ? 1u : 0u;
+    p.planes = (unsigned long long *)p.slev;          // 16-byte aligned either way
+    p.direct_levels = 0;
     p.level = (int32_t *const *)(b + L.lptr);
     p.parent = (int32_t *const *)(b + L.pptr);
     p.sources = (const int32_t *)(b + L.src);
@@ -1769,6 +1739,33 @@ static bfs_status ms_prepare(bfs_graph *g, int32_t nq, const int32_t *sources,
     // has settled saves whole rounds; below that the extra launch costs more)
     p.long_split = ((uint64_t)(g->nli_chunks - g->nli) > 2ull * grid * 4u) ? 1u : 0u;
     return BFS_OK;
+}
+
+// Before level k's launches: the bit planes have room for the levels it reaches
+// (k + 1).  A plane is cleared when its bit first appears; past the last one the
+// planes become staged levels, through the mask buffer that level k would
+// clear (F_{k-1}'s), and levels are stored directly from then on.
+static hipError_t ms_before_level(MsLevel &p, uint32_t k, uint32_t grid, hipStream_t s) {
+    const uint32_t next = k + 1;
+    if (p.direct_levels || (next & k) != 0) return hipSuccess;           // not a power of two
+    const size_t nw = (size_t)p.n * p.W;
+    for (uint32_t j = kMsPlanesFirst; j < kMsPlanes; ++j)
+        if (next == 1u << j) return launch_ms_zero(p.planes + nw * j, nw, s);
+    if (next != 1u << kMsPlanes) return hipSuccess;
+    unsigned long long *tmp = p.m[(k + 2) % 3];
+    hipError_t e = launch_ms_levels(p, kMsPlanes, tmp, grid, s);
+    if (e == hipSuccess) e = launch_ms_zero(tmp, nw, s);
+    p.direct_levels = 1;
+    return e;
+}
+
+// After the last level (`deepest` reached): per-source arrays, or the caller's
+// vertex-major levels.
+static hipError_t ms_finish(MsLevel &p, uint32_t deepest, bool vm, uint32_t grid, hipStream_t s) {
+    uint32_t planes = 0;
+    while (planes < kMsPlanes && deepest >> planes) ++planes;
+    if (!vm) return launch_ms_out(p, planes, grid, s);
+    return p.direct_levels ? hipSuccess : launch_ms_levels(p, planes, p.m[0], grid, s);
 }
 
 // One multi-source level k in the pull form (frontier = the union frontier's
@@ -1806,8 +1803,6 @@ static void ms_caller_order(const bfs_graph *g, MsLevel &p) {
     p.in_ptr = g->in_ptr;
     p.in_idx = g->in_idx;
     p.orig = p.pos = p.ent = p.out_ent = nullptr;
-    p.row_chunks = nullptr;
-    p.nrow_chunks = 0;
     p.stage_labels = 0;
     p.lo = g->lo;
     p.li = g->li;
@@ -1884,11 +1879,13 @@ static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sour
                                   : (pol == kPull) || (pol == kHeuristic &&
                                                        ((uint64_t)frontier << pull_shift) > (uint64_t)g->n);
         if (pull) {
+            HIP_TRY(ms_before_level(p, k, grid, s));
             HIP_TRY(ms_level(p, k, true, frontier, grid, s));
             ms_note(opt, k, 1, frontier);
         } else {
             const uint32_t group = (k >= kMsGroupFrom) ? kMsGroupLevels : 1u;
             for (uint32_t i = 0; i < group; ++i) {
+                HIP_TRY(ms_before_level(p, k + i, grid, s));
                 HIP_TRY(ms_level(p, k + i, false, 0, grid, s));
                 ms_note(opt, k + i, 0, i == 0 ? frontier : 0u);
             }
@@ -1902,7 +1899,7 @@ static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sour
         }
         dir = hs->h[2];
     }
-    if (vm_level == nullptr) HIP_TRY(launch_ms(p, kMsOut, k, grid, s));   // staged results -> per-source arrays
+    HIP_TRY(ms_finish(p, k, vm_level != nullptr, grid, s));
     if (opt) {
         opt->levels = k + 1;
         opt->trace_count = opt->trace ? std::min<uint32_t>(k + 1, opt->trace_capacity) : 0u;
@@ -2356,7 +2353,8 @@ extern "C" bfs_status bfs_ms_profile_levels(bfs_graph *g, int32_t num_sources, c
                 return e;
             if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
             const uint32_t t = k % 3, f = cnt[t];
-            if (f == 0) return hipSuccess;
+            if (f == 0) return ms_finish(p, k - 1, true, grid, s);      // (level 0 holds the sources)
+            if ((e = ms_before_level(p, k, grid, s)) != hipSuccess) return e;
             unsigned long long sd = 0, listed = 0, reached = 0;
             for (int gi = 0; gi < kMsDegGroups; ++gi) {
                 sd += stat[ms_line((int)t, gi)];

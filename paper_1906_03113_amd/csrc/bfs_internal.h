@@ -185,7 +185,9 @@ hipError_t launch_sl_level(const SlParams &p, uint32_t grid, hipStream_t s);
 // Multi-source search (64 sources per 64-bit word per vertex).
 constexpr uint32_t kMsLong = 512;      // degree from which a multi-source list entry is split
 constexpr uint32_t kMsChunk = 512;     // entries per chunk of a split entry
-constexpr uint32_t kMsRows = 512;      // most rows per chunk of the multi-source pull's row phase
+constexpr uint32_t kMsRows = 512;      // rows per chunk of the range-ordered pull
+constexpr uint32_t kMsPlanes = 5;      // level bit planes: searches of up to 2^kMsPlanes levels
+constexpr uint32_t kMsPlanesFirst = 3; // planes cleared at the start (the others when first needed)
 
 // A split entry of a multi-source work list: the vertex and the id of its
 // first chunk (chunks of one list are numbered consecutively in entry order).
@@ -217,10 +219,6 @@ struct MsLevel {
     // masks, vis, flags and lists use labels, the staged results and every
     // parent value the caller's ids
     const int32_t *orig, *pos, *ent, *out_ent;   // ent: in-list entries, out_ent: out-list entries
-    // the pull's row chunks: row_chunks[c] .. row_chunks[c + 1] - 1, at most
-    // kMsRows rows each (null: chunks of kMsRows consecutive rows)
-    const int32_t *row_chunks;
-    uint32_t nrow_chunks;
     uint32_t stage_labels;         // staged rows by label (the library's own staging with a degree order)
     // results staged vertex-major while the search runs, [n][W * 64]: row v
     // holds every source's level / parent of v (valid where vis has the bit),
@@ -228,15 +226,18 @@ struct MsLevel {
     // them into the callers' per-source arrays at the end (with stage_labels
     // the row of a vertex is its label, else its caller id; parents are
     // caller ids either way)
+    // The levels are bit planes in slev's memory, [kMsPlanes][n][W], until the
+    // search is over or past them (direct_levels: slev holds levels, as spar
+    // holds parents).
     int32_t *slev;
     uint32_t *spar;
+    unsigned long long *planes;
+    uint32_t direct_levels;
     int32_t *const *level;         // device array of nq device pointers
     int32_t *const *parent;
     const int32_t *sources;        // device, nq
     uint32_t *host_status;         // pinned host: [0] level, [1] its union frontier's size
                                    // (one 64-bit store), [2] its direction (stored before)
-    uint32_t fill_levels;          // slev / spar are the caller's vertex-major outputs:
-                                   // every level starts at -1 (no transpose at the end)
     // union-frontier bitmap of the level a pull runs on (bit v = some source
     // has v in its frontier), [ceil(n / 64)] words, built by k_ms_fbits when
     // use_fbits is set: the pull tests it before gathering a frontier mask
@@ -289,11 +290,16 @@ uint32_t persistent_max_grid(int device);
 // The multi-source launches: the start (clear, roots); a push level (push,
 // settle); a pull level (the frontier bitmap where it is used, rows by class,
 // the long rows' later chunks where they are split, close; after range passes
-// report); the staged results into per-source arrays.
+// report).
 enum MsPhase {
-    kMsClear, kMsRoots, kMsPush, kMsSettle, kMsFbits, kMsShortRows, kMsWide, kMsRest, kMsClose, kMsReport, kMsOut
+    kMsClear, kMsRoots, kMsPush, kMsSettle, kMsFbits, kMsShortRows, kMsWide, kMsRest, kMsClose, kMsReport
 };
 hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t grid, hipStream_t s);
+hipError_t launch_ms_zero(unsigned long long *a, size_t words, hipStream_t s);
+// The first `planes` level planes into vertex-major levels in place (tmp: n W words).
+hipError_t launch_ms_levels(const MsLevel &p, uint32_t planes, unsigned long long *tmp, uint32_t grid, hipStream_t s);
+// The staged results into per-source arrays.
+hipError_t launch_ms_out(const MsLevel &p, uint32_t planes, uint32_t grid, hipStream_t s);
 hipError_t launch_ms_rpull(const MsLevel &p, uint32_t k, uint32_t r, uint32_t grid, hipStream_t s);
 
 // ---------------------------------------------------------------------------

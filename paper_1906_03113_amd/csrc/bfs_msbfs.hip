@@ -70,40 +70,16 @@ __device__ __forceinline__ int32_t srow(const MsLevel &p, int32_t x) {
     return p.stage_labels ? x : caller_id(p, x);
 }
 
-// One step of the settle scan by a group of G lanes (G = 16 or 64, aligned
-// within the wave) over in_idx[eb + lane-in-group] (lanes past e1 hold
-// nothing): each bit of rem held by some lane's cur mask goes to the lowest
-// such lane, i.e. to the smallest in-neighbour of the step.  Returns the bits
-// found (the same in every lane of the group).  vo is the row's caller id
-// (its staged results), parents are written as the entries' caller ids.
-// scan_resolve is the second half, given each lane's entry (its caller id uc)
-// and its mask bits already restricted to rem.
+// One step of a scan by a group of G lanes (G = 16 or 64, aligned within the
+// wave), a list entry per lane (its caller id uc) with its mask's bits
+// restricted to the sources looked for (hit): each bit goes to the lowest lane
+// that holds it, i.e. to the smallest in-neighbour of the step.  Returns the
+// bits found (the same in every lane of the group).  vo is the row's staged
+// results' row.
 template <uint32_t G>
 __device__ __forceinline__ unsigned long long scan_resolve(const MsLevel &p, int32_t vo, uint32_t w,
                                                            int32_t uc, unsigned long long hit,
-                                                           uint32_t lk, bool owner_alone);
-
-template <uint32_t G>
-__device__ __forceinline__ unsigned long long scan_step(const MsLevel &p, const unsigned long long *cur,
-                                                        int32_t vo, uint32_t w, int32_t eb, int32_t e1,
-                                                        unsigned long long rem, uint32_t lk,
-                                                        bool owner_alone) {
-    const uint32_t li = __lane_id() & (G - 1u);
-    const int32_t e = eb + (int32_t)li;
-    int32_t uc = -1;
-    unsigned long long hit = 0ull;
-    if (e < e1) {
-        const int32_t u = p.in_idx[e];
-        if (in_frontier(p, u)) hit = row(cur, u, p.W)[w] & rem;
-        if (hit) uc = caller_id(p, u);                  // only an entry that may give a parent
-    }
-    return scan_resolve<G>(p, vo, w, uc, hit, lk, owner_alone);
-}
-
-template <uint32_t G>
-__device__ __forceinline__ unsigned long long scan_resolve(const MsLevel &p, int32_t vo, uint32_t w,
-                                                           int32_t uc, unsigned long long hit,
-                                                           uint32_t lk, bool owner_alone) {
+                                                           bool owner_alone) {
     const uint32_t li = __lane_id() & (G - 1u);
     if (__ballot(hit != 0ull) == 0ull) return 0ull;        // (uniform) nothing found in the wave
     unsigned long long incl = hit;
@@ -137,7 +113,6 @@ __device__ __forceinline__ unsigned long long scan_resolve(const MsLevel &p, int
         if ((found >> b) & 1ull) {
             const size_t at = stage(p, vo, w * 64u + b);
             const uint32_t pu = slot[b];
-            p.slev[at] = (int32_t)lk;
             if (owner_alone) p.spar[at] = pu;
             else atomicMin(&p.spar[at], pu);
         }
@@ -147,11 +122,8 @@ __device__ __forceinline__ unsigned long long scan_resolve(const MsLevel &p, int
 
 }  // namespace
 
-// Every mask to zero and every staged parent to 0xFFFFFFFF (parents are
-// combined with atomicMin).  Staged levels are written before they are read
-// (k_ms_out reads only entries whose vis bit is set), and k_ms_out writes
-// every output; when the staged arrays are the caller's vertex-major outputs
-// the levels start at -1 too (there is no k_ms_out).
+// Every mask and the first level planes to zero and every staged parent to
+// 0xFFFFFFFF (parents are combined with atomicMin).
 typedef int32_t v4i __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(kBlock) void k_ms_clear(MsLevel p) {
@@ -163,6 +135,8 @@ __global__ __launch_bounds__(kBlock) void k_ms_clear(MsLevel p) {
         p.m[0][i] = 0ull;
         p.m[1][i] = 0ull;
         p.m[2][i] = 0ull;
+#pragma unroll
+        for (uint32_t j = 0; j < kMsPlanesFirst; ++j) p.planes[nw * j + i] = 0ull;
     }
     for (size_t v = gid; v < (size_t)p.n; v += stride) p.flag[v] = 0u;
     // staged parents, 16 bytes at a time, streaming stores (not read by
@@ -170,11 +144,70 @@ __global__ __launch_bounds__(kBlock) void k_ms_clear(MsLevel p) {
     const size_t ns = (size_t)p.n * p.W * 16u;
     const v4i ones = {-1, -1, -1, -1};
     for (size_t i = gid; i < ns; i += stride) __builtin_nontemporal_store(ones, reinterpret_cast<v4i *>(p.spar) + i);
-    if (p.fill_levels)                                  // the caller's arrays: unreached = -1
-        for (size_t i = gid; i < ns; i += stride) __builtin_nontemporal_store(ones, reinterpret_cast<v4i *>(p.slev) + i);
     if (gid < 4) p.cnt[gid] = 0u;
     if (gid < 3) p.rcnt[gid] = 0u;
     if (gid < (size_t)kMsStatWords) p.mstat[gid] = 0ull;
+}
+
+// nw words to zero (a level plane before the first level that has its bit, a
+// mask buffer that held other data).
+__global__ __launch_bounds__(kBlock) void k_ms_zero(unsigned long long *a, size_t nw) {
+    const size_t stride = (size_t)gridDim.x * kBlock;
+    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < nw; i += stride) a[i] = 0ull;
+}
+
+// Lane t's word in every lane (t the same in all of them), and the lane's bit of
+// such a word.
+__device__ __forceinline__ unsigned long long word_of_lane(unsigned long long x, int t) {
+    return (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, t) |
+           ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), t) << 32);
+}
+__device__ __forceinline__ bool lane_bit(unsigned long long x, uint32_t lane) {
+    return __builtin_amdgcn_inverse_ballot_w64(x);
+}
+
+// The planes into vertex-major levels in the same memory (plane j's words are
+// [j n W, (j + 1) n W) of it, row v's levels the 32 words from 32 v W): row r0 =
+// ceil(planes n / 32) and those after it lie behind every plane and are written
+// first (part 0), while the planes' words that the rows before it need are
+// copied to tmp (planes r0 W words, at most 25 / 32 n W: one mask buffer); part 1
+// then writes those rows from tmp.  A wave takes 64 (row, word)s: a lane loads
+// the words of one each, then they go out one at a time with the 64 sources on
+// the lanes, a 256-byte store each (their words are the same in every lane: each
+// plane is one select by them).
+__global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes, unsigned long long *tmp, uint32_t part) {
+    const uint32_t W = p.W, lane = __lane_id();
+    const size_t nw = (size_t)p.n * W;
+    const size_t r0 = ((size_t)planes * (size_t)p.n + 31) / 32, split = r0 * W;
+    const size_t gid = (size_t)blockIdx.x * kBlock + threadIdx.x, stride = (size_t)gridDim.x * kBlock;
+    // (staged row, word) i has its masks at the row's label
+    const auto masks_of = [&](size_t i) -> size_t {
+        const size_t r = i / W;
+        return p.stage_labels ? i : (size_t)label_of(p, (int32_t)r) * W + (i - r * W);
+    };
+    if (part == 0)
+        for (size_t i = gid; i < split * planes; i += stride)
+            tmp[i] = p.planes[nw * (i / split) + masks_of(i % split)];
+    const size_t first = part == 0 ? split : 0, last = part == 0 ? nw : split;
+    for (size_t i0 = first + (gid - lane); i0 < last; i0 += stride) {            // uniform per wave
+        const size_t i = i0 + lane < last ? i0 + lane : last - 1;
+        const size_t m = masks_of(i);
+        const unsigned long long vis = p.vis[m];
+        unsigned long long pl[kMsPlanes];
+#pragma unroll
+        for (uint32_t j = 0; j < kMsPlanes; ++j) {
+            pl[j] = 0ull;
+            if (j < planes) pl[j] = part != 0 ? tmp[split * j + i] : p.planes[nw * j + m];
+        }
+        const int items = (int)(last - i0 < 64 ? last - i0 : 64);
+        for (int t = 0; t < items; ++t) {                                       // uniform
+            int32_t l = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < kMsPlanes; ++j)
+                if (j < planes) l |= lane_bit(word_of_lane(pl[j], t), lane) ? 1 << j : 0;
+            __builtin_nontemporal_store(lane_bit(word_of_lane(vis, t), lane) ? l : -1, p.slev + (i0 + (size_t)t) * 64u + lane);
+        }
+    }
 }
 
 // Level k, push half.  Work items: the frontier list, up to 64 columns per
@@ -409,6 +442,27 @@ __device__ __forceinline__ bool ms_last_to_arrive(const MsLevel &p) {
     return s_last != 0;
 }
 
+// Sources nb of word w reach label x at level k >= 1.  Levels are kept as bit
+// planes while the search is short: plane j, [n][W] like the masks, holds the
+// (vertex, source) pairs whose level has bit j, so a level costs one or two
+// mask-wide updates of consecutive words where staged levels cost a 4-byte store
+// per pair into 256-byte rows (R-MAT s22, 64 sources: 1 GB of them, in lines
+// written partly on each level and read again at the end).  With
+// direct_levels (a search past kMsPlaneLevels levels has turned its planes into
+// staged levels) they are stored one by one.
+__device__ __forceinline__ void set_levels(const MsLevel &p, int32_t x, uint32_t w, uint32_t k,
+                                           unsigned long long nb) {
+    if (p.direct_levels) {
+        const int32_t vo = srow(p, x);
+        for (unsigned long long b = nb; b; b &= b - 1ull)
+            p.slev[stage(p, vo, w * 64u + (uint32_t)__ffsll((long long)b) - 1u)] = (int32_t)k;
+        return;
+    }
+    unsigned long long *at = p.planes + (size_t)x * p.W + w;
+    const size_t step = (size_t)p.n * p.W;
+    for (uint32_t bits = k; bits; bits &= bits - 1u) at[step * ((uint32_t)__ffs((int)bits) - 1u)] |= nb;
+}
+
 // The direction of level k: the network's argmin between push (0) and pull (1)
 // over the level's twelve features, push when an output is not finite (or
 // without a network).  Features, from f = |F_k| (the union frontier), d = its
@@ -489,7 +543,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_roots(MsLevel p) {
         const unsigned long long bit = 1ull << (q & 63);
         atomicOr(&row(p.m[0], x, p.W)[q >> 6], bit);
         atomicOr(&row(p.vis, x, p.W)[q >> 6], bit);
-        p.slev[stage(p, srow(p, x), q)] = 0;
+        if (p.direct_levels) p.slev[stage(p, srow(p, x), q)] = 0;
         p.spar[stage(p, srow(p, x), q)] = (uint32_t)s;
         const int g = (int)(q % kMsDegGroups);
         atomicAdd(&p.mstat[ms_line(0, g) + 1], 1ull);              // one pair per source
@@ -524,9 +578,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_settle(MsLevel p, uint32_t k) {
             if (!nb) continue;
             pairs += (unsigned long long)__popcll(nb);
             row(p.vis, v, W)[w] |= nb;
-            const int32_t vo = srow(p, v);
-            for (unsigned long long b = nb; b; b &= b - 1ull)
-                p.slev[stage(p, vo, w * 64u + (uint32_t)__ffsll((long long)b) - 1u)] = (int32_t)(k + 1);
+            set_levels(p, v, w, k + 1, nb);
         }
     }
     add_stats(p, s1, deg, pairs);
@@ -563,8 +615,8 @@ __global__ __launch_bounds__(kBlock) void k_ms_fbits(MsLevel p, uint32_t k) {
 // keeps a source longer.
 __device__ __forceinline__ unsigned long long scan_wave4(const MsLevel &p, const unsigned long long *cur,
                                                          int32_t vo, uint32_t w, int32_t e0, int32_t e1,
-                                                         unsigned long long rem, uint32_t lk,
-                                                         bool owner_alone, bool prune) {
+                                                         unsigned long long rem, bool owner_alone,
+                                                         bool prune) {
     const uint32_t W = p.W;
     const int32_t lane = (int32_t)__lane_id();
     unsigned long long found = 0ull;
@@ -605,7 +657,7 @@ __device__ __forceinline__ unsigned long long scan_wave4(const MsLevel &p, const
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             if (rem) {                                                  // uniform
-                const unsigned long long f = scan_resolve<64>(p, vo, w, oo[t], mm[t] & rem, lk, owner_alone);
+                const unsigned long long f = scan_resolve<64>(p, vo, w, oo[t], mm[t] & rem, owner_alone);
                 rem &= ~f;
                 found |= f;
             }
@@ -640,8 +692,8 @@ __device__ __forceinline__ void long_chunk(const MsLevel &p, const unsigned long
     unsigned long long *vis = row(p.vis, v, W);
     for (uint32_t w = 0; w < W; ++w) {
         const unsigned long long full = (w == W - 1 && tail) ? ((1ull << tail) - 1ull) : ~0ull;
-        const unsigned long long found = scan_wave4(p, cur, srow(p, v), w, e0, e1, full & ~vis[w], k + 1,
-                                                    false, j != 0);
+        const unsigned long long found = scan_wave4(p, cur, srow(p, v), w, e0, e1, full & ~vis[w], false,
+                                                    j != 0);
         if (found && __lane_id() == 0) {
             atomicOr(&row(nxt, v, W)[w], found);
             if (first) vis[w] |= found;
@@ -681,7 +733,6 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_short(MsLevel p, uint32_t k)
         const uint32_t u = (uint32_t)fold[t / W];
         old[(size_t)u * W + (t % W)] = 0ull;
     }
-    const int32_t lk = (int32_t)(k + 1);
     const size_t items = (size_t)p.n * W;
     for (size_t i0 = gt - lane; i0 < items; i0 += gs) {                          // uniform per wave
         const size_t item = i0 + lane;
@@ -749,10 +800,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_short(MsLevel p, uint32_t k)
             }
 #pragma unroll
             for (int x = 0; x < kMsWriteRows; ++x) {
-                if (on[x]) {
-                    p.slev[at[x]] = lk;
-                    p.spar[at[x]] = (uint32_t)u[x];
-                }
+                if (on[x]) p.spar[at[x]] = (uint32_t)u[x];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -778,7 +826,7 @@ constexpr uint32_t kMsAlone = 2;               // open rows from which each gets
 __global__ __launch_bounds__(kBlock) void k_ms_pull_wide(MsLevel p, uint32_t k) {
     const unsigned long long *cur = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], k % 3);
     unsigned long long *nxt = pick3(p.m[0], p.m[1], p.m[2], (k + 1) % 3);
-    const uint32_t lane = __lane_id(), lk = k + 1;
+    const uint32_t lane = __lane_id();
     const uint32_t gw = (blockIdx.x * kBlock + threadIdx.x) >> 6, nw = (gridDim.x * kBlock) >> 6;
     const uint32_t nitems = p.long_split ? p.nli : p.nli_chunks;
     for (uint32_t c = gw; c < nitems; c += nw) {                                 // uniform per wave
@@ -844,7 +892,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_wide(MsLevel p, uint32_t k) 
             for (int t = 0; t < 4; ++t) {
                 const int32_t v = v0 + 4 * t + g;
                 const unsigned long long f = scan_resolve<16>(p, srow(p, v < p.n ? v : 0), 0u, oo[t], mm[t] & rem[t],
-                                                              lk, true);
+                                                              true);
                 rem[t] &= ~f;
                 fnd[t] |= f;
                 at[t] += 16;
@@ -860,7 +908,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_wide(MsLevel p, uint32_t k) 
                 const int og = (int)__ffsll((long long)o) - 1, src = 16 * og;
                 const int32_t a = __shfl(at[t], src, 64), z = __shfl(end[t], src, 64);
                 const unsigned long long rr = __shfl(rem[t], src, 64);
-                const unsigned long long f = scan_wave4(p, cur, srow(p, v0 + 4 * t + og), 0u, a, z, rr, lk, true, false);
+                const unsigned long long f = scan_wave4(p, cur, srow(p, v0 + 4 * t + og), 0u, a, z, rr, true, false);
                 if (g == og) fnd[t] |= f;
             }
         }
@@ -907,7 +955,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_rest(MsLevel p, uint32_t k) 
 // staged row.  Returns the bits found of the lane's word.
 template <uint32_t kWp>
 __device__ __forceinline__ unsigned long long words_resolve(const MsLevel &p, int32_t vo, uint32_t w0, int32_t uc,
-                                                            unsigned long long hit, uint32_t lk, bool owner_alone,
+                                                            unsigned long long hit, bool owner_alone,
                                                             uint32_t *slots) {
     if (__ballot(hit != 0ull) == 0ull) return 0ull;        // uniform
     const uint32_t lane = __lane_id(), word = lane % kWp;
@@ -939,7 +987,6 @@ __device__ __forceinline__ unsigned long long words_resolve(const MsLevel &p, in
         if ((fx >> lane) & 1ull) {
             const size_t at = stage(p, vo, (w0 + x) * 64u + lane);
             const uint32_t pu = slots[x * 64u + lane];
-            p.slev[at] = (int32_t)lk;
             if (owner_alone) p.spar[at] = pu;
             else atomicMin(&p.spar[at], pu);
         }
@@ -953,7 +1000,7 @@ __device__ __forceinline__ unsigned long long words_resolve(const MsLevel &p, in
 template <uint32_t kWp>
 __device__ __forceinline__ unsigned long long words_scan(const MsLevel &p, const unsigned long long *cur, int32_t vo,
                                                          uint32_t w0, int32_t e0, int32_t e1, unsigned long long rem,
-                                                         uint32_t lk, bool owner_alone, bool prune, uint32_t *slots) {
+                                                         bool owner_alone, bool prune, uint32_t *slots) {
     constexpr int32_t kStep = 64 / (int32_t)kWp;
     const uint32_t W = p.W, lane = __lane_id(), word = lane % kWp;
     const int32_t entry = (int32_t)(lane / kWp);
@@ -997,7 +1044,7 @@ __device__ __forceinline__ unsigned long long words_scan(const MsLevel &p, const
         for (int t = 0; t < 4; ++t) oo[t] = (mm[t] & rem) ? caller_id(p, uu[t]) : -1;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const unsigned long long f = words_resolve<kWp>(p, vo, w0, oo[t], mm[t] & rem, lk, owner_alone, slots);
+            const unsigned long long f = words_resolve<kWp>(p, vo, w0, oo[t], mm[t] & rem, owner_alone, slots);
             rem &= ~f;
             found |= f;
         }
@@ -1017,7 +1064,7 @@ __device__ __forceinline__ void words_chunk(const MsLevel &p, const unsigned lon
         const uint32_t w = w0 + lane % kWp;
         const unsigned long long rem = w < W ? full_word(p, w) & ~row(p.vis, v, W)[w] : 0ull;
         const unsigned long long found =
-            words_scan<kWp>(p, cur, srow(p, v), w0, e0, e1, rem, k + 1, false, j != 0, slots);
+            words_scan<kWp>(p, cur, srow(p, v), w0, e0, e1, rem, false, j != 0, slots);
         if (found && lane < kWp) {                          // lane x has word w0 + x
             atomicOr(&row(nxt, v, W)[w], found);
             if (first) row(p.vis, v, W)[w] |= found;
@@ -1033,7 +1080,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_wide_words(MsLevel p, uint32_t k)
     constexpr int32_t kStep = 64 / (int32_t)kWp;
     const unsigned long long *cur = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], k % 3);
     unsigned long long *nxt = pick3(p.m[0], p.m[1], p.m[2], (k + 1) % 3);
-    const uint32_t W = p.W, lane = __lane_id(), lk = k + 1, word = lane % kWp;
+    const uint32_t W = p.W, lane = __lane_id(), word = lane % kWp;
     const int32_t entry = (int32_t)(lane / kWp);
     const uint32_t gw = (blockIdx.x * kBlock + threadIdx.x) >> 6, nw = (gridDim.x * kBlock) >> 6;
     uint32_t *slots = s_par[threadIdx.x >> 6];
@@ -1090,9 +1137,9 @@ __global__ __launch_bounds__(kBlock) void k_ms_wide_words(MsLevel p, uint32_t k)
                 for (int t = 0; t < 4; ++t) {
                     if (v[t] < 0) continue;                                      // uniform
                     const int32_t vo = srow(p, v[t]);
-                    unsigned long long f = words_resolve<kWp>(p, vo, w0, oo[t], mm[t] & rem[t], lk, true, slots);
+                    unsigned long long f = words_resolve<kWp>(p, vo, w0, oo[t], mm[t] & rem[t], true, slots);
                     if (at[t] + kStep < end[t])
-                        f |= words_scan<kWp>(p, cur, vo, w0, at[t] + kStep, end[t], rem[t] & ~f, lk, true, false, slots);
+                        f |= words_scan<kWp>(p, cur, vo, w0, at[t] + kStep, end[t], rem[t] & ~f, true, false, slots);
                     if (f && lane < kWp) row(nxt, v[t], W)[w] = f;
                 }
             }
@@ -1144,6 +1191,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_close(MsLevel p, uint32_t k)
                 any = true;
                 pairs += (unsigned long long)__popcll(nb);
                 row(p.vis, (int32_t)v, W)[w] |= nb;
+                set_levels(p, (int32_t)v, w, k + 1, nb);
             }
             if (any) {
                 deg += (unsigned long long)(p.out_ptr[v + 1] - p.out_ptr[v]);
@@ -1161,42 +1209,87 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_close(MsLevel p, uint32_t k)
 }
 
 // The staged results into the callers' arrays: a block per 64 vertices and 64
-// sources, through an LDS tile, so that both the staged rows and the
+// sources.  Parents go through an LDS tile, so that both the staged rows and the
 // per-source output rows move in whole lines; each lane reads 4 sources of a
 // staged row and writes 4 vertices of an output row (16 bytes, or 4 scalar
 // stores where the caller's array is not 16-byte aligned or at the tail).
-// Entries whose vis bit is clear (never reached) become -1.
-__global__ __launch_bounds__(kBlock) void k_ms_out(MsLevel p) {
-    // one 64 x 64 tile (+1 column against bank conflicts), used for the
-    // levels and then for the parents: 16.6 KB per block, so that more blocks
-    // share a compute unit and keep more loads in flight
+// Levels need no transpose while they are bit planes: source q's level of a
+// vertex is bit q of the vertex's words, which the block keeps in LDS.  With
+// kPlanes false (a search past the planes) they are staged and go as the parents
+// do.  Pairs never reached become -1.
+template <bool kPlanes>
+__global__ __launch_bounds__(kBlock) void k_ms_out(MsLevel p, uint32_t planes) {
+    // one 64 x 64 tile (+1 column against bank conflicts): 16.6 KB per block, so
+    // that several blocks share a compute unit and keep more loads in flight
     __shared__ int32_t t_x[64][65];
-    const uint32_t W = p.W, S = W * 64u, tid = threadIdx.x;
+    __shared__ __align__(16) unsigned long long s_word[1 + kMsPlanes][64];   // visited, planes
+    __shared__ int32_t s_lab[64];
+    const uint32_t W = p.W, S = W * 64u, tid = threadIdx.x, lane = __lane_id(), wave = tid >> 6;
     const uint32_t ntiles = (uint32_t)(((size_t)p.n + 63) / 64);
     const uint32_t g4 = (tid & 15u) * 4u;          // first of this lane's 4 columns
+    const size_t nw = (size_t)p.n * W;
     for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int32_t v0 = (int32_t)(tile * 64u);
+        const bool in = v0 + (int32_t)lane < p.n;
+        const int32_t xl = in ? label_of(p, v0 + (int32_t)lane) : 0;
         for (uint32_t w = 0; w < W; ++w) {
+            if (wave == 0) {                       // a wave per kind of word, a lane per vertex
+                s_word[0][lane] = in ? row(p.vis, xl, W)[w] : 0ull;
+                s_lab[lane] = xl;
+            }
+            if (kPlanes)
+                for (uint32_t j = (wave + 3u) & 3u; j < planes; j += 4u)
+                    s_word[1 + j][lane] = in ? p.planes[nw * j + (size_t)xl * W + w] : 0ull;
+            __syncthreads();
             int4 lv[4], pa[4];
             uint32_t bits[4];
 #pragma unroll
             for (uint32_t r = 0; r < 4; ++r) {            // this lane's 4 sources of 4 staged rows
-                const int32_t v = v0 + (int32_t)((tid >> 4) + 16u * r);
+                const uint32_t vi = (tid >> 4) + 16u * r;
+                const int32_t v = v0 + (int32_t)vi;
                 lv[r] = make_int4(-1, -1, -1, -1);
                 pa[r] = lv[r];
-                bits[r] = 0;
-                const int32_t x = v < p.n ? label_of(p, v) : 0;
-                if (v < p.n) bits[r] = (uint32_t)(row(p.vis, x, W)[w] >> g4) & 15u;
+                bits[r] = (uint32_t)(s_word[0][vi] >> g4) & 15u;
                 if (bits[r]) {                          // read once: streaming loads
-                    const size_t at = (size_t)(p.stage_labels ? x : v) * S + w * 64u + g4;
-                    const v4i a = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(p.slev + at));
+                    const size_t at = (size_t)(p.stage_labels ? s_lab[vi] : v) * S + w * 64u + g4;
                     const v4i b = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(p.spar + at));
-                    lv[r] = make_int4(a.x, a.y, a.z, a.w);
                     pa[r] = make_int4(b.x, b.y, b.z, b.w);
+                    if (!kPlanes) {
+                        const v4i a = __builtin_nontemporal_load(reinterpret_cast<const v4i *>(p.slev + at));
+                        lv[r] = make_int4(a.x, a.y, a.z, a.w);
+                    }
                 }
             }
             int4 out_l[4], out_p[4];
-            for (int half = 0; half < 2; ++half) {         // levels, then parents
+            if (kPlanes) {
+                // sources qi = (tid >> 4) + 16 r of vertices g4 .. g4 + 3 (r < 2: the
+                // words' low halves)
+                int32_t l[4][4];
+#pragma unroll
+                for (uint32_t r = 0; r < 4; ++r)
+#pragma unroll
+                    for (uint32_t x = 0; x < 4; ++x) l[r][x] = 0;
+#pragma unroll
+                for (uint32_t j = 0; j <= kMsPlanes; ++j) {
+                    if (j > planes) break;
+                    const uint32_t sel = j < planes ? 1 + j : 0;         // the visited words last
+                    unsigned long long m[4];
+#pragma unroll
+                    for (uint32_t x = 0; x < 4; ++x) m[x] = s_word[sel][g4 + x];
+#pragma unroll
+                    for (uint32_t r = 0; r < 4; ++r)
+#pragma unroll
+                        for (uint32_t x = 0; x < 4; ++x) {
+                            const uint32_t half = r < 2 ? (uint32_t)m[x] : (uint32_t)(m[x] >> 32);
+                            const uint32_t bit = (half >> ((tid >> 4) + 16u * (r & 1u))) & 1u;
+                            if (j < planes) l[r][x] |= (int32_t)(bit << j);
+                            else l[r][x] = bit ? l[r][x] : -1;
+                        }
+                }
+#pragma unroll
+                for (uint32_t r = 0; r < 4; ++r) out_l[r] = make_int4(l[r][0], l[r][1], l[r][2], l[r][3]);
+            }
+            for (int half = kPlanes ? 1 : 0; half < 2; ++half) {         // levels, then parents
 #pragma unroll
                 for (uint32_t r = 0; r < 4; ++r) {        // staged rows -> tile[source][vertex]
                     const uint32_t vi = (tid >> 4) + 16u * r;
@@ -1221,24 +1314,21 @@ __global__ __launch_bounds__(kBlock) void k_ms_out(MsLevel p) {
                 const uint32_t qi = (tid >> 4) + 16u * r;
                 const uint32_t q = w * 64u + qi;
                 if (q >= p.nq) continue;
-                int32_t *lo = p.level[q] + v0 + g4;
-                int32_t *po = p.parent[q] + v0 + g4;
-                const int4 a = out_l[r], b = out_p[r];
                 const bool full = v0 + (int32_t)g4 + 3 < p.n;
-                if (full && ((reinterpret_cast<uintptr_t>(lo) | reinterpret_cast<uintptr_t>(po)) & 15u) == 0) {
-                    // written once and not read here again: streaming stores
-                    const v4i av = {a.x, a.y, a.z, a.w}, bv = {b.x, b.y, b.z, b.w};
-                    __builtin_nontemporal_store(av, reinterpret_cast<v4i *>(lo));
-                    __builtin_nontemporal_store(bv, reinterpret_cast<v4i *>(po));
-                } else {
-                    const int32_t av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
+                const auto put = [&](int32_t *o, const int4 &a) {
+                    if (full && (reinterpret_cast<uintptr_t>(o) & 15u) == 0) {
+                        // written once and not read here again: streaming stores
+                        const v4i av = {a.x, a.y, a.z, a.w};
+                        __builtin_nontemporal_store(av, reinterpret_cast<v4i *>(o));
+                        return;
+                    }
+                    const int32_t av[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        if (v0 + (int32_t)g4 + j < p.n) {
-                            lo[j] = av[j];
-                            po[j] = bv[j];
-                        }
-                }
+                        if (v0 + (int32_t)g4 + j < p.n) o[j] = av[j];
+                };
+                put(p.level[q] + v0 + g4, out_l[r]);
+                put(p.parent[q] + v0 + g4, out_p[r]);
             }
         }
     }
@@ -1264,7 +1354,7 @@ constexpr int32_t kRpShort = 64;
 // leaves e at the first entry not scanned.
 __device__ __forceinline__ unsigned long long rp_wave_row(const MsLevel &p, const unsigned long long *cur,
                                                           int32_t v, int32_t &e, int32_t e1, uint32_t rend,
-                                                          unsigned long long rem, uint32_t lk) {
+                                                          unsigned long long rem) {
     const uint32_t lane = __lane_id();
     unsigned long long found = 0ull;
     while (e < e1 && rem) {                                    // uniform
@@ -1293,7 +1383,6 @@ __device__ __forceinline__ unsigned long long rp_wave_row(const MsLevel &p, cons
                 const uint32_t b = (uint32_t)__ffsll((long long)own) - 1u;
                 own &= own - 1ull;
                 const size_t at = stage(p, v, b);
-                p.slev[at] = (int32_t)lk;
                 p.spar[at] = (uint32_t)u;
             }
             const unsigned long long f = __shfl(incl, 63, 64);
@@ -1324,7 +1413,6 @@ __global__ __launch_bounds__(kBlock) void k_ms_rpull(MsLevel p, uint32_t k, uint
     const uint32_t R = p.rp_ranges;
     const uint32_t rend = (r + 1 == R) ? (uint32_t)p.n : (uint32_t)(((uint64_t)(r + 1) * (uint64_t)p.n) / R);
     const unsigned long long full = (p.nq & 63u) ? ((1ull << (p.nq & 63u)) - 1ull) : ~0ull;
-    const uint32_t lk = k + 1;
     if (r == 0) {
         unsigned long long *old = pick3(p.m[0], p.m[1], p.m[2], s2);
         const int32_t *fold = pick3<const int32_t *>(p.fq[0], p.fq[1], p.fq[2], s2);
@@ -1417,7 +1505,6 @@ __global__ __launch_bounds__(kBlock) void k_ms_rpull(MsLevel p, uint32_t k, uint
                         const uint32_t j = (s_off[rr][lane >> 3] >> ((lane & 7u) * 4u)) & 15u;
                         const int32_t rv = all ? (int32_t)(r0 + rr) : lin[r0 + rr];
                         const size_t at = stage(p, rv, lane);
-                        p.slev[at] = (int32_t)lk;
                         p.spar[at] = (uint32_t)p.in_idx[s_e0[rr] + (int32_t)j];
                     }
                 }
@@ -1447,7 +1534,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_rpull(MsLevel p, uint32_t k, uint
             int32_t e = all ? b0 : p.rcur[v];
             const unsigned long long sv = p.vis[v];
             const unsigned long long rem = full & ~sv;
-            const unsigned long long got = rp_wave_row(p, cur, v, e, e1, rend, rem, lk);
+            const unsigned long long got = rp_wave_row(p, cur, v, e, e1, rend, rem);
             if (lane == 0) {
                 if (got) {
                     const unsigned long long before = nxt[v];
@@ -1492,7 +1579,11 @@ __global__ __launch_bounds__(kBlock) void k_ms_report(MsLevel p, uint32_t k) {
     for (uint32_t i = gt; i < nnext; i += gs) {
         const int32_t v = fnxt[i];
         deg += (unsigned long long)(p.out_ptr[v + 1] - p.out_ptr[v]);
-        for (uint32_t w = 0; w < W; ++w) pairs += (unsigned long long)__popcll(row(nxt, v, W)[w]);
+        for (uint32_t w = 0; w < W; ++w) {
+            const unsigned long long nb = row(nxt, v, W)[w];
+            pairs += (unsigned long long)__popcll(nb);
+            if (nb) set_levels(p, v, w, k + 1, nb);
+        }
     }
     add_stats(p, s1, deg, pairs);
     if (ms_last_to_arrive(p)) ms_close(p, k + 1, true, true);
@@ -1533,8 +1624,27 @@ hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t grid,
             break;
         case kMsClose: hipLaunchKernelGGL(k_ms_pull_close, dim3(close), b, 0, s, p, k); break;
         case kMsReport: hipLaunchKernelGGL(k_ms_report, dim3(small), b, 0, s, p, k); break;
-        case kMsOut: hipLaunchKernelGGL(k_ms_out, g, b, 0, s, p); break;
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_ms_zero(unsigned long long *a, size_t words, hipStream_t s) {
+    const size_t want = (words + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL(k_ms_zero, dim3((uint32_t)(want < 8192 ? want : 8192)), dim3(kBlock), 0, s, a, words);
+    return hipGetLastError();
+}
+
+hipError_t launch_ms_levels(const MsLevel &p, uint32_t planes, unsigned long long *tmp, uint32_t grid, hipStream_t s) {
+    hipLaunchKernelGGL(k_ms_levels, dim3(grid), dim3(kBlock), 0, s, p, planes, tmp, 0u);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || planes == 0) return e;
+    hipLaunchKernelGGL(k_ms_levels, dim3(grid), dim3(kBlock), 0, s, p, planes, tmp, 1u);
+    return hipGetLastError();
+}
+
+hipError_t launch_ms_out(const MsLevel &p, uint32_t planes, uint32_t grid, hipStream_t s) {
+    if (p.direct_levels) hipLaunchKernelGGL(k_ms_out<false>, dim3(grid), dim3(kBlock), 0, s, p, 0u);
+    else hipLaunchKernelGGL(k_ms_out<true>, dim3(grid), dim3(kBlock), 0, s, p, planes);
     return hipGetLastError();
 }
 
