@@ -221,6 +221,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes
 // through a per-wave LDS buffer flushed with one atomic per kMsFlush entries.
 // Also clears the masks of F_{k-1} (slot (k+2) % 3).
 constexpr uint32_t kMsWaveBuf = 256;
+constexpr int kMsBits = 4;               // sources of an entry handled together
 constexpr int32_t kMsShort = 16;         // longest column a group of lanes takes
 constexpr uint32_t kMsFlush = kMsWaveBuf - 64;
 
@@ -273,9 +274,23 @@ __global__ __launch_bounds__(kBlock) void k_ms_push(MsLevel p, uint32_t k) {
             // values in the caller's ids)
             const int32_t vo = p.stage_labels ? v : (p.out_ent ? p.out_ent[e] : v);
             const uint32_t uo = (uint32_t)caller_id(p, u);
-            for (unsigned long long b = nb; b; b &= b - 1ull) {
-                uint32_t *at = &p.spar[stage(p, vo, w * 64u + (uint32_t)__ffsll((long long)b) - 1u)];
-                if (*at > uo) atomicMin(at, uo);
+            // kMsBits sources at a time: their pre-reads are all in flight before
+            // the first atomic
+            for (unsigned long long b = nb; b;) {
+                uint32_t *at[kMsBits], cp[kMsBits];
+#pragma unroll
+                for (int x = 0; x < kMsBits; ++x) {
+                    cp[x] = 0u;                             // no source: nothing to lower
+                    at[x] = p.spar;
+                    if (b) {
+                        at[x] = &p.spar[stage(p, vo, w * 64u + (uint32_t)__ffsll((long long)b) - 1u)];
+                        cp[x] = *at[x];
+                    }
+                    b &= b - 1ull;
+                }
+#pragma unroll
+                for (int x = 0; x < kMsBits; ++x)
+                    if (cp[x] > uo) atomicMin(at[x], uo);
             }
             if (W == 1) {
                 // the lane whose OR turns nxt[v] nonzero lists v; a
@@ -315,7 +330,14 @@ __global__ __launch_bounds__(kBlock) void k_ms_push(MsLevel p, uint32_t k) {
     const uint32_t want = (ncur + nwaves - 1) / nwaves;
     const uint32_t C = (p.wide_steps || want >= 64u) ? 64u
                      : (want <= 1u ? 1u : 1u << (32 - __clz((int)(want - 1u))));
-    for (uint32_t b0 = (gt >> 6) * C; b0 < ncur; b0 += nwaves * C) {   // uniform per wave
+    // waves per group of C columns: 2, 4 or 8 where the list leaves that many
+    // (each takes every T-th 64 entries of a column longer than kMsShort, the
+    // first also the short ones; a wave alone would scan a column of up to 511
+    // entries in eight dependent steps)
+    const uint32_t groups = (ncur + C - 1) / C;
+    const uint32_t T = groups * 8u <= nwaves ? 8u : (groups * 4u <= nwaves ? 4u : (groups * 2u <= nwaves ? 2u : 1u));
+    const uint32_t seg = (gt >> 6) % T;
+    for (uint32_t b0 = (gt >> 6) / T * C; b0 < ncur; b0 += nwaves / T * C) {   // uniform per wave
         const uint32_t it = b0 + lane;
         int32_t u = -1, e0 = 0, d = 0;
         if (lane < C && it < ncur) {
@@ -323,7 +345,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_push(MsLevel p, uint32_t k) {
             e0 = p.out_ptr[u];
             d = p.out_ptr[u + 1] - e0;
         }
-        const int32_t ds = (d <= kMsShort) ? d : 0;
+        const int32_t ds = (d <= kMsShort && seg == 0u) ? d : 0;
         int32_t inc = ds;
 #pragma unroll
         for (uint32_t o = 1; o < 64; o <<= 1) {
@@ -354,7 +376,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_push(MsLevel p, uint32_t k) {
         for (unsigned long long mm = __ballot(d > kMsShort && (uint32_t)d < kMsLong); mm; mm &= mm - 1ull) {
             const int src = (int)__ffsll((long long)mm) - 1;
             const int32_t mu = __shfl(u, src, 64), me0 = __shfl(e0, src, 64), md = __shfl(d, src, 64);
-            for (int32_t eb = 0; eb < md; eb += 64) {               // uniform
+            for (int32_t eb = (int32_t)(64u * seg); eb < md; eb += (int32_t)(64u * T)) {    // uniform
                 int32_t v = -1;
                 const bool listed = (eb + (int32_t)lane < md) ? entry(mu, me0 + eb + (int32_t)lane, v) : false;
                 emit(listed, v);
@@ -364,16 +386,20 @@ __global__ __launch_bounds__(kBlock) void k_ms_push(MsLevel p, uint32_t k) {
         __builtin_amdgcn_wave_barrier();                           // LDS reused by the next step
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-    // the chunks of the graph's long columns, a wave each
-    for (uint32_t c = gt >> 6; c < p.nlo_chunks; c += gs >> 6) {
+    // the chunks of the graph's long columns, a wave each, or a part of one where
+    // there are fewer chunks than waves
+    const uint32_t parts = p.nlo_chunks * 8u <= nwaves ? 8u : (p.nlo_chunks * 4u <= nwaves ? 4u
+                         : (p.nlo_chunks * 2u <= nwaves ? 2u : 1u));
+    for (uint32_t c8 = gt >> 6; c8 < p.nlo_chunks * parts; c8 += nwaves) {
+        const uint32_t c = c8 / parts, part = c8 % parts;
         const MsLong L = p.lo[p.lomap[c]];
         const int32_t u = L.v;
         bool in_f = false;
         for (uint32_t w = 0; w < W; ++w) in_f = in_f || row(cur, u, W)[w] != 0ull;
         if (!in_f) continue;
-        const int32_t r1 = p.out_ptr[u + 1];
-        const int32_t e0 = p.out_ptr[u] + (int32_t)((c - L.chunk_base) * kMsChunk);
-        const int32_t e1 = (e0 + (int32_t)kMsChunk < r1) ? e0 + (int32_t)kMsChunk : r1;
+        const int32_t r1 = p.out_ptr[u + 1], len = (int32_t)(kMsChunk / parts);
+        const int32_t e0 = p.out_ptr[u] + (int32_t)((c - L.chunk_base) * kMsChunk) + (int32_t)part * len;
+        const int32_t e1 = (e0 + len < r1) ? e0 + len : r1;
         for (int32_t eb = e0; eb < e1; eb += 64) {       // uniform: whole waves step together
             const int32_t e = eb + (int32_t)lane;
             int32_t v = -1;
