@@ -2229,16 +2229,15 @@ extern "C" bfs_status bfs_masked_spmspv(bfs_graph *g, uint32_t semiring, const i
     P.st = (SpState *)(b + L.state);
     P.y_idx = y_idx;
     P.y_val = (unsigned long long *)y_val;
-    P.ny = (int32_t *)(b + L.ny);
+    HostSlot *hs = nullptr;
+    bfs_status st = host_slot(hs);
+    if (st != BFS_OK) return st;
+    P.host = hs->d;
     const uint32_t grid = (uint32_t)(8 * (g->cus > 0 ? g->cus : 256));
     HIP_TRY(launch_spmspv(P, grid, s));
-    SpState hst;
-    int32_t hny = 0;
-    HIP_TRY(hipMemcpyAsync(&hst, P.st, sizeof hst, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&hny, P.ny, sizeof hny, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    if (hst.bad) return fail(BFS_ERANGE, "a vector index lies outside [0, %d)", g->n);
-    *ny = hny;
+    if (hs->h[0]) return fail(BFS_ERANGE, "a vector index lies outside [0, %d)", g->n);
+    *ny = (int32_t)hs->h[1];
     return BFS_OK;
 }
 

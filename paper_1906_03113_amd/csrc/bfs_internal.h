@@ -476,7 +476,7 @@ struct SpParams {
     SpState *st;
     int32_t *y_idx;
     unsigned long long *y_val;
-    int32_t *ny;                           // device: the output's length
+    uint32_t *host;                        // pinned: [0] 1 = a vector index out of range, [1] output length
 };
 
 struct SpLayout {

@@ -8,16 +8,22 @@
 // modulo 2^64, and min-plus adds 1 with saturation at 2^64 - 1.
 //
 // Passes (one stream, the host waits at the end):
-//   k_sp_begin    counters to zero
-//   k_sp_check    every vector index in [0, n) (else nothing else runs)
-//   k_sp_product  vector entries 64 at a time: a lane per column of at most
-//                 kSpSerial entries, the wave for columns below kSpLong;
-//                 longer columns are listed for the chunk pass
+//   k_sp_check    every vector index in [0, n) (else no product runs)
+//   k_sp_product  up to 64 columns a wave, their entries dealt evenly to the
+//                 lanes; columns of kSpLong entries are listed for the chunk pass
 //   k_sp_items    chunk offsets of the listed columns (one workgroup scan)
 //   k_sp_long     chunks of kSpChunk entries, a wave each
 //   k_sp_count / k_sp_scan / k_sp_write
 //                 the support bitmap compacted in ascending order with the
-//                 values, resetting the accumulator and bitmap as it goes
+//                 values, resetting the accumulator, the bitmap and the state as
+//                 it goes; the outcome goes to a pinned host slot
+// What bounds it: a product is a chain of dependent random reads (row, its mask
+// word, its support word and accumulator) and then its atomics; a lane keeps
+// kSpBatch of them in flight.  R-MAT of 2^20 vertices, the widest level of a
+// search (min, select): product 161 + long columns 71 us with one entry after
+// another, 140 + 57 with eight of a lane in flight (the call 395 -> 298 us); a
+// random graph of 20,001 vertices 150 -> 50 us, most of it launches, copies and
+// the lockstep over the longest column.
 // Every product is an atomic on the row's accumulator (OR, add, or max of
 // the complement for the min semirings, so that every identity is zero) and
 // the row's support bit; products equal to the identity skip the value atomic.
@@ -31,7 +37,6 @@ namespace bfsi {
 
 namespace {
 
-constexpr int32_t kSpSerial = 16;
 constexpr uint32_t kWaves = kBlock / 64;
 constexpr int kScanBlock = 1024;
 
@@ -47,48 +52,75 @@ __device__ __forceinline__ unsigned long long mul(uint32_t sr, unsigned long lon
     return v;
 }
 
-// y(i) (+)= p, and i joins the support
-__device__ __forceinline__ void accumulate(const SpParams &P, int32_t i, unsigned long long p) {
-    const uint32_t bit = 1u << (i & 31);
-    if ((P.touched[(uint32_t)i >> 5] & bit) == 0u) atomicOr(&P.touched[(uint32_t)i >> 5], bit);
-    if (P.semiring == kSrBoolean) {
-        if (p) atomicOr(&P.acc[i], 1ull);
-    } else if (P.semiring == kSrArithmetic) {
-        if (p) atomicAdd(&P.acc[i], p);
-    } else {
-        const unsigned long long c = ~p;                 // min of p == max of ~p
-        if (c != 0ull && P.acc[i] < c) atomicMax(&P.acc[i], c);
+// y(i) (+)= p for kSpBatch entries of a lane (those with on), and their rows join
+// the support: the row-mask words of all of them are loaded together, then the
+// support words and (min semirings) the accumulators, then the atomics that are
+// still needed go out.  One entry after another a lane had one of these
+// dependent loads in flight at a time.  The pre-reads may be stale: bits are only
+// set and accumulators of the min semirings only raised, so a stale one lets an
+// atomic through that changes nothing.
+constexpr int kSpBatch = 8;
+
+__device__ __forceinline__ void accumulate(const SpParams &P, const int32_t (&i)[kSpBatch],
+                                           const unsigned long long (&p)[kSpBatch], bool (&on)[kSpBatch]) {
+    uint32_t m[kSpBatch], w[kSpBatch];
+    unsigned long long a[kSpBatch];
+    if (P.row_mask != nullptr) {
+#pragma unroll
+        for (int x = 0; x < kSpBatch; ++x) m[x] = on[x] ? P.row_mask[(uint32_t)i[x] >> 5] : 0u;
+#pragma unroll
+        for (int x = 0; x < kSpBatch; ++x) on[x] = on[x] && (((m[x] >> (i[x] & 31)) & 1u) ^ P.row_comp) != 0u;
+    }
+    const bool lowest = P.semiring == kSrMinPlus || P.semiring == kSrMinSelect;
+#pragma unroll
+    for (int x = 0; x < kSpBatch; ++x) {
+        w[x] = 0xFFFFFFFFu;
+        a[x] = ~0ull;
+        if (on[x]) {
+            w[x] = P.touched[(uint32_t)i[x] >> 5];
+            if (lowest) a[x] = P.acc[i[x]];
+        }
+    }
+#pragma unroll
+    for (int x = 0; x < kSpBatch; ++x) {
+        if (!on[x]) continue;
+        const uint32_t bit = 1u << (i[x] & 31);
+        if ((w[x] & bit) == 0u) atomicOr(&P.touched[(uint32_t)i[x] >> 5], bit);
+        if (lowest) {
+            const unsigned long long c = ~p[x];              // min of p == max of ~p
+            if (a[x] < c) atomicMax(&P.acc[i[x]], c);
+        } else if (p[x]) {
+            if (P.semiring == kSrBoolean) atomicOr(&P.acc[i[x]], 1ull);
+            else atomicAdd(&P.acc[i[x]], p[x]);
+        }
     }
 }
 
-// Exclusive prefix sum over a workgroup of kScanBlock threads (LDS), and the
-// total.
+// Exclusive prefix sum over a workgroup of kScanBlock threads, and the total:
+// within the waves by shuffles, over their sums through LDS.
 __device__ __forceinline__ unsigned long long block_scan(unsigned long long v, unsigned long long *s,
                                                          unsigned long long &total) {
-    const uint32_t t = threadIdx.x;
-    s[t] = v;
-    __syncthreads();
-    for (uint32_t d = 1; d < blockDim.x; d <<= 1) {
-        const unsigned long long o = (t >= d) ? s[t - d] : 0ull;
-        __syncthreads();
-        s[t] += o;
-        __syncthreads();
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
+    unsigned long long inc = v;
+#pragma unroll
+    for (uint32_t d = 1; d < 64; d <<= 1) {
+        const unsigned long long o = __shfl_up(inc, d, 64);
+        if (lane >= d) inc += o;
     }
-    total = s[blockDim.x - 1];
-    const unsigned long long ex = s[t] - v;
+    if (lane == 63) s[wave] = inc;
     __syncthreads();
-    return ex;
+    unsigned long long before = 0ull;
+    total = 0ull;
+    for (uint32_t k = 0; k < kScanBlock / 64; ++k) {
+        const unsigned long long x = s[k];
+        before += k < wave ? x : 0ull;
+        total += x;
+    }
+    __syncthreads();
+    return before + inc - v;
 }
 
 }  // namespace
-
-__global__ void k_sp_begin(SpParams P) {
-    if (threadIdx.x == 0) {
-        P.st->nitems = 0;
-        P.st->bad = 0;
-        P.st->nchunks = 0ull;
-    }
-}
 
 __global__ __launch_bounds__(kBlock) void k_sp_check(SpParams P) {
     bool bad = false;
@@ -99,15 +131,23 @@ __global__ __launch_bounds__(kBlock) void k_sp_check(SpParams P) {
     if (__ballot(bad) != 0ull && lane_id() == 0) atomicOr(&P.st->bad, 1u);
 }
 
+// The columns below kSpLong entries, C to a wave (64, or as few as spread the
+// vector over all waves): their entries on one line (a prefix sum of their
+// lengths), 64 kSpBatch of them a step whatever the columns' lengths.  Longer
+// columns are listed for k_sp_long.
 __global__ __launch_bounds__(kBlock) void k_sp_product(SpParams P) {
+    __shared__ int32_t s_pre[kWaves][64];
     if (P.st->bad) return;
     const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
-    const uint32_t ngroups = ((uint32_t)P.nx + 63u) / 64u;
-    for (uint32_t it = blockIdx.x * kWaves + wave; it < ngroups; it += gridDim.x * kWaves) {
-        const uint32_t x = it * 64u + lane;
+    const uint32_t gw = blockIdx.x * kWaves + wave, nw = gridDim.x * kWaves;
+    int32_t *pre = s_pre[wave];
+    const uint32_t want = ((uint32_t)P.nx + nw - 1u) / nw;
+    const uint32_t C = want >= 64u ? 64u : (want <= 1u ? 1u : 1u << (32 - __clz((int)(want - 1u))));
+    for (uint32_t x0 = gw * C; x0 < (uint32_t)P.nx; x0 += nw * C) {              // uniform per wave
+        const uint32_t x = x0 + lane;
         int32_t j = -1, r0 = 0, deg = 0;
         unsigned long long p = 0ull;
-        if (x < (uint32_t)P.nx) {
+        if (lane < C && x < (uint32_t)P.nx) {
             j = P.x_idx[x];
             if (allowed(P.col_mask, P.col_comp, j)) {
                 r0 = P.out_ptr[j];
@@ -115,40 +155,56 @@ __global__ __launch_bounds__(kBlock) void k_sp_product(SpParams P) {
                 p = mul(P.semiring, P.x_val[x]);
             }
         }
-        const int32_t dl = deg <= kSpSerial ? deg : 0;
-        const int32_t dmax = wave_max(dl);
-        for (int32_t t = 0; t < dmax; ++t) {
-            if (t < dl) {
-                const int32_t i = P.out_idx[r0 + t];
-                if (allowed(P.row_mask, P.row_comp, i)) accumulate(P, i, p);
+        const int32_t dl = deg < (int32_t)kSpLong ? deg : 0;
+        const int32_t inc = (int32_t)wave_incl_scan((uint32_t)dl);
+        const int32_t total = __shfl(inc, 63, 64);
+        pre[lane] = inc - dl;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int32_t t0 = 0; t0 < total; t0 += 64 * kSpBatch) {                  // uniform
+            int32_t i[kSpBatch], at[kSpBatch];
+            unsigned long long pp[kSpBatch];
+            bool on[kSpBatch];
+#pragma unroll
+            for (int q = 0; q < kSpBatch; ++q) {
+                const int32_t t = t0 + 64 * q + (int32_t)lane;
+                on[q] = t < total;
+                int c = 0;                                  // the last column with pre <= t
+#pragma unroll
+                for (int step = 32; step; step >>= 1)
+                    if (pre[c + step] <= t) c += step;
+                at[q] = __shfl(r0, c, 64) + (t - pre[c]);
+                pp[q] = __shfl(p, c, 64);
             }
+#pragma unroll
+            for (int q = 0; q < kSpBatch; ++q) i[q] = on[q] ? P.out_idx[at[q]] : 0;
+            accumulate(P, i, pp, on);
         }
-        unsigned long long mid = __ballot(deg > kSpSerial && deg < (int32_t)kSpLong);
-        while (mid) {
-            const int leader = __ffsll((long long)mid) - 1;
-            mid &= mid - 1ull;
-            const int32_t rr = __shfl(r0, leader, 64), dd = __shfl(deg, leader, 64);
-            const unsigned long long pp = __shfl(p, leader, 64);
-            for (int32_t e = (int32_t)lane; e < dd; e += 64) {
-                const int32_t i = P.out_idx[rr + e];
-                if (allowed(P.row_mask, P.row_comp, i)) accumulate(P, i, pp);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();                                        // pre is rewritten
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const bool lg = deg >= (int32_t)kSpLong;
+        const unsigned long long bm = __ballot(lg);
+        if (bm) {
+            uint32_t slot = 0;
+            if (lane == 0) slot = atomicAdd(&P.st->nitems, (uint32_t)__popcll(bm));
+            slot = __shfl(slot, 0, 64) + lanes_below(bm);
+            if (lg) {
+                SpItem it2;
+                it2.j = j;
+                it2.nch = ((uint32_t)deg + kSpChunk - 1u) / kSpChunk;
+                it2.v = p;
+                it2.base = 0ull;
+                P.items[slot] = it2;
             }
-        }
-        if (deg >= (int32_t)kSpLong) {
-            const uint32_t slot = atomicAdd(&P.st->nitems, 1u);
-            SpItem it2;
-            it2.j = j;
-            it2.nch = ((uint32_t)deg + kSpChunk - 1u) / kSpChunk;
-            it2.v = p;
-            it2.base = 0ull;
-            P.items[slot] = it2;
         }
     }
 }
 
 // Chunk offsets of the listed columns: one workgroup of kScanBlock threads.
 __global__ __launch_bounds__(kScanBlock) void k_sp_items(SpParams P) {
-    __shared__ unsigned long long s[kScanBlock];
+    __shared__ unsigned long long s[kScanBlock / 64];
     if (P.st->bad) return;
     const uint32_t m = P.st->nitems;
     unsigned long long run = 0ull;
@@ -179,9 +235,18 @@ __global__ __launch_bounds__(kBlock) void k_sp_long(SpParams P) {
         const int32_t r1 = P.out_ptr[it.j + 1];
         const int32_t e0 = P.out_ptr[it.j] + (int32_t)((c - it.base) * kSpChunk);
         const int32_t e1 = (e0 + (int32_t)kSpChunk < r1) ? e0 + (int32_t)kSpChunk : r1;
-        for (int32_t e = e0 + (int32_t)lane; e < e1; e += 64) {
-            const int32_t i = P.out_idx[e];
-            if (allowed(P.row_mask, P.row_comp, i)) accumulate(P, i, it.v);
+        for (int32_t eb = e0; eb < e1; eb += 64 * kSpBatch) {              // uniform
+            int32_t i[kSpBatch];
+            unsigned long long pp[kSpBatch];
+            bool on[kSpBatch];
+#pragma unroll
+            for (int q = 0; q < kSpBatch; ++q) {
+                const int32_t e = eb + 64 * q + (int32_t)lane;
+                on[q] = e < e1;
+                i[q] = on[q] ? P.out_idx[e] : 0;
+                pp[q] = it.v;
+            }
+            accumulate(P, i, pp, on);
         }
     }
 }
@@ -189,7 +254,6 @@ __global__ __launch_bounds__(kBlock) void k_sp_long(SpParams P) {
 // Output pass 1: set bits per workgroup of kSpOutWords words.
 __global__ __launch_bounds__(kSpOutWords) void k_sp_count(SpParams P) {
     __shared__ uint32_t s[kSpOutWords / 64];
-    if (P.st->bad) return;
     const uint32_t w = blockIdx.x * kSpOutWords + threadIdx.x;
     uint32_t c = w < P.words ? (uint32_t)__popc(P.touched[w]) : 0u;
 #pragma unroll
@@ -203,11 +267,10 @@ __global__ __launch_bounds__(kSpOutWords) void k_sp_count(SpParams P) {
     }
 }
 
-// Output pass 2: exclusive offsets of the workgroups (one workgroup of
-// kScanBlock threads) and the output length.
+// Output pass 2 where there are more than kSpSelf workgroups: their exclusive
+// offsets (one workgroup of kScanBlock threads).
 __global__ __launch_bounds__(kScanBlock) void k_sp_scan(SpParams P, uint32_t nblocks) {
-    __shared__ unsigned long long s[kScanBlock];
-    if (P.st->bad) return;
+    __shared__ unsigned long long s[kScanBlock / 64];
     unsigned long long run = 0ull;
     for (uint32_t b = 0; b < nblocks; b += kScanBlock) {
         const uint32_t t = b + threadIdx.x;
@@ -217,26 +280,40 @@ __global__ __launch_bounds__(kScanBlock) void k_sp_scan(SpParams P, uint32_t nbl
         if (t < nblocks) P.block_off[t] = (uint32_t)(run + ex);
         run += total;
     }
-    if (threadIdx.x == 0) *P.ny = (int32_t)run;
 }
 
 // Output pass 3: each word's rows in ascending order with their values; the
-// accumulator entries and the words go back to zero.
-__global__ __launch_bounds__(kSpOutWords) void k_sp_write(SpParams P) {
-    __shared__ uint32_t s[kSpOutWords];
-    if (P.st->bad) return;
+// accumulator entries and the words go back to zero.  With summed set
+// block_off holds the workgroups' offsets; otherwise their counts, which each
+// workgroup sums up to its own (a launch less; kSpSelf counts at most).  After a
+// bad vector no row is in the support and nothing is written.  The first
+// workgroup reports that (host[0]) and resets the state for the next call, the
+// last one reports the output's length (host[1]).
+constexpr uint32_t kSpSelf = 4096;
+
+__global__ __launch_bounds__(kSpOutWords) void k_sp_write(SpParams P, uint32_t summed) {
+    __shared__ uint32_t s[kSpOutWords / 64], s_before[kSpOutWords / 64];
+    const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
     const uint32_t w = blockIdx.x * kSpOutWords + threadIdx.x;
     uint32_t bits = w < P.words ? P.touched[w] : 0u;
     const uint32_t c = (uint32_t)__popc(bits);
-    s[threadIdx.x] = c;
-    __syncthreads();
-    for (uint32_t d = 1; d < kSpOutWords; d <<= 1) {   // inclusive scan
-        const uint32_t o = threadIdx.x >= d ? s[threadIdx.x - d] : 0u;
-        __syncthreads();
-        s[threadIdx.x] += o;
-        __syncthreads();
+    const uint32_t incl = wave_incl_scan(c);
+    uint32_t before = 0;
+    if (summed) {
+        if (threadIdx.x == 0) before = P.block_off[blockIdx.x];
+    } else {
+        for (uint32_t b = threadIdx.x; b < blockIdx.x; b += kSpOutWords) before += P.block_off[b];
     }
-    uint32_t pos = P.block_off[blockIdx.x] + s[threadIdx.x] - c;
+    before = wave_sum(before);
+    if (lane == 63) s[wave] = incl;
+    if (lane == 0) s_before[wave] = before;
+    __syncthreads();
+    uint32_t pos = incl - c, total = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kSpOutWords / 64; ++k) {
+        pos += (k < wave ? s[k] : 0u) + s_before[k];
+        total += s[k] + s_before[k];
+    }
     const bool min_sr = P.semiring == kSrMinPlus || P.semiring == kSrMinSelect;
     while (bits) {
         const int b = __ffs(bits) - 1;
@@ -249,6 +326,14 @@ __global__ __launch_bounds__(kSpOutWords) void k_sp_write(SpParams P) {
         ++pos;
     }
     if (c) P.touched[w] = 0u;
+    if (threadIdx.x != 0) return;
+    if (blockIdx.x == gridDim.x - 1) P.host[1] = total;
+    if (blockIdx.x == 0) {
+        P.host[0] = P.st->bad;
+        P.st->bad = 0;
+        P.st->nitems = 0;
+        P.st->nchunks = 0ull;
+    }
 }
 
 SpLayout sp_layout(int32_t n, int32_t max_nx) {
@@ -268,7 +353,6 @@ SpLayout sp_layout(int32_t n, int32_t max_nx) {
 }
 
 hipError_t launch_spmspv(const SpParams &p, uint32_t grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_sp_begin, dim3(1), dim3(64), 0, s, p);
     uint32_t cg = ((uint32_t)p.nx + kBlock - 1) / kBlock;
     if (cg > 1024) cg = 1024;
     if (cg == 0) cg = 1;
@@ -278,8 +362,9 @@ hipError_t launch_spmspv(const SpParams &p, uint32_t grid, hipStream_t s) {
     hipLaunchKernelGGL(k_sp_long, dim3(grid), dim3(kBlock), 0, s, p);
     const uint32_t nb = (p.words + kSpOutWords - 1) / kSpOutWords;
     hipLaunchKernelGGL(k_sp_count, dim3(nb), dim3(kSpOutWords), 0, s, p);
-    hipLaunchKernelGGL(k_sp_scan, dim3(1), dim3(kScanBlock), 0, s, p, nb);
-    hipLaunchKernelGGL(k_sp_write, dim3(nb), dim3(kSpOutWords), 0, s, p);
+    const bool summed = nb > kSpSelf;
+    if (summed) hipLaunchKernelGGL(k_sp_scan, dim3(1), dim3(kScanBlock), 0, s, p, nb);
+    hipLaunchKernelGGL(k_sp_write, dim3(nb), dim3(kSpOutWords), 0, s, p, summed ? 1u : 0u);
     return hipGetLastError();
 }
 
