@@ -20,15 +20,15 @@ using namespace bfsi;
 
 // What a captured level loop depends on: any difference means a new capture.
 struct LoopKey {
-    uint32_t kind = 0;                 // 0: list-form level kernel, 1: sliced push
+    uint32_t kind = 0;                 // 0: list-form level kernel, 1: sliced push, 2: list-form step launches
     const void *ws = nullptr, *level = nullptr, *parent = nullptr;
-    uint32_t policy = 0, grid = 0, heavy = 0, chunk = 0, levels = 0, fb = 0, small = 0;
+    uint32_t policy = 0, grid = 0, heavy = 0, chunk = 0, levels = 0, fb = 0, count = 0;
     const float *sel = nullptr;
     const void *trace = nullptr, *slot = nullptr;
     bool operator==(const LoopKey &o) const {
         return kind == o.kind && ws == o.ws && level == o.level && parent == o.parent &&
                policy == o.policy && grid == o.grid && heavy == o.heavy && chunk == o.chunk &&
-               levels == o.levels && fb == o.fb && small == o.small && sel == o.sel &&
+               levels == o.levels && fb == o.fb && count == o.count && sel == o.sel &&
                trace == o.trace && slot == o.slot;
     }
 };
@@ -534,6 +534,9 @@ bfs_status make_params(bfs_graph *g, int32_t *level, int32_t *parent, const RunC
     P.st = (BfsState *)(b + L.state);
     P.trace = trace ? (DevLevelRec *)(b + L.trace) : nullptr;
     P.mlp = c.sel;
+    // step launches unless the levels are looked at one by one (traced, counted,
+    // profiled) or one launch runs them all
+    P.steps = (c.loop != BFS_LOOP_PERSISTENT && !trace) ? 1u : 0u;
     P.maintain_fb = (c.policy == kBitmap || c.policy == kLearned || c.policy == kHeuristic) ? 1u : 0u;
     return BFS_OK;
 }
@@ -622,6 +625,37 @@ bfs_status wait_level(const HostSlot *hs, hipStream_t s, uint32_t want, uint32_t
     }
 }
 
+// The graph of `body`'s launches, captured once per key and kept with the
+// bfs_graph (the caller holds its lock).
+template <class Body>
+bfs_status captured(bfs_graph *g, const LoopKey &key, Body body) {
+    GraphExecCache &gc = g->gcache;
+    if (gc.valid && gc.key == key) return BFS_OK;
+    if (gc.exec) { (void)hipGraphExecDestroy(gc.exec); gc.exec = nullptr; }
+    if (gc.graph) { (void)hipGraphDestroy(gc.graph); gc.graph = nullptr; }
+    gc.valid = false;
+    hipStream_t cap;
+    HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
+    hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) e = body(cap);
+    hipGraph_t graph = nullptr;
+    hipError_t e2 = hipStreamEndCapture(cap, &graph);
+    (void)hipStreamDestroy(cap);
+    if (e != hipSuccess || e2 != hipSuccess)
+        return fail(BFS_EHIP, "graph capture failed: %s", hipGetErrorString(e != hipSuccess ? e : e2));
+    hipGraphExec_t exec = nullptr;
+    e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    if (e != hipSuccess) {
+        (void)hipGraphDestroy(graph);
+        return fail(BFS_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
+    }
+    gc.graph = graph;
+    gc.exec = exec;
+    gc.key = key;
+    gc.valid = true;
+    return BFS_OK;
+}
+
 // The host loop and the captured-graph loop around a level launch: `launch`
 // issues one level on a stream; levels are issued `per_sync` at a time
 // between two reads of the progress slot (launches past the end return at
@@ -637,31 +671,13 @@ bfs_status level_loop(bfs_graph *g, const LoopKey &key, uint32_t loop, hipStream
     std::unique_lock<std::mutex> lock(g->mu, std::defer_lock);
     if (loop == BFS_LOOP_GRAPH) {
         lock.lock();                  // the captured graph is cached per bfs_graph
+        bfs_status cst = captured(g, key, [&](hipStream_t c) {
+            hipError_t e = hipSuccess;
+            for (uint32_t l = 0; l < L && e == hipSuccess; ++l) e = launch(c);
+            return e;
+        });
+        if (cst != BFS_OK) return cst;
         GraphExecCache &gc = g->gcache;
-        if (!(gc.valid && gc.key == key)) {
-            if (gc.exec) { (void)hipGraphExecDestroy(gc.exec); gc.exec = nullptr; }
-            if (gc.graph) { (void)hipGraphDestroy(gc.graph); gc.graph = nullptr; }
-            gc.valid = false;
-            hipStream_t cap;
-            HIP_TRY(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
-            hipError_t e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-            for (uint32_t l = 0; l < L && e == hipSuccess; ++l) e = launch(cap);
-            hipGraph_t graph = nullptr;
-            hipError_t e2 = hipStreamEndCapture(cap, &graph);
-            (void)hipStreamDestroy(cap);
-            if (e != hipSuccess || e2 != hipSuccess)
-                return fail(BFS_EHIP, "graph capture failed: %s", hipGetErrorString(e != hipSuccess ? e : e2));
-            hipGraphExec_t exec = nullptr;
-            e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-            if (e != hipSuccess) {
-                (void)hipGraphDestroy(graph);
-                return fail(BFS_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-            }
-            gc.graph = graph;
-            gc.exec = exec;
-            gc.key = key;
-            gc.valid = true;
-        }
         for (uint64_t issued = 0; !done; issued += L) {
             if (issued > max_levels) return fail(BFS_EHIP, "level loop did not terminate");
             HIP_TRY(hipGraphLaunch(gc.exec, s));
@@ -765,6 +781,81 @@ bfs_status read_trace(const DevLevelRec *dtrace, uint32_t levels, const std::vec
     return BFS_OK;
 }
 
+// The host loop and the graph loop of the step launches (k_step), whose
+// progress arrives when a launch starts: (launches started, frontier size).  The
+// host loop issues a launch when the one before it is seen to start
+// (levels_per_sync: when the one that many before it is), and never waits for
+// the stream before the end.  A launch of 6 us or more hides the next one's way
+// to the device; a second launch in the stream hides it always, but leaves two
+// launches of about 5 us to run past the search's end (an 11-level search of a
+// 16,384-vertex random graph 109 us against 91).  What is past the end finds it
+// ended, and the stream is waited for once, so that nothing of it is left when
+// the call returns.  A replay of the captured group ends with k_step_fold, a
+// launch without a level.
+constexpr uint32_t kStepsAhead = 1;
+
+bfs_status step_loop(bfs_graph *g, const LoopKey &key, const LevelParams &P, const RunCfg &c, hipStream_t s,
+                     HostSlot *hs, uint32_t &level, bfs_run_options *opt) {
+    const uint64_t most = 2ull * (uint64_t)g->n + 8;
+    uint32_t size = 1;
+    hs->h[0] = kNoLevel;
+    hs->h[1] = 1;
+    if (c.loop == BFS_LOOP_GRAPH) {
+        std::lock_guard<std::mutex> lock(g->mu);
+        const uint32_t L = key.levels;
+        bfs_status st = captured(g, key, [&](hipStream_t cap) {
+            hipError_t e = hipSuccess;
+            for (uint32_t l = 0; l < L && e == hipSuccess; ++l) e = launch_step(P, l & 1u, c.grid, cap);
+            return e == hipSuccess ? launch_step_fold(P, L & 1u, cap) : e;
+        });
+        if (st != BFS_OK) return st;
+        for (uint64_t issued = L + 1; size != 0; issued += L + 1) {
+            if (issued > 2 * most + L) return fail(BFS_EHIP, "level loop did not terminate");
+            HIP_TRY(hipGraphLaunch(g->gcache.exec, s));
+            st = wait_level(hs, s, (uint32_t)issued, size);
+            if (st != BFS_OK) return st;
+        }
+        HIP_TRY(hipStreamSynchronize(s));
+        level = hs->h[2];
+        return BFS_OK;
+    }
+    const uint32_t ahead = opt && opt->levels_per_sync ? opt->levels_per_sync : kStepsAhead;
+    const bool tk = opt && opt->time_kernels;
+    std::unique_lock<std::mutex> lock(g->mu, std::defer_lock);
+    if (tk) lock.lock();                  // the event pool is per bfs_graph
+    uint32_t launched = 0;
+    while (size != 0) {
+        if (launched > most) return fail(BFS_EHIP, "level loop did not terminate");
+        if (tk) {
+            while (g->events.size() < 2 * (size_t)launched + 2) {
+                hipEvent_t e;
+                HIP_TRY(hipEventCreate(&e));
+                g->events.push_back(e);
+            }
+            HIP_TRY(hipEventRecord(g->events[2 * (size_t)launched], s));
+        }
+        HIP_TRY(launch_step(P, launched & 1u, c.grid, s));
+        if (tk) HIP_TRY(hipEventRecord(g->events[2 * (size_t)launched + 1], s));
+        ++launched;
+        if (launched < ahead) continue;
+        bfs_status st = wait_level(hs, s, launched - ahead + 1, size);
+        if (st != BFS_OK) return st;
+    }
+    HIP_TRY(hipStreamSynchronize(s));
+    level = hs->h[2];
+    if (tk) {
+        float total = 0.f;
+        for (uint32_t i = 0; i < launched; ++i) {
+            float ms = 0.f;
+            HIP_TRY(hipEventElapsedTime(&ms, g->events[2 * (size_t)i], g->events[2 * (size_t)i + 1]));
+            total += ms * 1000.f;
+        }
+        opt->launches = launched;
+        opt->kernel_us = total;
+    }
+    return BFS_OK;
+}
+
 bfs_status run_levels(bfs_graph *g, LevelParams &P, const RunCfg &c, hipStream_t s,
                       uint32_t &levels_out, bfs_run_options *opt) {
     HostSlot *hs = nullptr;
@@ -786,20 +877,19 @@ bfs_status run_levels(bfs_graph *g, LevelParams &P, const RunCfg &c, hipStream_t
         if (!done) return fail(BFS_EHIP, "persistent search stopped at level %u with a nonempty frontier "
                                          "(grid barrier spin limit)", level);
     } else {
-        // several small levels to a launch, unless the launches are the levels:
-        // traced (their times), or counted
-        P.small = (P.trace || P.atomics) ? 0u : 1u;
         LoopKey key;
-        key.kind = 0;
+        key.kind = P.steps ? 2 : 0;
         key.ws = P.st; key.level = P.level; key.parent = P.parent; key.policy = c.policy;
         key.grid = c.grid; key.heavy = c.heavy; key.chunk = c.chunk; key.levels = c.per_sync;
-        key.sel = c.sel; key.fb = P.maintain_fb; key.small = P.small;
+        key.sel = c.sel; key.fb = P.maintain_fb;
+        key.count = P.atomics ? 1u + P.no_preread : 0u;
         key.trace = (const void *)P.trace; key.slot = (const void *)P.host_status;
         const LevelParams Pc = P;
         const uint32_t grid = c.grid;
-        bfs_status st = level_loop(g, key, c.loop, s, hs,
-                                   [&Pc, grid](hipStream_t st_) { return launch_level(Pc, grid, st_); },
-                                   level, times, opt);
+        bfs_status st = P.steps ? step_loop(g, key, Pc, c, s, hs, level, opt)
+                                : level_loop(g, key, c.loop, s, hs,
+                                             [&Pc, grid](hipStream_t st_) { return launch_level(Pc, grid, st_); },
+                                             level, times, opt);
         if (st != BFS_OK) return st;
     }
     levels_out = level;
@@ -1546,6 +1636,7 @@ bfs_status bfs_run(bfs_graph *g, int32_t source, int32_t *level, int32_t *parent
     if (count) {                                    // zeroed by the init launch
         P.atomics = &P.st->atomics;
         P.no_preread = count == 2u ? 1u : 0u;
+        P.steps = 0;
     }
     st = timed_init(g, opt, s, [&]() { return launch_init(P, 1, nullptr, source, s); });
     if (st != BFS_OK) return st;
@@ -2027,6 +2118,7 @@ extern "C" bfs_status bfs_profile_levels(bfs_graph *g, int32_t source, int32_t *
     LevelParams P;
     make_params(g, level, parent, c, workspace, false, P);
     P.maintain_fb = 1;
+    P.steps = 0;
     HostSlot *hs = nullptr;
     st = host_slot(hs);
     if (st != BFS_OK) return st;

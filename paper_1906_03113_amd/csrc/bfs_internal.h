@@ -18,10 +18,15 @@ constexpr int kMlpTotal = kMlpParams + 2 * kMlpIn;
 
 enum Variant : uint32_t { kPush = 0, kPull = 1, kBitmap = 2, kLearned = 3, kHeuristic = 4, kShortCircuit = 5 };
 
-// What one workgroup's run of small levels leaves for the launch's close.
-struct SmallOut {
-    uint32_t level, variant, nf, visited_cnt;
-    unsigned long long heavy, sdf, visited_deg;
+// What a step launch (k_step) tells the next one about the search.  kStepDerive:
+// the level it ran, from whose counters the next launch works out its own;
+// kStepGiven: the next launch's level itself; kStepEnded: there is none.
+enum StepKind : uint32_t { kStepDerive = 0, kStepGiven = 1, kStepEnded = 2 };
+struct alignas(64) StepBase {
+    uint32_t kind, level, launch, variant;
+    uint32_t nf, visited_cnt, u_buf, u_len;      // nf: short columns of the level's frontier
+    unsigned long long heavy, sdf, visited_deg;  // visited_*: through the level
+    uint32_t before, before_short;               // kStepGiven: columns of the level before (short ones)
 };
 
 // Device-resident search state (first bytes of every workspace).
@@ -48,7 +53,8 @@ struct alignas(256) BfsState {
     // watched by the groups' last arrivals only, everyone else watches its group
     uint32_t bar_gen_group[kBarGroups * 16];
     unsigned long long atomics;          // parent atomicMin operations issued (when counted)
-    SmallOut small;
+    uint32_t step_wr[3];                 // k_step: unvisited-list appends of launch j in [j % 3]
+    StepBase base[2];                    // k_step: launch j reads base[j & 1], writes base[(j + 1) & 1]
 };
 // Per-level record kept on the device (a trace ring of kTraceCap entries).
 struct DevLevelRec {
@@ -89,7 +95,7 @@ struct LevelParams {
     const float *mlp;        // selector weights (kMlpTotal floats) or nullptr
     uint32_t *host_status;   // pinned host memory: [0] level, [1] its frontier size
     uint32_t maintain_fb;
-    uint32_t small;                // small levels run several to a launch (not while levels are timed apart)
+    uint32_t steps;                // the levels run as step launches (k_step)
     unsigned long long *atomics;   // count the push's parent atomicMin operations here, or nullptr
     uint32_t no_preread;           // 1: every unmasked pair issues its atomicMin (no pre-read)
 };
@@ -283,6 +289,8 @@ MsLayout ms_layout(int32_t n, int32_t nq, bool staged = true);
 hipError_t launch_init(const LevelParams &p, int32_t nroots, const int32_t *roots_dev,
                        int32_t single_root, hipStream_t s);
 hipError_t launch_level(const LevelParams &p, uint32_t grid, hipStream_t s);
+hipError_t launch_step(const LevelParams &p, uint32_t odd, uint32_t grid, hipStream_t s);
+hipError_t launch_step_fold(const LevelParams &p, uint32_t odd, hipStream_t s);
 hipError_t launch_parents(const LevelParams &p, uint32_t grid, hipStream_t s);
 hipError_t launch_persistent(const LevelParams &p, uint32_t grid, hipStream_t s);
 uint32_t persistent_max_grid(int device);

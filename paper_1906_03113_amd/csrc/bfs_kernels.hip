@@ -169,6 +169,7 @@ struct LevelPtrs {
     const uint32_t *c_cur;
     uint32_t *c_nxt;
     int32_t *u_nxt;
+    uint32_t *u_wr;           // appends to u_nxt so far
     uint32_t deg_sum;         // out-degrees of the vertices this thread appended (all of them: < 2^31)
 };
 
@@ -193,6 +194,7 @@ __device__ __forceinline__ LevelPtrs level_ptrs(const LevelParams &P, uint32_t k
     L.c_cur = odd ? P.cmap[1] : P.cmap[0];
     L.c_nxt = odd ? P.cmap[0] : P.cmap[1];
     L.u_nxt = nullptr;
+    L.u_wr = nullptr;
     L.sc = false;
     L.pre = true;
     L.deg_sum = 0;
@@ -248,7 +250,7 @@ __device__ __forceinline__ void out_flush(const LevelParams &P, const LevelPtrs 
             O.lpos = (uint32_t)old;
             O.lcb = (uint32_t)(old >> 32);
         }
-        if (un) O.ubase = atomicAdd(&P.st->u_wr, un);
+        if (un) O.ubase = atomicAdd(L.u_wr, un);
         if (final && O.sdf) atomicAdd(&P.st->sdf[L.ns], O.sdf);
     }
     __syncthreads();
@@ -678,7 +680,8 @@ struct PullLds {
 // finished one wave per row (64 entries per step, ballot for the first hit).
 // A row with no in-neighbour can never be reached and leaves the list.
 __device__ __forceinline__ void pull_level(const LevelParams &P, LevelPtrs &L, PullLds &S, OutLds &O,
-                           uint32_t nreg, uint32_t nlong, uint32_t bid, uint32_t nblocks) {
+                           uint32_t nreg, uint32_t nlong, uint32_t ub, uint32_t ulen, uint32_t bid,
+                           uint32_t nblocks) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     // F_k joins B_{k+1}; its frontier bits are cleared
     const bool wc = word_carry(P, nreg + nlong);
@@ -689,8 +692,6 @@ __device__ __forceinline__ void pull_level(const LevelParams &P, LevelPtrs &L, P
             atomicOr(&L.vb_nxt[(uint32_t)j >> 5], 1u << (j & 31));
         }
     }
-    const uint32_t ub = P.st->u_buf;
-    const uint32_t ulen = P.st->u_len;
     const bool all = (ulen == kAllVertices);
     const uint32_t len = all ? (uint32_t)P.n : ulen;
     const int32_t *U = ub ? P.ul[1] : P.ul[0];
@@ -911,31 +912,31 @@ union LevelLds {
     float w[kMlpTotal];                       // decision of the next level's form
 };
 
-// The counters of level k, read together with every other slot's (one round
-// trip instead of one for the level and one for its slot).
+// What a launch knows of the level it runs.
 struct Counters {
-    uint32_t nf, nf_before;                   // short columns of F_k; all of F_{k-1}
-    unsigned long long heavy, sdf;
-    uint32_t variant;
+    uint32_t nf;                              // short columns of F_k
+    uint32_t before, before_short;            // all columns of F_{k-1}; the short ones
+    unsigned long long heavy, sdf;            // long columns (and their chunks), entries of F_k
+    uint32_t variant;                         // the form decided for the level
+    uint32_t u_buf, u_len;                    // the unvisited list
+    uint32_t visited_cnt;                     // through level k
+    unsigned long long visited_deg;
+    uint32_t ns, fs;                          // counter slots: F_{k+1}'s, and the one to clear
+    uint32_t *u_wr;
 };
 
-template <typename T>
-__device__ __forceinline__ T ring(T a, T b, T c, T d, uint32_t i) {
-    return i == 0 ? a : (i == 1 ? b : (i == 2 ? c : d));
-}
-
-__device__ __forceinline__ Counters read_counters(const BfsState *st, uint32_t &k) {
-    k = st->level;
-    const uint32_t f0 = st->nf[0], f1 = st->nf[1], f2 = st->nf[2], f3 = st->nf[3];
-    const unsigned long long h0 = st->heavy[0], h1 = st->heavy[1], h2 = st->heavy[2], h3 = st->heavy[3];
-    const unsigned long long s0 = st->sdf[0], s1 = st->sdf[1], s2 = st->sdf[2], s3 = st->sdf[3];
-    Counters c;
+__device__ __forceinline__ Counters level_counters(const LevelParams &P, uint32_t k) {
+    BfsState *st = P.st;
+    Counters c{};
+    c.nf = st->nf[k & 3];
+    c.heavy = st->heavy[k & 3];
+    c.sdf = st->sdf[k & 3];
     c.variant = st->variant;
-    const uint32_t i = k & 3, j = (k + 3) & 3;
-    c.nf = ring(f0, f1, f2, f3, i);
-    c.heavy = ring(h0, h1, h2, h3, i);
-    c.sdf = ring(s0, s1, s2, s3, i);
-    c.nf_before = k == 0 ? 0u : ring(f0, f1, f2, f3, j) + (uint32_t)ring(h0, h1, h2, h3, j);
+    c.u_buf = st->u_buf;
+    c.u_len = st->u_len;
+    c.ns = (k + 1) & 3;
+    c.fs = (k + 2) & 3;
+    c.u_wr = &st->u_wr;
     return c;
 }
 
@@ -945,6 +946,8 @@ __device__ __forceinline__ void level_body(const LevelParams &P, uint32_t k, con
     PullLds &pl = lds.big.p;
     OutLds &ol = lds.big.out;
     LevelPtrs L = level_ptrs(P, k);
+    L.ns = c.ns;
+    L.u_wr = c.u_wr;
     // short-circuit claims on the levels whose frontier columns hold at least
     // n / 8 entries (there atomics bound the level, and the rows they reach
     // find their parent one level up quickly); the min-select elsewhere
@@ -956,17 +959,16 @@ __device__ __forceinline__ void level_body(const LevelParams &P, uint32_t k, con
     const uint32_t v = level_form(P, c.variant);       // decided before the launch
     if (bid == 0 && threadIdx.x == 0) {
         BfsState *w = P.st;
-        const uint32_t fs = (k + 2) & 3;     // slot of level k+2: free since level k-2
-        w->nf[fs] = 0;
-        w->heavy[fs] = 0ull;
-        w->sdf[fs] = 0ull;
+        w->nf[c.fs] = 0;                     // the slot of level k+2: free since level k-2
+        w->heavy[c.fs] = 0ull;
+        w->sdf[c.fs] = 0ull;
     }
     out_init(ol);
     if (P.maintain_fb) {          // fb[(k+2)%3] held F_{k-1}: nobody reads or writes it now
         for (uint32_t w = bid * kBlock + threadIdx.x; w < P.words; w += nblocks * kBlock)
             L.fb_old[w] = 0u;
     }
-    if (v == kPull) pull_level(P, L, pl, ol, nreg, nlong, bid, nblocks);
+    if (v == kPull) pull_level(P, L, pl, ol, nreg, nlong, c.u_buf, c.u_len, bid, nblocks);
     else if (v == kBitmap) bitmap_level(P, L, tl, ol, nlong, nchunks, bid, nblocks);
     else push_level(P, L, tl, ol, nreg, nlong, nchunks, bid, nblocks);
     out_flush(P, L, ol, true);
@@ -1011,6 +1013,16 @@ __global__ __launch_bounds__(kBlock) void k_init(LevelParams P, int32_t single_r
         st->visited_cnt = 0;
         st->visited_deg = 0ull;
         st->atomics = 0ull;
+        // the step launches start from "the level before the first": launch 0
+        // derives level 0 from counter slot 0
+        StepBase nb{};
+        nb.kind = kStepDerive;
+        nb.level = 0xFFFFFFFFu;
+        nb.launch = 0xFFFFFFFFu;
+        nb.variant = kPush;
+        nb.u_len = kAllVertices;
+        st->base[0] = nb;
+        for (int t = 0; t < 3; ++t) st->step_wr[t] = 0u;
         for (int r = 0; r < kRing; ++r) {
             st->nf[r] = 0;
             st->heavy[r] = 0ull;
@@ -1123,6 +1135,14 @@ __device__ __forceinline__ void report_status(const LevelParams &P, uint32_t lev
     P.host_status[1] = nf;
 }
 
+// The same from launch j of the step launches: the level, then, in one 64-bit
+// word, the launches started and the frontier's size.
+__device__ __forceinline__ void report_step(const LevelParams &P, uint32_t j, uint32_t level, uint32_t nf) {
+    P.host_status[2] = level;
+    __hip_atomic_store((unsigned long long *)P.host_status, (unsigned long long)(j + 1u) | ((unsigned long long)nf << 32),
+                       __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Close level k (every block of the level is done): fold the counters, decide
 // the next level's form, report.  Called by every thread of one block; s_w is
 // that block's LDS (kMlpTotal floats), free by now.  Everything it reads that
@@ -1147,8 +1167,8 @@ __device__ __forceinline__ void close_level(const LevelParams &P, uint32_t k, ui
 // With frontier bitmaps the level before has to be as small, so that its bits
 // can be cleared from its list.  Every workgroup of a launch finds the same.
 __device__ __forceinline__ bool small_level(const LevelParams &P, uint32_t k, const Counters &c) {
-    return P.small && level_form(P, c.variant) == kPush && P.policy != kShortCircuit && (uint32_t)c.heavy == 0u &&
-           c.nf <= kSmall && c.sdf <= (unsigned long long)kSmall && (!P.maintain_fb || c.nf_before <= kSmall);
+    return level_form(P, c.variant) == kPush && P.policy != kShortCircuit && (uint32_t)c.heavy == 0u &&
+           c.nf <= kSmall && c.sdf <= (unsigned long long)kSmall && (!P.maintain_fb || c.before <= kSmall);
 }
 
 constexpr uint32_t kSmallLevels = 4096;       // small levels in one launch at most
@@ -1160,20 +1180,16 @@ constexpr uint32_t kSmallLevels = 4096;       // small levels in one launch at m
 // counter, every workgroup's arrival and the close (Erdos-Renyi n = 16,384: 16.6
 // us a level).  The masks are read coherently and a level's new bits set (in
 // both visited bitmaps: either one is then B_k) after every thread's tests.
-// Nothing in the state changes while the other workgroups of the launch may
-// still read it: the outcome goes to st->small and the last to arrive takes it
-// over (take_small).
-__device__ __forceinline__ void small_levels(const LevelParams &P, uint32_t k, const Counters &c, SmallLds &S) {
-    BfsState *st = P.st;
+// The outcome is the next launch's base.  S.w holds the network's weights
+// (step_form).
+__device__ __forceinline__ void small_levels(const LevelParams &P, uint32_t k, const Counters &c, SmallLds &S,
+                                             StepBase &next) {
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     uint32_t *fbk = k % 3 == 0 ? P.fb[0] : (k % 3 == 1 ? P.fb[1] : P.fb[2]);
     uint32_t *fbo = k % 3 == 0 ? P.fb[2] : (k % 3 == 1 ? P.fb[0] : P.fb[1]);
     const QEnt *q = (k & 1) ? P.q[1] : P.q[0], *qo = (k & 1) ? P.q[0] : P.q[1];
     const HeavyItem *ho = (k & 1) ? P.hl[0] : P.hl[1];
     uint32_t *vbn = (k & 1) ? P.vb[0] : P.vb[1];
-    const bool net = (P.policy == kLearned) && P.mlp != nullptr;
-    if (net)
-        for (uint32_t i = tid; i < (uint32_t)kMlpTotal; i += kBlock) S.w[i] = P.mlp[i];
     // the level's columns into LDS; its bits into the other bitmap, its own and
     // the former level's frontier bits cleared (set again on the way out)
     uint32_t nf = c.nf;
@@ -1185,15 +1201,14 @@ __device__ __forceinline__ void small_levels(const LevelParams &P, uint32_t k, c
         atomicOr(&vbn[(uint32_t)e.v >> 5], 1u << (e.v & 31));
         if (P.maintain_fb) fbk[(uint32_t)e.v >> 5] = 0u;
     }
-    if (P.maintain_fb && k != 0) {
-        const uint32_t slot = (k + 3) & 3, ns = st->nf[slot];
-        for (uint32_t i = tid; i < c.nf_before; i += kBlock) {
-            const int32_t v = i < ns ? qo[i].v : ho[i - ns].v;
+    if (P.maintain_fb) {
+        for (uint32_t i = tid; i < c.before; i += kBlock) {
+            const int32_t v = i < c.before_short ? qo[i].v : ho[i - c.before_short].v;
             fbo[(uint32_t)v >> 5] = 0u;
         }
     }
-    uint32_t visited = st->visited_cnt;
-    unsigned long long vdeg = st->visited_deg, sdf = c.sdf;
+    uint32_t visited = c.visited_cnt;
+    unsigned long long vdeg = c.visited_deg, sdf = c.sdf;
     uint32_t form = kPush, n_long = 0;
     for (uint32_t done = 0;; ++done) {
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);            // the bits above are performed
@@ -1339,58 +1354,185 @@ __device__ __forceinline__ void small_levels(const LevelParams &P, uint32_t k, c
     }
     __syncthreads();
     if (tid == 0) {
-        SmallOut &o = st->small;
-        __hip_atomic_store(&o.level, k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&o.variant, form, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&o.nf, S.n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&o.visited_cnt, visited, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&o.visited_deg, vdeg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&o.sdf, sdf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&o.heavy, (unsigned long long)S.nlong | ((unsigned long long)S.wsum[0] << 32),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        next.kind = nf ? kStepGiven : kStepEnded;
+        next.level = k;
+        next.variant = form;
+        next.nf = S.n;
+        next.heavy = (unsigned long long)S.nlong | ((unsigned long long)S.wsum[0] << 32);
+        next.sdf = sdf;
+        next.visited_cnt = visited;
+        next.visited_deg = vdeg;
+        next.before = 0;                                    // F_{k-1}'s frontier bits are clear
+        next.before_short = 0;
+        report_step(P, next.launch, k, nf);
     }
 }
 
-// The state as the small levels left it (one thread, every workgroup of the
-// launch has arrived): the next level's counters in its slot, the other
-// slots empty (F_{k-1}'s frontier bits are cleared already).
-__device__ __forceinline__ void take_small(const LevelParams &P) {
+// The level a step launch runs, worked out by every workgroup from what the
+// launch before left: nothing closes a level, so a launch has no arrivals to
+// count and no workgroup to wait for (a closing workgroup's two arrivals,
+// counter reads and stores took about 4 us of a small level's 14).  Launch j
+// reads counter slot j & 3 (filled by launch j - 1), fills the next one and
+// clears the one after; the first workgroup writes the next launch's base, which
+// nobody reads during this one.  Returns false after the search's end.
+__device__ __forceinline__ bool step_counters(const LevelParams &P, uint32_t odd, uint32_t &k, uint32_t &j, Counters &c) {
     BfsState *st = P.st;
-    const SmallOut &o = st->small;
-    const uint32_t k = ld_agent(&o.level), nf = ld_agent(&o.nf), variant = ld_agent(&o.variant);
-    const uint32_t vc = ld_agent(&o.visited_cnt);
-    const unsigned long long vd = ld_agent64(&o.visited_deg), sdf = ld_agent64(&o.sdf), hv = ld_agent64(&o.heavy);
-    for (uint32_t r = 0; r < (uint32_t)kRing; ++r) {
-        const bool here = r == (k & 3);
-        st->nf[r] = here ? nf : 0u;
-        st->heavy[r] = here ? hv : 0ull;
-        st->sdf[r] = here ? sdf : 0ull;
+    const StepBase b = odd ? st->base[1] : st->base[0];
+    const uint32_t f0 = st->nf[0], f1 = st->nf[1], f2 = st->nf[2], f3 = st->nf[3];
+    const unsigned long long h0 = st->heavy[0], h1 = st->heavy[1], h2 = st->heavy[2], h3 = st->heavy[3];
+    const unsigned long long s0 = st->sdf[0], s1 = st->sdf[1], s2 = st->sdf[2], s3 = st->sdf[3];
+    const uint32_t w0 = st->step_wr[0], w1 = st->step_wr[1], w2 = st->step_wr[2];
+    if (b.kind == kStepEnded) return false;
+    j = b.launch + 1u;
+    c.variant = b.variant;
+    c.u_buf = b.u_buf;
+    c.u_len = b.u_len;
+    c.visited_cnt = b.visited_cnt;
+    c.visited_deg = b.visited_deg;
+    if (b.kind == kStepGiven) {
+        k = b.level;
+        c.nf = b.nf;
+        c.heavy = b.heavy;
+        c.sdf = b.sdf;
+        c.before = b.before;
+        c.before_short = b.before_short;
+    } else {
+        const uint32_t i = j & 3u;
+        k = b.level + 1u;
+        c.nf = i == 0 ? f0 : (i == 1 ? f1 : (i == 2 ? f2 : f3));
+        c.heavy = i == 0 ? h0 : (i == 1 ? h1 : (i == 2 ? h2 : h3));
+        c.sdf = i == 0 ? s0 : (i == 1 ? s1 : (i == 2 ? s2 : s3));
+        c.before = b.nf + (uint32_t)b.heavy;
+        c.before_short = b.nf;
+        c.visited_cnt += c.nf + (uint32_t)c.heavy;
+        c.visited_deg += c.sdf;
+        if (b.variant == kPull) {                           // its survivors are the unvisited list
+            const uint32_t x = (j + 2u) % 3u;
+            c.u_buf ^= 1u;
+            c.u_len = x == 0 ? w0 : (x == 1 ? w1 : w2);
+        }
     }
-    st->visited_cnt = vc;
-    st->visited_deg = vd;
-    st->variant = variant;
-    st->level = k;
-    report_status(P, k, nf + (uint32_t)hv);
+    c.ns = (j + 1u) & 3u;
+    c.fs = (j + 2u) & 3u;
+    c.u_wr = &st->step_wr[j % 3u];
+    return true;
+}
+
+// The form of the level a step launch runs, when the level before did not
+// decide it (kStepGiven carries it): every workgroup for itself.
+__device__ __forceinline__ uint32_t step_form(const LevelParams &P, uint32_t k, const Counters &c, float *s_w) {
+    if (P.policy != kLearned && P.policy != kHeuristic) return P.policy;
+    __shared__ uint32_t s_v;
+    if (P.policy == kLearned && P.mlp != nullptr) {
+        for (uint32_t i = threadIdx.x; i < (uint32_t)kMlpTotal; i += kBlock) s_w[i] = P.mlp[i];
+        __syncthreads();
+    }
+    if (threadIdx.x < 64) {
+        const uint32_t v = decide_wave(P, s_w, k, (float)(c.nf + (uint32_t)c.heavy), (float)c.sdf,
+                                       (float)((uint32_t)P.n - c.visited_cnt),
+                                       (float)((unsigned long long)P.nnz - c.visited_deg));
+        if (threadIdx.x == 0) s_v = v;
+    }
+    __syncthreads();
+    return s_v;
+}
+
+// The base of a launch after (k, j, c) with the level's form decided.
+__device__ __forceinline__ StepBase step_base(uint32_t kind, uint32_t k, uint32_t j, const Counters &c) {
+    StepBase n{};
+    n.kind = kind;
+    n.level = k;
+    n.launch = j;
+    n.variant = c.variant;
+    n.nf = c.nf;
+    n.heavy = c.heavy;
+    n.sdf = c.sdf;
+    n.visited_cnt = c.visited_cnt;
+    n.visited_deg = c.visited_deg;
+    n.u_buf = c.u_buf;
+    n.u_len = c.u_len;
+    n.before = c.before;
+    n.before_short = c.before_short;
+    return n;
 }
 
 // One level: the level body on every block, then the last block to finish
-// closes the level, so a level is one launch.  A small level, and those after
-// it while they are small, is the first block's alone.  Launches after the end
-// of the search (empty frontier) return at once.
+// closes the level, so a level is one launch (searches whose levels are traced,
+// counted or profiled one by one).  Launches after the end of the search (empty
+// frontier) return at once.
 __global__ __launch_bounds__(kBlock, 8) void k_level(LevelParams P) {
     __shared__ LevelLds lds;
     BfsState *st = P.st;
-    uint32_t k;
-    const Counters c = read_counters(st, k);
+    const uint32_t k = st->level;
+    const Counters c = level_counters(P, k);
     const uint32_t nf = c.nf + (uint32_t)c.heavy;
     if (nf == 0) return;
-    if (small_level(P, k, c)) {
-        if (blockIdx.x == 0) small_levels(P, k, c, lds.small);
-        if (last_to_arrive(st, gridDim.x) && threadIdx.x == 0) take_small(P);
-        return;
-    }
     level_body(P, k, c, blockIdx.x, gridDim.x, lds);
     if (last_to_arrive(st, gridDim.x)) close_level(P, k, nf, lds.w, false);
+}
+
+// One level, or the first block's run of small ones, as a step launch
+// (step_counters); odd: the launch's number is odd.
+__global__ __launch_bounds__(kBlock, 8) void k_step(LevelParams P, uint32_t odd) {
+    __shared__ LevelLds lds;
+    BfsState *st = P.st;
+    StepBase &next = odd ? st->base[0] : st->base[1];
+    uint32_t k = 0, j = 0;
+    Counters c;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (!step_counters(P, odd, k, j, c)) {
+        if (first) next.kind = kStepEnded;
+        return;
+    }
+    const uint32_t nf = c.nf + (uint32_t)c.heavy;
+    if (nf == 0) {
+        if (first) {
+            next.kind = kStepEnded;
+            report_step(P, j, k, 0u);
+        }
+        return;
+    }
+    c.variant = step_form(P, k, c, lds.small.w);
+    if (first) {
+        next = step_base(kStepDerive, k, j, c);
+        st->step_wr[(j + 1u) % 3u] = 0u;
+    }
+    if (small_level(P, k, c)) {
+        if (blockIdx.x != 0) return;
+        if (threadIdx.x == 0) {
+            st->nf[c.fs] = 0u;
+            st->heavy[c.fs] = 0ull;
+            st->sdf[c.fs] = 0ull;
+            // a growing search has levels after these: its next launch is on its
+            // way meanwhile.  A shrinking one mostly ends in this launch, and
+            // reports when it knows
+            if (nf > c.before) report_step(P, j, k, nf);
+        }
+        small_levels(P, k, c, lds.small, next);
+        return;
+    }
+    if (first) report_step(P, j, k, nf);
+    __syncthreads();                          // the network's weights are read
+    level_body(P, k, c, blockIdx.x, gridDim.x, lds);
+}
+
+// The end of a replayed group of step launches: the next level's base in
+// base[0], as a launch of its own without a level.
+__global__ void k_step_fold(LevelParams P, uint32_t odd) {
+    BfsState *st = P.st;
+    uint32_t k = 0, j = 0;
+    Counters c;
+    if (!step_counters(P, odd, k, j, c)) {
+        st->base[0].kind = kStepEnded;
+        return;
+    }
+    const uint32_t nf = c.nf + (uint32_t)c.heavy;
+    st->base[0] = step_base(nf ? kStepGiven : kStepEnded, k, j, c);
+    st->step_wr[(j + 1u) % 3u] = 0u;
+    st->nf[c.fs] = 0u;
+    st->heavy[c.fs] = 0ull;
+    st->sdf[c.fs] = 0ull;
+    report_step(P, j, k, nf);
 }
 
 // The form of level 0 (after the init kernels).
@@ -1484,7 +1626,7 @@ __global__ __launch_bounds__(kBlock) void k_persistent(LevelParams P) {
     const uint32_t nb = gridDim.x;
     for (;;) {
         const uint32_t k = ld_agent(&st->level);
-        Counters c{};
+        Counters c = level_counters(P, k);
         c.nf = ld_agent(&st->nf[k & 3]);
         c.heavy = ld_agent64(&st->heavy[k & 3]);
         c.sdf = ld_agent64(&st->sdf[k & 3]);
@@ -1584,7 +1726,7 @@ hipError_t launch_init(const LevelParams &p, int32_t nroots, const int32_t *root
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (p.policy == kLearned || p.policy == kHeuristic) {
+    if (!p.steps && (p.policy == kLearned || p.policy == kHeuristic)) {
         hipLaunchKernelGGL(k_decide, dim3(1), dim3(64), 0, s, p);
         e = hipGetLastError();
     }
@@ -1593,6 +1735,16 @@ hipError_t launch_init(const LevelParams &p, int32_t nroots, const int32_t *root
 
 hipError_t launch_level(const LevelParams &p, uint32_t grid, hipStream_t s) {
     hipLaunchKernelGGL(k_level, dim3(grid), dim3(kBlock), 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t launch_step(const LevelParams &p, uint32_t odd, uint32_t grid, hipStream_t s) {
+    hipLaunchKernelGGL(k_step, dim3(grid), dim3(kBlock), 0, s, p, odd);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_fold(const LevelParams &p, uint32_t odd, hipStream_t s) {
+    hipLaunchKernelGGL(k_step_fold, dim3(1), dim3(1), 0, s, p, odd);
     return hipGetLastError();
 }
 
