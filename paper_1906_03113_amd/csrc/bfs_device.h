@@ -66,36 +66,79 @@ __device__ __forceinline__ unsigned long long ld_agent64(const unsigned long lon
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The selector network 12 -> 32 (ReLU) -> 32 (ReLU) -> 3, row-major weights
+// The selector network 12 -> 32 (ReLU) -> 32 (ReLU) -> 3: row-major weights
 // [out][in] followed by the biases, then the feature mean and inverse std.
-// Evaluated by one wave: lane o < 32 holds hidden unit o, inputs are passed
-// between lanes with shuffles (no arrays, so nothing spills).  Returns, in
+//
+// A decision stands between two levels, so its latency counts in full.
+// Evaluated from global memory it took 4 to 5 us, a dependent read for each
+// layer; so a whole workgroup stages the weights in LDS first, one coalesced
+// trip (which a caller's own reads share) by kBlock threads, the rows an odd number of words
+// apart, so that 32 lanes reading one column hit 32 banks (rows of 32 words hit
+// two).
+constexpr int kMlpRow1 = kMlpIn + 1, kMlpRow2 = kMlpH + 1;
+constexpr int kMlpAt2 = kMlpRow1 * kMlpH;                   // the second layer's rows
+constexpr int kMlpAtRest = kMlpAt2 + kMlpRow2 * kMlpH;      // b1, b2, then W3 to the end as they are
+constexpr int kMlpLds = kMlpAtRest + kMlpTotal - kMlpIn * kMlpH - kMlpH * kMlpH;
+
+__device__ __forceinline__ void stage_mlp(const float *w, float *s) {
+    constexpr int B1 = kMlpIn * kMlpH, W2 = B1 + kMlpH, B2 = W2 + kMlpH * kMlpH;
+    constexpr int per = (kMlpTotal + kBlock - 1) / kBlock;   // all in flight together
+    float x[per];
+#pragma unroll
+    for (int t = 0; t < per; ++t) {
+        const int i = (int)threadIdx.x + t * kBlock;
+        x[t] = w[i < kMlpTotal ? i : kMlpTotal - 1];
+    }
+#pragma unroll
+    for (int t = 0; t < per; ++t) {
+        const int i = (int)threadIdx.x + t * kBlock;
+        const int j = i < B1 ? i + i / kMlpIn
+                    : i < W2 ? kMlpAtRest + (i - B1)
+                    : i < B2 ? kMlpAt2 + (i - W2) + (i - W2) / kMlpH
+                             : kMlpAtRest + kMlpH + (i - B2);
+        if (i < kMlpTotal) s[j] = x[t];
+    }
+}
+
+__device__ __forceinline__ float lane_value(float v, int i) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
+}
+
+// Evaluated by one wave from staged weights: lane o < 32 holds hidden unit o,
+// inputs pass between lanes (no arrays, so nothing spills).  Returns, in
 // every lane, the argmin of the first `nout` predicted log-times, or -1 when
 // one of them is not finite.
-__device__ __forceinline__ int mlp_argmin(const float *w, float feat, int nout = kMlpOut) {
-    const float *W1 = w, *b1 = W1 + kMlpIn * kMlpH, *W2 = b1 + kMlpH,
-                *b2 = W2 + kMlpH * kMlpH, *W3 = b2 + kMlpH, *b3 = W3 + kMlpH * kMlpOut;
-    const float *mean = w + kMlpParams, *istd = mean + kMlpIn;
+__device__ __forceinline__ int mlp_argmin(const float *s, float feat, int nout = kMlpOut) {
+    const float *W2 = s + kMlpAt2, *b1 = s + kMlpAtRest, *b2 = b1 + kMlpH, *W3 = b2 + kMlpH,
+                *b3 = W3 + kMlpH * kMlpOut, *mean = b3 + kMlpOut, *istd = mean + kMlpIn;
     const uint32_t lane = lane_id();
     const uint32_t li = lane < (uint32_t)kMlpIn ? lane : 0u;
     const float x = (lane < (uint32_t)kMlpIn) ? (feat - mean[li]) * istd[li] : 0.f;
     const uint32_t o = lane & (kMlpH - 1);
     float a = b1[o];
-    for (int i = 0; i < kMlpIn; ++i) a = fmaf(W1[o * kMlpIn + i], __shfl(x, i, 64), a);
+#pragma unroll 4
+    for (int i = 0; i < kMlpIn; ++i) a = fmaf(s[o * kMlpRow1 + i], lane_value(x, i), a);
     const float h1 = a > 0.f ? a : 0.f;
     float c = b2[o];
-    for (int i = 0; i < kMlpH; ++i) c = fmaf(W2[o * kMlpH + i], __shfl(h1, i, 64), c);
+#pragma unroll 4
+    for (int i = 0; i < kMlpH; ++i) c = fmaf(W2[o * kMlpRow2 + i], lane_value(h1, i), c);
     const float h2 = (c > 0.f ? c : 0.f) * (lane < (uint32_t)kMlpH ? 1.f : 0.f);
+    float y[kMlpOut];
+#pragma unroll
+    for (int u = 0; u < kMlpOut; ++u) y[u] = W3[u * kMlpH + o] * h2;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+        for (int u = 0; u < kMlpOut; ++u) y[u] += __shfl_xor(y[u], d, 64);
     int best = 0;
     float bestv = 0.f;
     bool ok = true;
-    for (int u = 0; u < nout; ++u) {
-        float y = W3[u * kMlpH + o] * h2;
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) y += __shfl_xor(y, d, 64);
-        y += b3[u];
-        if (!(y == y) || y > 1e30f || y < -1e30f) ok = false;
-        if (u == 0 || y < bestv) { bestv = y; best = u; }
+    for (int u = 0; u < kMlpOut; ++u) {
+        if (u >= nout) break;
+        const float z = y[u] + b3[u];
+        if (!(z == z) || z > 1e30f || z < -1e30f) ok = false;
+        if (u == 0 || z < bestv) { bestv = z; best = u; }
     }
     return ok ? best : -1;
 }

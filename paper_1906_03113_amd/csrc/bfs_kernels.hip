@@ -47,21 +47,22 @@ namespace {
 // column entries, the level, the mean degree, and their log-ratios.
 __device__ __forceinline__ float level_feature(uint32_t i, float nf, float sdf, float nu,
                                                float sdu, float k, float n, float nnz) {
-    switch (i) {
-        case 0: return logf(1.f + nf);
-        case 1: return logf(1.f + sdf);
-        case 2: return logf(1.f + nu);
-        case 3: return logf(1.f + sdu);
-        case 4: return logf(1.f + k);
-        case 5: return nnz / n;
-        case 6: return logf((nf + 1.f) / n);
-        case 7: return logf((sdf + 1.f) / (nnz + 1.f));
-        case 8: return logf((nu + 1.f) / n);
-        case 9: return logf((sdu + 1.f) / (nnz + 1.f));
-        case 10: return logf((sdf + 1.f) / (sdu + 1.f));
-        case 11: return logf((nf + 1.f) / (nu + 1.f));
-        default: return 0.f;
-    }
+    // a / b per lane, then one logarithm for all: as a switch over the lanes the
+    // wave ran eleven logarithms and seven divisions one after another
+    const float a = i == 0 || i == 6 || i == 11 ? nf + 1.f
+                  : i == 1 || i == 7 || i == 10 ? sdf + 1.f
+                  : i == 2 || i == 8            ? nu + 1.f
+                  : i == 3 || i == 9            ? sdu + 1.f
+                  : i == 4                      ? k + 1.f
+                  : i == 5                      ? nnz
+                                                : 1.f;
+    const float b = i == 5 || i == 6 || i == 8 ? n
+                  : i == 7 || i == 9           ? nnz + 1.f
+                  : i == 10                    ? sdu + 1.f
+                  : i == 11                    ? nu + 1.f
+                                               : 1.f;
+    const float x = a / b;
+    return i == 5 ? x : logf(x);
 }
 
 // The form level k runs, decided once per level by one full wave (all 64
@@ -103,13 +104,11 @@ __device__ __forceinline__ LevelStats level_stats(const LevelParams &P, uint32_t
 
 // The form of level k from its counters L, by the first wave of the calling
 // block (every thread of the block calls it), recorded in the state.  The
-// network's weights are first staged in the LDS buffer s_w (kMlpTotal floats)
-// with coalesced loads by the whole block; its evaluation then reads LDS only.
+// network's weights are first staged in the LDS buffer s_w (kMlpLds floats).
 __device__ __forceinline__ void decide_level(const LevelParams &P, uint32_t k, const LevelStats &L,
                                              float *s_w) {
     const bool net = (P.policy == kLearned) && P.mlp != nullptr;
-    if (net)
-        for (uint32_t i = threadIdx.x; i < (uint32_t)kMlpTotal; i += blockDim.x) s_w[i] = P.mlp[i];
+    if (net) stage_mlp(P.mlp, s_w);
     __syncthreads();
     if (threadIdx.x < 64) {
         const uint32_t v = decide_wave(P, s_w, k, L.nf, L.sdf, L.nu, L.sdu);
@@ -894,7 +893,7 @@ struct SmallLds {
     uint32_t pre[kSmall];
     uint32_t wsum[kBlock / 64];
     uint32_t n, nlong;
-    float w[kMlpTotal];
+    float w[kMlpLds];
 };
 
 // The level kernels' LDS: one level's tiles and staged output; a workgroup's
@@ -909,7 +908,7 @@ union LevelLds {
         OutLds out;
     } big;
     SmallLds small;
-    float w[kMlpTotal];                       // decision of the next level's form
+    float w[kMlpLds];                       // decision of the next level's form
 };
 
 // What a launch knows of the level it runs.
@@ -1145,7 +1144,7 @@ __device__ __forceinline__ void report_step(const LevelParams &P, uint32_t j, ui
 
 // Close level k (every block of the level is done): fold the counters, decide
 // the next level's form, report.  Called by every thread of one block; s_w is
-// that block's LDS (kMlpTotal floats), free by now.  Everything it reads that
+// that block's LDS (kMlpLds floats), free by now.  Everything it reads that
 // other blocks changed during the level it reads with coherent loads; the
 // persistent kernel also acquires (`acquire`) the state that an earlier
 // level's close wrote in the same launch.
@@ -1424,7 +1423,7 @@ __device__ __forceinline__ uint32_t step_form(const LevelParams &P, uint32_t k, 
     if (P.policy != kLearned && P.policy != kHeuristic) return P.policy;
     __shared__ uint32_t s_v;
     if (P.policy == kLearned && P.mlp != nullptr) {
-        for (uint32_t i = threadIdx.x; i < (uint32_t)kMlpTotal; i += kBlock) s_w[i] = P.mlp[i];
+        stage_mlp(P.mlp, s_w);
         __syncthreads();
     }
     if (threadIdx.x < 64) {
@@ -1538,7 +1537,7 @@ __global__ void k_step_fold(LevelParams P, uint32_t odd) {
 // The form of level 0 (after the init kernels).
 __global__ void k_decide(LevelParams P) {
     __shared__ LevelStats s_ls;
-    __shared__ float s_w[kMlpTotal];
+    __shared__ float s_w[kMlpLds];
     if (threadIdx.x == 0) s_ls = level_stats(P, 0);
     __syncthreads();
     const LevelStats L = s_ls;
@@ -1727,7 +1726,7 @@ hipError_t launch_init(const LevelParams &p, int32_t nroots, const int32_t *root
         if (e != hipSuccess) return e;
     }
     if (!p.steps && (p.policy == kLearned || p.policy == kHeuristic)) {
-        hipLaunchKernelGGL(k_decide, dim3(1), dim3(64), 0, s, p);
+        hipLaunchKernelGGL(k_decide, dim3(1), dim3(kBlock), 0, s, p);
         e = hipGetLastError();
     }
     return e;

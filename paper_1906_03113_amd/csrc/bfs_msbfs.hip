@@ -496,21 +496,25 @@ __device__ __forceinline__ void set_levels(const MsLevel &p, int32_t x, uint32_t
 // (vertex, source) pairs not reached through level k, q sources, k, n and nnz.
 __device__ __forceinline__ float ms_feature(uint32_t i, float f, float d, float c, float u, float q,
                                             float k, float n, float nnz) {
-    switch (i) {
-        case 0: return logf(1.f + f);
-        case 1: return logf(1.f + d);
-        case 2: return logf(1.f + c);
-        case 3: return logf(1.f + q);
-        case 4: return logf(1.f + k);
-        case 5: return nnz / n;
-        case 6: return logf((f + 1.f) / n);
-        case 7: return logf((d + 1.f) / (nnz + 1.f));
-        case 8: return logf((u + 1.f) / (n * q));
-        case 9: return logf((d + 1.f) / (f + 1.f));
-        case 10: return logf((f + 1.f) * q / n);
-        case 11: return logf((d + 1.f) / (nnz - d + 1.f));
-        default: return 0.f;
-    }
+    // a / b per lane, then one logarithm for all (a switch over the lanes runs
+    // its cases one after another)
+    const float a = i == 0 || i == 6                      ? f + 1.f
+                  : i == 1 || i == 7 || i == 9 || i == 11 ? d + 1.f
+                  : i == 2                                ? c + 1.f
+                  : i == 3                                ? q + 1.f
+                  : i == 4                                ? k + 1.f
+                  : i == 5                                ? nnz
+                  : i == 8                                ? u + 1.f
+                  : i == 10                               ? (f + 1.f) * q
+                                                          : 1.f;
+    const float b = i == 5 || i == 6 || i == 10 ? n
+                  : i == 7                      ? nnz + 1.f
+                  : i == 8                      ? n * q
+                  : i == 9                      ? f + 1.f
+                  : i == 11                     ? nnz - d + 1.f
+                                                : 1.f;
+    const float x = a / b;
+    return i == 5 ? x : logf(x);
 }
 
 // The end of a level, by the last block of its last launch (a launch of its own
@@ -519,15 +523,23 @@ __device__ __forceinline__ float ms_feature(uint32_t i, float f, float d, float 
 // level k is decided, and the level, the list's size and the direction go to
 // the host, which polls for them.  Every thread of the block calls it.
 __device__ __forceinline__ void ms_close(const MsLevel &p, uint32_t k, bool next_list, bool report) {
+    __shared__ float s_w[kMlpLds];
     const uint32_t lane = __lane_id(), t = k % 3, tn = (k + 1) % 3;
-    if (threadIdx.x >= 64) return;
-    const uint32_t f = ld_agent(&p.cnt[t]);
+    uint32_t f = 0;
     unsigned long long d = 0, c = 0, r = 0;
-    if (lane < (uint32_t)kMsDegGroups) {
+    long long nnz = 0;
+    if (threadIdx.x < 64) {
+        f = ld_agent(&p.cnt[t]);
+        if (p.mlp != nullptr) nnz = p.out_ptr[p.n];
+    }
+    if (threadIdx.x < (uint32_t)kMsDegGroups) {
         d = ld_agent64(&p.mstat[ms_line((int)t, (int)lane)]);
         c = ld_agent64(&p.mstat[ms_line(kMsCumSlot, (int)lane)]);
         r = ld_agent64(&p.mstat[ms_line(kMsCumSlot, (int)lane) + 1]);
     }
+    if (p.mlp != nullptr) stage_mlp(p.mlp, s_w);
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
     if (next_list) {
         // the sizes of the lists so far, this one with them; the next list's statistics
         if (lane < (uint32_t)kMsDegGroups) {
@@ -541,15 +553,15 @@ __device__ __forceinline__ void ms_close(const MsLevel &p, uint32_t k, bool next
         }
     }
     uint32_t dir = 0;
-    if (p.mlp != nullptr) {
+    if (p.mlp != nullptr && f != 0) {
         d = wave_sum64(d);
         c = wave_sum64(c);
         r = wave_sum64(r);
         const unsigned long long pairs = (unsigned long long)p.n * p.nq;
         const unsigned long long u = pairs > r ? pairs - r : 0ull;
         const float feat = ms_feature(lane, (float)f, (float)d, (float)c, (float)u, (float)p.nq, (float)k, (float)p.n,
-                                      (float)p.out_ptr[p.n]);
-        const int b = mlp_argmin(p.mlp, feat, 2);
+                                      (float)nnz);
+        const int b = mlp_argmin(s_w, feat, 2);
         dir = b < 0 ? 0u : (uint32_t)b;
     }
     if (lane == 0 && report) {
