@@ -80,24 +80,37 @@ constexpr int kMlpAt2 = kMlpRow1 * kMlpH;                   // the second layer'
 constexpr int kMlpAtRest = kMlpAt2 + kMlpRow2 * kMlpH;      // b1, b2, then W3 to the end as they are
 constexpr int kMlpLds = kMlpAtRest + kMlpTotal - kMlpIn * kMlpH - kMlpH * kMlpH;
 
-__device__ __forceinline__ void stage_mlp(const float *w, float *s) {
-    constexpr int B1 = kMlpIn * kMlpH, W2 = B1 + kMlpH, B2 = W2 + kMlpH * kMlpH;
-    constexpr int per = (kMlpTotal + kBlock - 1) / kBlock;   // all in flight together
+// (in two halves, so that reads of the caller's can be in flight as well)
+struct MlpTrip {
+    static constexpr int per = (kMlpTotal + kBlock - 1) / kBlock;
     float x[per];
+};
+
+__device__ __forceinline__ void load_mlp(const float *w, MlpTrip &m) {
 #pragma unroll
-    for (int t = 0; t < per; ++t) {
+    for (int t = 0; t < MlpTrip::per; ++t) {
         const int i = (int)threadIdx.x + t * kBlock;
-        x[t] = w[i < kMlpTotal ? i : kMlpTotal - 1];
+        m.x[t] = w[i < kMlpTotal ? i : kMlpTotal - 1];
     }
+}
+
+__device__ __forceinline__ void store_mlp(const MlpTrip &m, float *s) {
+    constexpr int B1 = kMlpIn * kMlpH, W2 = B1 + kMlpH, B2 = W2 + kMlpH * kMlpH;
 #pragma unroll
-    for (int t = 0; t < per; ++t) {
+    for (int t = 0; t < MlpTrip::per; ++t) {
         const int i = (int)threadIdx.x + t * kBlock;
         const int j = i < B1 ? i + i / kMlpIn
                     : i < W2 ? kMlpAtRest + (i - B1)
                     : i < B2 ? kMlpAt2 + (i - W2) + (i - W2) / kMlpH
                              : kMlpAtRest + kMlpH + (i - B2);
-        if (i < kMlpTotal) s[j] = x[t];
+        if (i < kMlpTotal) s[j] = m.x[t];
     }
+}
+
+__device__ __forceinline__ void stage_mlp(const float *w, float *s) {
+    MlpTrip m;
+    load_mlp(w, m);
+    store_mlp(m, s);
 }
 
 __device__ __forceinline__ float lane_value(float v, int i) {
@@ -116,11 +129,11 @@ __device__ __forceinline__ int mlp_argmin(const float *s, float feat, int nout =
     const float x = (lane < (uint32_t)kMlpIn) ? (feat - mean[li]) * istd[li] : 0.f;
     const uint32_t o = lane & (kMlpH - 1);
     float a = b1[o];
-#pragma unroll 4
+#pragma unroll
     for (int i = 0; i < kMlpIn; ++i) a = fmaf(s[o * kMlpRow1 + i], lane_value(x, i), a);
     const float h1 = a > 0.f ? a : 0.f;
     float c = b2[o];
-#pragma unroll 4
+#pragma unroll
     for (int i = 0; i < kMlpH; ++i) c = fmaf(W2[o * kMlpRow2 + i], lane_value(h1, i), c);
     const float h2 = (c > 0.f ? c : 0.f) * (lane < (uint32_t)kMlpH ? 1.f : 0.f);
     float y[kMlpOut];

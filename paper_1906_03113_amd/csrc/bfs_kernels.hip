@@ -1419,11 +1419,12 @@ __device__ __forceinline__ bool step_counters(const LevelParams &P, uint32_t odd
 
 // The form of the level a step launch runs, when the level before did not
 // decide it (kStepGiven carries it): every workgroup for itself.
-__device__ __forceinline__ uint32_t step_form(const LevelParams &P, uint32_t k, const Counters &c, float *s_w) {
+__device__ __forceinline__ uint32_t step_form(const LevelParams &P, uint32_t k, const Counters &c, const MlpTrip &net,
+                                              float *s_w) {
     if (P.policy != kLearned && P.policy != kHeuristic) return P.policy;
     __shared__ uint32_t s_v;
     if (P.policy == kLearned && P.mlp != nullptr) {
-        stage_mlp(P.mlp, s_w);
+        store_mlp(net, s_w);
         __syncthreads();
     }
     if (threadIdx.x < 64) {
@@ -1479,6 +1480,8 @@ __global__ __launch_bounds__(kBlock, 8) void k_step(LevelParams P, uint32_t odd)
     uint32_t k = 0, j = 0;
     Counters c;
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    MlpTrip net;                              // on its way together with the counters
+    if (P.policy == kLearned && P.mlp != nullptr) load_mlp(P.mlp, net);
     if (!step_counters(P, odd, k, j, c)) {
         if (first) next.kind = kStepEnded;
         return;
@@ -1491,7 +1494,7 @@ __global__ __launch_bounds__(kBlock, 8) void k_step(LevelParams P, uint32_t odd)
         }
         return;
     }
-    c.variant = step_form(P, k, c, lds.small.w);
+    c.variant = step_form(P, k, c, net, lds.small.w);
     if (first) {
         next = step_base(kStepDerive, k, j, c);
         st->step_wr[(j + 1u) % 3u] = 0u;
