@@ -335,11 +335,14 @@ def ms_training_sets(include_large: bool = True):
     import graphgen
     train = [("er16k", lambda: graphgen.workload("er16k"), [(64, 1), (256, 2)]),
              ("grid512", lambda: graphgen.grid(512, 0.9, 3), [(16, 3), (64, 4)]),
-             ("rmatd16", lambda: graphgen.rmat(16, 16, 1, directed=True), [(64, 5), (256, 6)])]
+             ("rmatd16", lambda: graphgen.rmat(16, 16, 1, directed=True), [(64, 5), (256, 6), (12, 13), (32, 14)]),
+             ("rmat15", lambda: graphgen.rmat(15, 16, 9), [(3, 15), (10, 16), (40, 17), (100, 18)])]
     if include_large:
-        train += [("rmat22", lambda: graphgen.workload("rmat22"), [(64, 7), (16, 8)]),
-                  ("rmat20d", lambda: graphgen.workload("rmat20d"), [(256, 9), (64, 10)]),
-                  ("rmat19", lambda: graphgen.rmat(19, 16, 7), [(128, 11)]),
+        train += [("rmat22", lambda: graphgen.workload("rmat22"), [(64, 7), (16, 8), (3, 19)]),
+                  ("rmat20d", lambda: graphgen.workload("rmat20d"), [(256, 9), (64, 10), (16, 21), (4, 22)]),
+                  ("rmat19", lambda: graphgen.rmat(19, 16, 7), [(128, 11), (30, 23), (5, 24), (48, 28)]),
+                  ("rmatd18", lambda: graphgen.rmat(18, 16, 10, directed=True), [(9, 29), (40, 30), (100, 31)]),
+                  ("rmat20", lambda: graphgen.rmat(20, 16, 8), [(3, 25), (12, 26), (40, 32), (160, 27)]),
                   ("grid1024", lambda: graphgen.grid(1024, 0.9, 5), [(16, 12)])]
     held = [(f"rmat{sc}", (lambda sc=sc: graphgen.rmat(sc, 16, 2000 + sc)), [(64, 20 + sc), (192, 40 + sc)])
             for sc in ((16, 18) if not include_large else (16, 17, 18, 21))]
