@@ -1962,7 +1962,8 @@ static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sour
     if (learned) {
         st = wait_level(hs, s, 0u, frontier);
         if (st != BFS_OK) return st;
-        dir = hs->h[2];
+        dir = frontier >> 31;                 // the size's top bit (k < n < 2^31)
+        frontier &= 0x7FFFFFFFu;
     }
     for (;; ++k) {
         if ((uint64_t)k > (uint64_t)g->n + 2) return fail(BFS_EHIP, "multi-source loop did not terminate");
@@ -1988,7 +1989,8 @@ static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sour
             k = hs->h[0] - 1;                 // the level whose step found nothing
             break;
         }
-        dir = hs->h[2];
+        dir = frontier >> 31;
+        frontier &= 0x7FFFFFFFu;
     }
     HIP_TRY(ms_finish(p, k, vm_level != nullptr, grid, s));
     if (opt) {

@@ -1135,11 +1135,13 @@ __device__ __forceinline__ void report_status(const LevelParams &P, uint32_t lev
 }
 
 // The same from launch j of the step launches: the level, then, in one 64-bit
-// word, the launches started and the frontier's size.
+// word, the launches started and the frontier's size.  Relaxed: the host reads
+// the level once the stream is done (a release at system scope writes the L2
+// back first).
 __device__ __forceinline__ void report_step(const LevelParams &P, uint32_t j, uint32_t level, uint32_t nf) {
     P.host_status[2] = level;
     __hip_atomic_store((unsigned long long *)P.host_status, (unsigned long long)(j + 1u) | ((unsigned long long)nf << 32),
-                       __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Close level k (every block of the level is done): fold the counters, decide

@@ -565,9 +565,10 @@ __device__ __forceinline__ void ms_close(const MsLevel &p, uint32_t k, bool next
         dir = b < 0 ? 0u : (uint32_t)b;
     }
     if (lane == 0 && report) {
-        p.host_status[2] = dir;
-        __hip_atomic_store((unsigned long long *)p.host_status, (unsigned long long)k | ((unsigned long long)f << 32),
-                           __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        // one word and relaxed: a release at system scope writes the L2 back first
+        __hip_atomic_store((unsigned long long *)p.host_status,
+                           (unsigned long long)k | ((unsigned long long)(f | (dir << 31)) << 32), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
