@@ -177,9 +177,12 @@ typedef struct bfs_run_options {
  *   BFS_PUSH_AUTO    from the out-degrees (after duplicates and self-loops are
  *                    removed): claim-word, with the host loop, when every
  *                    out-degree is at most 8 (grids, road-like graphs);
- *                    sliced when it applies, n >= 2^17 and the largest
- *                    out-degree is at least 16 times the average (hubs); the
- *                    list form otherwise.
+ *                    sliced when it applies and either the largest
+ *                    out-degree is at least 16 times the average (hubs; from
+ *                    3 x 2^14 vertices, or 2^17 with several roots or
+ *                    count_atomics) or single searches fan out over at least
+ *                    12 entries a vertex (2^18 vertices; 7 entries from
+ *                    7 x 2^18), not counted; the list form otherwise.
  */
 enum {
     BFS_PUSH_AUTO = 0,

@@ -84,6 +84,7 @@ struct bfs_graph {
     // a list's end, for the claim-word push's deep form
     int32_t *thin_rows = nullptr;
     uint32_t thin_width = 0;
+    bool fan_out = false;             // even degrees, wide levels early (sliced_applies)
     bool slow_growth = false;         // a thin graph whose searches look deep (grows_slowly)
     std::mutex mu;
     GraphExecCache gcache;
@@ -338,6 +339,40 @@ bool grows_slowly(int32_t n, const std::vector<int32_t> &ptr, const std::vector<
         }
     }
     return true;
+}
+
+// Whether searches on a graph fan out: from two of four of its vertices a level
+// through the fourth holds 1,000 vertices (a random graph of degree 8 holds some
+// 4,000 there, a mesh of 26 neighbours in three dimensions 386).  Collects at
+// most 8,192 entries per level.
+bool fans_out(int32_t n, const std::vector<int32_t> &ptr, const std::vector<int32_t> &idx) {
+    std::vector<int32_t> front, next, seen, both;
+    int wide = 0;
+    for (int32_t t = 0; t < 4; ++t) {
+        front.assign(1, (int32_t)((int64_t)n * t / 4));
+        seen = front;
+        for (uint32_t k = 1; k <= 4 && !front.empty(); ++k) {
+            next.clear();
+            for (int32_t u : front) {
+                const int64_t room = 8192 - (int64_t)next.size(), deg = ptr[(size_t)u + 1] - ptr[(size_t)u];
+                const auto b = idx.begin() + ptr[(size_t)u];
+                next.insert(next.end(), b, b + std::min(room, deg));
+                if (deg >= room) break;
+            }
+            std::sort(next.begin(), next.end());
+            next.erase(std::unique(next.begin(), next.end()), next.end());
+            front.clear();
+            std::set_difference(next.begin(), next.end(), seen.begin(), seen.end(), std::back_inserter(front));
+            if (front.size() >= 1000) {
+                ++wide;
+                break;
+            }
+            both.clear();
+            std::merge(seen.begin(), seen.end(), front.begin(), front.end(), std::back_inserter(both));
+            seen.swap(both);
+        }
+    }
+    return wide >= 2;
 }
 
 // The sliced push's graph data: S slices of sw words (sw a multiple of 4, at
@@ -1149,11 +1184,18 @@ uint32_t sl_grid(const bfs_graph *g) {
 //     road-like graphs, thousands of thin levels): the claim-word form (grid
 //     2048^2: 25.9 ms, list 57.4, sliced 122.9);
 //   - skewed degrees (the largest out-degree at least kSlSkew x the average:
-//     hubs) on 2^17 <= n <= 2^22: the sliced form (R-MAT s20: 0.42 ms, list
-//     0.72);
-//   - otherwise the list form (ER 2^18 x 16: 0.29 ms, sliced 0.57; the ER
-//     pack: 1.00 ms, sliced 2.74).
-constexpr int32_t kSlMinAuto = 1 << 17;
+//     hubs) on 3 x 2^14 <= n <= 2^22: the sliced form (R-MAT 60,001 vertices,
+//     directed: 141 us, list 176; 120,001: 152, list 245; 1,000,003: 301, list
+//     720; but 33,693 directed: 144, list 137);
+//   - even degrees that fan out (fans_out), 12 entries a vertex from 2^18
+//     vertices or 7 from 7 x 2^18: the sliced form (random graphs of 262,144
+//     vertices and degree 16: 177 us, list 206; 2,000,003 and 16: 417, list 608;
+//     2,000,003 and 8: 462, list 499; but 1,048,576 and 8: 340, list 335, and
+//     2,000,003 and 4: 579, list 488);
+//   - otherwise the list form (random 16,384 x 16: 95 us, sliced 129; the pack
+//     of 64: 1.06 ms, sliced 2.74).
+constexpr int32_t kSlMinAuto = 3 << 14;
+constexpr int32_t kSlMinOther = 1 << 17;           // counted searches, several roots (a pack's)
 constexpr uint64_t kSlSkew = 16;
 
 // Thin: every out-degree at most kClaimMaxDeg.
@@ -1163,11 +1205,22 @@ bool skewed_graph(const bfs_graph *g) {
     return (uint64_t)g->max_deg * (uint64_t)g->n >= kSlSkew * (uint64_t)g->nnz;
 }
 
-bool sliced_applies(const bfs_graph *g, const RunCfg &c, const bfs_run_options *opt) {
+// Where even degrees may take the sliced form, if searches fan out.
+bool even_sliced_size(const bfs_graph *g) {
+    return g->sl_S != 0 && ((g->n >= (1 << 18) && (uint64_t)g->nnz >= 12 * (uint64_t)g->n) ||
+                            (g->n >= (7 << 18) && (uint64_t)g->nnz >= 7 * (uint64_t)g->n));
+}
+
+bool sliced_applies(const bfs_graph *g, const RunCfg &c, const bfs_run_options *opt, int32_t nroots = 1) {
     const uint32_t impl = opt ? opt->push_impl : BFS_PUSH_AUTO;
     if (c.policy != kPush || g->sl_S == 0 || c.loop == BFS_LOOP_PERSISTENT) return false;
-    return impl == BFS_PUSH_SLICED ||
-           (impl == BFS_PUSH_AUTO && g->n >= kSlMinAuto && skewed_graph(g) && !thin_graph(g));
+    if (impl != BFS_PUSH_AUTO) return impl == BFS_PUSH_SLICED;
+    if (thin_graph(g)) return false;
+    // counted searches are the list form's (refused where the sliced form is the
+    // choice for them all the same), and the roots of a block-diagonal pack see
+    // its small graphs, not the whole
+    const bool other = (opt && opt->count_atomics) || nroots > 1;
+    return skewed_graph(g) ? g->n >= (other ? kSlMinOther : kSlMinAuto) : g->fan_out && !other;
 }
 
 bool claim_applies(const bfs_graph *g, const RunCfg &c, const bfs_run_options *opt) {
@@ -1374,6 +1427,12 @@ SlParams make_sl_params(bfs_graph *g, int32_t *level, int32_t *parent, void *ws,
     P.sw = g->sl_sw;
     P.words = g->sl_S * g->sl_sw;
     P.streams = sl_grid(g) / g->sl_S;
+    // half a wave's share of the bitmap, but no less than 8 words of it (two
+    // batches of vertices): R-MAT 2,000,003 vertices, a share of 32 words: by 32
+    // 439 us, 16 412, 8 455; 1,000,003, a share of 8: by 8 302, 4 329.  An even
+    // number (a level is written for pairs of words), one per lane at most
+    const uint32_t share = P.words / (P.streams * (uint32_t)bfsi::kSlWaves);
+    P.seg_words = std::min(64u, std::max(2u, std::max(std::min(share, 8u), share / 2u) & ~1u));
     P.near_deg = g->near_deg;
     P.seg = g->sl_seg;
     P.occ = g->sl_occ;
@@ -1540,6 +1599,7 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
         if (st == BFS_OK) st = build_long(n, ptr, &g->lo, &g->lomap, g->nlo, g->nlo_chunks, g->bytes);
         if (st == BFS_OK) st = build_slices(g, ptr, idx);
         if (st == BFS_OK && g->thin_rows) g->slow_growth = grows_slowly(n, ptr, idx);
+        if (st == BFS_OK && even_sliced_size(g) && !skewed_graph(g)) g->fan_out = fans_out(n, ptr, idx);
         if (st == BFS_OK && directed) {
             st = build_long(n, iptr, &g->li, &g->limap, g->nli, g->nli_chunks, g->bytes);
         } else if (st == BFS_OK) {
@@ -1685,7 +1745,7 @@ extern "C" bfs_status bfs_run_roots(bfs_graph *g, int32_t nroots, const int32_t 
     hipStream_t s = (hipStream_t)hip_stream;
     int32_t *roots_dev = (int32_t *)((char *)workspace + base);
     HIP_TRY(hipMemcpyAsync(roots_dev, roots_host, (size_t)nroots * 4, hipMemcpyHostToDevice, s));
-    const bool sliced = sliced_applies(g, c, opt);
+    const bool sliced = sliced_applies(g, c, opt, nroots);
     if (opt) opt->push_used = sliced ? BFS_PUSH_SLICED : BFS_PUSH_LIST;
     if (sliced)
         return run_sliced(g, -1, nroots, roots_dev, level, parent, c, workspace, s, opt);

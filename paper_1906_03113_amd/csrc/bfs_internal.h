@@ -158,6 +158,7 @@ struct SlParams {
     uint32_t sw;                     // 32-bit words per slice (a multiple of 4)
     uint32_t words;                  // S * sw: words of every bitmap (padded)
     uint32_t streams;                // workgroups per slice
+    uint32_t seg_words;              // bitmap words a wave takes at a time (even, at most 64)
     uint32_t near_deg;               // mean out-degree of a list entry (of a neighbour)
     const int4 *seg;                 // [n + 1]: {out_ptr[v], start of slices 1, 2, 3 in v's out-list}
     const uint32_t *occ;             // [S][words]: bit v of slice s = v's part in slice s is short and

@@ -695,8 +695,11 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
 
     // every frontier vertex: settle it (if this slice owns it and level k - 1
     // left it unsettled) and expand its short part in slice s.  The stream's
-    // words are cut into 64-word segments (2048 vertices) dealt to the waves; a
-    // batch takes the segment's next 64 kCols frontier vertices, kCols per lane.
+    // words are cut into segments of seg_words dealt to the waves; a batch takes
+    // the segment's next 64 kCols frontier vertices, kCols per lane.  Segments
+    // are as long as the waves' shares, 64 words (2048 vertices) at most: by 64
+    // words throughout a graph of 188,191 vertices had work for 92 of the 4,096
+    // waves.
     {
         // bits j of a word whose vertex 32 w + j this workgroup owns (owner
         // depends on v mod 4 only, and 32 w is a multiple of 4)
@@ -704,19 +707,22 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j)
             if (owner((int32_t)j, S) == s) own_bits |= 0x11111111u << j;
-        const uint32_t wps = (((P.words + P.streams - 1u) / P.streams) + 63u) & ~63u;
+        const uint32_t sgw = P.seg_words;
+        const uint32_t wps = (P.words + P.streams * sgw - 1u) / (P.streams * sgw) * sgw;
         const uint32_t ws0 = q * wps;
         const uint32_t ws1 = (ws0 + wps < P.words) ? ws0 + wps : P.words;
-        for (uint32_t sw0 = ws0 + wave * 64u; sw0 < ws1; sw0 += kSlWaves * 64u) {
+        uint32_t seg = wave;                                    // the segment's number in the stream
+        for (uint32_t sw0 = ws0 + wave * sgw; sw0 < ws1; sw0 += kSlWaves * sgw, seg += kSlWaves) {
             const uint32_t wi = sw0 + lane;
-            uint32_t fw = (wi < ws1) ? cur[wi] : 0u;
+            const bool mine = lane < sgw && wi < ws1;
+            uint32_t fw = mine ? cur[wi] : 0u;
             // level k for every vertex of the segment in C_k, by one of the
             // stream's S workgroups: for each pair of words 2j, 2j + 1 with a
             // bit, lane t writes vertex t of the pair, so each store covers
             // 64 consecutive vertices (two lines) instead of one line per
             // vertex
             const unsigned long long nzw = __ballot(fw != 0u);
-            if ((sw0 >> 6) % S == s) {
+            if (seg % S == s) {
                 unsigned long long pairs = (nzw | (nzw >> 1)) & 0x5555555555555555ull;
                 while (pairs) {                                      // uniform
                     const uint32_t j2 = (uint32_t)__ffsll((long long)pairs) - 1u;
@@ -728,7 +734,7 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
             // this workgroup's vertices of the segment: those whose part in
             // slice s is short and not empty (P.occ), and the ones it settles
             // and counts (owner s) whatever their part
-            const uint32_t fo = fw & (((wi < ws1) ? P.occ[s * P.words + wi] : 0u) | own_bits);
+            const uint32_t fo = fw & ((mine ? P.occ[s * P.words + wi] : 0u) | own_bits);
             const uint32_t cnt = (uint32_t)__popc(fo);
             const uint32_t incl = wave_incl_scan(cnt);
             const uint32_t total = (uint32_t)__shfl((int)incl, 63, 64);
