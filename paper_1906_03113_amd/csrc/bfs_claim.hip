@@ -898,41 +898,127 @@ hipError_t launch_cw_narrow(const CwParams &p, uint32_t k, uint32_t max_levels, 
     return hipGetLastError();
 }
 
+// The pack and its way back are streams: bound by HBM when every workgroup has
+// the same share.  A block row of the grid per query, as many blocks as the
+// largest one needed, left most of 65,536 workgroups empty and the largest
+// query's with 32 rounds of one 4-byte load each (64 random graphs, 44.8 M
+// entries: 138 us packed, 20 us unpacked).  So a workgroup takes a tile of the
+// packed entries (or vertices), whichever queries lie in it.
+constexpr uint32_t kPackEntries = 2048, kPackVerts = 1024, kPackBlocks = 2048;
+
+// A 16-byte load from an address aligned to 4 bytes only (a tile starts anywhere
+// in its query's list).
+typedef int Int4Any __attribute__((ext_vector_type(4), aligned(4)));
+
+__device__ __forceinline__ uint32_t pack_first(const PackQuery &Q, bool entries) { return entries ? Q.ebase : Q.base; }
+
+// The query that holds packed entry (vertex) x: the last of [q, nq) that starts
+// at or before it; q starts there too.  x is mostly q's or the next one's.
+__device__ __forceinline__ uint32_t pack_query(const PackParams &P, uint32_t q, uint32_t x, bool entries) {
+    for (uint32_t t = 0; t < 2; ++t) {
+        if (q + 1 >= P.nq || x < pack_first(P.q[q + 1], entries)) return q;
+        ++q;
+    }
+    uint32_t lo = q, hi = P.nq;                            // the answer is in [lo, hi)
+    while (hi - lo > 1) {
+        const uint32_t m = lo + (hi - lo) / 2;
+        if (pack_first(P.q[m], entries) <= x) lo = m;
+        else hi = m;
+    }
+    return lo;
+}
+
 // The queries' out-lists into one block-diagonal CSR: row base_q + v holds
-// query q's row v with every entry offset by base_q (a block row of the grid
-// per query; the packed offsets of a query's last row and the next query's
-// first are the same number, written by both).
-__global__ __launch_bounds__(kCwBlock) void k_pack(PackParams P) {
-    const PackQuery &Q = P.q[blockIdx.y];
-    const uint32_t t0 = blockIdx.x * kCwBlock + threadIdx.x, ts = gridDim.x * kCwBlock;
-    for (uint32_t v = t0; v <= Q.n; v += ts) P.ptr[Q.base + v] = Q.ptr[v] + (int32_t)Q.ebase;
-    for (uint32_t e = t0; e < Q.nnz; e += ts) P.idx[Q.ebase + e] = Q.idx[e] + (int32_t)Q.base;
-    if (blockIdx.y == 0)
-        for (uint32_t e = P.E + t0; e < P.pad_end; e += ts) P.idx[e] = 0;
+// query q's row v with every entry offset by base_q; and the packed sources.
+// Workgroups below `entry_blocks` copy entries, consecutive tiles each (finding a
+// tile's query by itself is a chain of reads as long as the copy: 116 us with a
+// workgroup per tile), the others row offsets.
+__global__ __launch_bounds__(kCwBlock) void k_pack(PackParams P, uint32_t entry_blocks) {
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x < entry_blocks) {
+        const uint64_t tiles = ((uint64_t)P.pad_end + kPackEntries - 1) / kPackEntries;
+        const uint64_t t0 = tiles * blockIdx.x / entry_blocks, t1 = tiles * (blockIdx.x + 1) / entry_blocks;
+        uint32_t q = 0;
+        for (uint64_t t = t0; t < t1; ++t) {
+            const uint64_t e0 = t * kPackEntries;
+            if (e0 < P.E) q = pack_query(P, q, (uint32_t)e0, true);
+            const uint32_t end = q + 1 < P.nq ? P.q[q + 1].ebase : P.E;
+            if (e0 + kPackEntries <= end) {                // one query's
+                constexpr uint32_t quads = kPackEntries / (4 * kCwBlock);
+                const int32_t *src = P.q[q].idx + (e0 - P.q[q].ebase);
+                int32_t *dst = P.idx + e0;
+                const int32_t add = (int32_t)P.q[q].base;
+                Int4Any x[quads];
+#pragma unroll
+                for (uint32_t i = 0; i < quads; ++i) x[i] = *(const Int4Any *)(src + 4 * (i * kCwBlock + tid));
+#pragma unroll
+                for (uint32_t i = 0; i < quads; ++i)
+                    *(int4 *)(dst + 4 * (i * kCwBlock + tid)) =
+                        make_int4(x[i].x + add, x[i].y + add, x[i].z + add, x[i].w + add);
+                continue;
+            }
+            uint32_t at = q;
+            for (uint32_t i = tid; i < kPackEntries; i += kCwBlock) {
+                const uint64_t e = e0 + i;
+                if (e < P.E) {
+                    at = pack_query(P, at, (uint32_t)e, true);
+                    P.idx[e] = P.q[at].idx[e - P.q[at].ebase] + (int32_t)P.q[at].base;
+                } else if (e < P.pad_end) {
+                    P.idx[e] = 0;
+                }
+            }
+        }
+        return;
+    }
+    const uint64_t v0 = (uint64_t)(blockIdx.x - entry_blocks) * kPackVerts;
+    uint32_t q = v0 < P.V ? pack_query(P, 0, (uint32_t)v0, false) : 0;
+    for (uint32_t i = tid; i < kPackVerts; i += kCwBlock) {
+        const uint64_t v = v0 + i;
+        if (v < P.V) {
+            q = pack_query(P, q, (uint32_t)v, false);
+            const uint32_t at = (uint32_t)v - P.q[q].base;
+            P.ptr[v] = P.q[q].ptr[at] + (int32_t)P.q[q].ebase;
+            if (at == 0) P.roots[q] = (int32_t)P.q[q].base + P.q[q].source;
+        } else if (v == P.V) {
+            P.ptr[v] = (int32_t)P.E;
+        }
+    }
 }
 
 // The packed results into the callers' arrays (parents back to the query's ids).
 __global__ __launch_bounds__(kCwBlock) void k_unpack(PackParams P) {
-    const PackQuery &Q = P.q[blockIdx.y];
-    for (uint32_t v = blockIdx.x * kCwBlock + threadIdx.x; v < Q.n; v += gridDim.x * kCwBlock) {
-        const int32_t l = P.level[Q.base + v], p = P.parent[Q.base + v];
-        Q.level[v] = l;
-        Q.parent[v] = p >= 0 ? p - (int32_t)Q.base : -1;
+    const uint64_t v0 = (uint64_t)blockIdx.x * kPackVerts;
+    uint32_t q = pack_query(P, 0, (uint32_t)v0, false);    // v0 < V
+    constexpr uint32_t per = kPackVerts / kCwBlock;
+    int32_t l[per], p[per];
+#pragma unroll
+    for (uint32_t i = 0; i < per; ++i) {
+        const uint64_t v = v0 + i * kCwBlock + threadIdx.x;
+        l[i] = v < P.V ? P.level[v] : 0;
+        p[i] = v < P.V ? P.parent[v] : 0;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < per; ++i) {
+        const uint64_t v = v0 + i * kCwBlock + threadIdx.x;
+        if (v >= P.V) break;
+        q = pack_query(P, q, (uint32_t)v, false);
+        const uint32_t base = P.q[q].base, at = (uint32_t)v - base;
+        P.q[q].level[at] = l[i];
+        P.q[q].parent[at] = p[i] >= 0 ? p[i] - (int32_t)base : -1;
     }
 }
 
 hipError_t launch_pack(const PackParams &p, hipStream_t s) {
-    const uint32_t work = p.max_nnz > p.max_n + 1u ? p.max_nnz : p.max_n + 1u;
-    uint32_t gx = (work + kCwBlock - 1) / kCwBlock;
-    gx = gx < 1024u ? (gx ? gx : 1u) : 1024u;
-    hipLaunchKernelGGL(k_pack, dim3(gx, p.nq), dim3(kCwBlock), 0, s, p);
+    uint32_t et = (uint32_t)(((uint64_t)p.pad_end + kPackEntries - 1) / kPackEntries);
+    et = et < kPackBlocks ? et : kPackBlocks;
+    const uint32_t vt = (uint32_t)(((uint64_t)p.V + 1 + kPackVerts - 1) / kPackVerts);
+    hipLaunchKernelGGL(k_pack, dim3(et + vt), dim3(kCwBlock), 0, s, p, et);
     return hipGetLastError();
 }
 
 hipError_t launch_unpack(const PackParams &p, hipStream_t s) {
-    uint32_t gx = (p.max_n + kCwBlock - 1) / kCwBlock;
-    gx = gx < 1024u ? (gx ? gx : 1u) : 1024u;
-    hipLaunchKernelGGL(k_unpack, dim3(gx, p.nq), dim3(kCwBlock), 0, s, p);
+    const uint32_t vt = (uint32_t)(((uint64_t)p.V + kPackVerts - 1) / kPackVerts);
+    hipLaunchKernelGGL(k_unpack, dim3(vt), dim3(kCwBlock), 0, s, p);
     return hipGetLastError();
 }
 

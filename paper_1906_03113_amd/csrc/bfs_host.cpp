@@ -1351,33 +1351,27 @@ bfs_status run_packed_list(const ClaimQuery *qs, int32_t nq, void *workspace, si
     if (ws_bytes < L.total) return fail(BFS_EINVAL, "workspace has %zu bytes, needs %zu", ws_bytes, L.total);
     char *b = (char *)workspace;
     std::vector<PackQuery> hq((size_t)nq);
-    std::vector<int32_t> roots((size_t)nq);
-    uint32_t base = 0, ebase = 0, max_n = 0, max_nnz = 0, max_deg = 0;
+    uint32_t base = 0, ebase = 0, max_deg = 0;
     for (int32_t q = 0; q < nq; ++q) {
         const bfs_graph *g = qs[q].g;
         hq[(size_t)q] = PackQuery{g->out_ptr, g->out_idx, qs[q].level, qs[q].parent, base, (uint32_t)g->n, ebase,
-                                  g->nnz};
-        roots[(size_t)q] = (int32_t)base + qs[q].source;
+                                  qs[q].source};
         base += (uint32_t)g->n;
         ebase += g->nnz;
-        max_n = std::max(max_n, (uint32_t)g->n);
-        max_nnz = std::max(max_nnz, g->nnz);
         max_deg = std::max(max_deg, g->max_deg);
     }
     PackParams PP{};
     PP.q = (const PackQuery *)(b + L.q);
     PP.nq = (uint32_t)nq;
-    PP.max_n = max_n;
-    PP.max_nnz = max_nnz;
+    PP.V = (uint32_t)L.V;
     PP.E = (uint32_t)L.E;
     PP.pad_end = (uint32_t)L.pad_end;
     PP.ptr = (int32_t *)(b + L.ptr);
     PP.idx = (int32_t *)(b + L.idx);
     PP.level = (const int32_t *)(b + L.level);
     PP.parent = (const int32_t *)(b + L.parent);
-    int32_t *roots_dev = (int32_t *)(b + L.roots);
+    PP.roots = (int32_t *)(b + L.roots);
     HIP_TRY(hipMemcpyAsync(b + L.q, hq.data(), hq.size() * sizeof(PackQuery), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(roots_dev, roots.data(), roots.size() * 4, hipMemcpyHostToDevice, s));
     HIP_TRY(launch_pack(PP, s));
     // the packed graph for the list form's kernels (push only: no CSC)
     bfs_graph T;
@@ -1394,7 +1388,7 @@ bfs_status run_packed_list(const ClaimQuery *qs, int32_t nq, void *workspace, si
     LevelParams P;
     uint32_t levels = 0;
     if (st == BFS_OK) st = make_params(&T, (int32_t *)PP.level, (int32_t *)PP.parent, c, b + L.ws, false, P);
-    if (st == BFS_OK && launch_init(P, nq, roots_dev, -1, s) != hipSuccess) st = fail(BFS_EHIP, "init launch failed");
+    if (st == BFS_OK && launch_init(P, nq, PP.roots, -1, s) != hipSuccess) st = fail(BFS_EHIP, "init launch failed");
     if (st == BFS_OK) st = run_levels(&T, P, c, s, levels, opt);
     if (st == BFS_OK && launch_unpack(PP, s) != hipSuccess) st = fail(BFS_EHIP, "unpack launch failed");
     for (hipEvent_t e : T.events) (void)hipEventDestroy(e);   // per-launch timing, if it ran

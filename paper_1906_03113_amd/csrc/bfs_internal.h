@@ -400,14 +400,16 @@ struct PackQuery {
     const int32_t *ptr, *idx;                 // the query's graph (out-lists)
     int32_t *level, *parent;                  // the caller's outputs
     uint32_t base, n;                         // first packed vertex, vertices
-    uint32_t ebase, nnz;                      // first packed entry, entries
+    uint32_t ebase;                           // first packed entry (its last: before the next query's)
+    int32_t source;
 };
 struct PackParams {
     const PackQuery *q;                       // device, nq
     uint32_t nq;
-    uint32_t max_n, max_nnz;
+    uint32_t V;                               // packed vertices
     uint32_t E, pad_end;                      // packed entries; idx is zero-filled in [E, pad_end)
-    int32_t *ptr, *idx;                       // packed CSR: V + 1 offsets, pad_end entries
+    int32_t *ptr, *idx;                       // packed CSR: V + 1 offsets, pad_end entries (idx 16-byte aligned)
+    int32_t *roots;                           // the packed sources [nq]
     const int32_t *level, *parent;            // packed results [V]
 };
 hipError_t launch_pack(const PackParams &p, hipStream_t s);
