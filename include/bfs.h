@@ -282,9 +282,9 @@ bfs_status bfs_run(bfs_graph *g, int32_t source,
  * the frontier masks along out-edges; PULL lets every unsettled vertex gather
  * its in-neighbours' masks in ascending order; HEURISTIC pushes while the
  * union frontier holds at most n >> ms_pull_shift vertices and pulls after;
- * LEARNED asks the selector network (opt->selector) before every level (a
- * one-wave launch over the level's multi-source features, see
- * bfs_ms_profile_levels) and runs the argmin of its push and pull outputs,
+ * LEARNED asks the selector network (opt->selector) before every level (the
+ * last workgroup of the level before, over the level's multi-source features,
+ * see bfs_ms_profile_levels) and runs the argmin of its push and pull outputs,
  * push when an output is not finite and on every level when opt->selector is
  * NULL; from level 16 on, a push decision covers the next 8 levels.  With
  * opt->trace set, record k holds level k's direction (variant 0 push, 1 pull)

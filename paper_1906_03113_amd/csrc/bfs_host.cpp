@@ -2003,7 +2003,7 @@ static bfs_status run_multi_source(bfs_graph *g, int32_t nq, const int32_t *sour
     // direction per level: HEURISTIC pushes while the union frontier is
     // small and pulls (no atomics) once it holds more than n >> pull_shift
     // vertices; LEARNED takes the network's argmin over push and pull, which
-    // a one-wave launch after each level's list leaves in the progress slot
+    // the last workgroup of a level's closing launch leaves in the progress slot
     // (push on every level without a network); PUSH / PULL as forced
     const uint32_t pol = opt ? opt->variant : kPush;
     const bool learned = pol == kLearned && opt->selector != nullptr;

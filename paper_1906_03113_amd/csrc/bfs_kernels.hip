@@ -22,8 +22,8 @@
 // B_{k-1} on entry and receives F_k and F_{k+1}.  So the test is stable and
 // the result does not depend on scheduling.
 //
-// Level k's counters live in ring slot k & 3; its kernels read k from the
-// device state, so the same launches can be issued from a host loop, replayed
+// Level k's counters live in ring slot k & 3 (launch j's in slot j & 3 for the
+// step launches); its kernels read k from the device state, so the same launches can be issued from a host loop, replayed
 // from a captured graph, or run inside one persistent kernel.
 #include <hip/hip_runtime.h>
 #include <hip/hip_cooperative_groups.h>

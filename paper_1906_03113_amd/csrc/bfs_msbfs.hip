@@ -715,7 +715,7 @@ __device__ __forceinline__ unsigned long long scan_wave4(const MsLevel &p, const
 // with new bits are listed (one atomicAdd per block chunk).  The graph's long
 // rows (kMsLong entries or more) are scanned in chunks by waves across the
 // grid: each chunk gives its first hits (atomicMin on the staged parent) and
-// ORs its bits into the next mask; k_ms_fixup then folds those into vis and
+// ORs its bits into the next mask; k_ms_pull_close then folds those into vis and
 // lists the rows.  Also clears F_{k-1}'s masks.
 // Chunk j (kMsChunk entries) of long row v, scanned by one wave in ascending
 // order until every unsettled source is found: first hits go to the staged
@@ -961,7 +961,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_wide(MsLevel p, uint32_t k) 
 // each looks only for the sources the row's first chunk left unsettled (vis
 // holds those found there), gives its first hits to the staged parents by
 // atomicMin (the smallest over the chunks) and ORs its bits into the next
-// mask; k_ms_fixup then folds those into vis and lists the rows.  The chunks
+// mask; k_ms_pull_close then folds those into vis and lists the rows.  The chunks
 // are taken every row's second chunk first, then the third, ..., so that
 // most chunks find their row's earlier chunks done and skip the sources
 // those settled.
