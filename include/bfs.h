@@ -99,7 +99,7 @@ typedef struct bfs_run_options {
     uint32_t levels_per_sync;  /* host loop / graph loop: levels launched between two reads of
                                   the frontier size (0 = 4); the list form's host loop, not
                                   traced or counted: launches kept ahead of the last one seen
-                                  to start (0 = 1)                                             */
+                                  to start (0 = 1, at most 2)                                  */
     uint32_t grid_blocks;      /* workgroups per level launch (0 = 8 per compute unit)          */
     uint32_t heavy_degree;     /* out-degree from which a column is split into chunks (0 = 512) */
     uint32_t chunk_edges;      /* entries per chunk of a split column (0 = 1024)                */

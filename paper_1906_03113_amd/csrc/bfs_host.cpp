@@ -818,16 +818,17 @@ bfs_status read_trace(const DevLevelRec *dtrace, uint32_t levels, const std::vec
 
 // The host loop and the graph loop of the step launches (k_step), whose
 // progress arrives when a launch starts: (launches started, frontier size).  The
-// host loop issues a launch when the one before it is seen to start
-// (levels_per_sync: when the one that many before it is), and never waits for
+// host loop issues a launch when the one before it is seen to start (when the
+// one before that is, with levels_per_sync of 2 or more), and never waits for
 // the stream before the end.  A launch of 6 us or more hides the next one's way
 // to the device; a second launch in the stream hides it always, but leaves two
 // launches of about 5 us to run past the search's end (an 11-level search of a
-// 16,384-vertex random graph 109 us against 91).  What is past the end finds it
-// ended, and the stream is waited for once, so that nothing of it is left when
-// the call returns.  A replay of the captured group ends with k_step_fold, a
-// launch without a level.
-constexpr uint32_t kStepsAhead = 1;
+// 16,384-vertex random graph 109 us against 91); a third hides nothing more and
+// is one more to run past the end, so levels_per_sync asks for no more than
+// that.  What is past the end finds it ended, and the stream is waited for once,
+// so that nothing of it is left when the call returns.  A replay of the
+// captured group ends with k_step_fold, a launch without a level.
+constexpr uint32_t kStepsAhead = 1, kStepsAheadMost = 2;
 
 bfs_status step_loop(bfs_graph *g, const LoopKey &key, const LevelParams &P, const RunCfg &c, hipStream_t s,
                      HostSlot *hs, uint32_t &level, bfs_run_options *opt) {
@@ -854,7 +855,7 @@ bfs_status step_loop(bfs_graph *g, const LoopKey &key, const LevelParams &P, con
         level = hs->h[2];
         return BFS_OK;
     }
-    const uint32_t ahead = opt && opt->levels_per_sync ? opt->levels_per_sync : kStepsAhead;
+    const uint32_t ahead = std::min(opt && opt->levels_per_sync ? opt->levels_per_sync : kStepsAhead, kStepsAheadMost);
     const bool tk = opt && opt->time_kernels;
     std::unique_lock<std::mutex> lock(g->mu, std::defer_lock);
     if (tk) lock.lock();                  // the event pool is per bfs_graph

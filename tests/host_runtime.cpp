@@ -1,0 +1,154 @@
+// The host runtime (bfs_host.cpp) against a HIP runtime and kernels of its own
+// that only keep count: level loops, group sizes and refusals without a GPU.
+// Usage: host_runtime CASE; prints what differs from what is wanted.
+#include "../paper_1906_03113_amd/csrc/bfs_host.cpp"
+
+#include <cstdlib>
+
+static struct {
+    uint32_t levels = 1;                    // levels the search has
+    uint32_t steps = 0, past = 0;           // step launches; those after the first that reported the end
+    uint32_t deep_wanted = 1;               // deep launches until the list is empty
+    uint32_t deep = 0, deep_past = 0, wide = 0, narrow = 0, cw_inits = 0, ms = 0;
+    uint64_t most_vertices = 0;
+} fake;
+
+static uint32_t *slot;                      // the progress slot
+
+// ---- the HIP runtime ------------------------------------------------------------------------
+extern "C" {
+hipError_t hipMalloc(void **p, size_t b) { *p = malloc(b); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t b, unsigned) { slot = (uint32_t *)(*p = calloc(1, b)); return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void **d, void *p, unsigned) { *d = p; return hipSuccess; }
+hipError_t hipMemset(void *p, int v, size_t b) { memset(p, v, b); return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t b, hipMemcpyKind) { memcpy(d, s, b); return hipSuccess; }
+// workspaces are addresses nobody looks at; what comes back is a claim-word state
+hipError_t hipMemcpyAsync(void *d, const void *, size_t b, hipMemcpyKind kind, hipStream_t) {
+    if (kind != hipMemcpyDeviceToHost) return hipSuccess;
+    memset(d, 0, b);
+    if (b == sizeof(CwState))
+        for (auto &c : ((CwState *)d)->cnt) c[0] = fake.deep < fake.deep_wanted ? 1u : 0u;
+    return hipSuccess;
+}
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 0.f; return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = nullptr; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorNotSupported; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t *) { return hipErrorNotSupported; }
+hipError_t hipGraphInstantiate(hipGraphExec_t *, hipGraph_t, hipGraphNode_t *, char *, size_t) { return hipErrorNotSupported; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "refused"; }
+hipError_t hipGetLastError() { return hipSuccess; }
+}
+
+// ---- the kernels ----------------------------------------------------------------------------
+namespace bfsi {
+hipError_t launch_init(const LevelParams &, int32_t, const int32_t *, int32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_level(const LevelParams &, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_step(const LevelParams &p, uint32_t, uint32_t, hipStream_t) {
+    const uint32_t j = fake.steps++;
+    if (j > fake.levels) {
+        ++fake.past;
+        return hipSuccess;
+    }
+    p.host_status[0] = j + 1;
+    p.host_status[1] = j < fake.levels ? 1u : 0u;
+    p.host_status[2] = j;
+    return hipSuccess;
+}
+hipError_t launch_step_fold(const LevelParams &, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_parents(const LevelParams &, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_persistent(const LevelParams &, uint32_t, hipStream_t) { return hipErrorNotSupported; }
+uint32_t persistent_max_grid(int) { return 0; }
+hipError_t launch_sl_init(const SlParams &, int32_t, const int32_t *, int32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_sl_level(const SlParams &, uint32_t, hipStream_t) { return hipSuccess; }
+SlLayout sl_layout(uint32_t) { return SlLayout{}; }
+hipError_t static_scratch(void **) { return hipErrorNotSupported; }
+hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t, hipStream_t) {
+    ++fake.ms;
+    if (phase == kMsSettle || phase == kMsClose || phase == kMsRoots) {
+        const uint32_t at = phase == kMsRoots ? 0u : k + 1;
+        if (at <= fake.levels) {
+            p.host_status[0] = at;
+            p.host_status[1] = at < fake.levels ? 1u : 0u;
+        }
+    }
+    return hipSuccess;
+}
+hipError_t launch_ms_zero(unsigned long long *, size_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_ms_levels(const MsLevel &, uint32_t, unsigned long long *, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_ms_out(const MsLevel &, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_ms_rpull(const MsLevel &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_cw_init(const CwParams &p, hipStream_t) {
+    ++fake.cw_inits;
+    fake.deep = 0;
+    fake.most_vertices = std::max<uint64_t>(fake.most_vertices, p.V);
+    return hipSuccess;
+}
+hipError_t launch_cw_wide(const CwParams &, uint32_t, uint32_t, hipStream_t) { ++fake.wide; ++fake.deep; return hipSuccess; }
+hipError_t launch_cw_narrow(const CwParams &, uint32_t, uint32_t, uint32_t, uint32_t, hipStream_t) { ++fake.narrow; ++fake.deep; return hipSuccess; }
+hipError_t launch_cw_rows(const int32_t *, const int32_t *, int32_t, int32_t, int32_t *, hipStream_t) { return hipSuccess; }
+hipError_t launch_cw_deep(const CwParams &, uint32_t, uint32_t, uint32_t, bool, hipStream_t) {
+    if (fake.deep >= fake.deep_wanted) ++fake.deep_past;
+    ++fake.deep;
+    return hipSuccess;
+}
+hipError_t launch_cw_out(const CwParams &, bool, hipStream_t) { return hipSuccess; }
+hipError_t launch_pack(const PackParams &, hipStream_t) { return hipSuccess; }
+hipError_t launch_unpack(const PackParams &, hipStream_t) { return hipSuccess; }
+CmpLayout cmp_layout(int32_t) { return CmpLayout{}; }
+SpLayout sp_layout(int32_t, int32_t) { return SpLayout{}; }
+hipError_t launch_spmspv(const SpParams &, uint32_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_cmp_init(const CmpParams &, int32_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_cmp_step(const CmpParams &, uint32_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_mlp_forward(const float *, const float *, float *, int32_t, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_mlp_grad(const float *, const float *, const float *, const float *, int32_t, float, float *, float *,
+                           hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_mlp_adam(float *, float *, float *, float *, int32_t, float, hipStream_t) { return hipErrorNotSupported; }
+}  // namespace bfsi
+
+// ---- the cases ------------------------------------------------------------------------------
+static int bad = 0;
+#define WANT(cond, ...) do { if (!(cond)) { ++bad; printf("%s: ", #cond); printf(__VA_ARGS__); printf("\n"); } } while (0)
+
+static void *address(size_t i = 1) { return (void *)(i << 40); }      // of device memory: aligned, never read
+
+// The step launches' host loop ends whatever levels_per_sync is, and issues no
+// more than two launches past the one that finds the end.
+static void steps() {
+    for (uint32_t levels : {1u, 2u, 5u, 17u, 200u})
+        for (int32_t n : {(int32_t)levels, 300})
+            for (uint32_t per : {0u, 1u, 2u, 8u, 64u, 4096u}) {
+                if (n < (int32_t)levels) continue;
+                bfs_graph g;
+                g.n = n;
+                g.max_deg = 20;                 // not a thin graph
+                fake.levels = levels;
+                fake.steps = fake.past = 0;
+                bfs_run_options opt{};
+                opt.levels_per_sync = per;
+                const bfs_status st = bfs_run(&g, 0, (int32_t *)address(2), (int32_t *)address(3), &opt, address(), size_t(1) << 40, nullptr);
+                WANT(st == BFS_OK, "n %d, %u levels, levels_per_sync %u: %s", n, levels, per, bfs_last_error_detail());
+                WANT(opt.levels == levels, "n %d, levels_per_sync %u: %u levels, not %u", n, per, opt.levels, levels);
+                WANT(fake.past <= 2, "n %d, levels_per_sync %u: %u launches past the end", n, per, fake.past);
+            }
+}
+
+int main(int argc, char **argv) {
+    const std::string which = argc > 1 ? argv[1] : "";
+    if (which == "steps") steps();
+    else return 2;
+    printf("%d wrong\n", bad);
+    return bad != 0;
+}

@@ -1,0 +1,31 @@
+"""The host runtime's loops, group sizes and refusals, without a GPU: bfs_host.cpp
+compiled by g++ against a HIP runtime and kernels that only keep count
+(tests/host_runtime.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.isdir(f"{ROCM}/include/hip"),
+                                reason="needs g++ and the HIP headers")
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("host") / "host_runtime")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", "-w",
+                    "-o", exe, os.path.join(HERE, "host_runtime.cpp")], check=True)
+    return exe
+
+
+def run(exe, case):
+    r = subprocess.run([exe, case], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+def test_step_loop_ends_for_any_levels_per_sync(runtime):
+    run(runtime, "steps")
