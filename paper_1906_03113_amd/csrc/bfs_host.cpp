@@ -965,6 +965,10 @@ constexpr uint32_t kCwWideMinGrid = 64;          // workgroups of a wide launch 
 constexpr uint32_t kDeepGrid = 4096;
 constexpr uint32_t kDeepIters = 128;
 constexpr uint32_t kDeepPerSync = 8;
+// Vertices of the deep form's searches together, at most: a list may hold two
+// entries a vertex, and the waves' 32-bit positions in it go one step of the
+// grid past its end.
+constexpr uint64_t kDeepMost = (1ull << 31) - (uint64_t)kDeepGrid * 64u;
 
 struct ClaimQuery {
     const bfs_graph *g;
@@ -1035,15 +1039,15 @@ bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t w
                          (uint32_t *)(b + L.c1)};
     P.spill = (uint32_t *)(b + L.spill);
     P.st = (CwState *)(b + L.st);
-    // every graph thin: the deep form, its stamps in the narrow form's spill
-    // array (its lists may hold 2 V entries, counted in 32 bits)
-    bool thin = V < (1ull << 31), same = true;
+    // every graph thin: the deep form, its stamps in the narrow form's spill array
+    bool thin = V <= kDeepMost, same = true;
     uint32_t width = 4;
     for (int32_t q = 0; q < nq; ++q) {
         thin = thin && qs[q].g->thin_rows != nullptr;
         same = same && qs[q].g == qs[0].g;
         width = std::max(width, qs[q].g->thin_width);
     }
+    if (compact && !thin) return fail(BFS_EINVAL, "%llu vertices in one group of deep searches", (unsigned long long)V);
     P.stamp = thin ? P.spill : nullptr;
     P.same_n = same ? (uint32_t)qs[0].g->n : 0u;
     HIP_TRY(hipMemcpyAsync(b + L.q, hq.data(), hq.size() * sizeof(CwQuery), hipMemcpyHostToDevice, s));
@@ -1263,8 +1267,13 @@ size_t deep_workspace(const bfs_graph *g, int32_t m) {
     return cw_layout((uint64_t)g->n * (uint64_t)m, 0, (uint32_t)m, true).total;
 }
 
+// Sources side by side at most (0: the graph alone holds too many vertices).
+int32_t deep_group(const bfs_graph *g, int32_t nq) {
+    return (int32_t)std::min<uint64_t>((uint64_t)std::min(nq, kDeepGroup), kDeepMost / (uint64_t)g->n);
+}
+
 bool deep_batch_applies(const bfs_graph *g, const bfs_run_options *opt) {
-    if (!g->slow_growth) return false;
+    if (!g->slow_growth || deep_group(g, 1) == 0) return false;
     if (!opt) return true;
     return opt->push_impl == BFS_PUSH_AUTO && opt->loop_mode == BFS_LOOP_HOST && !opt->trace &&
            opt->ms_ranges <= 1 && (opt->variant == kPush || opt->variant == kHeuristic || opt->variant == kLearned);
@@ -1273,7 +1282,7 @@ bool deep_batch_applies(const bfs_graph *g, const bfs_run_options *opt) {
 bfs_status run_deep_batch(bfs_graph *g, int32_t nq, const int32_t *sources, int32_t *const *level,
                           int32_t *const *parent, bfs_run_options *opt, void *workspace, size_t ws_bytes,
                           hipStream_t s) {
-    int32_t most = std::min(nq, kDeepGroup);
+    int32_t most = deep_group(g, nq);
     while (most > 1 && deep_workspace(g, most) > ws_bytes) --most;   // one search fits what bfs_run asks for
     const int32_t groups = (nq + most - 1) / most, per = (nq + groups - 1) / groups;
     std::vector<ClaimQuery> qs;
@@ -1645,9 +1654,8 @@ size_t bfs_workspace_size(const bfs_graph *g, int32_t num_queries, uint32_t run_
     const size_t single = ws_single(g);
     if (num_queries == 1) return single;
     size_t need = std::max(single, ms_layout(g->n, num_queries).total);
-    // room for kDeepGroup claim-word searches side by side (fewer run in turn)
-    if (g->slow_growth)
-        need = std::max(need, deep_workspace(g, std::min(num_queries, kDeepGroup)));
+    // room for a group of claim-word searches side by side (fewer run in turn)
+    if (g->slow_growth) need = std::max(need, deep_workspace(g, deep_group(g, num_queries)));
     // thin graphs (or when asked): room for the claim-word batch too (see
     // claim_batch_applies)
     if ((thin_graph(g) && g->sl_S == 0) || (run_flags & BFS_WS_CLAIM))

@@ -145,9 +145,47 @@ static void steps() {
             }
 }
 
+static void thin(bfs_graph &g, int32_t n, uint32_t depth) {            // a road-like graph of n vertices
+    g.n = n;
+    g.nnz = 3u * (uint32_t)std::min(n, 1 << 29);
+    g.max_deg = 4;
+    g.thin_rows = (int32_t *)address(9);
+    g.thin_width = 4;
+    g.slow_growth = depth > 0;
+}
+
+// A batch on a slowly growing graph runs claim-word searches side by side, as
+// many as their 32-bit counts and the workspace allow, never refused for their
+// number and never by the forms that launch a level at a time.
+static void deep_groups() {
+    for (int32_t n : {1000, 4000000, 33000000, 33554432, 40000000, 67108863, 67200000, 1 << 30, 2147480000, 2147483647})
+        for (int32_t nq : {2, 64, 65, 200}) {
+            bfs_graph g;
+            thin(g, n, 5000);
+            std::vector<bfs_graph *> gs((size_t)nq, &g);
+            std::vector<int32_t> src((size_t)nq, 0);
+            std::vector<int32_t *> out((size_t)nq, (int32_t *)address(5));
+            for (size_t bytes : {bfs_workspace_size(&g, nq, 0), size_t(1) << 50}) {
+                for (uint32_t variant : {kHeuristic, kLearned}) {
+                    fake.levels = fake.deep_wanted = 3;
+                    fake.cw_inits = fake.wide = fake.narrow = 0;
+                    fake.most_vertices = 0;
+                    bfs_run_options opt{};
+                    opt.variant = variant;
+                    const bfs_status st = bfs_run_batch(nq, gs.data(), src.data(), out.data(), out.data(), &opt, address(), bytes, nullptr);
+                    WANT(st == BFS_OK, "n %d, %d sources, %zu bytes: %s", n, nq, bytes, bfs_last_error_detail());
+                    WANT(fake.wide + fake.narrow == 0, "n %d, %d sources: %u wide and %u narrow launches", n, nq, fake.wide, fake.narrow);
+                    WANT(2 * fake.most_vertices + 4096 * 64 < 1ull << 32, "n %d, %d sources: %llu vertices side by side", n, nq,
+                         (unsigned long long)fake.most_vertices);
+                }
+            }
+        }
+}
+
 int main(int argc, char **argv) {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "steps") steps();
+    else if (which == "deep_groups") deep_groups();
     else return 2;
     printf("%d wrong\n", bad);
     return bad != 0;

@@ -29,3 +29,7 @@ def run(exe, case):
 
 def test_step_loop_ends_for_any_levels_per_sync(runtime):
     run(runtime, "steps")
+
+
+def test_deep_batches_of_any_size(runtime):
+    run(runtime, "deep_groups")
