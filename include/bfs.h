@@ -97,7 +97,9 @@ typedef struct bfs_run_options {
     uint32_t variant;          /* BFS_VARIANT_*                                  (default PUSH)  */
     uint32_t loop_mode;        /* BFS_LOOP_*                                     (default HOST)  */
     uint32_t levels_per_sync;  /* host loop / graph loop: levels launched between two reads of
-                                  the frontier size (0 = 4); the list form's host loop, not
+                                  the frontier size (0 = 4); claim-word searches of thin
+                                  graphs: launches between two reads, at most (up to 8 as the
+                                  search goes on; 0 = 8); the list form's host loop, not
                                   traced or counted: launches kept ahead of the last one seen
                                   to start (0 = 1, at most 2)                                  */
     uint32_t grid_blocks;      /* workgroups per level launch (0 = 8 per compute unit)          */

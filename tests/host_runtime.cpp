@@ -100,7 +100,7 @@ hipError_t launch_cw_wide(const CwParams &, uint32_t, uint32_t, hipStream_t) { +
 hipError_t launch_cw_narrow(const CwParams &, uint32_t, uint32_t, uint32_t, uint32_t, hipStream_t) { ++fake.narrow; ++fake.deep; return hipSuccess; }
 hipError_t launch_cw_rows(const int32_t *, const int32_t *, int32_t, int32_t, int32_t *, hipStream_t) { return hipSuccess; }
 hipError_t launch_cw_deep(const CwParams &, uint32_t, uint32_t, uint32_t, bool, hipStream_t) {
-    if (fake.deep >= fake.deep_wanted) ++fake.deep_past;
+    if (fake.deep >= fake.deep_wanted && ++fake.deep_past > 1u << 20) return hipErrorUnknown;   // (ends a runaway loop)
     ++fake.deep;
     return hipSuccess;
 }
@@ -182,10 +182,36 @@ static void deep_groups() {
         }
 }
 
+// The deep form's launches past the end of a search: no more than the eight
+// between two reads of the count, whatever levels_per_sync is, and no more than
+// by default where it asks for fewer.
+static void deep_syncs() {
+    for (uint32_t launches : {1u, 2u, 3u, 7u, 40u})
+        for (uint32_t per : {0u, 1u, 2u, 8u, 64u, 4096u, 0xFFFFFFFFu})
+            for (int32_t nq : {1, 3}) {
+                if (nq == 1 && per > 4096) continue;           // refused
+                bfs_graph g;
+                thin(g, 1000, 500);
+                std::vector<bfs_graph *> gs((size_t)nq, &g);
+                std::vector<int32_t> src((size_t)nq, 0);
+                std::vector<int32_t *> out((size_t)nq, (int32_t *)address(5));
+                fake.deep_wanted = launches;
+                fake.deep_past = 0;
+                bfs_run_options opt{};
+                opt.levels_per_sync = per;
+                const bfs_status st = bfs_run_batch(nq, gs.data(), src.data(), out.data(), out.data(), &opt, address(), size_t(1) << 40, nullptr);
+                const uint32_t most = launches <= 2 ? 1u : (launches <= 6 ? 3u : 7u);
+                WANT(st == BFS_OK, "%u launches, levels_per_sync %u, %d sources: %s", launches, per, nq, bfs_last_error_detail());
+                WANT(fake.deep_past <= most && (per != 1 || fake.deep_past == 0), "%u launches, levels_per_sync %u, %d sources: %u past the end", launches, per, nq,
+                     fake.deep_past);
+            }
+}
+
 int main(int argc, char **argv) {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "steps") steps();
     else if (which == "deep_groups") deep_groups();
+    else if (which == "deep_syncs") deep_syncs();
     else return 2;
     printf("%d wrong\n", bad);
     return bad != 0;

@@ -33,3 +33,7 @@ def test_step_loop_ends_for_any_levels_per_sync(runtime):
 
 def test_deep_batches_of_any_size(runtime):
     run(runtime, "deep_groups")
+
+
+def test_deep_launches_past_the_end(runtime):
+    run(runtime, "deep_syncs")
