@@ -242,8 +242,9 @@ enum {
  * masks and, on a graph where bfs_run_batch picks the claim-word form by
  * itself (see bfs_run_batch) or with run_flags BFS_WS_CLAIM, the claim-word
  * batch (about 36 bytes per vertex per query; 28, and at most 64 queries side
- * by side, on the slowly growing graphs of at most 2^22 vertices, where a
- * workspace of the multi-source masks alone is enough too).  0 on a bad argument (unknown
+ * by side, so up to 1,792 bytes a vertex, on graphs of at most 2^22 vertices
+ * with many thin levels, where a workspace of the multi-source masks alone, 600
+ * bytes a vertex for up to 64 queries, is enough too).  0 on a bad argument (unknown
  * run_flags bits included).
  */
 size_t bfs_workspace_size(const bfs_graph *g, int32_t num_queries, uint32_t run_flags);
@@ -280,9 +281,10 @@ bfs_status bfs_run(bfs_graph *g, int32_t source,
  * it) - except with opt->push_impl BFS_PUSH_CLAIM, or with the automatic
  * choice for variant PUSH (host loop) on a graph beyond 2^22 vertices whose
  * out-degrees are all at most 8, or for PUSH, HEURISTIC or LEARNED (host loop,
- * no trace) on one whose out-degrees are all at most 8 and whose searches grow
- * slowly (grids, road-like graphs: looked at when the graph is created), where
- * they run as claim-word searches (below).  opt->variant picks the direction per level: PUSH (default) scatters
+ * no trace) on one whose out-degrees are all at most 8 and whose searches have
+ * many thin levels for its vertices and the number of sources (grids, road-like
+ * graphs: looked at when the graph is created), where they run as claim-word
+ * searches (below).  opt->variant picks the direction per level: PUSH (default) scatters
  * the frontier masks along out-edges; PULL lets every unsettled vertex gather
  * its in-neighbours' masks in ascending order; HEURISTIC pushes while the
  * union frontier holds at most n >> ms_pull_shift vertices and pulls after;

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -85,7 +86,7 @@ struct bfs_graph {
     int32_t *thin_rows = nullptr;
     uint32_t thin_width = 0;
     bool fan_out = false;             // even degrees, wide levels early (sliced_applies)
-    bool slow_growth = false;         // a thin graph whose searches look deep (grows_slowly)
+    uint32_t deep_levels = 0;         // a thin graph's searches' levels where they grow slowly (thin_levels)
     std::mutex mu;
     GraphExecCache gcache;
     std::vector<hipEvent_t> events;   // pool for per-launch timing
@@ -310,35 +311,61 @@ bfs_status upload_lists(bfs_graph *g, const std::vector<int32_t> &idx) {
     return BFS_OK;
 }
 
-// Whether searches on a thin graph look deep: from four of its vertices, level k
-// of the first kGrowthLevels holds at most 5 k^2 + 8 vertices (planar graphs hold
-// about 4 k to 8 k, three-dimensional grids 4 k^2; a random graph of degree 3
-// holds 3 x 2^(k-1) and is through in 25 levels).  Visits a few thousand
-// vertices at most.
+// How many levels searches on a thin graph look to have; 0 where they grow fast:
+// from one of four of its vertices a level k of the first kGrowthLevels holds more
+// than 5 k^2 + 8 vertices (planar graphs hold about 4 k to 8 k, three-dimensional
+// grids 4 k^2; a random graph of degree 3 holds 3 x 2^(k-1) and is through in 25
+// levels).  The levels are judged from the search's first kDepthProbe vertices, V
+// of them in k levels, V' in k / 2: it goes on as the power d = log(V / V') / log 2
+// of the level, so the n vertices take k (n / V)^(1 / d).  That is 1 / 1.5 of the
+// levels measured, from d = 2 (grids) to 6 (random graphs, growing by 1.4 a level).
+// The median of the first three vertices of eight whose search is that large;
+// where there is none, the deepest search seen.  Visits some 15,000 vertices at
+// most.
 constexpr uint32_t kGrowthLevels = 12;
+constexpr size_t kDepthProbe = 4096;
 
-bool grows_slowly(int32_t n, const std::vector<int32_t> &ptr, const std::vector<int32_t> &idx) {
-    std::vector<int32_t> front, next, seen;
-    for (int32_t t = 0; t < 4; ++t) {
-        int64_t s = (int64_t)n * t / 4;
+uint32_t thin_levels(int32_t n, const std::vector<int32_t> &ptr, const std::vector<int32_t> &idx) {
+    std::vector<bool> seen((size_t)n, false);
+    std::vector<int32_t> order;                                // the vertices in the order of the search
+    std::vector<size_t> ends;                                  // ... through each level
+    std::vector<double> levels;
+    uint32_t deepest = 0;
+    for (int32_t t = 0; t < 8; ++t) {
+        const bool grows = t % 2 == 0, depth = levels.size() < 3;
+        int64_t s = (int64_t)n * t / 8;
         while (s < n && ptr[(size_t)s + 1] == ptr[(size_t)s]) ++s;
-        if (s == n) continue;
-        front.assign(1, (int32_t)s);
-        seen = front;
-        for (uint32_t k = 1; k <= kGrowthLevels && !front.empty(); ++k) {
-            next.clear();
-            for (int32_t u : front) next.insert(next.end(), idx.begin() + ptr[(size_t)u], idx.begin() + ptr[(size_t)u + 1]);
-            std::sort(next.begin(), next.end());
-            next.erase(std::unique(next.begin(), next.end()), next.end());
-            front.clear();
-            std::set_difference(next.begin(), next.end(), seen.begin(), seen.end(), std::back_inserter(front));
-            if (front.size() > 5u * k * k + 8u) return false;
-            const size_t mid = seen.size();
-            seen.insert(seen.end(), front.begin(), front.end());
-            std::inplace_merge(seen.begin(), seen.begin() + (std::ptrdiff_t)mid, seen.end());
+        if (s == n || (!grows && !depth)) continue;
+        for (int32_t v : order) seen[(size_t)v] = false;
+        order.assign(1, (int32_t)s);
+        seen[(size_t)s] = true;
+        ends.assign(1, 1);
+        bool over = false;
+        for (uint32_t k = 1; !over && ((grows && k <= kGrowthLevels) || (depth && order.size() < kDepthProbe)); ++k) {
+            const size_t e0 = k > 1 ? ends[k - 2] : 0, e1 = ends[k - 1];
+            for (size_t i = e0; i < e1; ++i)
+                for (int32_t e = ptr[(size_t)order[i]]; e < ptr[(size_t)order[i] + 1]; ++e) {
+                    const int32_t v = idx[(size_t)e];
+                    if (seen[(size_t)v]) continue;
+                    seen[(size_t)v] = true;
+                    order.push_back(v);
+                }
+            const size_t got = order.size() - e1;
+            if (grows && k <= kGrowthLevels && got > 5u * k * k + 8u) return 0;
+            over = got == 0;
+            if (!over) ends.push_back(order.size());
         }
+        const size_t k = ends.size() - 1;                      // the last level with a vertex
+        if (over || !depth || k < 2) {
+            if (over) deepest = std::max(deepest, (uint32_t)k);
+            continue;
+        }
+        const double V = (double)ends[k], d = std::log(V / (double)ends[k / 2]) / std::log((double)k / (double)(k / 2));
+        levels.push_back(1.5 * (double)k * std::pow(std::max(1.0, (double)n / V), 1.0 / std::max(1.0, d)));
     }
-    return true;
+    if (levels.empty()) return deepest;
+    std::sort(levels.begin(), levels.end());
+    return (uint32_t)std::min(levels[(levels.size() - 1) / 2], (double)n);
 }
 
 // Whether searches on a graph fan out: from two of four of its vertices a level
@@ -1253,19 +1280,27 @@ bool claim_batch_applies(const bfs_graph *g, const bfs_run_options *opt) {
     return impl == BFS_PUSH_AUTO && pol == kPush && loop == BFS_LOOP_HOST && thin_graph(g) && g->sl_S == 0;
 }
 
-// Many sources on one thin graph whose searches look deep (slow_growth), under
+// Many sources on one thin graph whose searches look deep (deep_levels), under
 // the direction policies that leave the form open: claim-word searches in
 // lockstep, as many at a time as the workspace holds (28 bytes per vertex and
 // source; bfs_workspace_size asks for room for kDeepGroup, the multi-source
-// workspace alone holds about 20 per mask word).  The multi-source
-// kernels pay two grid-wide launches and a host round trip for each of the
-// hundreds of thin levels.  Measured with 2 / 16 / 64 sources (all at once),
-// multi-source learned against claim-word: 512^2 grid 17.3 / 20.6 / 25.1 against
-// 1.10 / 1.58 / 2.42 ms, 128^2 grid 3.56 / 5.92 / 5.91 against 0.30 / 0.36 /
-// 0.55 ms, 32^2 grid 1.26 / 1.83 / 1.97 against 0.15 / 0.15 / 0.20 ms; on graphs
-// that grow fast many sources share the multi-source levels' reads (a random
-// graph of degree 8 and 200,000 vertices, 64 sources: 0.74 against 2.89 ms), so
-// those stay.  A call that asks for the levels' directions (trace) gets them.
+// workspace alone holds about 20 per mask word).  The multi-source kernels pay two
+// grid-wide launches and a host round trip for each of the hundreds of thin
+// levels, but their sources share the levels and a row's reads, where a
+// claim-word search offers every entry for every source.  Fitted to 268
+// measurements (grids of two and three dimensions, random graphs that grow by 1.1
+// to 1.4 a level, small worlds; 2,000 to 1,000,000 vertices, 2 to 1,024 sources),
+// in us: a multi-source batch takes 20 a level, 4 more per mask word, and 0.06 ns
+// a vertex and source held (0.10 where a mask word of every vertex is more than
+// the 4 MB of an L2); claim-word searches 90 a group, 1.2 a level, and 0.17 ns a
+// vertex and source (0.12 on those larger graphs, whose levels are wider).  The
+// form it picks is at most 1.5 times slower than the other and on average 1%.
+// Multi-source learned against claim-word: 447^2 grid
+// (841 levels), 64 / 256 sources 23.0 / 34.5 against 2.0 / 7.8 ms; 58^3 grid (167),
+// 64 / 256 sources 6.0 / 9.9 against 5.0 / 19.9 ms; three matchings of 200,000
+// vertices, each edge kept with 0.7 (62), 16 / 64 / 256 sources 1.85 / 2.25 / 4.2
+// against 1.0 / 2.15 / 8.5 ms.  A call that asks for the levels' directions
+// (trace) gets them.
 constexpr int32_t kDeepGroup = 64;
 
 size_t deep_workspace(const bfs_graph *g, int32_t m) {
@@ -1277,18 +1312,31 @@ int32_t deep_group(const bfs_graph *g, int32_t nq) {
     return (int32_t)std::min<uint64_t>((uint64_t)std::min(nq, kDeepGroup), kDeepMost / (uint64_t)g->n);
 }
 
-bool deep_batch_applies(const bfs_graph *g, const bfs_run_options *opt) {
-    if (!g->slow_growth || deep_group(g, 1) == 0) return false;
-    if (!opt) return true;
-    return opt->push_impl == BFS_PUSH_AUTO && opt->loop_mode == BFS_LOOP_HOST && !opt->trace &&
-           opt->ms_ranges <= 1 && (opt->variant == kPush || opt->variant == kHeuristic || opt->variant == kLearned);
+// Whether nq claim-word searches, `most` at a time, look faster than one
+// multi-source search of them.
+bool deep_pays(const bfs_graph *g, int32_t nq, int32_t most) {
+    if (g->deep_levels == 0 || most <= 0) return false;
+    const double n = (double)g->n, L = (double)g->deep_levels, words = (double)((nq + 63) / 64);
+    const double groups = (double)((nq + most - 1) / most);
+    const bool large = g->n > (1 << 19);
+    const double claim = groups * (90.0 + 1.2 * L) + (large ? 0.12e-3 : 0.17e-3) * n * (double)nq;
+    return claim < L * (20.0 + 4.0 * words) + (large ? 0.10e-3 : 0.06e-3) * n * 64.0 * words;
 }
 
-bfs_status run_deep_batch(bfs_graph *g, int32_t nq, const int32_t *sources, int32_t *const *level,
-                          int32_t *const *parent, bfs_run_options *opt, void *workspace, size_t ws_bytes,
-                          hipStream_t s) {
+// Sources of a batch to run side by side as claim-word searches; 0: none, the
+// multi-source kernels run it.
+int32_t deep_batch(const bfs_graph *g, int32_t nq, const bfs_run_options *opt, size_t ws_bytes) {
+    if (opt && !(opt->push_impl == BFS_PUSH_AUTO && opt->loop_mode == BFS_LOOP_HOST && !opt->trace && opt->ms_ranges <= 1 &&
+                 (opt->variant == kPush || opt->variant == kHeuristic || opt->variant == kLearned)))
+        return 0;
     int32_t most = deep_group(g, nq);
     while (most > 1 && deep_workspace(g, most) > ws_bytes) --most;   // one search fits what bfs_run asks for
+    return deep_pays(g, nq, most) ? most : 0;
+}
+
+bfs_status run_deep_batch(bfs_graph *g, int32_t nq, int32_t most, const int32_t *sources, int32_t *const *level,
+                          int32_t *const *parent, bfs_run_options *opt, void *workspace, size_t ws_bytes,
+                          hipStream_t s) {
     const int32_t groups = (nq + most - 1) / most, per = (nq + groups - 1) / groups;
     std::vector<ClaimQuery> qs;
     uint32_t levels = 0, launches = 0;
@@ -1607,7 +1655,7 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
     try {
         if (st == BFS_OK) st = build_long(n, ptr, &g->lo, &g->lomap, g->nlo, g->nlo_chunks, g->bytes);
         if (st == BFS_OK) st = build_slices(g, ptr, idx);
-        if (st == BFS_OK && g->thin_rows) g->slow_growth = grows_slowly(n, ptr, idx);
+        if (st == BFS_OK && g->thin_rows) g->deep_levels = thin_levels(n, ptr, idx);
         if (st == BFS_OK && even_sliced_size(g) && !skewed_graph(g)) g->fan_out = fans_out(n, ptr, idx);
         if (st == BFS_OK && directed) {
             st = build_long(n, iptr, &g->li, &g->limap, g->nli, g->nli_chunks, g->bytes);
@@ -1660,7 +1708,8 @@ size_t bfs_workspace_size(const bfs_graph *g, int32_t num_queries, uint32_t run_
     if (num_queries == 1) return single;
     size_t need = std::max(single, ms_layout(g->n, num_queries).total);
     // room for a group of claim-word searches side by side (fewer run in turn)
-    if (g->slow_growth) need = std::max(need, deep_workspace(g, deep_group(g, num_queries)));
+    const int32_t most = deep_group(g, num_queries);
+    if (deep_pays(g, num_queries, most)) need = std::max(need, deep_workspace(g, most));
     // thin graphs (or when asked): room for the claim-word batch too (see
     // claim_batch_applies)
     if ((thin_graph(g) && g->sl_S == 0) || (run_flags & BFS_WS_CLAIM))
@@ -2089,8 +2138,8 @@ extern "C" bfs_status bfs_run_batch(int32_t num_queries, bfs_graph *const *graph
         if (ws_bytes < need) return fail(BFS_EINVAL, "workspace has %zu bytes, needs %zu", ws_bytes, need);
         bfs_status st = check_multi_source(graphs[0], opt);
         if (st != BFS_OK) return st;
-        if (deep_batch_applies(graphs[0], opt))
-            return run_deep_batch(graphs[0], num_queries, sources, level, parent, opt, workspace, ws_bytes,
+        if (const int32_t most = deep_batch(graphs[0], num_queries, opt, ws_bytes))
+            return run_deep_batch(graphs[0], num_queries, most, sources, level, parent, opt, workspace, ws_bytes,
                                   (hipStream_t)hip_stream);
         return run_multi_source(graphs[0], num_queries, sources, level, parent, opt, workspace,
                                 (hipStream_t)hip_stream);

@@ -4,6 +4,7 @@
 #include "../paper_1906_03113_amd/csrc/bfs_host.cpp"
 
 #include <cstdlib>
+#include <random>
 
 static struct {
     uint32_t levels = 1;                    // levels the search has
@@ -151,7 +152,7 @@ static void thin(bfs_graph &g, int32_t n, uint32_t depth) {            // a road
     g.max_deg = 4;
     g.thin_rows = (int32_t *)address(9);
     g.thin_width = 4;
-    g.slow_growth = depth > 0;
+    g.deep_levels = depth;
 }
 
 // A batch on a slowly growing graph runs claim-word searches side by side, as
@@ -161,7 +162,7 @@ static void deep_groups() {
     for (int32_t n : {1000, 4000000, 33000000, 33554432, 40000000, 67108863, 67200000, 1 << 30, 2147480000, 2147483647})
         for (int32_t nq : {2, 64, 65, 200}) {
             bfs_graph g;
-            thin(g, n, 5000);
+            thin(g, n, 1u << 30);
             std::vector<bfs_graph *> gs((size_t)nq, &g);
             std::vector<int32_t> src((size_t)nq, 0);
             std::vector<int32_t *> out((size_t)nq, (int32_t *)address(5));
@@ -207,11 +208,99 @@ static void deep_syncs() {
             }
 }
 
+// ---- graphs for the choice of a batch's form ----
+typedef std::vector<std::pair<int32_t, int32_t>> Edges;
+
+static bfs_graph *undirected(int32_t n, const Edges &edges) {
+    std::vector<int32_t> ptr((size_t)n + 1, 0), idx(2 * edges.size() + 1);
+    for (auto &e : edges) ++ptr[(size_t)e.first + 1], ++ptr[(size_t)e.second + 1];
+    for (int32_t v = 0; v < n; ++v) ptr[(size_t)v + 1] += ptr[(size_t)v];
+    std::vector<int32_t> at(ptr.begin(), ptr.end() - 1);
+    for (auto &e : edges) {
+        idx[(size_t)at[(size_t)e.first]++] = e.second;
+        idx[(size_t)at[(size_t)e.second]++] = e.first;
+    }
+    bfs_graph *g = nullptr;
+    const bfs_status st = bfs_graph_create(n, ptr.data(), idx.data(), nullptr, nullptr, 0, nullptr, &g);
+    WANT(st == BFS_OK, "create: %s", bfs_last_error_detail());
+    return g;
+}
+
+// k random perfect matchings, each edge kept with probability p, none at the
+// vertices n t / 4 when `apart`.
+static bfs_graph *matchings(int32_t n, int k, double p, bool apart = false) {
+    std::mt19937 r(5);
+    std::uniform_real_distribution<double> u(0, 1);
+    std::vector<int32_t> perm((size_t)n);
+    Edges e;
+    const auto alone = [&](int32_t v) { return apart && v % (n / 4) == 0; };
+    for (int m = 0; m < k; ++m) {
+        for (int32_t v = 0; v < n; ++v) perm[(size_t)v] = v;
+        std::shuffle(perm.begin(), perm.end(), r);
+        for (int32_t v = 0; v + 1 < n; v += 2)
+            if (u(r) < p && !alone(perm[(size_t)v]) && !alone(perm[(size_t)v + 1])) e.push_back({perm[(size_t)v], perm[(size_t)v + 1]});
+    }
+    return undirected(n, e);
+}
+
+static bfs_graph *grid(int32_t a, int32_t b, int32_t c) {                // a x b x c, each vertex with its neighbours
+    Edges e;
+    for (int32_t x = 0; x < a; ++x)
+        for (int32_t y = 0; y < b; ++y)
+            for (int32_t z = 0; z < c; ++z) {
+                const int32_t v = (x * b + y) * c + z;
+                if (x + 1 < a) e.push_back({v, v + b * c});
+                if (y + 1 < b) e.push_back({v, v + c});
+                if (z + 1 < c) e.push_back({v, v + 1});
+            }
+    return undirected(a * b * c, e);
+}
+
+// A learned batch takes the claim-word searches where its levels are many and
+// thin for its vertices and sources, and the multi-source levels elsewhere.
+static void deep_choice() {
+    struct Case {
+        const char *name;
+        bfs_graph *g;
+        std::vector<int32_t> deep, shared;          // numbers of sources for either form
+    };
+    Case cases[] = {
+        {"grid 400 x 400", grid(400, 400, 1), {2, 16, 64, 256}, {}},
+        {"grid 45 x 44", grid(45, 44, 1), {2, 64, 256, 1024}, {}},
+        {"path of 3,000", grid(3000, 1, 1), {2, 64, 256}, {}},
+        {"grid 58^3", grid(58, 58, 58), {2, 16, 64}, {256, 1024}},
+        {"3 matchings, 0.6", matchings(200000, 3, 0.6), {2, 16}, {256, 1024}},
+        {"3 matchings, 0.7", matchings(200000, 3, 0.7), {2, 16}, {128, 256, 1024}},
+        {"8 matchings, the probed vertices apart", matchings(200000, 8, 1.0, true), {}, {2, 16, 64, 256}},
+        {"one vertex", grid(1, 1, 1), {}, {2, 64, 130}},
+        {"path of 5", grid(5, 1, 1), {}, {70, 130}},
+    };
+    for (const Case &c : cases)
+        for (int kind = 0; kind < 2; ++kind)
+            for (int32_t nq : kind ? c.shared : c.deep)
+                for (uint32_t variant : {kPush, kHeuristic, kLearned}) {
+                    std::vector<bfs_graph *> gs((size_t)nq, c.g);
+                    std::vector<int32_t> src((size_t)nq, 0);
+                    std::vector<int32_t *> out((size_t)nq, (int32_t *)address(5));
+                    fake.levels = fake.deep_wanted = 3;
+                    fake.cw_inits = fake.ms = 0;
+                    bfs_run_options opt{};
+                    opt.variant = variant;
+                    const bfs_status st = bfs_run_batch(nq, gs.data(), src.data(), out.data(), out.data(), &opt, address(),
+                                                        bfs_workspace_size(c.g, nq, 0), nullptr);
+                    WANT(st == BFS_OK, "%s, %d sources: %s", c.name, nq, bfs_last_error_detail());
+                    WANT((kind == 0) == (fake.cw_inits > 0) && (kind == 1) == (fake.ms > 0), "%s, %d sources, variant %u: %s", c.name, nq, variant,
+                         fake.cw_inits ? "claim-word" : "multi-source");
+                }
+    for (Case &c : cases) bfs_graph_destroy(c.g);
+}
+
 int main(int argc, char **argv) {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "steps") steps();
     else if (which == "deep_groups") deep_groups();
     else if (which == "deep_syncs") deep_syncs();
+    else if (which == "deep_choice") deep_choice();
     else return 2;
     printf("%d wrong\n", bad);
     return bad != 0;

@@ -37,3 +37,7 @@ def test_deep_batches_of_any_size(runtime):
 
 def test_deep_launches_past_the_end(runtime):
     run(runtime, "deep_syncs")
+
+
+def test_form_of_a_batch_on_thin_graphs(runtime):
+    run(runtime, "deep_choice")
