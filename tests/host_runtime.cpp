@@ -10,7 +10,7 @@ static struct {
     uint32_t levels = 1;                    // levels the search has
     uint32_t steps = 0, past = 0;           // step launches; those after the first that reported the end
     uint32_t deep_wanted = 1;               // deep launches until the list is empty
-    uint32_t deep = 0, deep_past = 0, wide = 0, narrow = 0, cw_inits = 0, ms = 0;
+    uint32_t deep = 0, deep_past = 0, wide = 0, narrow = 0, cw_inits = 0, ms = 0, decided = 0;
     uint64_t most_vertices = 0;
 } fake;
 
@@ -80,6 +80,7 @@ hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t, hipS
     ++fake.ms;
     if (phase == kMsSettle || phase == kMsClose || phase == kMsRoots) {
         const uint32_t at = phase == kMsRoots ? 0u : k + 1;
+        if (p.mlp != nullptr) ++fake.decided;
         if (at <= fake.levels) {
             p.host_status[0] = at;
             p.host_status[1] = at < fake.levels ? 1u : 0u;
@@ -208,6 +209,30 @@ static void deep_syncs() {
             }
 }
 
+// The network is asked for the levels that the host decides on alone: from level
+// 16 on a push decision covers eight levels, whose first seven closing launches
+// leave no direction behind.
+static void ms_decisions() {
+    for (uint32_t levels : {1u, 3u, 16u, 17u, 24u, 100u}) {
+        bfs_graph g;
+        g.n = 5000;
+        g.nnz = 100000;
+        g.max_deg = 20;                         // not a thin graph
+        std::vector<bfs_graph *> gs(3, &g);
+        std::vector<int32_t> src(3, 0);
+        std::vector<int32_t *> out(3, (int32_t *)address(5));
+        fake.levels = levels;
+        fake.ms = fake.decided = 0;
+        bfs_run_options opt{};
+        opt.variant = kLearned;
+        opt.selector = (const float *)address(7);
+        const bfs_status st = bfs_run_batch(3, gs.data(), src.data(), out.data(), out.data(), &opt, address(), size_t(1) << 40, nullptr);
+        WANT(st == BFS_OK && opt.levels == levels, "%u levels: %u, %s", levels, opt.levels, bfs_last_error_detail());
+        const uint32_t alone = std::min(levels, 16u), groups = (levels - alone + 7) / 8;
+        WANT(fake.decided == 1 + alone + groups, "%u levels: the network asked %u times, not %u", levels, fake.decided, 1 + alone + groups);
+    }
+}
+
 // ---- graphs for the choice of a batch's form ----
 typedef std::vector<std::pair<int32_t, int32_t>> Edges;
 
@@ -301,6 +326,7 @@ int main(int argc, char **argv) {
     else if (which == "deep_groups") deep_groups();
     else if (which == "deep_syncs") deep_syncs();
     else if (which == "deep_choice") deep_choice();
+    else if (which == "ms_decisions") ms_decisions();
     else return 2;
     printf("%d wrong\n", bad);
     return bad != 0;

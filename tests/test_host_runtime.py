@@ -41,3 +41,7 @@ def test_deep_launches_past_the_end(runtime):
 
 def test_form_of_a_batch_on_thin_graphs(runtime):
     run(runtime, "deep_choice")
+
+
+def test_network_asked_once_a_decision(runtime):
+    run(runtime, "ms_decisions")
