@@ -171,10 +171,11 @@ __device__ __forceinline__ bool lane_bit(unsigned long long x, uint32_t lane) {
 // ceil(planes n / 32) and those after it lie behind every plane and are written
 // first (part 0), while the planes' words that the rows before it need are
 // copied to tmp (planes r0 W words, at most 25 / 32 n W: one mask buffer); part 1
-// then writes those rows from tmp.  A wave takes 64 (row, word)s: a lane loads
-// the words of one each, then they go out one at a time with the 64 sources on
-// the lanes, a 256-byte store each (their words are the same in every lane: each
-// plane is one select by them).
+// then writes those rows from tmp.  A wave takes 64 (row, word)s, fewer where
+// there are not that many for each: a lane loads the words of one, then they go out
+// one at a time with the 64 sources on the lanes, a 256-byte store each (their
+// words are the same in every lane: each plane is one select by them).  With 64 for
+// every wave a graph of 3,000 vertices took 13 us a part, all of it 47 waves' loops.
 __global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes, unsigned long long *tmp, uint32_t part) {
     const uint32_t W = p.W, lane = __lane_id();
     const size_t nw = (size_t)p.n * W;
@@ -182,15 +183,16 @@ __global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes
     const size_t gid = (size_t)blockIdx.x * kBlock + threadIdx.x, stride = (size_t)gridDim.x * kBlock;
     // (staged row, word) i has its masks at the row's label
     const auto masks_of = [&](size_t i) -> size_t {
-        const size_t r = i / W;
+        const size_t r = W == 1 ? i : i / W;
         return p.stage_labels ? i : (size_t)label_of(p, (int32_t)r) * W + (i - r * W);
     };
     if (part == 0)
         for (size_t i = gid; i < split * planes; i += stride)
             tmp[i] = p.planes[nw * (i / split) + masks_of(i % split)];
     const size_t first = part == 0 ? split : 0, last = part == 0 ? nw : split;
-    for (size_t i0 = first + (gid - lane); i0 < last; i0 += stride) {            // uniform per wave
-        const size_t i = i0 + lane < last ? i0 + lane : last - 1;
+    const size_t waves = stride / 64u, share = (last - first + waves - 1) / waves, per = share < 64 ? share : 64;
+    for (size_t i0 = first + gid / 64u * per; i0 < last; i0 += waves * per) {    // uniform per wave
+        const size_t i = lane < per && i0 + lane < last ? i0 + lane : last - 1;
         const size_t m = masks_of(i);
         const unsigned long long vis = p.vis[m];
         unsigned long long pl[kMsPlanes];
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes
             pl[j] = 0ull;
             if (j < planes) pl[j] = part != 0 ? tmp[split * j + i] : p.planes[nw * j + m];
         }
-        const int items = (int)(last - i0 < 64 ? last - i0 : 64);
+        const int items = (int)(last - i0 < per ? last - i0 : per);
         for (int t = 0; t < items; ++t) {                                       // uniform
             int32_t l = 0;
 #pragma unroll
