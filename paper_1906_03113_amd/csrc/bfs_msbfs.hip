@@ -451,6 +451,7 @@ __device__ __forceinline__ bool ms_last_to_arrive(const MsLevel &p) {
     __shared__ uint32_t s_last;
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
+    if (gridDim.x == 1) return true;                       // nobody else (the sources, small graphs)
     if (threadIdx.x == 0) {
         const uint32_t nb = gridDim.x;
         const uint32_t groups = nb < (uint32_t)kMsDegGroups ? nb : (uint32_t)kMsDegGroups;
@@ -470,25 +471,35 @@ __device__ __forceinline__ bool ms_last_to_arrive(const MsLevel &p) {
     return s_last != 0;
 }
 
-// Sources nb of word w reach label x at level k >= 1.  Levels are kept as bit
-// planes while the search is short: plane j, [n][W] like the masks, holds the
-// (vertex, source) pairs whose level has bit j, so a level costs one or two
-// mask-wide updates of consecutive words where staged levels cost a 4-byte store
-// per pair into 256-byte rows (R-MAT s22, 64 sources: 1 GB of them, in lines
-// written partly on each level and read again at the end).  With
-// direct_levels (a search past kMsPlaneLevels levels has turned its planes into
-// staged levels) they are stored one by one.
+// Sources nb of word w reach label x at level k >= 1; with join they join vis
+// as well.  Levels are kept as bit planes while the search is short: plane j,
+// [n][W] like the masks, holds the (vertex, source) pairs whose level has bit j,
+// so a level costs one or two mask-wide updates of consecutive words where staged
+// levels cost a 4-byte store per pair into 256-byte rows (R-MAT s22, 64 sources: 1
+// GB of them, in lines written partly on each level and read again at the end).
+// With direct_levels (a search past 2^kMsPlanes levels has turned its planes into
+// staged levels) they are stored one by one.  Every word is loaded before the
+// first is stored: one trip to memory instead of one for each word.
 __device__ __forceinline__ void set_levels(const MsLevel &p, int32_t x, uint32_t w, uint32_t k,
-                                           unsigned long long nb) {
+                                           unsigned long long nb, bool join) {
+    const size_t at = (size_t)x * p.W + w, step = (size_t)p.n * p.W;
+    unsigned long long seen = 0ull, pl[kMsPlanes];
+    if (join) seen = p.vis[at];
+#pragma unroll
+    for (uint32_t j = 0; j < kMsPlanes; ++j) {
+        pl[j] = 0ull;
+        if (!p.direct_levels && ((k >> j) & 1u) != 0u) pl[j] = p.planes[step * j + at];
+    }
+    if (join) p.vis[at] = seen | nb;
     if (p.direct_levels) {
         const int32_t vo = srow(p, x);
         for (unsigned long long b = nb; b; b &= b - 1ull)
             p.slev[stage(p, vo, w * 64u + (uint32_t)__ffsll((long long)b) - 1u)] = (int32_t)k;
         return;
     }
-    unsigned long long *at = p.planes + (size_t)x * p.W + w;
-    const size_t step = (size_t)p.n * p.W;
-    for (uint32_t bits = k; bits; bits &= bits - 1u) at[step * ((uint32_t)__ffs((int)bits) - 1u)] |= nb;
+#pragma unroll
+    for (uint32_t j = 0; j < kMsPlanes; ++j)
+        if (((k >> j) & 1u) != 0u) p.planes[step * j + at] = pl[j] | nb;
 }
 
 // The direction of level k: the network's argmin between push (0) and pull (1)
@@ -519,6 +530,25 @@ __device__ __forceinline__ float ms_feature(uint32_t i, float f, float d, float 
     return i == 5 ? x : logf(x);
 }
 
+// The next list (slot t) starts empty, its size and its statistics, and the summed
+// sizes of the lists so far become `sum` (in lane 0): the first lanes of one wave.
+__device__ __forceinline__ void ms_next_list(const MsLevel &p, uint32_t t, unsigned long long sum) {
+    const uint32_t lane = __lane_id();
+    p.mstat[ms_line((int)t, (int)lane)] = 0ull;
+    p.mstat[ms_line((int)t, (int)lane) + 1] = 0ull;
+    if (lane == 0) {
+        p.mstat[ms_line(kMsCumSlot, 0)] = sum;
+        p.cnt[t] = 0u;
+    }
+}
+
+// Level k and its list's size, with the direction in the top bit, to the host.
+__device__ __forceinline__ void ms_report(const MsLevel &p, uint32_t k, uint32_t size_dir) {
+    // one word and relaxed: a release at system scope writes the L2 back first
+    __hip_atomic_store((unsigned long long *)p.host_status, (unsigned long long)k | ((unsigned long long)size_dir << 32),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The end of a level, by the last block of its last launch (a launch of its own
 // for the direction cost 5 us a level): level k's list (slot k % 3) is
 // complete, the next level's list starts empty (next_list), the direction of
@@ -542,17 +572,9 @@ __device__ __forceinline__ void ms_close(const MsLevel &p, uint32_t k, bool next
     if (p.mlp != nullptr) stage_mlp(p.mlp, s_w);
     __syncthreads();
     if (threadIdx.x >= 64) return;
-    if (next_list) {
-        // the sizes of the lists so far, this one with them; the next list's statistics
-        if (lane < (uint32_t)kMsDegGroups) {
-            p.mstat[ms_line((int)tn, (int)lane)] = 0ull;
-            p.mstat[ms_line((int)tn, (int)lane) + 1] = 0ull;
-        }
-        if (lane == 0) {
-            p.mstat[ms_line(kMsCumSlot, 0)] = c + f;
-            p.cnt[tn] = 0u;
-            c += f;
-        }
+    if (next_list && lane < (uint32_t)kMsDegGroups) {
+        if (lane == 0) c += f;                // this one with them
+        ms_next_list(p, tn, c);
     }
     uint32_t dir = 0;
     if (p.mlp != nullptr && f != 0) {
@@ -566,12 +588,7 @@ __device__ __forceinline__ void ms_close(const MsLevel &p, uint32_t k, bool next
         const int b = mlp_argmin(s_w, feat, 2);
         dir = b < 0 ? 0u : (uint32_t)b;
     }
-    if (lane == 0 && report) {
-        // one word and relaxed: a release at system scope writes the L2 back first
-        __hip_atomic_store((unsigned long long *)p.host_status,
-                           (unsigned long long)k | ((unsigned long long)(f | (dir << 31)) << 32), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-    }
+    if (lane == 0 && report) ms_report(p, k, f | (dir << 31));
 }
 
 // Sources: bit q set in cur and vis of its vertex, level 0, parent itself; each
@@ -602,7 +619,10 @@ __global__ __launch_bounds__(kBlock) void k_ms_roots(MsLevel p) {
 // (nxt[v]) join vis and get level k+1 (their parents were set by the push).
 // The level is reported only when it had a frontier, so levels launched past
 // the end of the search (an empty frontier: push and settle then change
-// nothing) leave the last level's report in place.
+// nothing) leave the last level's report in place.  Where no direction is decided
+// on it the level closes as this launch starts - its list is complete since the
+// push - so that the next level's launches come meanwhile and no workgroup waits
+// for the others (1.7 us of a thin level's 6.5).
 __global__ __launch_bounds__(kBlock) void k_ms_settle(MsLevel p, uint32_t k) {
     const uint32_t s0 = k % 3, s1 = (k + 1) % 3;
     const unsigned long long *nxt = pick3<const unsigned long long *>(p.m[0], p.m[1], p.m[2], s1);
@@ -610,6 +630,10 @@ __global__ __launch_bounds__(kBlock) void k_ms_settle(MsLevel p, uint32_t k) {
     const uint32_t nnext = p.cnt[s1], ncur = p.cnt[s0];
     const uint32_t W = p.W;
     const uint32_t gt = blockIdx.x * kBlock + threadIdx.x, gs = gridDim.x * kBlock;
+    if (p.mlp == nullptr && gt < (uint32_t)kMsDegGroups) {
+        ms_next_list(p, (k + 2) % 3, p.mstat[ms_line(kMsCumSlot, 0)] + nnext);
+        if (gt == 0 && ncur != 0u) ms_report(p, k + 1, nnext);
+    }
     unsigned long long deg = 0, pairs = 0;
     for (uint32_t i = gt; i < nnext; i += gs) {
         const int32_t v = fnxt[i];
@@ -618,12 +642,11 @@ __global__ __launch_bounds__(kBlock) void k_ms_settle(MsLevel p, uint32_t k) {
             const unsigned long long nb = row(nxt, v, W)[w];
             if (!nb) continue;
             pairs += (unsigned long long)__popcll(nb);
-            row(p.vis, v, W)[w] |= nb;
-            set_levels(p, v, w, k + 1, nb);
+            set_levels(p, v, w, k + 1, nb, true);
         }
     }
     add_stats(p, s1, deg, pairs);
-    if (ms_last_to_arrive(p)) ms_close(p, k + 1, true, ncur != 0u);
+    if (p.mlp != nullptr && ms_last_to_arrive(p)) ms_close(p, k + 1, true, ncur != 0u);
 }
 
 // The union-frontier bitmap of level k: bit v of fbits = some word of v's
@@ -1231,8 +1254,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_close(MsLevel p, uint32_t k)
                 if (!nb) continue;
                 any = true;
                 pairs += (unsigned long long)__popcll(nb);
-                row(p.vis, (int32_t)v, W)[w] |= nb;
-                set_levels(p, (int32_t)v, w, k + 1, nb);
+                set_levels(p, (int32_t)v, w, k + 1, nb, true);
             }
             if (any) {
                 deg += (unsigned long long)(p.out_ptr[v + 1] - p.out_ptr[v]);
@@ -1623,7 +1645,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_report(MsLevel p, uint32_t k) {
         for (uint32_t w = 0; w < W; ++w) {
             const unsigned long long nb = row(nxt, v, W)[w];
             pairs += (unsigned long long)__popcll(nb);
-            if (nb) set_levels(p, v, w, k + 1, nb);
+            if (nb) set_levels(p, v, w, k + 1, nb, false);
         }
     }
     add_stats(p, s1, deg, pairs);
