@@ -183,8 +183,9 @@ typedef struct bfs_run_options {
  *                    out-degree is at most 8 (grids, road-like graphs);
  *                    sliced when it applies and either the largest
  *                    out-degree is at least 16 times the average (hubs; from
- *                    3 x 2^14 vertices, or 2^17 with several roots or
- *                    count_atomics) or single searches fan out over at least
+ *                    2^17 vertices, single searches without count_atomics also
+ *                    from 3 x 2^14 where there are 3 x 2^17 entries and four a
+ *                    vertex) or single searches fan out over at least
  *                    12 entries a vertex (2^18 vertices; 7 entries from
  *                    7 x 2^18), not counted; the list form otherwise.
  */

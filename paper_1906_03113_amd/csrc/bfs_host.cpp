@@ -1221,9 +1221,14 @@ uint32_t sl_grid(const bfs_graph *g) {
 //     road-like graphs, thousands of thin levels): the claim-word form (grid
 //     2048^2: 25.9 ms, list 57.4, sliced 122.9);
 //   - skewed degrees (the largest out-degree at least kSlSkew x the average:
-//     hubs) on 3 x 2^14 <= n <= 2^22: the sliced form (R-MAT 60,001 vertices,
-//     directed: 141 us, list 176; 120,001: 152, list 245; 1,000,003: 301, list
-//     720; but 33,693 directed: 144, list 137);
+//     hubs) on 2^17 <= n <= 2^22, and from 3 x 2^14 where there are 3 x 2^17
+//     entries, four a vertex: the sliced form (R-MAT 60,001 vertices, directed:
+//     141 us, list 176; 120,001: 152, list 245; 1,000,003: 301, list 720; but
+//     33,693 directed: 144, list 137).  With fewer entries the list form's small
+//     levels win (R-MAT of 50,000 vertices, 2 / 4 / 6 / 8 entries a vertex: 181 /
+//     152 / 154 / 160 us, list 120 / 131 / 148 / 164; a star of 130,000: 84, list
+//     73; a 330^2 grid with a hub: 638, list 297; a hub at the head of a path of
+//     30,000: 399 ms, list 59);
 //   - even degrees that fan out (fans_out), 12 entries a vertex from 2^18
 //     vertices or 7 from 7 x 2^18: the sliced form (random graphs of 262,144
 //     vertices and degree 16: 177 us, list 206; 2,000,003 and 16: 417, list 608;
@@ -1232,6 +1237,7 @@ uint32_t sl_grid(const bfs_graph *g) {
 //   - otherwise the list form (random 16,384 x 16: 95 us, sliced 129; the pack
 //     of 64: 1.06 ms, sliced 2.74).
 constexpr int32_t kSlMinAuto = 3 << 14;
+constexpr uint32_t kSlMinEntries = 3u << 17;       // below kSlMinOther vertices, and four a vertex
 constexpr int32_t kSlMinOther = 1 << 17;           // counted searches, several roots (a pack's)
 constexpr uint64_t kSlSkew = 16;
 
@@ -1257,7 +1263,8 @@ bool sliced_applies(const bfs_graph *g, const RunCfg &c, const bfs_run_options *
     // choice for them all the same), and the roots of a block-diagonal pack see
     // its small graphs, not the whole
     const bool other = (opt && opt->count_atomics) || nroots > 1;
-    return skewed_graph(g) ? g->n >= (other ? kSlMinOther : kSlMinAuto) : g->fan_out && !other;
+    if (!skewed_graph(g)) return g->fan_out && !other;
+    return g->n >= kSlMinOther || (!other && g->n >= kSlMinAuto && g->nnz >= kSlMinEntries && g->nnz / 4 >= (uint32_t)g->n);
 }
 
 bool claim_applies(const bfs_graph *g, const RunCfg &c, const bfs_run_options *opt) {

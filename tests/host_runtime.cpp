@@ -73,7 +73,11 @@ hipError_t launch_parents(const LevelParams &, uint32_t, hipStream_t) { return h
 hipError_t launch_persistent(const LevelParams &, uint32_t, hipStream_t) { return hipErrorNotSupported; }
 uint32_t persistent_max_grid(int) { return 0; }
 hipError_t launch_sl_init(const SlParams &, int32_t, const int32_t *, int32_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_sl_level(const SlParams &, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_sl_level(const SlParams &p, uint32_t, hipStream_t) {
+    p.host_status[0] = 1;
+    p.host_status[1] = 0;
+    return hipSuccess;
+}
 SlLayout sl_layout(uint32_t) { return SlLayout{}; }
 hipError_t static_scratch(void **) { return hipErrorNotSupported; }
 hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t, hipStream_t) {
@@ -209,6 +213,35 @@ static void deep_syncs() {
             }
 }
 
+// The automatic form of a push on graphs with hubs: by the vertices and the
+// entries, the list form on small ones and on medium ones of few entries.
+static void sliced_choice() {
+    struct Case { int32_t n; uint32_t nnz, hub; uint32_t form; };
+    const Case cases[] = {
+        {49151, 1400000, 9000, BFS_PUSH_LIST},   {50000, 1410000, 8000, BFS_PUSH_SLICED},   // R-MAT, 28 a vertex
+        {50000, 400000, 3300, BFS_PUSH_SLICED},  {50000, 290000, 2500, BFS_PUSH_LIST},      // 8 and 6 a vertex
+        {131071, 520000, 4000, BFS_PUSH_LIST},   {131071, 700000, 4000, BFS_PUSH_SLICED},
+        {50000, 99998, 49999, BFS_PUSH_LIST},    {130000, 259998, 129999, BFS_PUSH_LIST},   // stars
+        {60000, 119998, 30000, BFS_PUSH_LIST},                                               // a hub with a long tail
+        {108900, 393000, 1000, BFS_PUSH_LIST},                                               // a grid with a hub
+        {131072, 262142, 131071, BFS_PUSH_SLICED}, {1 << 20, 30000000, 30000, BFS_PUSH_SLICED},
+    };
+    for (const Case &c : cases) {
+        bfs_graph g;
+        g.n = c.n;
+        g.nnz = c.nnz;
+        g.max_deg = c.hub;
+        g.sl_S = 1;
+        g.sl_sw = 32768;
+        fake.levels = 1;
+        fake.steps = 0;
+        bfs_run_options opt{};
+        const bfs_status st = bfs_run(&g, 0, (int32_t *)address(2), (int32_t *)address(3), &opt, address(), size_t(1) << 40, nullptr);
+        WANT(st == BFS_OK && opt.push_used == c.form, "%d vertices, %u entries, hub of %u: form %u, %s", c.n, c.nnz, c.hub, opt.push_used,
+             bfs_last_error_detail());
+    }
+}
+
 // The network is asked for the levels that the host decides on alone: from level
 // 16 on a push decision covers eight levels, whose first seven closing launches
 // leave no direction behind.
@@ -327,6 +360,7 @@ int main(int argc, char **argv) {
     else if (which == "deep_syncs") deep_syncs();
     else if (which == "deep_choice") deep_choice();
     else if (which == "ms_decisions") ms_decisions();
+    else if (which == "sliced_choice") sliced_choice();
     else return 2;
     printf("%d wrong\n", bad);
     return bad != 0;

@@ -45,3 +45,7 @@ def test_form_of_a_batch_on_thin_graphs(runtime):
 
 def test_network_asked_once_a_decision(runtime):
     run(runtime, "ms_decisions")
+
+
+def test_form_of_a_push_on_graphs_with_hubs(runtime):
+    run(runtime, "sliced_choice")
