@@ -187,7 +187,9 @@ typedef struct bfs_run_options {
  *                    from 3 x 2^14 where there are 3 x 2^17 entries and four a
  *                    vertex) or single searches fan out over at least
  *                    12 entries a vertex (2^18 vertices; 7 entries from
- *                    7 x 2^18), not counted; the list form otherwise.
+ *                    7 x 2^18) in at most 11 levels, which is looked at when
+ *                    the graph is created, not counted; the list form
+ *                    otherwise.
  */
 enum {
     BFS_PUSH_AUTO = 0,

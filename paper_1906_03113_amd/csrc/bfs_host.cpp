@@ -85,7 +85,7 @@ struct bfs_graph {
     // a list's end, for the claim-word push's deep form
     int32_t *thin_rows = nullptr;
     uint32_t thin_width = 0;
-    bool fan_out = false;             // even degrees, wide levels early (sliced_applies)
+    bool fan_out = false;             // even degrees, wide levels early and few of them (sliced_applies)
     uint32_t deep_levels = 0;         // a thin graph's searches' levels where they grow slowly (thin_levels)
     std::mutex mu;
     GraphExecCache gcache;
@@ -1230,10 +1230,13 @@ uint32_t sl_grid(const bfs_graph *g) {
 //     73; a 330^2 grid with a hub: 638, list 297; a hub at the head of a path of
 //     30,000: 399 ms, list 59);
 //   - even degrees that fan out (fans_out), 12 entries a vertex from 2^18
-//     vertices or 7 from 7 x 2^18: the sliced form (random graphs of 262,144
-//     vertices and degree 16: 177 us, list 206; 2,000,003 and 16: 417, list 608;
-//     2,000,003 and 8: 462, list 499; but 1,048,576 and 8: 340, list 335, and
-//     2,000,003 and 4: 579, list 488);
+//     vertices or 7 from 7 x 2^18, and searches of at most kEvenLevels levels: the
+//     sliced form (random graphs of 262,144 vertices and degree 16: 177 us, list
+//     206; 2,000,003 and 16: 417, list 608; 2,000,003 and 8, 11 levels: 462, list
+//     499; but 1,048,576 and 8: 340, list 335, and 2,000,003 and 4: 579, list 488;
+//     eight random graphs in a row, one edge between neighbours, 4,000,000
+//     vertices, degree 14, 44 levels: 5.27 ms, list 1.72; a ring of 300,000 with
+//     16 neighbours, one edge in twenty moved, 12 levels: 275, list 247);
 //   - otherwise the list form (random 16,384 x 16: 95 us, sliced 129; the pack
 //     of 64: 1.06 ms, sliced 2.74).
 constexpr int32_t kSlMinAuto = 3 << 14;
@@ -1247,6 +1250,8 @@ bool thin_graph(const bfs_graph *g) { return g->max_deg <= kClaimMaxDeg; }
 bool skewed_graph(const bfs_graph *g) {
     return (uint64_t)g->max_deg * (uint64_t)g->n >= kSlSkew * (uint64_t)g->nnz;
 }
+
+constexpr uint32_t kEvenLevels = 11;
 
 // Where even degrees may take the sliced form, if searches fan out.
 bool even_sliced_size(const bfs_graph *g) {
@@ -1564,6 +1569,28 @@ const char *bfs_status_string(bfs_status s) {
 
 const char *bfs_last_error_detail(void) { return g_detail.c_str(); }
 
+// Whether searches are through in kEvenLevels levels, by two searches of the list
+// form (how a graph goes on past the neighbourhoods that fans_out sees takes a
+// whole search to know; creating the graph takes a hundred times as long).  Not
+// where there is no memory for them.
+static bool shallow(bfs_graph *g) {
+    const size_t need = ws_single(g), nb = align256((size_t)g->n * 4);
+    char *b = nullptr;
+    if (hipMalloc((void **)&b, need + 2 * nb) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    bool yes = true;
+    for (int32_t t = 0; yes && t < 2; ++t) {
+        bfs_run_options opt{};
+        opt.push_impl = BFS_PUSH_LIST;
+        yes = bfs_run(g, (int32_t)((int64_t)g->n * t / 2), (int32_t *)(b + need), (int32_t *)(b + need + nb), &opt, b, need,
+                      nullptr) == BFS_OK && opt.levels <= kEvenLevels;
+    }
+    (void)hipFree(b);
+    return yes;
+}
+
 bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *out_idx,
                             const int32_t *in_ptr, const int32_t *in_idx, uint32_t flags,
                             void *hip_stream, bfs_graph **out) {
@@ -1690,6 +1717,7 @@ bfs_status bfs_graph_create(int32_t n, const int32_t *out_ptr, const int32_t *ou
         g_detail = keep;
         return st;
     }
+    if (g->fan_out) g->fan_out = shallow(g);
     *out = g;
     return BFS_OK;
 }

@@ -9,6 +9,7 @@
 static struct {
     uint32_t levels = 1;                    // levels the search has
     uint32_t steps = 0, past = 0;           // step launches; those after the first that reported the end
+    bool restart = false;                   // a search's first launch is number 0 again
     uint32_t deep_wanted = 1;               // deep launches until the list is empty
     uint32_t deep = 0, deep_past = 0, wide = 0, narrow = 0, cw_inits = 0, ms = 0, decided = 0;
     uint64_t most_vertices = 0;
@@ -18,7 +19,7 @@ static uint32_t *slot;                      // the progress slot
 
 // ---- the HIP runtime ------------------------------------------------------------------------
 extern "C" {
-hipError_t hipMalloc(void **p, size_t b) { *p = malloc(b); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipMalloc(void **p, size_t b) { *p = aligned_alloc(256, (b + 511) & ~size_t(255)); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t b, unsigned) { slot = (uint32_t *)(*p = calloc(1, b)); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void **d, void *p, unsigned) { *d = p; return hipSuccess; }
@@ -55,7 +56,10 @@ hipError_t hipGetLastError() { return hipSuccess; }
 
 // ---- the kernels ----------------------------------------------------------------------------
 namespace bfsi {
-hipError_t launch_init(const LevelParams &, int32_t, const int32_t *, int32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_init(const LevelParams &, int32_t, const int32_t *, int32_t, hipStream_t) {
+    if (fake.restart) fake.steps = 0;
+    return hipSuccess;
+}
 hipError_t launch_level(const LevelParams &, uint32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_step(const LevelParams &p, uint32_t, uint32_t, hipStream_t) {
     const uint32_t j = fake.steps++;
@@ -314,6 +318,24 @@ static bfs_graph *grid(int32_t a, int32_t b, int32_t c) {                // a x 
     return undirected(a * b * c, e);
 }
 
+// Even degrees that fan out take the sliced push where a search is through in a
+// few levels: two searches at the graph's creation tell.
+static void even_choice() {
+    for (uint32_t levels : {7u, 11u, 12u, 40u}) {
+        fake.levels = levels;
+        fake.steps = 0;
+        fake.restart = true;
+        bfs_graph *g = matchings(1 << 18, 14, 1.0);
+        fake.restart = false;
+        fake.steps = 0;
+        bfs_run_options opt{};
+        const bfs_status st = bfs_run(g, 0, (int32_t *)address(2), (int32_t *)address(3), &opt, address(), size_t(1) << 40, nullptr);
+        WANT(st == BFS_OK && opt.push_used == (levels <= 11 ? BFS_PUSH_SLICED : BFS_PUSH_LIST), "%u levels: form %u, %s", levels, opt.push_used,
+             bfs_last_error_detail());
+        bfs_graph_destroy(g);
+    }
+}
+
 // A learned batch takes the claim-word searches where its levels are many and
 // thin for its vertices and sources, and the multi-source levels elsewhere.
 static void deep_choice() {
@@ -361,6 +383,7 @@ int main(int argc, char **argv) {
     else if (which == "deep_choice") deep_choice();
     else if (which == "ms_decisions") ms_decisions();
     else if (which == "sliced_choice") sliced_choice();
+    else if (which == "even_choice") even_choice();
     else return 2;
     printf("%d wrong\n", bad);
     return bad != 0;

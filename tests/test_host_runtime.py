@@ -49,3 +49,7 @@ def test_network_asked_once_a_decision(runtime):
 
 def test_form_of_a_push_on_graphs_with_hubs(runtime):
     run(runtime, "sliced_choice")
+
+
+def test_form_of_a_push_on_even_degrees(runtime):
+    run(runtime, "even_choice")
