@@ -232,18 +232,18 @@ __global__ __launch_bounds__(kBlock) void k_sp_long(SpParams P) {
             if (P.items[mid].base <= c) lo = mid; else hi = mid - 1u;
         }
         const SpItem it = P.items[lo];
-        const int32_t r1 = P.out_ptr[it.j + 1];
+        // positions within the chunk: 512 past an entry near 2^31 is no int32
         const int32_t e0 = P.out_ptr[it.j] + (int32_t)((c - it.base) * kSpChunk);
-        const int32_t e1 = (e0 + (int32_t)kSpChunk < r1) ? e0 + (int32_t)kSpChunk : r1;
-        for (int32_t eb = e0; eb < e1; eb += 64 * kSpBatch) {              // uniform
+        const int32_t left = P.out_ptr[it.j + 1] - e0, len = left < (int32_t)kSpChunk ? left : (int32_t)kSpChunk;
+        for (int32_t t0 = 0; t0 < len; t0 += 64 * kSpBatch) {              // uniform
             int32_t i[kSpBatch];
             unsigned long long pp[kSpBatch];
             bool on[kSpBatch];
 #pragma unroll
             for (int q = 0; q < kSpBatch; ++q) {
-                const int32_t e = eb + 64 * q + (int32_t)lane;
-                on[q] = e < e1;
-                i[q] = on[q] ? P.out_idx[e] : 0;
+                const int32_t t = t0 + 64 * q + (int32_t)lane;
+                on[q] = t < len;
+                i[q] = on[q] ? P.out_idx[e0 + t] : 0;
                 pp[q] = it.v;
             }
             accumulate(P, i, pp, on);
@@ -347,7 +347,6 @@ SpLayout sp_layout(int32_t n, int32_t max_nx) {
     L.touched = take(words * 4);
     L.items = take((size_t)(max_nx > 0 ? max_nx : 1) * sizeof(SpItem));
     L.block_off = take(nblocks * 4);
-    L.ny = take(4);
     L.total = off;
     return L;
 }
