@@ -305,7 +305,12 @@ enum MsPhase {
 };
 hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t grid, hipStream_t s);
 hipError_t launch_ms_zero(unsigned long long *a, size_t words, hipStream_t s);
-// The first `planes` level planes into vertex-major levels in place (tmp: n W words).
+// The first `planes` level planes into vertex-major levels in place (tmp: n W
+// words).  Staged row ms_levels_row and those after it lie behind the planes; the
+// words of the rows before it go through tmp and fit wherever a level with bit
+// planes - 1 was reached or may be (n > 2^(planes - 1)); refused elsewhere.
+__host__ __device__ constexpr size_t ms_levels_row(int32_t n, uint32_t planes) { return ((size_t)planes * (size_t)n + 31) / 32; }
+constexpr bool ms_levels_fit(int32_t n, uint32_t planes) { return planes * ms_levels_row(n, planes) <= (size_t)n; }
 hipError_t launch_ms_levels(const MsLevel &p, uint32_t planes, unsigned long long *tmp, uint32_t grid, hipStream_t s);
 // The staged results into per-source arrays.
 hipError_t launch_ms_out(const MsLevel &p, uint32_t planes, uint32_t grid, hipStream_t s);

@@ -170,7 +170,7 @@ __device__ __forceinline__ bool lane_bit(unsigned long long x, uint32_t lane) {
 // [j n W, (j + 1) n W) of it, row v's levels the 32 words from 32 v W): row r0 =
 // ceil(planes n / 32) and those after it lie behind every plane and are written
 // first (part 0), while the planes' words that the rows before it need are
-// copied to tmp (planes r0 W words, at most 25 / 32 n W: one mask buffer); part 1
+// copied to tmp (planes r0 W words, in one mask buffer: ms_levels_fit); part 1
 // then writes those rows from tmp.  A wave takes 64 (row, word)s, fewer where
 // there are not that many for each: a lane loads the words of one, then they go out
 // one at a time with the 64 sources on the lanes, a 256-byte store each (their
@@ -179,7 +179,7 @@ __device__ __forceinline__ bool lane_bit(unsigned long long x, uint32_t lane) {
 __global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes, unsigned long long *tmp, uint32_t part) {
     const uint32_t W = p.W, lane = __lane_id();
     const size_t nw = (size_t)p.n * W;
-    const size_t r0 = ((size_t)planes * (size_t)p.n + 31) / 32, split = r0 * W;
+    const size_t split = ms_levels_row(p.n, planes) * W;
     const size_t gid = (size_t)blockIdx.x * kBlock + threadIdx.x, stride = (size_t)gridDim.x * kBlock;
     // (staged row, word) i has its masks at the row's label
     const auto masks_of = [&](size_t i) -> size_t {
@@ -1698,6 +1698,7 @@ hipError_t launch_ms_zero(unsigned long long *a, size_t words, hipStream_t s) {
 }
 
 hipError_t launch_ms_levels(const MsLevel &p, uint32_t planes, unsigned long long *tmp, uint32_t grid, hipStream_t s) {
+    if (!ms_levels_fit(p.n, planes)) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_ms_levels, dim3(grid), dim3(kBlock), 0, s, p, planes, tmp, 0u);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || planes == 0) return e;

@@ -11,7 +11,7 @@ static struct {
     uint32_t steps = 0, past = 0;           // step launches; those after the first that reported the end
     bool restart = false;                   // a search's first launch is number 0 again
     uint32_t deep_wanted = 1;               // deep launches until the list is empty
-    uint32_t deep = 0, deep_past = 0, wide = 0, narrow = 0, cw_inits = 0, ms = 0, decided = 0;
+    uint32_t deep = 0, deep_past = 0, wide = 0, narrow = 0, cw_inits = 0, ms = 0, decided = 0, conversions = 0;
     uint64_t most_vertices = 0;
 } fake;
 
@@ -97,7 +97,10 @@ hipError_t launch_ms(const MsLevel &p, MsPhase phase, uint32_t k, uint32_t, hipS
     return hipSuccess;
 }
 hipError_t launch_ms_zero(unsigned long long *, size_t, hipStream_t) { return hipSuccess; }
-hipError_t launch_ms_levels(const MsLevel &, uint32_t, unsigned long long *, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t launch_ms_levels(const MsLevel &p, uint32_t planes, unsigned long long *, uint32_t, hipStream_t) {
+    ++fake.conversions;
+    return ms_levels_fit(p.n, planes) ? hipSuccess : hipErrorInvalidValue;
+}
 hipError_t launch_ms_out(const MsLevel &, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_ms_rpull(const MsLevel &, uint32_t, uint32_t, uint32_t, hipStream_t) { return hipSuccess; }
 hipError_t launch_cw_init(const CwParams &p, hipStream_t) {
@@ -214,6 +217,29 @@ static void deep_syncs() {
                 WANT(st == BFS_OK, "%u launches, levels_per_sync %u, %d sources: %s", launches, per, nq, bfs_last_error_detail());
                 WANT(fake.deep_past <= most && (per != 1 || fake.deep_past == 0), "%u launches, levels_per_sync %u, %d sources: %u past the end", launches, per, nq,
                      fake.deep_past);
+            }
+}
+
+// The planes become levels only where the words in the way fit one mask buffer,
+// whatever the vertices and the levels, launches past the end among them.
+static void levels_fit() {
+    for (uint32_t planes = 1; planes <= kMsPlanes; ++planes)
+        for (int32_t n = (1 << (planes - 1)) + 1; n < 5000; ++n)
+            WANT(ms_levels_fit(n, planes), "%d vertices, %u planes", n, planes);
+    WANT(!ms_levels_fit(2, 3) && !ms_levels_fit(8, 5), "too few vertices for the planes");
+    for (int32_t n = 1; n <= 120; ++n)
+        for (uint32_t levels = 1; levels <= (uint32_t)n; ++levels)
+            for (uint32_t variant : {kPush, kPull}) {
+                bfs_graph g;
+                g.n = n;
+                const int32_t src[2] = {0, 0};
+                fake.levels = levels;
+                fake.conversions = 0;
+                bfs_run_options opt{};
+                opt.variant = variant;
+                const bfs_status st = bfs_run_batch_vm(&g, 2, src, (int32_t *)address(2), (int32_t *)address(3), &opt, address(), size_t(1) << 40, nullptr);
+                WANT(st == BFS_OK && opt.levels == levels, "%d vertices, %u levels: %s", n, levels, bfs_last_error_detail());
+                WANT(fake.conversions == 1, "%d vertices, %u levels: %u conversions", n, levels, fake.conversions);
             }
 }
 
@@ -384,6 +410,7 @@ int main(int argc, char **argv) {
     else if (which == "ms_decisions") ms_decisions();
     else if (which == "sliced_choice") sliced_choice();
     else if (which == "even_choice") even_choice();
+    else if (which == "levels_fit") levels_fit();
     else return 2;
     printf("%d wrong\n", bad);
     return bad != 0;

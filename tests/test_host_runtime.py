@@ -53,3 +53,7 @@ def test_form_of_a_push_on_graphs_with_hubs(runtime):
 
 def test_form_of_a_push_on_even_degrees(runtime):
     run(runtime, "even_choice")
+
+
+def test_planes_become_levels_where_they_fit(runtime):
+    run(runtime, "levels_fit")
