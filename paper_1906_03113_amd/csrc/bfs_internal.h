@@ -93,7 +93,8 @@ struct LevelParams {
     BfsState *st;
     DevLevelRec *trace;      // kTraceCap records, or nullptr
     const float *mlp;        // selector weights (kMlpTotal floats) or nullptr
-    uint32_t *host_status;   // pinned host memory: [0] level, [1] its frontier size
+    uint32_t *host_status;   // pinned host memory: [0] level, [1] its frontier size; step launches:
+                             // [0] launches started, [1] the frontier size, [2] level
     uint32_t maintain_fb;
     uint32_t steps;                // the levels run as step launches (k_step)
     unsigned long long *atomics;   // count the push's parent atomicMin operations here, or nullptr
@@ -243,8 +244,8 @@ struct MsLevel {
     int32_t *const *level;         // device array of nq device pointers
     int32_t *const *parent;
     const int32_t *sources;        // device, nq
-    uint32_t *host_status;         // pinned host: [0] level, [1] its union frontier's size
-                                   // (one 64-bit store), [2] its direction (stored before)
+    uint32_t *host_status;         // pinned host: [0] level, [1] its union frontier's size with
+                                   // its direction in the top bit (one 64-bit store)
     // union-frontier bitmap of the level a pull runs on (bit v = some source
     // has v in its frontier), [ceil(n / 64)] words, built by k_ms_fbits when
     // use_fbits is set: the pull tests it before gathering a frontier mask
@@ -496,7 +497,7 @@ struct SpParams {
 };
 
 struct SpLayout {
-    size_t state, acc, touched, items, block_off, ny, total;
+    size_t state, acc, touched, items, block_off, total;
 };
 SpLayout sp_layout(int32_t n, int32_t max_nx);
 hipError_t launch_spmspv(const SpParams &p, uint32_t grid, hipStream_t s);

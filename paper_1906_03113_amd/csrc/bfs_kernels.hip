@@ -154,7 +154,7 @@ struct OutLds {
 };
 
 struct LevelPtrs {
-    uint32_t k, cs, ns;
+    uint32_t k, ns;
     bool sc;                  // this level claims rows short-circuit (parents set afterwards)
     bool pre;                 // pre-read the parent before its atomicMin
     const uint32_t *vb_cur;
@@ -175,7 +175,6 @@ struct LevelPtrs {
 __device__ __forceinline__ LevelPtrs level_ptrs(const LevelParams &P, uint32_t k) {
     LevelPtrs L;
     L.k = k;
-    L.cs = k & 3;
     L.ns = (k + 1) & 3;
     // selects instead of indexing the parameter arrays with a runtime index
     // (which would force the kernel-argument struct into scratch memory)
@@ -1419,8 +1418,9 @@ __device__ __forceinline__ bool step_counters(const LevelParams &P, uint32_t odd
     return true;
 }
 
-// The form of the level a step launch runs, when the level before did not
-// decide it (kStepGiven carries it): every workgroup for itself.
+// The form of the level a step launch runs: decided by every workgroup for itself,
+// on every launch.  (A base's variant is a former level's form, but after small
+// levels, where it is this level's and comes out the same.)
 __device__ __forceinline__ uint32_t step_form(const LevelParams &P, uint32_t k, const Counters &c, const MlpTrip &net,
                                               float *s_w) {
     if (P.policy != kLearned && P.policy != kHeuristic) return P.policy;
