@@ -1106,7 +1106,7 @@ bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t w
             hipError_t e = hipMemcpyAsync(&hst, P.st, sizeof hst, hipMemcpyDeviceToHost, s);
             return e == hipSuccess ? hipStreamSynchronize(s) : e;
         };
-        HIP_TRY(read_state());
+        if (!thin) HIP_TRY(read_state());     // (a thin graph's sources are all short columns)
         uint32_t k = 0;
         bool narrow_refused = false;          // the narrow kernel handed level k back
         const uint32_t wide_max = 8u * (uint32_t)(cus > 0 ? cus : 256);
@@ -1122,7 +1122,7 @@ bfs_status run_claim(const ClaimQuery *qs, int32_t nq, void *workspace, size_t w
             const uint32_t most = fixed_sync ? std::min(fixed_sync, kDeepPerSync) : kDeepPerSync;
             uint32_t seq = 0;
             per_sync = std::min(2u, most);
-            for (uint64_t guard = 0; hst.cnt[seq % 3][0] != 0u; ++guard) {
+            for (uint64_t guard = 0; guard == 0 || hst.cnt[seq % 3][0] != 0u; ++guard) {
                 if (guard > V + 4) return fail(BFS_EHIP, "claim-word loop did not terminate");
                 for (uint32_t i = 0; i < per_sync; ++i) {
                     HIP_TRY(launch([&]() {
