@@ -368,10 +368,25 @@ def ms_collect(entries, reps: int = 2, log=None):
     return np.concatenate(Xs), np.concatenate(Ts), np.concatenate(Ms)
 
 
+MS_GROUP_FROM = 16          # the level from which pushes are launched in groups
+MS_ROUND_TRIP = 8.0         # us from a level's end to the next one's start through the host
+
+
+def ms_with_round_trips(X: np.ndarray, T: np.ndarray) -> np.ndarray:
+    """The targets with what a level's launches cost beyond their device time where
+    the two directions differ in it: from level MS_GROUP_FROM on a pull ends in a
+    round trip to the host, which eight pushes share."""
+    T = T.copy()
+    late = X[:, 4] >= math.log1p(MS_GROUP_FROM) - 1e-6
+    T[late, 1] = np.log(np.exp(T[late, 1]) + MS_ROUND_TRIP)
+    return T
+
+
 def ms_main(args, log):
     train_e, held_e = ms_training_sets(include_large=not args.small)
     X, T, M = ms_collect(train_e, log=log)
     Xh, Th, Mh = ms_collect(held_e, log=log)
+    T, Th = ms_with_round_trips(X, T), ms_with_round_trips(Xh, Th)
     log(f"[selector-ms] training rows {len(X)}, held-out rows {len(Xh)}")
     w = train(X, T, M, steps=args.steps, log=log)
     res = {}
