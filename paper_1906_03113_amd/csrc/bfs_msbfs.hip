@@ -175,7 +175,10 @@ __device__ __forceinline__ bool lane_bit(unsigned long long x, uint32_t lane) {
 // there are not that many for each: a lane loads the words of one, then they go out
 // one at a time with the 64 sources on the lanes, a 256-byte store each (their
 // words are the same in every lane: each plane is one select by them).  With 64 for
-// every wave a graph of 3,000 vertices took 13 us a part, all of it 47 waves' loops.
+// every wave a graph of 3,000 vertices took 13 us a part, all of it 47 waves' loops
+// (kShare; where there are 64 for each the bound is a constant: directed 2^20, 256
+// sources 135 us a part, 141 without).
+template <bool kShare>
 __global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes, unsigned long long *tmp, uint32_t part) {
     const uint32_t W = p.W, lane = __lane_id();
     const size_t nw = (size_t)p.n * W;
@@ -190,7 +193,8 @@ __global__ __launch_bounds__(kBlock) void k_ms_levels(MsLevel p, uint32_t planes
         for (size_t i = gid; i < split * planes; i += stride)
             tmp[i] = p.planes[nw * (i / split) + masks_of(i % split)];
     const size_t first = part == 0 ? split : 0, last = part == 0 ? nw : split;
-    const size_t waves = stride / 64u, share = (last - first + waves - 1) / waves, per = share < 64 ? share : 64;
+    const size_t waves = stride / 64u, share = (last - first + waves - 1) / waves;
+    const size_t per = kShare && share < 64 ? share : 64;
     for (size_t i0 = first + gid / 64u * per; i0 < last; i0 += waves * per) {    // uniform per wave
         const size_t i = lane < per && i0 + lane < last ? i0 + lane : last - 1;
         const size_t m = masks_of(i);
@@ -471,32 +475,47 @@ __device__ __forceinline__ bool ms_last_to_arrive(const MsLevel &p) {
     return s_last != 0;
 }
 
-// Sources nb of word w reach label x at level k >= 1; with join they join vis
-// as well.  Levels are kept as bit planes while the search is short: plane j,
-// [n][W] like the masks, holds the (vertex, source) pairs whose level has bit j,
-// so a level costs one or two mask-wide updates of consecutive words where staged
-// levels cost a 4-byte store per pair into 256-byte rows (R-MAT s22, 64 sources: 1
-// GB of them, in lines written partly on each level and read again at the end).
-// With direct_levels (a search past 2^kMsPlanes levels has turned its planes into
-// staged levels) they are stored one by one.  Every word is loaded before the
-// first is stored: one trip to memory instead of one for each word.
+// Sources nb of word w reach label x at level k >= 1.  Levels are kept as bit
+// planes while the search is short: plane j, [n][W] like the masks, holds the
+// (vertex, source) pairs whose level has bit j, so a level costs one or two
+// mask-wide updates of consecutive words where staged levels cost a 4-byte store
+// per pair into 256-byte rows (R-MAT s22, 64 sources: 1 GB of them, in lines
+// written partly on each level and read again at the end).  With
+// direct_levels (a search past 2^kMsPlanes levels has turned its planes into
+// staged levels) they are stored one by one.
 __device__ __forceinline__ void set_levels(const MsLevel &p, int32_t x, uint32_t w, uint32_t k,
-                                           unsigned long long nb, bool join) {
-    const size_t at = (size_t)x * p.W + w, step = (size_t)p.n * p.W;
-    unsigned long long seen = 0ull, pl[kMsPlanes];
-    if (join) seen = p.vis[at];
-#pragma unroll
-    for (uint32_t j = 0; j < kMsPlanes; ++j) {
-        pl[j] = 0ull;
-        if (!p.direct_levels && ((k >> j) & 1u) != 0u) pl[j] = p.planes[step * j + at];
-    }
-    if (join) p.vis[at] = seen | nb;
+                                           unsigned long long nb) {
     if (p.direct_levels) {
         const int32_t vo = srow(p, x);
         for (unsigned long long b = nb; b; b &= b - 1ull)
             p.slev[stage(p, vo, w * 64u + (uint32_t)__ffsll((long long)b) - 1u)] = (int32_t)k;
         return;
     }
+    unsigned long long *at = p.planes + (size_t)x * p.W + w;
+    const size_t step = (size_t)p.n * p.W;
+    for (uint32_t bits = k; bits; bits &= bits - 1u) at[step * ((uint32_t)__ffs((int)bits) - 1u)] |= nb;
+}
+
+// The same, and they join vis, where the rows lie apart (a push's list): every word
+// is loaded before the first is stored, one trip to memory instead of one for each
+// word.  (Rows in order - the close of a pull - are bound by bandwidth: 59 us a
+// level of directed 2^20, 256 sources, 64 this way.)
+__device__ __forceinline__ void join_levels(const MsLevel &p, int32_t x, uint32_t w, uint32_t k,
+                                            unsigned long long nb) {
+    const size_t at = (size_t)x * p.W + w, step = (size_t)p.n * p.W;
+    const unsigned long long seen = p.vis[at];
+    if (p.direct_levels) {
+        p.vis[at] = seen | nb;
+        set_levels(p, x, w, k, nb);
+        return;
+    }
+    unsigned long long pl[kMsPlanes];
+#pragma unroll
+    for (uint32_t j = 0; j < kMsPlanes; ++j) {
+        pl[j] = 0ull;
+        if (((k >> j) & 1u) != 0u) pl[j] = p.planes[step * j + at];
+    }
+    p.vis[at] = seen | nb;
 #pragma unroll
     for (uint32_t j = 0; j < kMsPlanes; ++j)
         if (((k >> j) & 1u) != 0u) p.planes[step * j + at] = pl[j] | nb;
@@ -642,7 +661,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_settle(MsLevel p, uint32_t k) {
             const unsigned long long nb = row(nxt, v, W)[w];
             if (!nb) continue;
             pairs += (unsigned long long)__popcll(nb);
-            set_levels(p, v, w, k + 1, nb, true);
+            join_levels(p, v, w, k + 1, nb);
         }
     }
     add_stats(p, s1, deg, pairs);
@@ -1254,7 +1273,8 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_close(MsLevel p, uint32_t k)
                 if (!nb) continue;
                 any = true;
                 pairs += (unsigned long long)__popcll(nb);
-                set_levels(p, (int32_t)v, w, k + 1, nb, true);
+                row(p.vis, (int32_t)v, W)[w] |= nb;
+                set_levels(p, (int32_t)v, w, k + 1, nb);
             }
             if (any) {
                 deg += (unsigned long long)(p.out_ptr[v + 1] - p.out_ptr[v]);
@@ -1645,7 +1665,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_report(MsLevel p, uint32_t k) {
         for (uint32_t w = 0; w < W; ++w) {
             const unsigned long long nb = row(nxt, v, W)[w];
             pairs += (unsigned long long)__popcll(nb);
-            if (nb) set_levels(p, v, w, k + 1, nb, false);
+            if (nb) set_levels(p, v, w, k + 1, nb);
         }
     }
     add_stats(p, s1, deg, pairs);
@@ -1699,11 +1719,14 @@ hipError_t launch_ms_zero(unsigned long long *a, size_t words, hipStream_t s) {
 
 hipError_t launch_ms_levels(const MsLevel &p, uint32_t planes, unsigned long long *tmp, uint32_t grid, hipStream_t s) {
     if (!ms_levels_fit(p.n, planes)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_ms_levels, dim3(grid), dim3(kBlock), 0, s, p, planes, tmp, 0u);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || planes == 0) return e;
-    hipLaunchKernelGGL(k_ms_levels, dim3(grid), dim3(kBlock), 0, s, p, planes, tmp, 1u);
-    return hipGetLastError();
+    const size_t behind = ms_levels_row(p.n, planes), waves = (size_t)grid * (kBlock / 64);     // (row, word)s of the parts
+    const auto part = [&](uint32_t which, size_t rows) -> hipError_t {
+        if (rows * p.W < 64 * waves) hipLaunchKernelGGL(k_ms_levels<true>, dim3(grid), dim3(kBlock), 0, s, p, planes, tmp, which);
+        else hipLaunchKernelGGL(k_ms_levels<false>, dim3(grid), dim3(kBlock), 0, s, p, planes, tmp, which);
+        return hipGetLastError();
+    };
+    const hipError_t e = part(0u, (size_t)p.n - behind);
+    return e != hipSuccess || planes == 0 ? e : part(1u, behind);
 }
 
 hipError_t launch_ms_out(const MsLevel &p, uint32_t planes, uint32_t grid, hipStream_t s) {
