@@ -1498,10 +1498,15 @@ SlParams make_sl_params(bfs_graph *g, int32_t *level, int32_t *parent, void *ws,
     P.streams = sl_grid(g) / g->sl_S;
     // half a wave's share of the bitmap, but no less than 8 words of it (two
     // batches of vertices): R-MAT 2,000,003 vertices, a share of 32 words: by 32
-    // 439 us, 16 412, 8 455; 1,000,003, a share of 8: by 8 302, 4 329.  An even
+    // 439 us, 16 412, 8 455; 1,000,003, a share of 8: by 8 302, 4 329.  Rounded up,
+    // so that a stream has no more segments than two for each wave (33 of 60 words
+    // where 31 of 64 do took a third round: 2000^2 grid 108 against 98 ms).  An even
     // number (a level is written for pairs of words), one per lane at most
-    const uint32_t share = P.words / (P.streams * (uint32_t)bfsi::kSlWaves);
-    P.seg_words = std::min(64u, std::max(2u, std::max(std::min(share, 8u), share / 2u) & ~1u));
+    const uint32_t wave_words = P.streams * (uint32_t)bfsi::kSlWaves, share = (P.words + wave_words - 1u) / wave_words;
+    P.seg_words = std::min(64u, (std::max(std::min(share, 8u), (share + 1u) / 2u) + 1u) & ~1u);
+    // longer ones on thin levels, a workgroup's share at most, from 2^18 vertices
+    // (R-MAT of 60,001 and 132,000 vertices: 179 against 171 us with longer ones)
+    P.seg_most = g->n < (1 << 18) ? P.seg_words : std::min(64u, P.words / (P.streams * P.S));
     P.near_deg = g->near_deg;
     P.seg = g->sl_seg;
     P.occ = g->sl_occ;

@@ -137,7 +137,7 @@ struct alignas(256) SlState {
     uint32_t pad0[3];
     uint32_t nclaim[kRing];                  // claim bits the level that built C_k found
                                              // (>= |C_k| since workgroups overlap; 0 iff empty)
-    uint32_t eager[kRing];                   // 1: the level runs eager
+    uint32_t mode[kRing];                    // how the level runs (level_mode)
     uint32_t nf[kRing];                      // |F_k|, counted as F_k is settled
     unsigned long long sdf[kRing];           // sum of out-degrees over F_k
     uint32_t visited_cnt;                    // |B_k| after level k closes
@@ -160,6 +160,7 @@ struct SlParams {
     uint32_t words;                  // S * sw: words of every bitmap (padded)
     uint32_t streams;                // workgroups per slice
     uint32_t seg_words;              // bitmap words a wave takes at a time (even, at most 64)
+    uint32_t seg_most;               // on levels of few vertices for the bitmap up to this many (at most 64)
     uint32_t near_deg;               // mean out-degree of a list entry (of a neighbour)
     const int4 *seg;                 // [n + 1]: {out_ptr[v], start of slices 1, 2, 3 in v's out-list}
     const uint32_t *occ;             // [S][words]: bit v of slice s = v's part in slice s is short and

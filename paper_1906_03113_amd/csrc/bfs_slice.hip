@@ -76,6 +76,15 @@ __device__ __forceinline__ bool eager_level(uint32_t nclaim, unsigned long long 
     return nclaim <= lim && nclaim * degree <= kEagerEntries;
 }
 
+// How a level runs, decided once before it: bit 0 eager, above it the bitmap words
+// a wave takes at a time - its share (seg_words), and up to seg_most while a segment
+// holds few of the frontier's vertices (16 on average).
+__device__ __forceinline__ uint32_t level_mode(const SlParams &P, uint32_t nclaim, unsigned long long degree) {
+    uint32_t sgw = P.seg_words;
+    while (2u * sgw <= P.seg_most && 4ull * sgw * nclaim <= (unsigned long long)P.n) sgw *= 2u;
+    return (eager_level(nclaim, degree, P.n) ? 1u : 0u) | (sgw << 1);
+}
+
 // Orders a wave's LDS writes before the same wave's later LDS reads by other lanes.
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -460,7 +469,7 @@ __device__ __forceinline__ void sl_close(const SlParams &P, uint32_t k) {
     const unsigned long long vd = st->visited_deg + deg;
     st->nclaim[(k + 1) & 3] = claims;
     const unsigned long long mean = nf ? deg / nf : 0ull;
-    st->eager[(k + 1) & 3] = eager_level(claims, k == 0 && P.near_deg > mean ? P.near_deg : mean, P.n) ? 1u : 0u;
+    st->mode[(k + 1) & 3] = level_mode(P, claims, k == 0 && P.near_deg > mean ? P.near_deg : mean);
     st->nf[k & 3] = nf;
     st->sdf[k & 3] = deg;
     st->visited_cnt = vc;
@@ -511,7 +520,7 @@ __global__ __launch_bounds__(256) void k_sl_init(SlParams P, int32_t single_root
             st->sdf[r] = 0ull;
         }
         st->nclaim[0] = nroots;
-        st->eager[0] = eager_level(nroots, 1ull, P.n) ? 1u : 0u;
+        st->mode[0] = level_mode(P, nroots, 1ull);
         st->visited_cnt = 0;
         st->visited_deg = 0ull;
         for (int g = 0; g < kBarGroups; ++g) {
@@ -599,9 +608,10 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
     const uint32_t k = st->level;
     const uint32_t nck = st->nclaim[k & 3];
     if (nck == 0u) return;
-    const bool eager = st->eager[k & 3] != 0u;
+    const uint32_t mode = st->mode[k & 3];
+    const bool eager = (mode & 1u) != 0u;
     // F_k was settled by level k - 1 when that level ran eager
-    const bool settle_now = (k == 0) || st->eager[(k + 3) & 3] == 0u;
+    const bool settle_now = (k == 0) || (st->mode[(k + 3) & 3] & 1u) == 0u;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const uint32_t b = blockIdx.x;
     const uint32_t S = P.S;
@@ -695,11 +705,13 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
 
     // every frontier vertex: settle it (if this slice owns it and level k - 1
     // left it unsettled) and expand its short part in slice s.  The stream's
-    // words are cut into segments of seg_words dealt to the waves; a batch takes
-    // the segment's next 64 kCols frontier vertices, kCols per lane.  Segments
-    // are as long as the waves' shares, 64 words (2048 vertices) at most: by 64
-    // words throughout a graph of 188,191 vertices had work for 92 of the 4,096
-    // waves.
+    // words are cut into segments dealt to the waves; a batch takes the segment's
+    // next 64 kCols frontier vertices, kCols per lane.  Segments are as long as the
+    // waves' shares (seg_words), 64 words (2048 vertices) at most: by 64 words
+    // throughout a graph of 188,191 vertices had work for 92 of the 4,096 waves.
+    // They are longer while one holds few of the frontier's vertices (level_mode): a
+    // thin level is a wave's chain for each segment with a vertex, and by shares of 8
+    // words a 1000^2 grid took 37.6 ms, 31.0 so.
     {
         // bits j of a word whose vertex 32 w + j this workgroup owns (owner
         // depends on v mod 4 only, and 32 w is a multiple of 4)
@@ -707,7 +719,7 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j)
             if (owner((int32_t)j, S) == s) own_bits |= 0x11111111u << j;
-        const uint32_t sgw = P.seg_words;
+        const uint32_t sgw = mode >> 1;
         const uint32_t wps = (P.words + P.streams * sgw - 1u) / (P.streams * sgw) * sgw;
         const uint32_t ws0 = q * wps;
         const uint32_t ws1 = (ws0 + wps < P.words) ? ws0 + wps : P.words;
