@@ -66,6 +66,8 @@ struct bfs_graph {
     bfsi::MsLong *do_long = nullptr;
     uint32_t *do_map = nullptr, *do_rest = nullptr;
     uint32_t do_nlong = 0, do_nchunks = 0;
+    int32_t *do_rows = nullptr;       // the pull's row chunks over the labels: their bounds
+    uint32_t do_nrows = 0;
     // a directed graph's out-lists over the same labels (the lists above are
     // then its in-lists), with their caller ids and long columns
     int32_t *do_optr = nullptr, *do_oidx = nullptr, *do_oent = nullptr;
@@ -173,7 +175,7 @@ void free_graph(bfs_graph *g) {
     if (g->lo) (void)hipFree(g->lo);
     if (g->lomap) (void)hipFree(g->lomap);
     if (g->lirest) (void)hipFree(g->lirest);
-    for (int32_t *a : {g->do_ptr, g->do_idx, g->do_ent, g->do_orig, g->do_pos, g->do_optr,
+    for (int32_t *a : {g->do_ptr, g->do_idx, g->do_ent, g->do_orig, g->do_pos, g->do_rows, g->do_optr,
                        g->do_oidx, g->do_oent})
         if (a) (void)hipFree(a);
     if (g->do_olong) (void)hipFree(g->do_olong);
@@ -229,6 +231,37 @@ bfs_status build_rest(int32_t n, const std::vector<int32_t> &ptr, uint32_t **out
     std::vector<uint32_t> order;
     for (const auto &b : by_pos) order.insert(order.end(), b.begin(), b.end());
     return upload(out, order.data(), order.size(), bytes);
+}
+
+// The row chunks of the pull's waves over the degree-ordered copy: kMsWideRows
+// labels, fewer where their entries would be more than kMsWideEntries and than
+// four shares of a resident wave (8 workgroups per compute unit) of all lists -
+// the longest rows lie side by side, and a wave with sixteen of 500 entries
+// scanned on after all the others.  R-MAT of
+// 1,000,000 vertices and 4 entries a vertex (490 entries a wave), 64 sources,
+// pulls: 55 us a sparse level before, 43 with 2,048 entries a chunk, whole
+// search 1,280 -> 1,050 us; where a wave has 2,000 entries or more to scan in
+// any case such chunks cost 1% (scale 20, directed, 256 sources: 3,200 us,
+// 3,235 split): no bounds then, and kMsWideRows rows each.
+static bfs_status build_row_chunks(int32_t n, int cus, const std::vector<int32_t> &ptr, int32_t **out,
+                                   uint32_t &count, size_t &bytes) {
+    const uint32_t waves = 8u * (uint32_t)(cus > 0 ? cus : 256) * (bfsi::kBlock / 64);
+    const uint32_t share = (uint32_t)ptr[(size_t)n] / waves * 4u;
+    const uint32_t most = share > bfsi::kMsWideEntries ? share : bfsi::kMsWideEntries;
+    std::vector<int32_t> rows{0};
+    uint32_t entries = 0;
+    for (int32_t x = 0; x < n; ++x) {
+        const uint32_t d = (uint32_t)(ptr[(size_t)x + 1] - ptr[(size_t)x]), scan = d < bfsi::kMsLong ? d : 0u;
+        if (x - rows.back() == bfsi::kMsWideRows || (x > rows.back() && entries + scan > most)) {
+            rows.push_back(x);
+            entries = 0;
+        }
+        entries += scan;
+    }
+    if (rows.size() == ((size_t)n + bfsi::kMsWideRows - 1) / bfsi::kMsWideRows) return BFS_OK;
+    count = (uint32_t)rows.size();
+    rows.push_back(n);
+    return upload(out, rows.data(), rows.size(), bytes);
 }
 
 // The degree-ordered copy of a graph for the multi-source search.
@@ -289,6 +322,7 @@ bfs_status build_degree_order(bfs_graph *g, const std::vector<int32_t> &ptr, con
     if (st == BFS_OK) st = upload(&g->do_pos, pos.data(), pos.size(), g->bytes);
     if (st == BFS_OK) st = build_long(n, dptr, &g->do_long, &g->do_map, g->do_nlong, g->do_nchunks, g->bytes);
     if (st == BFS_OK) st = build_rest(n, dptr, &g->do_rest, g->bytes);
+    if (st == BFS_OK) st = build_row_chunks(n, g->cus, dptr, &g->do_rows, g->do_nrows, g->bytes);
     return st;
 }
 
@@ -1939,6 +1973,7 @@ static bfs_status ms_prepare(bfs_graph *g, int32_t nq, const int32_t *sources,
     p.nli = g->nli;
     p.nli_chunks = g->nli_chunks;
     p.lirest = g->lirest;
+    p.nrow_chunks = ((uint32_t)g->n + bfsi::kMsWideRows - 1) / bfsi::kMsWideRows;
     p.orig = p.pos = p.ent = nullptr;
     // the degree-ordered copy (undirected: one list set serves both ways); a
     // directed graph's only for batches of more than one mask word (directed
@@ -1955,6 +1990,8 @@ static bfs_status ms_prepare(bfs_graph *g, int32_t nq, const int32_t *sources,
         p.nlo_chunks = p.nli_chunks = g->do_nchunks;
         p.nli = g->do_nlong;
         p.lirest = g->do_rest;
+        p.row_chunks = g->do_rows;
+        if (g->do_rows) p.nrow_chunks = g->do_nrows;
         if (g->directed) {            // the out-lists for the push
             p.out_ptr = g->do_optr;
             p.out_idx = g->do_oidx;
@@ -2051,6 +2088,8 @@ static void ms_caller_order(const bfs_graph *g, MsLevel &p) {
     p.in_ptr = g->in_ptr;
     p.in_idx = g->in_idx;
     p.orig = p.pos = p.ent = p.out_ent = nullptr;
+    p.row_chunks = nullptr;
+    p.nrow_chunks = ((uint32_t)g->n + bfsi::kMsWideRows - 1) / bfsi::kMsWideRows;
     p.stage_labels = 0;
     p.lo = g->lo;
     p.li = g->li;

@@ -195,6 +195,8 @@ hipError_t launch_sl_level(const SlParams &p, uint32_t grid, hipStream_t s);
 constexpr uint32_t kMsLong = 512;      // degree from which a multi-source list entry is split
 constexpr uint32_t kMsChunk = 512;     // entries per chunk of a split entry
 constexpr uint32_t kMsRows = 512;      // rows per chunk of the range-ordered pull
+constexpr int32_t kMsWideRows = 16;    // consecutive rows that a wave of the pull looks at together
+constexpr uint32_t kMsWideEntries = 2048;   // ... their entries, at most, in the degree-ordered copy
 constexpr uint32_t kMsPlanes = 5;      // level bit planes: searches of up to 2^kMsPlanes levels
 constexpr uint32_t kMsPlanesFirst = 3; // planes cleared at the start (the others when first needed)
 
@@ -228,6 +230,8 @@ struct MsLevel {
     // masks, vis, flags and lists use labels, the staged results and every
     // parent value the caller's ids
     const int32_t *orig, *pos, *ent, *out_ent;   // ent: in-list entries, out_ent: out-list entries
+    const int32_t *row_chunks;     // the pull's row chunk bounds over the labels (null: kMsWideRows rows each)
+    uint32_t nrow_chunks;
     uint32_t stage_labels;         // staged rows by label (the library's own staging with a degree order)
     // results staged vertex-major while the search runs, [n][W * 64]: row v
     // holds every source's level / parent of v (valid where vis has the bit),

@@ -892,15 +892,26 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_short(MsLevel p, uint32_t k)
     }
 }
 
-constexpr int32_t kMsWideRows = 16;            // consecutive rows a wave looks at together
 constexpr uint32_t kMsAlone = 2;               // open rows from which each gets the whole wave
+constexpr int kMsTogether = 4;                 // steps of 16 entries before each open row gets it in any case
+
+// Row chunk c of the pull: rows [v0, v1), kMsWideRows at most.
+__device__ __forceinline__ void row_chunk(const MsLevel &p, uint32_t c, int32_t &v0, int32_t &v1) {
+    if (p.row_chunks) {
+        v0 = p.row_chunks[c];
+        v1 = p.row_chunks[c + 1];
+        return;
+    }
+    v0 = (int32_t)c * kMsWideRows;
+    v1 = p.n - v0 < kMsWideRows ? p.n : v0 + kMsWideRows;
+}
 
 // One mask word: the rows of more than kMsSerial entries below kMsLong, a wave
 // per kMsWideRows consecutive rows, four rows to a step with 16 lanes each, four
 // such steps (all sixteen rows) in flight together: a row's scan is a chain of
 // dependent loads (entry, mask, caller's id), and with one row group after
 // another a wave had one of them in flight at a time.  Once at most kMsAlone
-// rows are open, each is finished by the whole wave.  Before that the long
+// rows are open, or after kMsTogether steps, each is finished by the whole wave.  Before that the long
 // rows, a wave per chunk: with long_split only each row's first chunk - it
 // holds the row's smallest in-neighbours, so what it finds is final: those
 // bits go into vis now and k_ms_pull_rest then scans the later chunks for the
@@ -925,14 +936,13 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_wide(MsLevel p, uint32_t k) 
         long_chunk(p, cur, nxt, v, j, k, p.long_split != 0u);
     }
     const unsigned long long full = full_word(p, 0u);
-    const uint32_t nsteps = ((uint32_t)p.n + kMsWideRows - 1) / kMsWideRows;
     const int g = (int)(lane >> 4);
     const int32_t gl = (int32_t)(lane & 15u);
-    for (uint32_t c = gw; c < nsteps; c += nw) {                                 // uniform per wave
-        const int32_t v0 = (int32_t)(c * kMsWideRows);
-        int32_t b = 0, e = 0;
+    for (uint32_t c = gw; c < p.nrow_chunks; c += nw) {                          // uniform per wave
+        int32_t v0, v1, b = 0, e = 0;
+        row_chunk(p, c, v0, v1);
         unsigned long long r0 = 0ull;
-        if (lane < (uint32_t)kMsWideRows && v0 + (int32_t)lane < p.n) {
+        if ((int32_t)lane < v1 - v0) {
             b = p.in_ptr[v0 + (int32_t)lane];
             e = p.in_ptr[v0 + (int32_t)lane + 1];
             r0 = full & ~p.vis[v0 + (int32_t)lane];
@@ -950,7 +960,7 @@ __global__ __launch_bounds__(kBlock) void k_ms_pull_wide(MsLevel p, uint32_t k) 
             rem[t] = __shfl(r0, src, 64);
             fnd[t] = 0ull;
         }
-        while ((uint32_t)__popcll(open) > kMsAlone) {                            // uniform
+        for (int step = 0; step < kMsTogether && (uint32_t)__popcll(open) > kMsAlone; ++step) {     // uniform
             int32_t uu[4], oo[4];
             bool ok[4];
             unsigned long long mm[4];
@@ -1180,11 +1190,10 @@ __global__ __launch_bounds__(kBlock) void k_ms_wide_words(MsLevel p, uint32_t k)
         }
         words_chunk<kWp>(p, cur, nxt, v, j, k, p.long_split != 0u, slots);
     }
-    const uint32_t nsteps = ((uint32_t)p.n + kMsWideRows - 1) / kMsWideRows;
-    for (uint32_t c = gw; c < nsteps; c += nw) {                                 // uniform per wave
-        const int32_t v0 = (int32_t)(c * kMsWideRows);
-        int32_t b = 0, e = 0;
-        if (lane < (uint32_t)kMsWideRows && v0 + (int32_t)lane < p.n) {
+    for (uint32_t c = gw; c < p.nrow_chunks; c += nw) {                          // uniform per wave
+        int32_t v0, v1, b = 0, e = 0;
+        row_chunk(p, c, v0, v1);
+        if ((int32_t)lane < v1 - v0) {
             b = p.in_ptr[v0 + (int32_t)lane];
             e = p.in_ptr[v0 + (int32_t)lane + 1];
         }
