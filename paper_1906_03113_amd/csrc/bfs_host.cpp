@@ -354,8 +354,10 @@ bfs_status upload_lists(bfs_graph *g, const std::vector<int32_t> &idx) {
 // of the level, so the n vertices take k (n / V)^(1 / d).  That is 1 / 1.5 of the
 // levels measured, from d = 2 (grids) to 6 (random graphs, growing by 1.4 a level).
 // The median of the first three vertices of eight whose search is that large;
-// where there is none, the deepest search seen.  Visits some 15,000 vertices at
-// most.
+// where there is none, the deepest search seen, the first through half of the
+// graph as the last that is followed past kGrowthLevels (a 40 x 40 grid's
+// creation 183 us with all eight, 113 with one).  Visits some 15,000 vertices
+// at most.
 constexpr uint32_t kGrowthLevels = 12;
 constexpr size_t kDepthProbe = 4096;
 
@@ -365,8 +367,9 @@ uint32_t thin_levels(int32_t n, const std::vector<int32_t> &ptr, const std::vect
     std::vector<size_t> ends;                                  // ... through each level
     std::vector<double> levels;
     uint32_t deepest = 0;
+    bool known = false;                                        // a search went through half of the graph
     for (int32_t t = 0; t < 8; ++t) {
-        const bool grows = t % 2 == 0, depth = levels.size() < 3;
+        const bool grows = t % 2 == 0, depth = levels.size() < 3 && !known;
         int64_t s = (int64_t)n * t / 8;
         while (s < n && ptr[(size_t)s + 1] == ptr[(size_t)s]) ++s;
         if (s == n || (!grows && !depth)) continue;
@@ -392,6 +395,7 @@ uint32_t thin_levels(int32_t n, const std::vector<int32_t> &ptr, const std::vect
         const size_t k = ends.size() - 1;                      // the last level with a vertex
         if (over || !depth || k < 2) {
             if (over) deepest = std::max(deepest, (uint32_t)k);
+            known |= over && 2 * order.size() >= (size_t)n;
             continue;
         }
         const double V = (double)ends[k], d = std::log(V / (double)ends[k / 2]) / std::log((double)k / (double)(k / 2));
