@@ -328,10 +328,65 @@ def ms_heuristic_choice(X: np.ndarray, shift: int = 5) -> np.ndarray:
     return ((np.round(f) * 2.0 ** shift) > np.round(n)).astype(np.int64)
 
 
+def _attached(n: int, m: int, seed: int):
+    """Each vertex with m edges to ends of earlier edges (preferential attachment)."""
+    import graphgen
+    r = np.random.default_rng(seed)
+    src = np.repeat(np.arange(1, n), m)
+    at = r.integers(0, np.maximum(2 * np.arange(src.size), 1))     # 2 i: edge i's first end, 2 i + 1: its second
+    while (at & 1).any():                                          # a second end is what that edge picked
+        at = np.where(at & 1, at[at >> 1], at)
+    return graphgen.from_edges(n, src, src[at >> 1])
+
+
+def _blocks(n: int, blocks: int, degree: int, seed: int):
+    """Random graphs, each tied to the next by one edge."""
+    import graphgen
+    r = np.random.default_rng(seed)
+    size = n // blocks
+    s = r.integers(0, size * blocks, n * degree // 2)
+    ties = np.arange(1, blocks) * size
+    return graphgen.from_edges(n, np.concatenate([s, ties]),
+                               np.concatenate([s // size * size + r.integers(0, size, s.size), ties - 1]))
+
+
+def _mesh(shape: Sequence[int], diagonals: bool = False):
+    """A full grid of two or three dimensions, in two with its diagonals if asked."""
+    import graphgen
+    v = np.arange(int(np.prod(shape))).reshape(shape)
+    e = [(np.take(v, range(k - 1), d), np.take(v, range(1, k), d)) for d, k in enumerate(shape)]
+    if diagonals:
+        e += [(v[:-1, :-1], v[1:, 1:]), (v[1:, :-1], v[:-1, 1:])]
+    return graphgen.from_edges(v.size, np.concatenate([x.ravel() for x, _ in e]),
+                               np.concatenate([y.ravel() for _, y in e]))
+
+
+def _matchings(n: int, k: int, seed: int):
+    """k random matchings: k neighbours a vertex."""
+    import graphgen
+    r = np.random.default_rng(seed)
+    ps = [r.permutation(n) for _ in range(k)]
+    return graphgen.from_edges(n, np.concatenate([x[0:n - 1:2] for x in ps]), np.concatenate([x[1:n:2] for x in ps]))
+
+
+def _ring(n: int, k: int, share: float, seed: int):
+    """A ring of 2 k neighbours with that share of the edges' ends moved anywhere."""
+    import graphgen
+    r = np.random.default_rng(seed)
+    v = np.arange(n)
+    to = np.concatenate([(v + j) % n for j in range(1, k + 1)])
+    moved = r.random(to.size) < share
+    to[moved] = r.integers(0, n, int(moved.sum()))
+    return graphgen.from_edges(n, np.concatenate([v] * k), to)
+
+
 def ms_training_sets(include_large: bool = True):
     """(train, held-out) lists of (name, graph builder, source batches); a batch
-    is (count, seed) of seeded picks.  Held out: R-MAT scales and batch sizes
-    never trained on."""
+    is (count, seed) of seeded picks.  Besides R-MAT and the thin grids: even and
+    attached degrees, meshes, rings, chained blocks and thin skewed graphs (a
+    network without them chose worse by a quarter there: a random graph of
+    1,000,003 vertices and 30 neighbours, 2 sources, 1,020 us for 810).  Held out:
+    R-MAT scales, batch sizes and sizes of those families never trained on."""
     import graphgen
     train = [("er16k", lambda: graphgen.workload("er16k"), [(64, 1), (256, 2)]),
              ("grid512", lambda: graphgen.grid(512, 0.9, 3), [(16, 3), (64, 4)]),
@@ -343,9 +398,25 @@ def ms_training_sets(include_large: bool = True):
                   ("rmat19", lambda: graphgen.rmat(19, 16, 7), [(128, 11), (30, 23), (5, 24), (48, 28)]),
                   ("rmatd18", lambda: graphgen.rmat(18, 16, 10, directed=True), [(9, 29), (40, 30), (100, 31)]),
                   ("rmat20", lambda: graphgen.rmat(20, 16, 8), [(3, 25), (12, 26), (40, 32), (160, 27)]),
-                  ("grid1024", lambda: graphgen.grid(1024, 0.9, 5), [(16, 12)])]
+                  ("grid1024", lambda: graphgen.grid(1024, 0.9, 5), [(16, 12)]),
+                  ("er200k", lambda: graphgen.erdos_renyi(200000, 8, 6), [(2, 41), (16, 42), (64, 43)]),
+                  ("er500k", lambda: graphgen.erdos_renyi(500000, 16, 7), [(2, 44), (16, 45), (100, 46)]),
+                  ("er1m", lambda: graphgen.erdos_renyi(1000000, 30, 8), [(2, 47), (16, 48), (64, 49)]),
+                  ("attached300k", lambda: _attached(300000, 3, 2), [(2, 50), (16, 51), (64, 52)]),
+                  ("blocks500k", lambda: _blocks(500000, 8, 16, 2), [(2, 53), (16, 54)]),
+                  ("mesh500", lambda: _mesh((500, 500), True), [(2, 55), (16, 56), (64, 57)]),
+                  ("rmat20thin", lambda: graphgen.rmat(20, 2, 11), [(2, 58), (16, 59), (64, 60), (100, 61)]),
+                  ("matchings300k", lambda: _matchings(300000, 3, 2), [(2, 62), (16, 63)]),
+                  ("mesh60", lambda: _mesh((60, 60, 60)), [(2, 64), (16, 65), (64, 66)]),
+                  ("ring200k", lambda: _ring(200000, 8, 0.2, 2), [(2, 67), (16, 68), (64, 69)])]
     held = [(f"rmat{sc}", (lambda sc=sc: graphgen.rmat(sc, 16, 2000 + sc)), [(64, 20 + sc), (192, 40 + sc)])
             for sc in ((16, 18) if not include_large else (16, 17, 18, 21))]
+    if include_large:
+        held += [("er800k", lambda: graphgen.erdos_renyi(800000, 20, 9), [(4, 71), (40, 72)]),
+                 ("attached150k", lambda: _attached(150000, 5, 3), [(8, 73), (100, 74)]),
+                 ("mesh350", lambda: _mesh((350, 350), True), [(8, 75), (40, 76)]),
+                 ("blocks800k", lambda: _blocks(800000, 5, 12, 3), [(8, 77)]),
+                 ("rmat19thin", lambda: graphgen.rmat(19, 3, 12), [(40, 78)])]
     return train, held
 
 
@@ -388,13 +459,13 @@ def ms_main(args, log):
     Xh, Th, Mh = ms_collect(held_e, log=log)
     T, Th = ms_with_round_trips(X, T), ms_with_round_trips(Xh, Th)
     log(f"[selector-ms] training rows {len(X)}, held-out rows {len(Xh)}")
-    w = train(X, T, M, steps=args.steps, log=log)
+    w = train(X, T, M, steps=args.steps, seed=args.seed, log=log)
     res = {}
     for tag, (x, t, m) in (("train", (X, T, M)), ("held_out", (Xh, Th, Mh))):
         res[tag] = regret(ms_choose(w, x), t, m)
         res[tag]["heuristic_regret"] = regret(ms_heuristic_choice(x), t, m)["regret"]
         log(f"[selector-ms] {tag}: {res[tag]}")
-    meta = dict(res, train_rows=int(len(X)), held_rows=int(len(Xh)),
+    meta = dict(res, train_rows=int(len(X)), held_rows=int(len(Xh)), steps=args.steps, seed=args.seed,
                 outputs="push, pull (the third output is unused)")
     save_weights(args.ms_out, w, meta)
     print(json.dumps(res))
@@ -464,6 +535,8 @@ def main(argv=None):
     ap = argparse.ArgumentParser(description="collect per-level timings, train the selector, evaluate regret")
     ap.add_argument("--out", default=DEFAULT_WEIGHTS)
     ap.add_argument("--steps", type=int, default=3000)
+    ap.add_argument("--seed", type=int, default=0, help="of the multi-source network's first weights (the one "
+                    "kept: 6,000 steps from seed 1)")
     ap.add_argument("--small", action="store_true", help="skip the large training graphs")
     ap.add_argument("--cap", type=int, default=300, help="levels kept per training search")
     ap.add_argument("--eval", action="store_true",
