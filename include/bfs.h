@@ -348,8 +348,9 @@ size_t bfs_roots_workspace_size(const bfs_graph *g, int32_t nroots);
  * one vertex-major pair of arrays instead of one array per source: with
  * ld = 64 * ceil(num_sources / 64), level[v * ld + q] and parent[v * ld + q]
  * are source q's level and parent of vertex v (the same values bfs_run gives);
- * columns q >= num_sources hold -1.  This is the layout the search builds
- * anyway, so no transpose pass runs at the end.
+ * columns q >= num_sources hold -1.  The search builds its parents in this
+ * layout anyway and holds its levels as bit planes in the level array, so one
+ * pass over the levels runs at the end and no transpose.
  * sources: host, num_sources ints in [0, n) (duplicates allowed).
  * level, parent: device int32[n * ld] each, caller-owned, 16-byte aligned.
  * workspace: bfs_batch_vm_workspace_size(g, num_sources) bytes or more,

@@ -1257,7 +1257,7 @@ uint32_t sl_grid(const bfs_graph *g) {
 // 2^20 x 8, 1024^2 / 2048^2 / 4096^2 grids, a pack of 64 ER graphs):
 //   - bounded small degree (every out-degree <= kClaimMaxDeg: grids,
 //     road-like graphs, thousands of thin levels): the claim-word form (grid
-//     2048^2: 25.9 ms, list 57.4, sliced 122.9);
+//     2048^2: 3.9 ms, list 57.4, sliced 120);
 //   - skewed degrees (the largest out-degree at least kSlSkew x the average:
 //     hubs) on 2^17 <= n <= 2^22, and from 3 x 2^14 where there are 3 x 2^17
 //     entries, four a vertex: the sliced form (R-MAT 60,001 vertices, directed:
