@@ -1542,9 +1542,11 @@ SlParams make_sl_params(bfs_graph *g, int32_t *level, int32_t *parent, void *ws,
     // number (a level is written for pairs of words), one per lane at most
     const uint32_t wave_words = P.streams * (uint32_t)bfsi::kSlWaves, share = (P.words + wave_words - 1u) / wave_words;
     P.seg_words = std::min(64u, (std::max(std::min(share, 8u), (share + 1u) / 2u) + 1u) & ~1u);
-    // longer ones on thin levels, a workgroup's share at most, from 2^18 vertices
-    // (R-MAT of 60,001 and 132,000 vertices: 179 against 171 us with longer ones)
-    P.seg_most = g->n < (1 << 18) ? P.seg_words : std::min(64u, P.words / (P.streams * P.S));
+    // longer ones on thin levels, a workgroup's share at most, from 3 x 2^17 vertices
+    // (R-MAT of 262,144 and 8 entries a vertex, 12 sources: 195 us, 202 with longer
+    // ones, of 270,000 and 4: 197, 203, but of 400,000 and 8: 211 either way, of
+    // 2,000,003: 375, 365, and a 700^2 grid with a hub: 1,850, 1,555)
+    P.seg_most = g->n < 3 * (1 << 17) ? P.seg_words : std::min(64u, P.words / (P.streams * P.S));
     P.near_deg = g->near_deg;
     P.seg = g->sl_seg;
     P.occ = g->sl_occ;

@@ -137,7 +137,7 @@ struct alignas(256) SlState {
     uint32_t pad0[3];
     uint32_t nclaim[kRing];                  // claim bits the level that built C_k found
                                              // (>= |C_k| since workgroups overlap; 0 iff empty)
-    uint32_t mode[kRing];                    // how the level runs (level_mode)
+    uint32_t eager[kRing];                   // 1: the level runs eager
     uint32_t nf[kRing];                      // |F_k|, counted as F_k is settled
     unsigned long long sdf[kRing];           // sum of out-degrees over F_k
     uint32_t visited_cnt;                    // |B_k| after level k closes

@@ -76,13 +76,19 @@ __device__ __forceinline__ bool eager_level(uint32_t nclaim, unsigned long long 
     return nclaim <= lim && nclaim * degree <= kEagerEntries;
 }
 
-// How a level runs, decided once before it: bit 0 eager, above it the bitmap words
-// a wave takes at a time - its share (seg_words), and up to seg_most while a segment
-// holds few of the frontier's vertices (16 on average).
-__device__ __forceinline__ uint32_t level_mode(const SlParams &P, uint32_t nclaim, unsigned long long degree) {
-    uint32_t sgw = P.seg_words;
-    while (2u * sgw <= P.seg_most && 4ull * sgw * nclaim <= (unsigned long long)P.n) sgw *= 2u;
-    return (eager_level(nclaim, degree, P.n) ? 1u : 0u) | (sgw << 1);
+// The bitmap words a wave takes at a time on a level of nclaim vertices: its share
+// (seg_words), and up to seg_most while a segment holds few of the frontier's
+// vertices (16 on average) - as often doubled as 2 nclaim times the result stays
+// within n.  By the leading bits, and by every wave for itself: as a loop or decided
+// by the thread that closes the level before, 0.3 us of a path's 17.4 a level.
+__device__ __forceinline__ uint32_t level_words(const SlParams &P, uint32_t nclaim) {
+    const uint32_t a = (uint32_t)P.n, b = P.seg_words * nclaim;          // below 2^29
+    int l = b ? __clz((int)b) - __clz((int)a) : 0;
+    if (l > 0 && (b << l) > a) --l;
+    int most = __clz((int)P.seg_words) - __clz((int)P.seg_most);
+    if (most > 0 && (P.seg_words << most) > P.seg_most) --most;
+    const int j = l - 1 < most ? l - 1 : most;
+    return P.seg_words << (j > 0 ? j : 0);
 }
 
 // Orders a wave's LDS writes before the same wave's later LDS reads by other lanes.
@@ -469,7 +475,7 @@ __device__ __forceinline__ void sl_close(const SlParams &P, uint32_t k) {
     const unsigned long long vd = st->visited_deg + deg;
     st->nclaim[(k + 1) & 3] = claims;
     const unsigned long long mean = nf ? deg / nf : 0ull;
-    st->mode[(k + 1) & 3] = level_mode(P, claims, k == 0 && P.near_deg > mean ? P.near_deg : mean);
+    st->eager[(k + 1) & 3] = eager_level(claims, k == 0 && P.near_deg > mean ? P.near_deg : mean, P.n) ? 1u : 0u;
     st->nf[k & 3] = nf;
     st->sdf[k & 3] = deg;
     st->visited_cnt = vc;
@@ -520,7 +526,7 @@ __global__ __launch_bounds__(256) void k_sl_init(SlParams P, int32_t single_root
             st->sdf[r] = 0ull;
         }
         st->nclaim[0] = nroots;
-        st->mode[0] = level_mode(P, nroots, 1ull);
+        st->eager[0] = eager_level(nroots, 1ull, P.n) ? 1u : 0u;
         st->visited_cnt = 0;
         st->visited_deg = 0ull;
         for (int g = 0; g < kBarGroups; ++g) {
@@ -601,17 +607,19 @@ __device__ __forceinline__ void load_starts(const SlParams &P, const int32_t (&v
 
 constexpr uint32_t kCopyUnroll = 4;      // 16-byte groups a thread moves per step of a bitmap pass
 
-// One level k.  Launches after the end of the search (C_k empty) return.
+// One level k.  Launches after the end of the search (C_k empty) return.  kLong: the
+// graph has thin levels' longer segments (with the choice behind a test of the
+// parameters 0.15 us of a path's 17.4 a level more).
+template <bool kLong>
 __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
     __shared__ SlLds L;
     SlState *st = P.st;
     const uint32_t k = st->level;
     const uint32_t nck = st->nclaim[k & 3];
     if (nck == 0u) return;
-    const uint32_t mode = st->mode[k & 3];
-    const bool eager = (mode & 1u) != 0u;
+    const bool eager = st->eager[k & 3] != 0u;
     // F_k was settled by level k - 1 when that level ran eager
-    const bool settle_now = (k == 0) || (st->mode[(k + 3) & 3] & 1u) == 0u;
+    const bool settle_now = (k == 0) || st->eager[(k + 3) & 3] == 0u;
     const uint32_t tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const uint32_t b = blockIdx.x;
     const uint32_t S = P.S;
@@ -709,7 +717,7 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
     // next 64 kCols frontier vertices, kCols per lane.  Segments are as long as the
     // waves' shares (seg_words), 64 words (2048 vertices) at most: by 64 words
     // throughout a graph of 188,191 vertices had work for 92 of the 4,096 waves.
-    // They are longer while one holds few of the frontier's vertices (level_mode): a
+    // They are longer while one holds few of the frontier's vertices (level_words): a
     // thin level is a wave's chain for each segment with a vertex, and by shares of 8
     // words a 1000^2 grid took 37.6 ms, 31.0 so.
     {
@@ -719,7 +727,7 @@ __global__ __launch_bounds__(kSlThreads) void k_sl_level(SlParams P) {
 #pragma unroll
         for (uint32_t j = 0; j < 4; ++j)
             if (owner((int32_t)j, S) == s) own_bits |= 0x11111111u << j;
-        const uint32_t sgw = mode >> 1;
+        const uint32_t sgw = kLong ? level_words(P, (uint32_t)__builtin_amdgcn_readfirstlane((int)nck)) : P.seg_words;
         const uint32_t wps = (P.words + P.streams * sgw - 1u) / (P.streams * sgw) * sgw;
         const uint32_t ws0 = q * wps;
         const uint32_t ws1 = (ws0 + wps < P.words) ? ws0 + wps : P.words;
@@ -906,7 +914,8 @@ hipError_t launch_sl_init(const SlParams &p, int32_t nroots, const int32_t *root
 }
 
 hipError_t launch_sl_level(const SlParams &p, uint32_t grid, hipStream_t s) {
-    hipLaunchKernelGGL(k_sl_level, dim3(grid), dim3(kSlThreads), 0, s, p);
+    if (p.seg_most > p.seg_words) hipLaunchKernelGGL(k_sl_level<true>, dim3(grid), dim3(kSlThreads), 0, s, p);
+    else hipLaunchKernelGGL(k_sl_level<false>, dim3(grid), dim3(kSlThreads), 0, s, p);
     return hipGetLastError();
 }
 

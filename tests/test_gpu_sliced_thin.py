@@ -1,6 +1,6 @@
 """Sliced push on levels of few and of many vertices in one search: the bitmap words
 that a wave takes at a time change from level to level (longer segments on thin
-levels from 2^18 vertices), at the sizes where they start, with a ragged last
+levels of large graphs), at sizes where they start, with a ragged last
 segment and with several slices.  Bit for bit the oracle's."""
 import numpy as np
 import pytest
