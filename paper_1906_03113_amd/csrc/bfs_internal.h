@@ -194,6 +194,7 @@ hipError_t launch_sl_level(const SlParams &p, uint32_t grid, hipStream_t s);
 // Multi-source search (64 sources per 64-bit word per vertex).
 constexpr uint32_t kMsLong = 512;      // degree from which a multi-source list entry is split
 constexpr uint32_t kMsChunk = 512;     // entries per chunk of a split entry
+constexpr int32_t kMsSerial = 16;      // longest row that one lane of the pull scans alone
 constexpr uint32_t kMsRows = 512;      // rows per chunk of the range-ordered pull
 constexpr int32_t kMsWideRows = 16;    // consecutive rows that a wave of the pull looks at together
 constexpr uint32_t kMsWideEntries = 2048;   // ... their entries, at most, in the degree-ordered copy
@@ -232,6 +233,7 @@ struct MsLevel {
     const int32_t *orig, *pos, *ent, *out_ent;   // ent: in-list entries, out_ent: out-list entries
     const int32_t *row_chunks;     // the pull's row chunk bounds over the labels (null: kMsWideRows rows each)
     uint32_t nrow_chunks;
+    uint32_t wide_rows;            // some row may have more than kMsSerial entries
     uint32_t stage_labels;         // staged rows by label (the library's own staging with a degree order)
     // results staged vertex-major while the search runs, [n][W * 64]: row v
     // holds every source's level / parent of v (valid where vis has the bit),

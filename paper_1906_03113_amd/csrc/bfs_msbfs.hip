@@ -784,7 +784,6 @@ __device__ __forceinline__ void long_chunk(const MsLevel &p, const unsigned long
     }
 }
 
-constexpr int32_t kMsSerial = 16;        // longest row one lane scans alone
 constexpr int kMsWriteRows = 8;          // rows whose staged results a wave writes together
 
 __device__ __forceinline__ unsigned long long full_word(const MsLevel &p, uint32_t w) {
